@@ -330,29 +330,58 @@ __global__ void k_clustering(int64_t n, const int64_t *__restrict__ row_ptr, con
 
 // ----------------------------------------------------------- components --
 
-__global__ void k_parent_init(int64_t n, int32_t *__restrict__ parent) {
-    for (int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; i < n; i += (int64_t)gridDim.x * blockDim.x)
-        parent[i] = (int32_t)i;
+// Every vertex starts under the smaller of itself and its first neighbour (the
+// smallest one: rows are ascending), a plain store per vertex.  In a
+// connected power-law graph stored by degree that already hangs most
+// vertices under vertex 0, two or three steps up.
+__global__ void k_hook_first(int64_t n, const int64_t *__restrict__ row_ptr, const int32_t *__restrict__ col,
+                             int32_t *__restrict__ parent) {
+    for (int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; i < n; i += (int64_t)gridDim.x * blockDim.x) {
+        const int64_t b = row_ptr[i];
+        parent[i] = row_ptr[i + 1] > b ? min((int32_t)i, col[b]) : (int32_t)i;
+    }
+}
+
+// Parent of x as this workgroup may see it: a load that the vector L1 and the
+// XCD's L2 serve, so that the many lookups of one popular root stay on the
+// chip (the same loads with device scope go to the memory side, where a
+// million reads of one address are answered one after another).  It can be
+// an older value: that is still a vertex of the same tree, smaller than x.
+__device__ __forceinline__ int32_t uf_seen(const int32_t *parent, int32_t x) {
+    return __hip_atomic_load(&parent[x], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
 }
 
 // Root of x, halving the path on the way: x is pointed at its grandparent
 // with atomicMin.  Ids decrease along every path, so the smaller of two
 // ancestors is the one nearer the root: a halving never moves a vertex away
 // from its root, whatever other halvings or final writes it races with.
+// The first UF_NEAR steps read cached values; a longer path (a chain of
+// vertices) is followed with device scope, where it sees the other
+// threads' halvings.  Vertex 0 is a root whatever happens.  The answer can be
+// a vertex that has been joined since; joins confirm it (uf_union).
+constexpr int UF_NEAR = 8;
+
 __device__ __forceinline__ int32_t uf_root(int32_t *parent, int32_t x) {
+    for (int t = 0; t < UF_NEAR; ++t) {
+        const int32_t px = uf_seen(parent, x);
+        if (px == x || px == 0) return px;
+        x = px;
+    }
     int32_t px = __hip_atomic_load(&parent[x], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-    while (px != x) {
+    while (px != x && px != 0) {
         const int32_t ppx = __hip_atomic_load(&parent[px], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
         if (ppx != px) atomicMin(&parent[x], ppx);
         x = px;
         px = ppx;
     }
-    return x;
+    return px;
 }
 
-// Join the trees of a and b: the larger root goes under the smaller; a
-// failed compare-and-swap means that root was just joined elsewhere, and
-// the roots are looked up again.
+// Join the trees of a and b: the larger root goes under the smaller.  The
+// compare-and-swap succeeds only on a vertex that is a root at that moment
+// (the smaller vertex may be an inner one of its tree: the larger root then
+// hangs below it); a failed one returns the vertex the larger was joined to,
+// which is smaller, and the lookup goes on from there, so the loop ends.
 __device__ __forceinline__ void uf_union(int32_t *parent, int32_t a, int32_t b) {
     for (;;) {
         a = uf_root(parent, a);
@@ -363,48 +392,69 @@ __device__ __forceinline__ void uf_union(int32_t *parent, int32_t a, int32_t b) 
             a = b;
             b = t;
         }
-        if (atomicCAS(&parent[b], b, a) == b) return;
+        const int32_t was = atomicCAS(&parent[b], b, a);
+        if (was == b) return;
+        b = was;
     }
 }
 
-// Joins in two passes (the sampling idea of Afforest, Sutton et al., 2018):
-// first the first UF_FIRST entries of every row, which in a connected
-// power-law graph already gather most vertices under the root of vertex 0
-// (its component's smallest id); then the remaining entries of every row
-// whose root is not 0 at that moment.  A skipped row's vertex is joined to
-// 0, and any edge from it to a vertex outside 0's tree is taken from that
-// vertex's own row, which is not skipped, so every component is found.
-constexpr int UF_FIRST = 2;
+// Every vertex points at its root (atomicMin: the root is the smallest
+// ancestor, so a late halving by another thread cannot replace it).  Between
+// the joins the root may be out of date, which is harmless; after the last
+// join's kernel it is the tree's.
+__global__ void k_flatten(int64_t n, int32_t *__restrict__ parent) {
+    for (int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; i < n; i += (int64_t)gridDim.x * blockDim.x) {
+        const int32_t p = uf_seen(parent, (int32_t)i);
+        if (p == (int32_t)i || p == 0) continue;
+        const int32_t r = uf_root(parent, p);
+        if (r != p) atomicMin(&parent[i], r);
+    }
+}
 
-__global__ void k_union_first(int64_t n, const int64_t *__restrict__ row_ptr, const int32_t *__restrict__ col,
+// Joins in two passes (the sampling idea of Afforest, Sutton et al., 2018)
+// after k_hook_first: the first UF_ROOT entries of every vertex that hooked
+// nowhere, then all entries of the rows whose root is not 0 at that moment.
+// A skipped row's vertex is joined to 0, and any edge from it to a vertex
+// outside 0's tree is taken from that vertex's own row, which is not skipped,
+// so every component is found.  Only the roots join in the first pass, each
+// mostly moving itself: had every vertex of a hub's tree joined its own
+// second entry, all of them would have tried the same compare-and-swap on the
+// hub (n = 2^20, m = 16M by degree: 1.57 ms of it).
+constexpr int64_t UF_ROOT = 4;
+
+__global__ void k_union_roots(int64_t n, const int64_t *__restrict__ row_ptr, const int32_t *__restrict__ col,
                               int32_t *__restrict__ parent) {
     for (int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; i < n; i += (int64_t)gridDim.x * blockDim.x) {
-        const int64_t b = row_ptr[i], e = min(row_ptr[i + 1], b + UF_FIRST);
+        if (i == 0 || uf_seen(parent, (int32_t)i) != (int32_t)i) continue;
+        const int64_t b = row_ptr[i], e = min(row_ptr[i + 1], b + UF_ROOT);
         for (int64_t p = b; p < e; ++p) uf_union(parent, (int32_t)i, col[p]);
     }
 }
 
-// One wave per row: the entries after the first UF_FIRST, unless the row's
-// vertex already hangs under 0.
-__global__ void k_union_rest(int64_t n, const int64_t *__restrict__ row_ptr, const int32_t *__restrict__ col,
-                             int32_t *__restrict__ parent) {
+// All entries of the remaining rows (an entry joined before finds its two
+// roots equal): a wave finds the rows of its 64 that do not hang under 0 and
+// walks each of them with all its lanes.
+__global__ __launch_bounds__(PBLOCK) void k_union_rest(int64_t n, const int64_t *__restrict__ row_ptr,
+                                                       const int32_t *__restrict__ col, int32_t *__restrict__ parent) {
     const int lane = threadIdx.x & (WAVE - 1);
     const int64_t nw = (int64_t)gridDim.x * (PBLOCK / WAVE);
-    for (int64_t i = (int64_t)blockIdx.x * (PBLOCK / WAVE) + (threadIdx.x >> 6); i < n; i += nw) {
-        const int64_t b = row_ptr[i] + UF_FIRST, b1 = row_ptr[i + 1];
-        if (b >= b1) continue;                                    // uniform across the wave
-        int32_t r = 0;
-        if (lane == 0) r = uf_root(parent, (int32_t)i);
-        if (shfl(r, 0) == 0) continue;
-        for (int64_t p = b + lane; p < b1; p += WAVE) uf_union(parent, (int32_t)i, col[p]);
+    for (int64_t base = ((int64_t)blockIdx.x * (PBLOCK / WAVE) + (threadIdx.x >> 6)) * WAVE; base < n;
+         base += nw * WAVE) {
+        const int64_t mine = base + lane;
+        int64_t b = 0, e = 0;
+        if (mine < n && uf_seen(parent, (int32_t)mine) != 0) {
+            b = row_ptr[mine];
+            e = row_ptr[mine + 1];
+        }
+        unsigned long long todo = __ballot(b < e);
+        while (todo) {
+            const int t = __ffsll((long long)todo) - 1;
+            todo &= todo - 1;
+            const int64_t i = base + t, b0 = shfl(b, t), b1 = shfl(e, t);
+            if (shfl(uf_seen(parent, (int32_t)i), t) == 0) continue;      // joined to 0 meanwhile
+            for (int64_t p = b0 + lane; p < b1; p += WAVE) uf_union(parent, (int32_t)i, col[p]);
+        }
     }
-}
-
-// Every vertex points at the root of its tree (atomicMin: the root is the
-// smallest ancestor, so a late halving by another thread cannot replace it).
-__global__ void k_flatten(int64_t n, int32_t *__restrict__ parent) {
-    for (int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; i < n; i += (int64_t)gridDim.x * blockDim.x)
-        atomicMin(&parent[i], uf_root(parent, (int32_t)i));
 }
 
 __global__ void k_count_roots(int64_t n, const int32_t *__restrict__ parent, unsigned long long *__restrict__ cnt) {
@@ -563,27 +613,36 @@ static size_t prop_layout(const ad_graph *g, void *ws, size_t ws_bytes, PropLayo
     return c.ok() ? c.used : 0;
 }
 
-// Connected components by union-find: the entries (i, j) join the trees of
-// i and j (k_union_first, then k_union_rest for the rows not yet under 0),
-// hanging the larger root under the smaller with a compare-and-swap, then
-// every vertex is pointed at its root.  Parent ids only ever decrease (a
-// parent is always smaller than its child), so the trees have no cycles,
-// every root search ends, and each component's root is its smallest vertex
-// whatever the order of the joins.  flags is unused.  No host round trips.
+// Connected components by union-find: every vertex starts under its smallest
+// neighbour (k_hook_first), the other entries (i, j) join the trees of i and j
+// (k_union_roots, k_union_rest for the rows not yet under 0), hanging the
+// larger root under the smaller with a compare-and-swap, then every vertex
+// is pointed at its root.  A parent is always smaller than its child, so the
+// trees have no cycles, every root search ends, and each component's root is
+// its smallest vertex whatever the order of the joins.  flags is unused.  No
+// host round trips.
+// Bound by the dependent parent lookups.  n = 2^20, m = 16M stored by degree:
+// 2.3 ms with the first two entries of every row joined by compare-and-swap
+// and every lookup at device scope (2.1 ms of it one address, the hub's),
+// 0.035 ms here (six launches).
 ad_status label_components(const ad_graph *g, int32_t *parent, unsigned int *flags, hipStream_t stream) {
     (void)flags;
     const int64_t n = g->n;
-    const unsigned wgrid = (unsigned)std::max<int64_t>(1, std::min<int64_t>(4096, ceil_div(n, PBLOCK / WAVE)));
-    hipLaunchKernelGGL(k_parent_init, dim3(pgrid(n)), dim3(PBLOCK), 0, stream, n, parent);
-    AD_LAUNCH_CHECK("k_parent_init");
+    hipLaunchKernelGGL(k_hook_first, dim3(pgrid(n)), dim3(PBLOCK), 0, stream, n, g->row_ptr, g->col, parent);
+    AD_LAUNCH_CHECK("k_hook_first");
     if (g->m > 0) {
-        hipLaunchKernelGGL(k_union_first, dim3(pgrid(n)), dim3(PBLOCK), 0, stream, n, g->row_ptr, g->col, parent);
-        AD_LAUNCH_CHECK("k_union_first");
-        hipLaunchKernelGGL(k_union_rest, dim3(wgrid), dim3(PBLOCK), 0, stream, n, g->row_ptr, g->col, parent);
+        hipLaunchKernelGGL(k_flatten, dim3(pgrid(n)), dim3(PBLOCK), 0, stream, n, parent);
+        AD_LAUNCH_CHECK("k_flatten");
+        hipLaunchKernelGGL(k_union_roots, dim3(pgrid(n)), dim3(PBLOCK), 0, stream, n, g->row_ptr, g->col, parent);
+        AD_LAUNCH_CHECK("k_union_roots");
+        hipLaunchKernelGGL(k_flatten, dim3(pgrid(n)), dim3(PBLOCK), 0, stream, n, parent);
+        AD_LAUNCH_CHECK("k_flatten");
+        hipLaunchKernelGGL(k_union_rest, dim3((unsigned)std::max<int64_t>(1, std::min<int64_t>(4096, ceil_div(n, PBLOCK)))),
+                           dim3(PBLOCK), 0, stream, n, g->row_ptr, g->col, parent);
         AD_LAUNCH_CHECK("k_union_rest");
+        hipLaunchKernelGGL(k_flatten, dim3(pgrid(n)), dim3(PBLOCK), 0, stream, n, parent);
+        AD_LAUNCH_CHECK("k_flatten");
     }
-    hipLaunchKernelGGL(k_flatten, dim3(pgrid(n)), dim3(PBLOCK), 0, stream, n, parent);
-    AD_LAUNCH_CHECK("k_flatten");
     return AD_OK;
 }
 

@@ -1,0 +1,69 @@
+"""Kernels at the sizes where they can go wrong: edges of tiles and chunks,
+remainders, the smallest and largest sizes of a path.  Results that are whole
+numbers equal the oracle's; others carry the tolerance stated with the test.
+"""
+import numpy as np
+import pytest
+
+import oracle
+from paper_1601_05527_amd import graphs as G
+
+from gpu_helpers import announce
+
+pytestmark = pytest.mark.gpu
+
+torch = pytest.importorskip("torch")
+
+
+@pytest.fixture(scope="module")
+def api():
+    from paper_1601_05527_amd import api as _api
+    return _api
+
+
+def _np(t):
+    return t.detach().cpu().numpy()
+
+
+# ------------------------------------------------------------- components --
+
+def _component_graph(kind):
+    rng = np.random.default_rng(5)
+    if kind == "star-hub-last":                      # no vertex hangs under 0 but through the hub
+        n = 70_001
+        return G.from_edges(n, np.arange(n - 1), np.full(n - 1, n - 1))
+    if kind == "giant-without-0":                    # vertex 0 isolated, a random graph on the rest
+        u, v = rng.integers(1, 20_000, 60_000), rng.integers(1, 20_000, 60_000)
+        key = np.unique(np.minimum(u, v) * 20_000 + np.maximum(u, v))
+        key = key[key // 20_000 != key % 20_000]
+        return G.from_edges(20_000, key // 20_000, key % 20_000)
+    if kind == "tree":                               # a random tree under random labels
+        n = 50_000
+        parent = np.array([0] + [rng.integers(max(0, i - 7), i) for i in range(1, n)])
+        p = rng.permutation(n)
+        return G.from_edges(n, p[np.arange(1, n)], p[parent[1:]])
+    if kind == "pairs":                              # thousands of two-vertex components
+        n = 12_346
+        p = rng.permutation(n)
+        return G.from_edges(n, p[0::2], p[1::2])
+    # a chain of cliques: long paths of joins between hubs of equal degree
+    us, vs = [], []
+    for c in range(600):
+        a, b = np.triu_indices(9, 1)
+        us.append(9 * c + a)
+        vs.append(9 * c + b)
+        if c:
+            us.append(np.array([9 * c - 1]))
+            vs.append(np.array([9 * c]))
+    g = G.from_edges(9 * 600, np.concatenate(us), np.concatenate(vs))
+    return G.relabel(g, rng.permutation(g.n))
+
+
+@pytest.mark.parametrize("kind", ["star-hub-last", "giant-without-0", "tree", "pairs", "cliques"])
+def test_component_labels(api, kind):
+    announce(f"component labels {kind}")
+    g = _component_graph(kind)
+    ref = oracle.properties(g.n, g.row_ptr, g.col)
+    got = api.graph_properties(api.DeviceGraph.from_host(g, "cuda"))
+    np.testing.assert_array_equal(_np(got["comp"]), ref["comp"])
+    assert got["n_components"] == ref["n_components"]
