@@ -67,3 +67,21 @@ def test_component_labels(api, kind):
     got = api.graph_properties(api.DeviceGraph.from_host(g, "cuda"))
     np.testing.assert_array_equal(_np(got["comp"]), ref["comp"])
     assert got["n_components"] == ref["n_components"]
+
+
+# ------------------------------------------------------------------ batch --
+
+@pytest.mark.parametrize("sizes", [(16384, 1, 16383, 15, 17, 16385), (3, 5, 7, 40_000, 2), (32768,)])
+def test_batch_counts_at_chunk_edges(api, sizes):
+    """Kept counts of graphs whose edge ranges start and end at, before and
+    after the counting kernel's chunks of 16,384 edges."""
+    announce(f"batch counts {sizes}")
+    dgs = [api.DeviceGraph.from_host(G.gnm(m // 3, m, q) if m > 20 else
+                                     G.from_edges(m + 1, np.arange(m), np.arange(1, m + 1)), "cuda")
+           for q, m in enumerate(sizes)]
+    b = api.Batch(dgs, 4, 5, seed=1, e=0.4, autotune=False)
+    b.run()
+    _, keep, n_kept, _ = [_np(t) for t in b.fetch()]
+    for q in range(len(sizes)):
+        assert n_kept[q] == keep[b.edge_off[q]:b.edge_off[q + 1]].sum(), q
+    b.close()
