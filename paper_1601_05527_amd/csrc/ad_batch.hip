@@ -45,7 +45,7 @@ __global__ void k_fill_graph(int64_t count, int32_t g, int32_t *__restrict__ dst
 // consecutive edges, sums each graph's share of them and adds it with one
 // atomic per graph it meets.  Streaming: one byte per edge; an atomic per wave
 // of 64 edges instead would queue at the memory side, thousands on one
-// graph's counter (64 graphs, 21M edges: 2,480 us that way, 16 us here).
+// graph's counter (64 graphs, 31M edges: 2,480 us that way, 16 us here).
 constexpr int64_t COUNT_EDGES = 16384;
 
 __global__ __launch_bounds__(TB) void k_count_per_graph(int64_t m, const uint8_t *__restrict__ keep,

@@ -14,8 +14,8 @@
 // workgroup per row sized to the row: a radix sort of the distance bits, or,
 // for a caller's own 64-bit keys, counting inside one wave (<= 512) and a
 // bitonic network (<= 8192).  Longer rows are cut into buckets by a sorted
-// sample and rank inside their bucket.  FP64 distances above 64 count
-// against keys read from memory.
+// sample and rank inside their bucket.  FP64 distances take the same sorts
+// and buckets on 64-bit codes.
 //
 // Selection at fixed e: entry (i, j) selects its edge when rank < budget[d_i];
 // keep[e] = 1 is written by any selecting entry (all writers store the same
@@ -44,8 +44,8 @@ namespace ad {
 
 constexpr int SBLOCK = 256;
 constexpr int NCLASS = 8;            // degree classes above 64 (see CLASS_LO)
-constexpr int HUB_CLASS = 7;         // FP32 rows of class >= HUB_CLASS take the bucket partition
-constexpr int SORT_CAP = 8192;       // longest FP32 row ranked in one wave or one LDS sort
+constexpr int HUB_CLASS = 7;         // rows of class >= HUB_CLASS take the bucket partition
+constexpr int SORT_CAP = 8192;       // longest row ranked in one wave or one LDS sort
 constexpr int DIST_UNROLL = 8;       // entries per slot in flight in the distance pass (FP32 vectors)
 
 // Entries per slot in flight: FP64 vectors hold twice the registers per entry.
@@ -723,22 +723,44 @@ __global__ __launch_bounds__(TB) void k_rank_bitonic(
 // Largest sort key of a real entry: padding (0xffffffff) must sort after
 // every entry, so the one bit pattern that could equal it (a negative NaN)
 // is clamped below it; valid distances (>= 0) are far below.
+// FP64 distances sort on 64-bit codes that order as the values compare
+// (negative values included, -0 as +0).  A NaN compares with nothing: its
+// code sorts behind every value's, so no value counts it as smaller, and it
+// takes rank 0 in the LOCAL order and rank d in the GLOBAL one, as counting
+// comparisons would give it.
 constexpr uint32_t KEY_LAST = 0xfffffffeu;
+constexpr unsigned long long KEY_NAN = ~0ull - 1;
 
-template <int TB, int IPT>
+template <typename Tr> struct rank_code_of { typedef uint32_t type; };
+template <> struct rank_code_of<double> { typedef unsigned long long type; };
+__device__ __forceinline__ uint32_t rank_code(float r) { return min(__float_as_uint(r), KEY_LAST); }
+__device__ __forceinline__ unsigned long long rank_code(double r) {
+    return r == r ? ord_encode(r + 0.0) : KEY_NAN;
+}
+__device__ __forceinline__ bool rank_code_nan(uint32_t) { return false; }
+__device__ __forceinline__ bool rank_code_nan(unsigned long long k) { return k == KEY_NAN; }
+
+// What bounds it: the sort's LDS passes (four digits of a 32-bit code, eight
+// of a 64-bit one) and the scattered records.  FP64 rows were counted
+// against keys read from memory before, d comparisons per entry and three
+// loads for each: n = 2^16, m = 500,000 (d up to about 1,000), all rows above
+// 64: 1,533 us counted, about 110 us sorted.
+template <int TB, int IPT, typename Tr = float>
 __global__ __launch_bounds__(TB) void k_rank_radix(
     const int32_t *__restrict__ list, const unsigned int *__restrict__ count,
     const int64_t *__restrict__ row_ptr, const int32_t *__restrict__ col,
     const int32_t *__restrict__ eid, const int32_t *__restrict__ orig_id,
-    const int32_t *__restrict__ col_orig, const float *__restrict__ rho, const float *__restrict__ rho_ent, Emit em,
+    const int32_t *__restrict__ col_orig, const Tr *__restrict__ rho, const Tr *__restrict__ rho_ent, Emit em,
     int slice, int nslices) {
     constexpr int P = TB * IPT;
     static_assert(P <= 65536, "places are 16-bit");
-    using Sorter = rocprim::block_radix_sort<uint32_t, TB, IPT, uint16_t>;
+    typedef typename rank_code_of<Tr>::type K;
+    constexpr K PAD = ~(K)0;
+    using Sorter = rocprim::block_radix_sort<K, TB, IPT, uint16_t>;
     __shared__ union {
         typename Sorter::storage_type sort;
         struct {
-            uint32_t key[P];
+            K key[P];
             uint32_t rank[P];                        // both ranks of entry q of the row, 16 bits each
             uint16_t place[P];
         } row;
@@ -751,13 +773,13 @@ __global__ __launch_bounds__(TB) void k_rank_radix(
         const int d = (int)(row_ptr[row + 1] - beg);
         // striped load (item s of thread t is entry s * TB + t); places past d
         // carry the largest key and sort last
-        uint32_t k[IPT];
+        K k[IPT];
         uint16_t v[IPT];
         if (rho_ent) {                               // distances in entry order: contiguous
 #pragma unroll
             for (int s = 0; s < IPT; ++s) {
                 const int q = s * TB + (int)threadIdx.x;
-                k[s] = q < d ? min(__float_as_uint(rho_ent[beg + q]), KEY_LAST) : 0xffffffffu;
+                k[s] = q < d ? rank_code(rho_ent[beg + q]) : PAD;
                 v[s] = (uint16_t)q;
             }
         } else {
@@ -770,7 +792,7 @@ __global__ __launch_bounds__(TB) void k_rank_radix(
 #pragma unroll
             for (int s = 0; s < IPT; ++s) {
                 const int q = s * TB + (int)threadIdx.x;
-                k[s] = q < d ? min(__float_as_uint(rho[e[s]]), KEY_LAST) : 0xffffffffu;
+                k[s] = q < d ? rank_code(rho[e[s]]) : PAD;
                 v[s] = (uint16_t)q;
             }
         }
@@ -792,7 +814,11 @@ __global__ __launch_bounds__(TB) void k_rank_radix(
             const int q = (int)threadIdx.x * IPT + s;
             if (q >= d) continue;
             uint32_t rk = (uint32_t)q | ((uint32_t)(d - 1 - q) << 16);
-            const uint32_t key = k[s];
+            const K key = k[s];
+            if (rank_code_nan(key)) {
+                sh.row.rank[v[s]] = (uint32_t)d << 16;
+                continue;
+            }
             const bool tie = (q > 0 && sh.row.key[q - 1] == key) || (q + 1 < d && sh.row.key[q + 1] == key);
             if (tie) {
                 int a = 0, hi = q;                        // first place with this key
@@ -832,40 +858,7 @@ __global__ __launch_bounds__(TB) void k_rank_radix(
     }
 }
 
-// Listed rows ranked by counting against keys read from memory (FP64
-// distances with d > 64).
-template <typename Tr>
-__global__ __launch_bounds__(SBLOCK) void k_rank_count(
-    const int32_t *__restrict__ list, const unsigned int *__restrict__ count,
-    const int64_t *__restrict__ row_ptr, const int32_t *__restrict__ col,
-    const int32_t *__restrict__ eid, const int32_t *__restrict__ orig_id,
-    const int32_t *__restrict__ col_orig, const Tr *__restrict__ rho, Emit em) {
-    const unsigned int nr = *count;
-    for (unsigned int h = blockIdx.x; h < nr; h += gridDim.x) {
-        const int64_t row = list[h];
-        const int64_t beg = row_ptr[row];
-        const int64_t d = row_ptr[row + 1] - beg;
-        for (int64_t t = threadIdx.x; t < d; t += SBLOCK) {
-            const int32_t j = col[beg + t];
-            const int32_t e = eid[beg + t];
-            const Tr r = rho[e];
-            const int32_t id = nbr_id(beg + t, j, col_orig, orig_id);
-            int64_t lt = 0, eq = 0, eqlt = 0;
-            for (int64_t u = 0; u < d; ++u) {
-                const int32_t ju = col[beg + u];
-                const Tr ru = rho[eid[beg + u]];
-                const int32_t iu = nbr_id(beg + u, ju, col_orig, orig_id);
-                lt += (ru < r) ? 1 : 0;
-                eq += (ru == r) ? 1 : 0;
-                eqlt += (ru == r && iu < id) ? 1 : 0;
-            }
-            emit_ranks(em, row, j, e, d, lt + eqlt, d - lt - eq + eqlt);
-        }
-    }
-}
-
-// Rows longer than SORT_CAP (FP32 distances): bucket partition, then one
-// wave per bucket.  A workgroup per row sorts a regular sample of the row's
+// Rows longer than SORT_CAP: bucket partition, then one wave per bucket.  A workgroup per row sorts a regular sample of the row's
 // keys in LDS; runs of consecutive sorted samples delimit the buckets,
 // whose sizes are counted and scanned, and the row's entries are scattered
 // to their bucket's range of a scratch copy (key and offset in the row).  An
@@ -944,22 +937,24 @@ __device__ __forceinline__ int hub_upper(const K *samp, int S, K k) {
 
 // Key of entry p for the bucket partition: 64-bit (rho, id) or caller keys
 // of one orientation, or, with K = uint32_t, the 32-bit distance bits alone
-// (both orientations from one partition: equal distances share a bucket).
-template <typename K>
-__device__ __forceinline__ K hub_key(const unsigned long long *__restrict__ keys, const float *__restrict__ rho,
-                                     const float *__restrict__ rho_ent, int64_t p, const int32_t *__restrict__ eid,
+// (both orientations from one partition: equal distances share a bucket);
+// for FP64 distances (Tr double) their 64-bit codes, both orientations too.
+template <typename K, typename Tr>
+__device__ __forceinline__ K hub_key(const unsigned long long *__restrict__ keys, const Tr *__restrict__ rho,
+                                     const Tr *__restrict__ rho_ent, int64_t p, const int32_t *__restrict__ eid,
                                      const int32_t *__restrict__ col, const int32_t *__restrict__ col_orig,
                                      const int32_t *__restrict__ orig_id, int orient) {
-    if constexpr (sizeof(K) == 4) return __float_as_uint(rho_ent ? rho_ent[p] : rho[eid[p]]);
+    if constexpr (sizeof(Tr) == 8) return rank_code(rho[eid[p]]);
+    else if constexpr (sizeof(K) == 4) return __float_as_uint(rho_ent ? rho_ent[p] : rho[eid[p]]);
     else return entry_key(keys, rho, p, eid[p], nbr_id(p, col[p], col_orig, orig_id), orient);
 }
 
-template <typename K>
+template <typename K, typename Tr = float>
 __global__ __launch_bounds__(HUB_TB) void k_hub_partition(
     const int32_t *__restrict__ list, const unsigned int *__restrict__ count,
     const int64_t *__restrict__ row_ptr, const int32_t *__restrict__ col,
     const int32_t *__restrict__ eid, const int32_t *__restrict__ orig_id,
-    const int32_t *__restrict__ col_orig, const float *__restrict__ rho, const float *__restrict__ rho_ent,
+    const int32_t *__restrict__ col_orig, const Tr *__restrict__ rho, const Tr *__restrict__ rho_ent,
     const unsigned long long *__restrict__ keys, int orient, HubScratch hs) {
     __shared__ K samp[HUB_SAMPLE];
     __shared__ uint32_t cnt[HUB_MAX_B];
@@ -977,7 +972,7 @@ __global__ __launch_bounds__(HUB_TB) void k_hub_partition(
         const int B = (int)min((int64_t)(S / HUB_MIN_SP), (d + HUB_BUCKET - 1) / HUB_BUCKET);
         for (int t = threadIdx.x; t < S; t += HUB_TB) {
             const int64_t p = beg + ((int64_t)t * d) / S;
-            samp[t] = hub_key<K>(keys, rho, rho_ent, p, eid, col, col_orig, orig_id, orient);
+            samp[t] = hub_key<K, Tr>(keys, rho, rho_ent, p, eid, col, col_orig, orig_id, orient);
         }
         for (int b = threadIdx.x; b < B; b += HUB_TB) cnt[b] = 0;
         __syncthreads();
@@ -998,7 +993,7 @@ __global__ __launch_bounds__(HUB_TB) void k_hub_partition(
         }
         for (int64_t q = threadIdx.x; q < d; q += HUB_TB) {
             const int64_t p = beg + q;
-            const K k = hub_key<K>(keys, rho, rho_ent, p, eid, col, col_orig, orig_id, orient);
+            const K k = hub_key<K, Tr>(keys, rho, rho_ent, p, eid, col, col_orig, orig_id, orient);
             atomicAdd(&cnt[min(B - 1, hub_upper(samp, S, k) * B / S)], 1u);
             // 32-bit keys: kept at the entry's own place for the scatter pass
             // (one gather of the distance per entry instead of two)
@@ -1029,7 +1024,7 @@ __global__ __launch_bounds__(HUB_TB) void k_hub_partition(
                 const uint32_t at = atomicAdd(&cnt[min(B - 1, hub_upper(samp, S, k) * B / S)], 1u);
                 hs.key[beg + at] = ((unsigned long long)k << 32) | (uint32_t)q;
             } else {
-                const K k = hub_key<K>(keys, rho, rho_ent, p, eid, col, col_orig, orig_id, orient);
+                const K k = hub_key<K, Tr>(keys, rho, rho_ent, p, eid, col, col_orig, orig_id, orient);
                 const uint32_t at = atomicAdd(&cnt[min(B - 1, hub_upper(samp, S, k) * B / S)], 1u);
                 hs.key[beg + at] = (unsigned long long)k;
                 hs.pos[beg + at] = (uint32_t)q;
@@ -1177,6 +1172,86 @@ __global__ __launch_bounds__(SBLOCK) void k_hub_rank32(
                         hs.pos[p] = (uint32_t)rl;
                     }
                 }
+            }
+        }
+    }
+}
+
+// The same for a partition on the 64-bit codes of FP64 distances: keys in
+// hs.key, places in hs.pos, every entry emitted here (a NaN with the ranks
+// k_rank_radix gives it).
+__global__ __launch_bounds__(SBLOCK) void k_hub_rank64(
+    const int64_t *__restrict__ row_ptr, const int32_t *__restrict__ col, const int32_t *__restrict__ eid,
+    const int32_t *__restrict__ orig_id, const int32_t *__restrict__ col_orig, Emit em, HubScratch hs) {
+    constexpr int KPL = HUB_KPL / 2;
+    const int lane = threadIdx.x & (WAVE - 1);
+    const unsigned int nb = (unsigned int)min((int64_t)(*hs.nbk), hs.cap);
+    const unsigned int waves = gridDim.x * (SBLOCK / WAVE);
+    for (unsigned int w = blockIdx.x * (SBLOCK / WAVE) + (threadIdx.x >> 6); w < nb; w += waves) {
+        const uint32_t c = hs.bk_cnt[w];
+        const int64_t row = hs.bk_row[w];
+        const int64_t beg = row_ptr[row];
+        const int64_t d = row_ptr[row + 1] - beg;
+        const uint32_t off = hs.bk_off[w];
+        const unsigned long long *bk = hs.key + beg + off;
+        const uint32_t *bp = hs.pos + beg + off;
+        for (uint32_t c0 = 0; c0 < c; c0 += KPL * WAVE) {
+            unsigned long long key[KPL];
+            int64_t pos[KPL];
+            int32_t id[KPL];
+            int lt[KPL], eq[KPL], eqlt[KPL];
+            bool tie = false;
+#pragma unroll
+            for (int t = 0; t < KPL; ++t) {
+                const uint32_t q = c0 + t * WAVE + lane;
+                key[t] = q < c ? bk[q] : 0ull;
+                pos[t] = q < c ? beg + bp[q] : beg;
+                lt[t] = eq[t] = eqlt[t] = id[t] = 0;
+            }
+            for (uint32_t s0 = 0; s0 < c; s0 += WAVE) {
+                const unsigned long long mine = (s0 + lane < c) ? bk[s0 + lane] : 0ull;
+                const int lim = (int)min((uint32_t)WAVE, c - s0);
+                for (int src = 0; src < lim; ++src) {
+                    const unsigned long long kb = shfl(mine, src);
+#pragma unroll
+                    for (int t = 0; t < KPL; ++t) {
+                        lt[t] += (kb < key[t]) ? 1 : 0;
+                        eq[t] += (kb == key[t]) ? 1 : 0;
+                    }
+                }
+            }
+#pragma unroll
+            for (int t = 0; t < KPL; ++t) tie = tie || (c0 + t * WAVE + lane < c && eq[t] > 1);
+            if (__any(tie)) {                          // uniform across the wave
+#pragma unroll
+                for (int t = 0; t < KPL; ++t)
+                    if (c0 + t * WAVE + lane < c) id[t] = nbr_id(pos[t], col[pos[t]], col_orig, orig_id);
+                for (uint32_t s0 = 0; s0 < c; s0 += WAVE) {
+                    unsigned long long mine = 0ull;
+                    int32_t mid = 0;
+                    if (s0 + lane < c) {
+                        mine = bk[s0 + lane];
+                        const int64_t p = beg + bp[s0 + lane];
+                        mid = nbr_id(p, col[p], col_orig, orig_id);
+                    }
+                    const int lim = (int)min((uint32_t)WAVE, c - s0);
+                    for (int src = 0; src < lim; ++src) {
+                        const unsigned long long kb = shfl(mine, src);
+                        const int32_t ib = shfl(mid, src);
+#pragma unroll
+                        for (int t = 0; t < KPL; ++t) eqlt[t] += (kb == key[t] && ib < id[t]) ? 1 : 0;
+                    }
+                }
+            }
+#pragma unroll
+            for (int t = 0; t < KPL; ++t) {
+                if (c0 + t * WAVE + lane >= c) continue;
+                int64_t rl = (int64_t)off + lt[t] + eqlt[t], rg = d - (int64_t)off - lt[t] - eq[t] + eqlt[t];
+                if (rank_code_nan(key[t])) {
+                    rl = 0;
+                    rg = d;
+                }
+                emit_ranks(em, row, col[pos[t]], eid[pos[t]], d, rl, rg);
             }
         }
     }
@@ -1810,8 +1885,7 @@ struct SelLayout {
 };
 
 // Degree classes above 64: wave counting with 2/4/8 keys per lane, bitonic
-// sorts in LDS of 1024/2048/4096/8192 keys, then the bucket partition (FP32;
-// FP64 rows above 64 are counted from memory).
+// sorts in LDS of 1024/2048/4096/8192 keys, then the bucket partition.
 static const int64_t CLASS_LO[NCLASS + 1] = {64, 128, 256, 512, 1024, 2048, 4096, 8192, (int64_t)1 << 62};
 
 static size_t sel_layout(const ad_graph *g, void *ws, size_t ws_bytes, SelLayout *L, bool both = false) {
@@ -2124,7 +2198,7 @@ static ad_status rank_all(const ad_graph *g, const Tr *rho, const Emit &em, cons
                 for (int k = HUB_CLASS; k < NCLASS; ++k) {
                     if (g->d_max <= CLASS_LO[k]) break;
                     hipLaunchKernelGGL(k_hub_partition<unsigned long long>, dim3(512), dim3(HUB_TB), 0, cls[2], lst[k], &L.cnt[k],
-                                       g->row_ptr, g->col, g->eid, g->orig_id, g->col_orig, rf, nullptr, keys,
+                                       g->row_ptr, g->col, g->eid, g->orig_id, g->col_orig, rf, (const float *)nullptr, keys,
                                        one.orient, L.hub);
                     AD_LAUNCH_CHECK("k_hub_partition");
                 }
@@ -2141,11 +2215,32 @@ static ad_status rank_all(const ad_graph *g, const Tr *rho, const Emit &em, cons
             }
         }
     } else {
-        for (int k = 0; k < NCLASS; ++k) {
-            if (g->d_max <= CLASS_LO[k]) break;
-            hipLaunchKernelGGL((k_rank_count<Tr>), dim3(grid), dim3(SBLOCK), 0, st, lst[k], &L.cnt[k],
-                               g->row_ptr, g->col, g->eid, g->orig_id, g->col_orig, rho, em);
-            AD_LAUNCH_CHECK("k_rank_count");
+        // FP64 rows: the same sorts on 64-bit codes, every class on the caller's stream
+        const double *rd = (const double *)rho;
+        const unsigned grid_w = (unsigned)std::min<int64_t>(8192, n);
+#define AD_RANK_D(TB, IPT, GRID, K)                                                                            \
+    if (g->d_max > CLASS_LO[K])                                                                                \
+    hipLaunchKernelGGL((k_rank_radix<TB, IPT, double>), dim3(GRID), dim3(TB), 0, st, lst[K], &L.cnt[K], g->row_ptr, \
+                       g->col, g->eid, g->orig_id, g->col_orig, rd, (const double *)nullptr, em, 0, 1)
+        AD_RANK_D(512, 16, grid, 6);
+        AD_RANK_D(512, 8, grid, 5);
+        AD_RANK_D(256, 8, grid, 4);
+        AD_RANK_D(256, 4, grid, 3);
+        AD_RANK_D(64, 8, grid_w, 2);
+        AD_RANK_D(64, 4, grid_w, 1);
+        AD_RANK_D(64, 2, grid_w, 0);
+#undef AD_RANK_D
+        AD_LAUNCH_CHECK("k_rank_radix");
+        if (g->d_max > SORT_CAP) {
+            s = fill_i32((int32_t *)L.hub.nbk, 0, 1, st);
+            if (s != AD_OK) return s;
+            hipLaunchKernelGGL((k_hub_partition<unsigned long long, double>), dim3(512), dim3(HUB_TB), 0, st,
+                               lst[HUB_CLASS], &L.cnt[HUB_CLASS], g->row_ptr, g->col, g->eid, g->orig_id, g->col_orig,
+                               rd, (const double *)nullptr, (const unsigned long long *)nullptr, em.orient, L.hub);
+            AD_LAUNCH_CHECK("k_hub_partition");
+            hipLaunchKernelGGL(k_hub_rank64, dim3(2048), dim3(SBLOCK), 0, st, g->row_ptr, g->col, g->eid, g->orig_id,
+                               g->col_orig, em, L.hub);
+            AD_LAUNCH_CHECK("k_hub_rank64");
         }
     }
     return AD_OK;

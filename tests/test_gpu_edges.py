@@ -85,3 +85,62 @@ def test_batch_counts_at_chunk_edges(api, sizes):
     for q in range(len(sizes)):
         assert n_kept[q] == keep[b.edge_off[q]:b.edge_off[q + 1]].sum(), q
     b.close()
+
+
+# --------------------------------------------------- FP64 distances ranked --
+
+def _counted_ranks(g, rho, i):
+    """(LOCAL, GLOBAL) ranks of row i's entries by counting comparisons (a NaN
+    compares with nothing), ties by the neighbour's id."""
+    p = slice(g.row_ptr[i], g.row_ptr[i + 1])
+    r, ids = rho[g.eid[p]], g.orig_id[g.col[p]]
+    d = len(r)
+    order = np.argsort(r, kind="stable")
+    s = r[order]
+    n_num = d - int(np.isnan(r).sum())
+    lt = np.searchsorted(s[:n_num], r, "left")
+    eq = np.searchsorted(s[:n_num], r, "right") - lt
+    eqlt = np.zeros(d, np.int64)
+    for k in np.nonzero(eq > 1)[0]:
+        eqlt[k] = np.sum((r == r[k]) & (ids < ids[k]))
+    lt[np.isnan(r)] = 0
+    eq[np.isnan(r)] = 0
+    return lt + eqlt, d - lt - eq + eqlt
+
+
+@pytest.mark.parametrize("values", ["distances", "quantised", "special"])
+def test_fp64_rows_of_every_length(api, values):
+    """FP64 selection on rows at the bounds of every sort and of the bucket
+    partition (up to 40,000 entries), with ties, and with infinities, signed
+    zeros, negative values and NaNs, against ranks counted on the host."""
+    announce(f"fp64 rows {values}")
+    rng = np.random.default_rng(8)
+    degs = [1, 2, 63, 64, 65, 128, 129, 256, 257, 512, 513, 1024, 1025, 2048, 2049, 4096, 4097, 8192, 8193, 12_000, 40_000]
+    us, vs, n = [], [], 0
+    leaf = len(degs)
+    for q, d in enumerate(degs):                       # stars, whose leaves are chained in threes
+        us.append(np.full(d, q))
+        vs.append(np.arange(leaf, leaf + d))
+        leaf += d
+    chain = np.arange(len(degs), leaf - 1)
+    chain = chain[chain % 3 != 0]
+    g = G.from_edges(leaf, np.concatenate(us + [chain]), np.concatenate(vs + [chain + 1]))
+    rho = rng.random(g.m)
+    if values == "quantised":
+        rho = np.round(rho, 2)
+    elif values == "special":
+        pick = rng.integers(0, 12, g.m)
+        for k, v in enumerate([np.nan, np.inf, -np.inf, 0.0, -0.0, -0.25]):
+            rho[pick == k] = v
+    dg = api.DeviceGraph.from_host(g, "cuda")
+    t = torch.from_numpy(rho).cuda()
+    for orient, e in ((0, 0.5), (1, 0.7)):
+        keep, nk = api.sparsify(dg, t, orient, e)
+        bud = api.budget_table(g.d_max, e)
+        ref = np.zeros(g.m, np.uint8)
+        for i in range(g.n):
+            p = slice(g.row_ptr[i], g.row_ptr[i + 1])
+            rank = _counted_ranks(g, rho, i)[orient]
+            ref[g.eid[p][rank < bud[p.stop - p.start]]] = 1
+        np.testing.assert_array_equal(_np(keep), ref)
+        assert int(nk.item()) == ref.sum()
