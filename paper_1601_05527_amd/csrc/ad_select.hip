@@ -493,69 +493,164 @@ __global__ __launch_bounds__(SBLOCK) void k_rank_packed(
     }
 }
 
-// Packing of rows with 1 <= degree <= 64 per tile of RANK_TILE rows: a wave
-// holds consecutive such rows (isolated rows ride along) while their entries
-// fit in 64 lanes; a longer row closes the wave.  fill == 0 counts waves per
-// tile, fill == 1 writes the plan entries at the scanned offsets.
-__global__ void k_rank_plan(int64_t n, const int64_t *__restrict__ row_ptr, int fill,
-                            unsigned int *__restrict__ tile_waves, long long *__restrict__ plan) {
-    const int64_t ntiles = ceil_div_dev(n, RANK_TILE);
-    for (int64_t t = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; t < ntiles;
-         t += (int64_t)gridDim.x * blockDim.x) {
-        const int64_t r0 = t * RANK_TILE, r1 = min(n, r0 + RANK_TILE);
-        unsigned int waves = 0;
-        unsigned int o = fill ? tile_waves[t] : 0;
-        int64_t first = -1;
-        int cur = 0, nr = 0;
-        for (int64_t r = r0; r < r1; ++r) {
-            const int64_t d = row_ptr[r + 1] - row_ptr[r];
-            const bool small = d <= WAVE;
-            if (first >= 0 && (!small || cur + d > WAVE)) {
-                if (fill && cur > 0) plan[o++] = ((long long)first << 8) | nr;
-                if (cur > 0) ++waves;
-                first = -1;
-            }
-            if (!small) continue;
-            if (first < 0) {
-                first = r;
-                cur = 0;
-                nr = 0;
-            }
-            cur += (int)d;
-            ++nr;
-        }
-        if (first >= 0 && cur > 0) {
-            if (fill) plan[o++] = ((long long)first << 8) | nr;
-            ++waves;
-        }
-        if (!fill) tile_waves[t] = waves;
-    }
-}
-
-// Rows with degree > 64 into per-class lists (class c holds rows with
-// lo[c] < d <= lo[c + 1]); one pass, atomic slots per class.
+// Rows with degree > 64 go to per-class lists: class c holds the rows with
+// 64 << c < d <= 128 << c, the last one all longer rows; its list starts at
+// off[c].
 struct ClassBounds {
-    int64_t lo[NCLASS + 1];
     int64_t off[NCLASS];
 };
 
-__global__ void k_classify(int64_t n, const int64_t *__restrict__ row_ptr, ClassBounds cb,
-                           int32_t *__restrict__ lists, unsigned int *__restrict__ counts) {
-    const int64_t stride = (int64_t)gridDim.x * blockDim.x;
-    const int64_t n_pad = ceil_div_dev(n, stride) * stride;
-    for (int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; i < n_pad; i += stride) {
-        int c = -1;
-        if (i < n) {
-            const int64_t d = row_ptr[i + 1] - row_ptr[i];
-            if (d > cb.lo[0]) {
-                c = 0;
-                while (c + 1 < NCLASS && d > cb.lo[c + 1]) ++c;
-            }
+// First kernel of a selection: every counter the call's kernels add to starts
+// at zero, keep[] too where they only set flags, and a fit's log tables
+// (logs[v] = log(v) for v = 1 .. nlogs - 1, logs[nlogs + v] = 1 / log(v) for
+// v >= 2) are filled.  One launch (about 4.6 us each, back to back, whatever
+// they do) instead of one per buffer.
+struct SelInit {
+    unsigned int *cnt = nullptr;           // [NCLASS + 1] rows per class, packed waves
+    unsigned int *nbk = nullptr;           // [1] buckets of the bucket partition, or NULL
+    unsigned long long *counts = nullptr;  // [COUNT_WORDS]
+    int64_t m = 0;
+    uint8_t *keep = nullptr;               // [m] zeroed, or NULL
+    int64_t nlogs = 0;
+    double *logs = nullptr;                // [2 * nlogs], or NULL
+};
+constexpr int COUNT_WORDS = 8;
+
+__global__ __launch_bounds__(SBLOCK) void k_sel_init(SelInit in) {
+    const int64_t idx = (int64_t)blockIdx.x * blockDim.x + threadIdx.x, step = (int64_t)gridDim.x * blockDim.x;
+    if (idx <= NCLASS) in.cnt[idx] = 0u;
+    if (idx < COUNT_WORDS) in.counts[idx] = 0ull;
+    if (idx == 0 && in.nbk) *in.nbk = 0u;
+    if (in.logs) {
+        for (int64_t v = idx; v < in.nlogs; v += step) {
+            const double l = v > 0 ? log((double)v) : 0.0;
+            in.logs[v] = l;
+            in.logs[in.nlogs + v] = v > 1 ? 1.0 / l : 0.0;
         }
-        if (!__any(c >= 0)) continue;       // uniform across the wave
-        for (int k = 0; k < NCLASS; ++k) {
-            const unsigned int at = wave_append(c == k, &counts[k]);
-            if (c == k) lists[cb.off[k] + at] = (int32_t)i;
+    }
+    if (in.keep) {
+        // bytes up to the first 16-byte boundary, whole words, the remaining bytes
+        const int64_t head = min(in.m, (int64_t)((16 - ((uintptr_t)in.keep & 15)) & 15));
+        const int64_t nw = (in.m - head) / 16;
+        uint4 *w = reinterpret_cast<uint4 *>(in.keep + head);
+        for (int64_t q = idx; q < nw; q += step) w[q] = make_uint4(0u, 0u, 0u, 0u);
+        if (idx < head) in.keep[idx] = 0;
+        if (idx < in.m - head - 16 * nw) in.keep[head + 16 * nw + idx] = 0;
+    }
+}
+
+// Second kernel of a selection: the packed waves' plan and the class lists
+// from one read of row_ptr.  One wave per tile of RANK_TILE rows, a lane per
+// row: a packed wave takes consecutive rows of degree <= 64 (isolated rows
+// ride along) while their entries fit in 64 lanes; a longer row closes it.
+// All 64 possible ends come from prefix sums at once and the chain of ends
+// from the first row by doubling (a loop over the packed waves took 12 us
+// for a tile of 64 of them).  A workgroup collects its tiles' waves and long rows in LDS
+// and reserves their places with one atomic per list, so their order in the
+// lists is that of the workgroups' arrival (the ranks do not depend on it).
+// Bound by launch and memory latency: one thread per tile walking its 64 rows
+// twice, three scan launches between and a pass of its own for the classes
+// took 107 us before the first row was ranked (n = 2^20; 15 + 20 us of it in
+// the two plan passes of a 4,096-vertex graph), 15 us here (4.4 us).
+constexpr int SETUP_TB = 1024;             // sixteen tiles at a time
+constexpr int SETUP_TILES = 4;             // tiles per wave, at most
+
+__global__ __launch_bounds__(SETUP_TB) void k_rank_setup(int64_t n, const int64_t *__restrict__ row_ptr,
+                                                         ClassBounds cb, int tiles_per_wave,
+                                                         unsigned int *__restrict__ cnt, int32_t *__restrict__ lists,
+                                                         long long *__restrict__ plan) {
+    __shared__ unsigned int part[NCLASS + 1], base[NCLASS + 1];
+    __shared__ int64_t off[NCLASS];
+    const int lane = threadIdx.x & (WAVE - 1), wave = threadIdx.x >> 6;
+    const unsigned long long below = lane ? (~0ull >> (WAVE - lane)) : 0ull;
+    if (threadIdx.x <= NCLASS) part[threadIdx.x] = 0u;
+    if (threadIdx.x == 0) {
+#pragma unroll
+        for (int c = 0; c < NCLASS; ++c) off[c] = cb.off[c];
+    }
+    __syncthreads();
+    long long mine[SETUP_TILES];           // the packed wave that starts at this lane's row of each tile (-1: none)
+    int cls[SETUP_TILES];                  // the class of this lane's row (-1: short)
+    unsigned int at_wave[SETUP_TILES], at_row[SETUP_TILES];
+    int64_t deg[SETUP_TILES];              // every tile's degrees first: one wait for memory, not one per tile
+#pragma unroll
+    for (int k = 0; k < SETUP_TILES; ++k) {
+        const int64_t r =
+            (((int64_t)blockIdx.x * tiles_per_wave + k) * (SETUP_TB / WAVE) + wave) * RANK_TILE + lane;
+        deg[k] = k < tiles_per_wave && r < n ? row_ptr[r + 1] - row_ptr[r] : 0;
+    }
+#pragma unroll
+    for (int k = 0; k < SETUP_TILES; ++k) {
+        mine[k] = -1;
+        cls[k] = -1;
+        at_wave[k] = at_row[k] = 0u;
+        if (k >= tiles_per_wave) continue;
+        const int64_t t = ((int64_t)blockIdx.x * tiles_per_wave + k) * (SETUP_TB / WAVE) + wave;
+        const int64_t r0 = t * RANK_TILE;
+        if (r0 >= n) continue;                                       // uniform across the wave
+        const int nr = (int)min((int64_t)RANK_TILE, n - r0);
+        const int64_t d = deg[k];
+        const bool big = d > WAVE;
+        if (big) cls[k] = min(NCLASS - 1, 31 - __clz((int)((min(d, (int64_t)1 << 30) - 1) >> 6)));
+        int inc = big ? 0 : (int)d;                                  // prefix sums of the short rows
+        for (int o = 1; o < WAVE; o <<= 1) {
+            const int y = __shfl_up(inc, o, WAVE);
+            if (lane >= o) inc += y;
+        }
+        const int exc = inc - (big ? 0 : (int)d);
+        const unsigned long long bigs = __ballot(big);
+        // where a packed wave that starts at this lane's row ends: at the first
+        // long row, or at the first row whose entries no longer fit
+        int stop = 0;                                                // rows with inc <= exc + 64: a binary search
+#pragma unroll
+        for (int step = WAVE / 2; step >= 1; step >>= 1)
+            if (__shfl(inc, stop + step - 1, WAVE) <= exc + WAVE) stop += step;
+        if (stop == WAVE - 1 && __shfl(inc, WAVE - 1, WAVE) <= exc + WAVE) stop = WAVE;
+        const unsigned long long bl = bigs & ~below;                 // long rows from this one on
+        stop = min(min(stop, nr), bl ? __ffsll((long long)bl) - 1 : WAVE);
+        const int exc_stop = __shfl(exc, stop & (WAVE - 1), WAVE);
+        const int entries = (stop < WAVE ? exc_stop : __shfl(inc, WAVE - 1, WAVE)) - exc;
+        // the rows at which packed waves start: the chain from row 0 through the
+        // ends, as bit sets doubled six times (a lane's set: the starts reached
+        // from it in 1, 2, 4, ... steps)
+        int next = stop + (stop < nr && ((bigs >> (stop & (WAVE - 1))) & 1ull) ? 1 : 0);
+        if (next >= nr || lane >= nr) next = lane;
+        unsigned long long chain = 1ull << lane;
+#pragma unroll
+        for (int r = 0; r < 6; ++r) {
+            chain |= __shfl(chain, next, WAVE);
+            next = __shfl(next, next, WAVE);
+        }
+        chain = __shfl(chain, 0, WAVE);
+        const bool starts = ((chain >> lane) & 1ull) && lane < nr && entries > 0;
+        const unsigned long long sm = __ballot(starts);
+        const int w = __popcll(sm);
+        mine[k] = ((r0 + lane) << 8) | (long long)(stop - lane);
+        if (!starts) mine[k] = -1;
+        at_wave[k] = (unsigned int)__popcll(sm & below);
+        unsigned int o_w = 0;
+        if (lane == 0 && w) o_w = atomicAdd(&part[NCLASS], (unsigned int)w);
+        at_wave[k] += __shfl(o_w, 0, WAVE);
+        unsigned long long left = bigs;
+        while (left) {                                               // one turn per class present
+            const int c = __shfl(cls[k], __ffsll((long long)left) - 1, WAVE);
+            const unsigned long long same = __ballot(cls[k] == c);
+            unsigned int o = 0;
+            if (lane == 0) o = atomicAdd(&part[c], (unsigned int)__popcll(same));
+            o = __shfl(o, 0, WAVE);
+            if (cls[k] == c) at_row[k] = o + (unsigned int)__popcll(same & below);
+            left &= ~same;
+        }
+    }
+    __syncthreads();
+    if (threadIdx.x <= NCLASS) base[threadIdx.x] = part[threadIdx.x] ? atomicAdd(&cnt[threadIdx.x], part[threadIdx.x]) : 0u;
+    __syncthreads();
+#pragma unroll
+    for (int k = 0; k < SETUP_TILES; ++k) {
+        if (mine[k] >= 0) plan[base[NCLASS] + at_wave[k]] = mine[k];
+        if (cls[k] >= 0) {
+            const int64_t t = ((int64_t)blockIdx.x * tiles_per_wave + k) * (SETUP_TB / WAVE) + wave;
+            lists[off[cls[k]] + base[cls[k]] + at_row[k]] = (int32_t)(t * RANK_TILE + lane);
         }
     }
 }
@@ -745,6 +840,117 @@ __device__ __forceinline__ bool rank_code_nan(unsigned long long k) { return k =
 // against keys read from memory before, d comparisons per entry and three
 // loads for each: n = 2^16, m = 500,000 (d up to about 1,000), all rows above
 // 64: 1,533 us counted, about 110 us sorted.
+template <int TB, int IPT, typename Tr>
+union RadixShared {
+    static constexpr int P = TB * IPT;
+    typedef typename rank_code_of<Tr>::type K;
+    typename rocprim::block_radix_sort<K, TB, IPT, uint16_t>::storage_type sort;
+    struct {
+        K key[P];
+        uint32_t rank[P];                            // both ranks of entry q of the row, 16 bits each
+        uint16_t place[P];
+    } row;
+};
+
+// One row of at most TB * IPT entries by a workgroup of TB threads.
+template <int TB, int IPT, typename Tr>
+__device__ __forceinline__ void rank_radix_row(RadixShared<TB, IPT, Tr> &sh, int64_t row,
+                                               const int64_t *__restrict__ row_ptr, const int32_t *__restrict__ col,
+                                               const int32_t *__restrict__ eid, const int32_t *__restrict__ orig_id,
+                                               const int32_t *__restrict__ col_orig, const Tr *__restrict__ rho,
+                                               const Tr *__restrict__ rho_ent, const Emit &em) {
+    static_assert(TB * IPT <= 65536, "places are 16-bit");
+    typedef typename rank_code_of<Tr>::type K;
+    constexpr K PAD = ~(K)0;
+    using Sorter = rocprim::block_radix_sort<K, TB, IPT, uint16_t>;
+    const int64_t beg = row_ptr[row];
+    const int d = (int)(row_ptr[row + 1] - beg);
+    // striped load (item s of thread t is entry s * TB + t); places past d
+    // carry the largest key and sort last
+    K k[IPT];
+    uint16_t v[IPT];
+    if (rho_ent) {                               // distances in entry order: contiguous
+#pragma unroll
+        for (int s = 0; s < IPT; ++s) {
+            const int q = s * TB + (int)threadIdx.x;
+            k[s] = q < d ? rank_code(rho_ent[beg + q]) : PAD;
+            v[s] = (uint16_t)q;
+        }
+    } else {
+        int32_t e[IPT];
+#pragma unroll
+        for (int s = 0; s < IPT; ++s) {
+            const int q = s * TB + (int)threadIdx.x;
+            e[s] = q < d ? eid[beg + q] : 0;
+        }
+#pragma unroll
+        for (int s = 0; s < IPT; ++s) {
+            const int q = s * TB + (int)threadIdx.x;
+            k[s] = q < d ? rank_code(rho[e[s]]) : PAD;
+            v[s] = (uint16_t)q;
+        }
+    }
+    Sorter().sort(k, v, sh.sort);                // blocked: thread t holds sorted places t * IPT + s
+    __syncthreads();
+#pragma unroll
+    for (int s = 0; s < IPT; ++s) {
+        const int q = (int)threadIdx.x * IPT + s;
+        sh.row.key[q] = k[s];
+        sh.row.place[q] = v[s];
+    }
+    __syncthreads();
+    // both ranks of sorted place q (each below d <= 65536: 16 bits each),
+    // stored at the entry's place in the row, so that the records are
+    // written by consecutive entries of the row (its upper entries hold
+    // consecutive edge ids)
+#pragma unroll
+    for (int s = 0; s < IPT; ++s) {
+        const int q = (int)threadIdx.x * IPT + s;
+        if (q >= d) continue;
+        uint32_t rk = (uint32_t)q | ((uint32_t)(d - 1 - q) << 16);
+        const K key = k[s];
+        if (rank_code_nan(key)) {
+            sh.row.rank[v[s]] = (uint32_t)d << 16;
+            continue;
+        }
+        const bool tie = (q > 0 && sh.row.key[q - 1] == key) || (q + 1 < d && sh.row.key[q + 1] == key);
+        if (tie) {
+            int a = 0, hi = q;                        // first place with this key
+            while (a < hi) {
+                const int mid = (a + hi) >> 1;
+                if (sh.row.key[mid] < key) a = mid + 1;
+                else hi = mid;
+            }
+            int b = q + 1;                            // first place past the run
+            hi = d;
+            while (b < hi) {
+                const int mid = (b + hi) >> 1;
+                if (sh.row.key[mid] <= key) b = mid + 1;
+                else hi = mid;
+            }
+            const int64_t p = beg + v[s];
+            const int32_t id = nbr_id(p, col[p], col_orig, orig_id);
+            int before = 0;
+            for (int r = a; r < b; ++r) {
+                const int64_t pr = beg + sh.row.place[r];
+                before += nbr_id(pr, col[pr], col_orig, orig_id) < id ? 1 : 0;
+            }
+            rk = (uint32_t)(a + before) | ((uint32_t)(d - b + before) << 16);
+        }
+        sh.row.rank[v[s]] = rk;
+    }
+    __syncthreads();
+#pragma unroll 2
+    for (int s = 0; s < IPT; ++s) {
+        const int q = s * TB + (int)threadIdx.x;
+        if (q < d) {
+            const uint32_t r = sh.row.rank[q];
+            emit_ranks(em, row, col[beg + q], eid[beg + q], d, r & 0xffffu, r >> 16);
+        }
+    }
+    __syncthreads();
+}
+
 template <int TB, int IPT, typename Tr = float>
 __global__ __launch_bounds__(TB) void k_rank_radix(
     const int32_t *__restrict__ list, const unsigned int *__restrict__ count,
@@ -752,109 +958,37 @@ __global__ __launch_bounds__(TB) void k_rank_radix(
     const int32_t *__restrict__ eid, const int32_t *__restrict__ orig_id,
     const int32_t *__restrict__ col_orig, const Tr *__restrict__ rho, const Tr *__restrict__ rho_ent, Emit em,
     int slice, int nslices) {
-    constexpr int P = TB * IPT;
-    static_assert(P <= 65536, "places are 16-bit");
-    typedef typename rank_code_of<Tr>::type K;
-    constexpr K PAD = ~(K)0;
-    using Sorter = rocprim::block_radix_sort<K, TB, IPT, uint16_t>;
-    __shared__ union {
-        typename Sorter::storage_type sort;
-        struct {
-            K key[P];
-            uint32_t rank[P];                        // both ranks of entry q of the row, 16 bits each
-            uint16_t place[P];
-        } row;
-    } sh;
+    __shared__ RadixShared<TB, IPT, Tr> sh;
     const unsigned int nr = *count;
     // this launch takes rows slice, slice + nslices, ... of the list
-    for (unsigned int h = blockIdx.x * nslices + slice; h < nr; h += gridDim.x * nslices) {
-        const int64_t row = list[h];
-        const int64_t beg = row_ptr[row];
-        const int d = (int)(row_ptr[row + 1] - beg);
-        // striped load (item s of thread t is entry s * TB + t); places past d
-        // carry the largest key and sort last
-        K k[IPT];
-        uint16_t v[IPT];
-        if (rho_ent) {                               // distances in entry order: contiguous
-#pragma unroll
-            for (int s = 0; s < IPT; ++s) {
-                const int q = s * TB + (int)threadIdx.x;
-                k[s] = q < d ? rank_code(rho_ent[beg + q]) : PAD;
-                v[s] = (uint16_t)q;
-            }
-        } else {
-            int32_t e[IPT];
-#pragma unroll
-            for (int s = 0; s < IPT; ++s) {
-                const int q = s * TB + (int)threadIdx.x;
-                e[s] = q < d ? eid[beg + q] : 0;
-            }
-#pragma unroll
-            for (int s = 0; s < IPT; ++s) {
-                const int q = s * TB + (int)threadIdx.x;
-                k[s] = q < d ? rank_code(rho[e[s]]) : PAD;
-                v[s] = (uint16_t)q;
-            }
-        }
-        Sorter().sort(k, v, sh.sort);                // blocked: thread t holds sorted places t * IPT + s
-        __syncthreads();
-#pragma unroll
-        for (int s = 0; s < IPT; ++s) {
-            const int q = (int)threadIdx.x * IPT + s;
-            sh.row.key[q] = k[s];
-            sh.row.place[q] = v[s];
-        }
-        __syncthreads();
-        // both ranks of sorted place q (each below d <= 65536: 16 bits each),
-        // stored at the entry's place in the row, so that the records are
-        // written by consecutive entries of the row (its upper entries hold
-        // consecutive edge ids)
-#pragma unroll
-        for (int s = 0; s < IPT; ++s) {
-            const int q = (int)threadIdx.x * IPT + s;
-            if (q >= d) continue;
-            uint32_t rk = (uint32_t)q | ((uint32_t)(d - 1 - q) << 16);
-            const K key = k[s];
-            if (rank_code_nan(key)) {
-                sh.row.rank[v[s]] = (uint32_t)d << 16;
-                continue;
-            }
-            const bool tie = (q > 0 && sh.row.key[q - 1] == key) || (q + 1 < d && sh.row.key[q + 1] == key);
-            if (tie) {
-                int a = 0, hi = q;                        // first place with this key
-                while (a < hi) {
-                    const int mid = (a + hi) >> 1;
-                    if (sh.row.key[mid] < key) a = mid + 1;
-                    else hi = mid;
-                }
-                int b = q + 1;                            // first place past the run
-                hi = d;
-                while (b < hi) {
-                    const int mid = (b + hi) >> 1;
-                    if (sh.row.key[mid] <= key) b = mid + 1;
-                    else hi = mid;
-                }
-                const int64_t p = beg + v[s];
-                const int32_t id = nbr_id(p, col[p], col_orig, orig_id);
-                int before = 0;
-                for (int r = a; r < b; ++r) {
-                    const int64_t pr = beg + sh.row.place[r];
-                    before += nbr_id(pr, col[pr], col_orig, orig_id) < id ? 1 : 0;
-                }
-                rk = (uint32_t)(a + before) | ((uint32_t)(d - b + before) << 16);
-            }
-            sh.row.rank[v[s]] = rk;
-        }
-        __syncthreads();
-#pragma unroll 2
-        for (int s = 0; s < IPT; ++s) {
-            const int q = s * TB + (int)threadIdx.x;
-            if (q < d) {
-                const uint32_t r = sh.row.rank[q];
-                emit_ranks(em, row, col[beg + q], eid[beg + q], d, r & 0xffffu, r >> 16);
-            }
-        }
-        __syncthreads();
+    for (unsigned int h = blockIdx.x * nslices + slice; h < nr; h += gridDim.x * nslices)
+        rank_radix_row<TB, IPT, Tr>(sh, list[h], row_ptr, col, eid, orig_id, col_orig, rho, rho_ent, em);
+}
+
+// The three one-wave classes (64 < d <= 512) in one launch, each row by the
+// sort of its class: where the classes run one after another on one stream
+// (smaller graphs, FP64, captured calls) two launches less.
+template <typename Tr>
+__global__ __launch_bounds__(WAVE) void k_rank_radix_waves(
+    ClassBounds cb, const int32_t *__restrict__ lists, const unsigned int *__restrict__ cnt,
+    const int64_t *__restrict__ row_ptr, const int32_t *__restrict__ col,
+    const int32_t *__restrict__ eid, const int32_t *__restrict__ orig_id,
+    const int32_t *__restrict__ col_orig, const Tr *__restrict__ rho, const Tr *__restrict__ rho_ent, Emit em) {
+    __shared__ union {
+        RadixShared<WAVE, 8, Tr> a;
+        RadixShared<WAVE, 4, Tr> b;
+        RadixShared<WAVE, 2, Tr> c;
+    } sh;
+    const unsigned int n2 = cnt[2], n1 = n2 + cnt[1], n0 = n1 + cnt[0];    // the longest rows first
+    for (unsigned int h = blockIdx.x; h < n0; h += gridDim.x) {
+        if (h < n2)
+            rank_radix_row<WAVE, 8, Tr>(sh.a, lists[cb.off[2] + h], row_ptr, col, eid, orig_id, col_orig, rho, rho_ent, em);
+        else if (h < n1)
+            rank_radix_row<WAVE, 4, Tr>(sh.b, lists[cb.off[1] + h - n2], row_ptr, col, eid, orig_id, col_orig, rho,
+                                        rho_ent, em);
+        else
+            rank_radix_row<WAVE, 2, Tr>(sh.c, lists[cb.off[0] + h - n1], row_ptr, col, eid, orig_id, col_orig, rho,
+                                        rho_ent, em);
     }
 }
 
@@ -1387,14 +1521,32 @@ constexpr int COUNT_BLOCKS = 2048;
 constexpr int SUM_BLOCKS = 256;    // grids that end in block_add
 constexpr int HIST_BLOCKS = 2048;
 
-// Sum of a byte mask into a 64-bit device counter.
+// Sum of keep's flags (0 or 1): counts[0] gathers the workgroups' sums and
+// counts[1] their tickets (both zero before), and the last one to arrive stores
+// the total.  Streaming, 16 bytes a load; with the ticket no launch of its own
+// stores the count (4.6 us).
 __global__ __launch_bounds__(SBLOCK) void k_count_bytes(int64_t m, const uint8_t *__restrict__ keep,
-                                                       unsigned long long *out) {
+                                                       unsigned long long *__restrict__ counts,
+                                                       int64_t *__restrict__ out) {
+    const int64_t idx = (int64_t)blockIdx.x * blockDim.x + threadIdx.x, step = (int64_t)gridDim.x * blockDim.x;
+    const int64_t head = min(m, (int64_t)((16 - ((uintptr_t)keep & 15)) & 15));
+    const int64_t nw = (m - head) / 16;
+    const uint4 *w = reinterpret_cast<const uint4 *>(keep + head);
     unsigned long long c = 0;
-    for (int64_t q = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; q < m;
-         q += (int64_t)gridDim.x * blockDim.x)
-        c += keep[q];
-    block_add(c, out);
+    for (int64_t q = idx; q < nw; q += step) {
+        const uint4 v = w[q];
+        c += (unsigned)(__popc(v.x) + __popc(v.y) + __popc(v.z) + __popc(v.w));
+    }
+    if (idx < head) c += keep[idx];
+    if (idx < m - head - 16 * nw) c += keep[head + 16 * nw + idx];
+    block_add(c, counts);
+    if (threadIdx.x == 0) {
+        __threadfence();
+        if (atomicAdd(&counts[1], 1ull) == gridDim.x - 1) {
+            __threadfence();
+            *out = (int64_t)__hip_atomic_load(counts, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        }
+    }
 }
 
 // ---------------------------------------------------------------------- fit --
@@ -1420,17 +1572,6 @@ constexpr int FIT_LDS_TB = 1024;   // threads of the grid pass with the log tabl
 struct alignas(16) U64x2 {
     unsigned long long a, b;
 };
-
-// logs[v] = log(v) for v = 1 .. count - 1 (logs[0] unused), and
-// logs[count + v] = 1 / log(v) for v >= 2.
-__global__ void k_log_table(int64_t count, double *__restrict__ logs) {
-    for (int64_t v = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; v < count;
-         v += (int64_t)gridDim.x * blockDim.x) {
-        const double l = v > 0 ? log((double)v) : 0.0;
-        logs[v] = l;
-        logs[count + v] = v > 1 ? 1.0 / l : 0.0;
-    }
-}
 
 // Estimated grid index of a side's threshold (0: kept at every e): the side
 // (d, r) selects once d^e >= r + 1, i.e. e >= log(r + 1) / log(d); inv_ld =
@@ -1865,11 +2006,9 @@ __global__ void k_store_count(const unsigned long long *__restrict__ c, int64_t 
 
 struct SelLayout {
     int32_t *lists;               // rows of degree > 64, by class
-    unsigned int *cnt;            // [NCLASS]
+    unsigned int *cnt;            // [NCLASS + 1]: rows per class, packed waves
     ClassBounds cb;
     long long *plan;              // packed small-row waves
-    unsigned int *tile_waves, *plan_count;
-    ScanScratch scan;
     uint4 *recs;                  // [2m] side records (Emit, MODE_REC*)
     unsigned long long *G, *G2;   // [m] grid indices per fitted orientation (G2 when both)
     unsigned long long *cand, *cand2, *cand_n;   // select candidates (CandArrays), per orientation
@@ -1877,8 +2016,8 @@ struct SelLayout {
     int64_t cand_cap;
     unsigned int *hist;           // [2][NBINS]
     unsigned long long *state;    // [4]: two words per fitted orientation
-    unsigned long long *counts;   // [6]: counts at the upper and lower grid point per orientation, then
-                                  // the listed edges per orientation (k_fit_count LIST form)
+    unsigned long long *counts;   // [COUNT_WORDS]: counts at the upper and lower grid point per orientation,
+                                  // the listed edges per orientation (k_fit_count LIST form), a ticket
     int32_t *tabs;                // [4][d_max + 1]: upper and lower budget tables, per orientation
     double *logs;                 // [2][d_max + 2]: log(v), then 1 / log(v)
     HubScratch hub;               // rows longer than SORT_CAP (d_max > SORT_CAP only)
@@ -1894,7 +2033,6 @@ static size_t sel_layout(const ad_graph *g, void *ws, size_t ws_bytes, SelLayout
     const int64_t ntiles = std::max<int64_t>(1, ceil_div(g->n, RANK_TILE));
     SelLayout l;
     int64_t total = 0;
-    for (int k = 0; k <= NCLASS; ++k) l.cb.lo[k] = CLASS_LO[k];
     for (int k = 0; k < NCLASS; ++k) {
         // rows in class k have degree > lo[k]: at most 2m / (lo[k] + 1) of them
         const int64_t cap = std::min<int64_t>(n, ceil_div(2 * m, CLASS_LO[k] + 1));
@@ -1902,14 +2040,8 @@ static size_t sel_layout(const ad_graph *g, void *ws, size_t ws_bytes, SelLayout
         total += cap;
     }
     l.lists = c.take<int32_t>(total);
-    l.cnt = c.take<unsigned int>(NCLASS);
+    l.cnt = c.take<unsigned int>(NCLASS + 1);
     l.plan = c.take<long long>(n + ntiles);
-    l.tile_waves = c.take<unsigned int>(ntiles);
-    l.plan_count = c.take<unsigned int>(1);
-    const size_t nblk = scan_scratch_blocks(ntiles);
-    l.scan.blk_v = c.take<unsigned int>(nblk);
-    l.scan.blk_w = c.take<unsigned long long>(nblk);
-    l.scan.total_w = c.take<unsigned long long>(1);
     l.recs = c.take<uint4>(2 * m);
     l.G = c.take<unsigned long long>(m);
     l.G2 = both ? c.take<unsigned long long>(m) : nullptr;
@@ -1920,7 +2052,7 @@ static size_t sel_layout(const ad_graph *g, void *ws, size_t ws_bytes, SelLayout
     l.fit_part = c.take<unsigned long long>(4 * (size_t)COUNT_BLOCKS);
     l.hist = c.take<unsigned int>(2 * NBINS);
     l.state = c.take<unsigned long long>(4);
-    l.counts = c.take<unsigned long long>(6);
+    l.counts = c.take<unsigned long long>(COUNT_WORDS);
     l.tabs = c.take<int32_t>(4 * ((size_t)g->d_max + 1));
     l.logs = c.take<double>(2 * ((size_t)g->d_max + 2));
     l.hub = HubScratch{};
@@ -1994,7 +2126,6 @@ static void budget_table(int32_t d_max, double e, std::vector<int32_t> &t) {
     budget_fill(d_max, e, t.data());
 }
 
-// Rank every entry of every row and emit per `em`.
 // Helper streams for the ranking classes.  The classes rank disjoint rows
 // (their outputs are distinct side records or set-only keep flags), and the long
 // classes are latency-bound (one workgroup sorts one row), so outside stream
@@ -2027,6 +2158,39 @@ static RankFork *rank_fork() {
     return f->ok ? f : nullptr;
 }
 
+// Outside stream capture the classes fork when the graph has at least this
+// many stored entries: an event and a wait per stream cost the host about
+// 40 us, more than the classes of a smaller graph take one after another
+// (n = 4096, m = 40,000: 30 us of ranking; n = 2^20, m = 16M: 2.0 ms on one
+// stream, 0.86 ms on four).
+constexpr int64_t FORK_ENTRIES = (int64_t)1 << 21;
+
+// The launches every selection starts with: counters (with keep[] zeroed and
+// the log tables filled where asked), then the plan and the class lists.
+static ad_status rank_setup(const ad_graph *g, const SelLayout &L, uint8_t *zero_keep, bool logs, hipStream_t st) {
+    SelInit in;
+    in.cnt = L.cnt;
+    in.nbk = L.hub.nbk;
+    in.counts = L.counts;
+    in.m = g->m;
+    in.keep = zero_keep;
+    in.nlogs = (int64_t)g->d_max + 2;
+    in.logs = logs ? L.logs : nullptr;
+    const int64_t items = std::max<int64_t>(zero_keep ? ceil_div(g->m, 16) : 1, logs ? in.nlogs : 1);
+    hipLaunchKernelGGL(k_sel_init, dim3((unsigned)std::min<int64_t>(2048, ceil_div(items, SBLOCK))), dim3(SBLOCK), 0, st,
+                       in);
+    AD_LAUNCH_CHECK("k_sel_init");
+    // tiles per wave: one while 256 workgroups cover the tiles so, up to four on
+    // larger graphs (an atomic per list and workgroup: they queue at about 45 ns)
+    const int64_t ntiles = ceil_div(g->n, RANK_TILE), per = SETUP_TB / WAVE;
+    const int tpw = (int)std::min<int64_t>(SETUP_TILES, std::max<int64_t>(1, ceil_div(ntiles, 256 * per)));
+    hipLaunchKernelGGL(k_rank_setup, dim3((unsigned)ceil_div(ntiles, tpw * per)), dim3(SETUP_TB), 0, st, g->n,
+                       g->row_ptr, L.cb, tpw, L.cnt, L.lists, L.plan);
+    AD_LAUNCH_CHECK("k_rank_setup");
+    return AD_OK;
+}
+
+// Rank every entry of every row and emit per `em`, after rank_setup.
 template <typename Tr>
 static ad_status rank_all(const ad_graph *g, const Tr *rho, const Emit &em, const SelLayout &L, hipStream_t st,
                           const unsigned long long *keys = nullptr, const float *rho_ent = nullptr) {
@@ -2034,16 +2198,11 @@ static ad_status rank_all(const ad_graph *g, const Tr *rho, const Emit &em, cons
     if (n <= 0 || g->m <= 0) return AD_OK;
     TraceScope trace("k_rank", st);
     ad_status s;
-    // FP32 rows above 64: classify first, then fork the classes off
+    // FP32 rows above 64 of larger graphs: fork the classes off
     RankFork *fk = nullptr;
     std::unique_lock<std::mutex> hold;
     hipStream_t cls[3] = {st, st, st};
-    if (sizeof(Tr) == 4 && g->d_max > 64) {
-        s = fill_i32((int32_t *)L.cnt, 0, NCLASS, st);
-        if (s != AD_OK) return s;
-        hipLaunchKernelGGL(k_classify, dim3(grid_for(n, SBLOCK)), dim3(SBLOCK), 0, st, n, g->row_ptr, L.cb, L.lists,
-                           L.cnt);
-        AD_LAUNCH_CHECK("k_classify");
+    if (sizeof(Tr) == 4 && g->d_max > 64 && 2 * g->m >= FORK_ENTRIES) {
         hipStreamCaptureStatus cap = hipStreamCaptureStatusNone;
         if (hipStreamIsCapturing(st, &cap) == hipSuccess && cap == hipStreamCaptureStatusNone) fk = rank_fork();
         else (void)hipGetLastError();
@@ -2056,29 +2215,18 @@ static ad_status rank_all(const ad_graph *g, const Tr *rho, const Emit &em, cons
             }
         }
     }
-    // rows of degree <= 64, packed into waves
-    const int64_t ntiles = ceil_div(n, RANK_TILE);
-    hipLaunchKernelGGL(k_rank_plan, dim3(grid_for(ntiles, SBLOCK)), dim3(SBLOCK), 0, st, n, g->row_ptr, 0,
-                       L.tile_waves, L.plan);
-    AD_LAUNCH_CHECK("k_rank_plan");
-    s = scan_exclusive(ntiles, L.tile_waves, nullptr, L.plan_count, nullptr, L.scan, st);
-    if (s != AD_OK) return s;
-    hipLaunchKernelGGL(k_rank_plan, dim3(grid_for(ntiles, SBLOCK)), dim3(SBLOCK), 0, st, n, g->row_ptr, 1,
-                       L.tile_waves, L.plan);
-    AD_LAUNCH_CHECK("k_rank_plan");
-    const unsigned packed_blocks = (unsigned)std::min<int64_t>(4096, ceil_div(n, SBLOCK / WAVE));
-    hipLaunchKernelGGL((k_rank_packed<Tr>), dim3(packed_blocks), dim3(SBLOCK), 0, st, L.plan, L.plan_count,
-                       g->row_ptr, g->col, g->eid, g->orig_id, g->col_orig, rho, keys, em, rho_ent);
+    // rows of degree <= 64, packed into waves: after the longest rows' launches
+    // where those run on their own streams (their large workgroups would wait
+    // for room behind the packed waves), else first
+    auto rank_packed = [&]() {
+        const unsigned blocks = (unsigned)std::min<int64_t>(4096, ceil_div(n, SBLOCK / WAVE));
+        hipLaunchKernelGGL((k_rank_packed<Tr>), dim3(blocks), dim3(SBLOCK), 0, st, L.plan, L.cnt + NCLASS, g->row_ptr,
+                           g->col, g->eid, g->orig_id, g->col_orig, rho, keys, em, rho_ent);
+    };
+    if (!fk) rank_packed();
     AD_LAUNCH_CHECK("k_rank_packed");
     if (g->d_max <= 64) return AD_OK;
 
-    if (sizeof(Tr) != 4) {
-        s = fill_i32((int32_t *)L.cnt, 0, NCLASS, st);
-        if (s != AD_OK) return s;
-        hipLaunchKernelGGL(k_classify, dim3(grid_for(n, SBLOCK)), dim3(SBLOCK), 0, st, n, g->row_ptr, L.cb, L.lists,
-                           L.cnt);
-        AD_LAUNCH_CHECK("k_classify");
-    }
     const unsigned grid = (unsigned)std::min<int64_t>(2048, n);
     const int32_t *lst[NCLASS];
     for (int k = 0; k < NCLASS; ++k) lst[k] = L.lists + L.cb.off[k];
@@ -2101,32 +2249,36 @@ static ad_status rank_all(const ad_graph *g, const Tr *rho, const Emit &em, cons
             // neither kind of graph piles its work on one stream; the bucket
             // partition follows the packed short rows on the caller's stream.
             if (g->d_max > 4096) {
-                hipLaunchKernelGGL((k_rank_radix<512, 16>), dim3(grid), dim3(512), 0, cls[0], lst[6], &L.cnt[6],
-                                   AD_RANK_ARGS_R, 0, 2);
-                hipLaunchKernelGGL((k_rank_radix<512, 16>), dim3(grid), dim3(512), 0, cls[1], lst[6], &L.cnt[6],
-                                   AD_RANK_ARGS_R, 1, 2);
+                const int halves = fk ? 2 : 1;
+                for (int h = 0; h < halves; ++h)
+                    hipLaunchKernelGGL((k_rank_radix<512, 16>), dim3(grid), dim3(512), 0, cls[h], lst[6], &L.cnt[6],
+                                       AD_RANK_ARGS_R, h, halves);
             }
             if (g->d_max > 2048)
                 hipLaunchKernelGGL((k_rank_radix<512, 8>), dim3(grid), dim3(512), 0, cls[2], lst[5], &L.cnt[5],
                                    AD_RANK_ARGS_R, 0, 1);
+            if (fk) rank_packed();
             if (g->d_max > 1024)
                 hipLaunchKernelGGL((k_rank_radix<256, 8>), dim3(grid), dim3(256), 0, cls[0], lst[4], &L.cnt[4],
                                    AD_RANK_ARGS_R, 0, 1);
-            if (g->d_max > 64)
+            if (g->d_max > 64 && fk)
                 hipLaunchKernelGGL((k_rank_radix<64, 2>), dim3(grid_w), dim3(64), 0, cls[1], lst[0], &L.cnt[0],
                                    AD_RANK_ARGS_R, 0, 1);
             if (g->d_max > 512)
                 hipLaunchKernelGGL((k_rank_radix<256, 4>), dim3(grid), dim3(256), 0, cls[2], lst[3], &L.cnt[3],
                                    AD_RANK_ARGS_R, 0, 1);
-            if (g->d_max > 256)
+            if (g->d_max > 256 && fk)
                 hipLaunchKernelGGL((k_rank_radix<64, 8>), dim3(grid_w), dim3(64), 0, cls[2], lst[2], &L.cnt[2],
                                    AD_RANK_ARGS_R, 0, 1);
             // 128..256 after the first half of the longest class, or, with no
             // rows for the bucket partition, after the short rows on the
             // caller's stream
-            if (g->d_max > 128)
+            if (g->d_max > 128 && fk)
                 hipLaunchKernelGGL((k_rank_radix<64, 4>), dim3(grid_w), dim3(64), 0,
                                    g->d_max > SORT_CAP ? cls[0] : st, lst[1], &L.cnt[1], AD_RANK_ARGS_R, 0, 1);
+            if (!fk)
+                hipLaunchKernelGGL((k_rank_radix_waves<float>), dim3(grid_w), dim3(WAVE), 0, st, L.cb, L.lists, L.cnt,
+                                   AD_RANK_ARGS_R);
             AD_LAUNCH_CHECK("k_rank_radix");
 #undef AD_RANK_ARGS_R
         } else {
@@ -2136,6 +2288,7 @@ static ad_status rank_all(const ad_graph *g, const Tr *rho, const Emit &em, cons
             if (g->d_max > 2048)
                 hipLaunchKernelGGL((k_rank_bitonic<4096, 512>), dim3(grid), dim3(512), 0, cls[1], lst[5], &L.cnt[5],
                                    AD_RANK_ARGS_F);
+            if (fk) rank_packed();
             if (g->d_max > 1024)
                 hipLaunchKernelGGL((k_rank_bitonic<2048, 256>), dim3(grid), dim3(256), 0, cls[2], lst[4], &L.cnt[4],
                                    AD_RANK_ARGS_F);
@@ -2160,8 +2313,6 @@ static ad_status rank_all(const ad_graph *g, const Tr *rho, const Emit &em, cons
 #undef AD_RANK_ARGS_F
         if (g->d_max > SORT_CAP && !keys) {
             // distance keys: one partition on the 32-bit distance bits serves both orders
-            s = fill_i32((int32_t *)L.hub.nbk, 0, 1, st);
-            if (s != AD_OK) return s;
             for (int k = HUB_CLASS; k < NCLASS; ++k) {
                 if (g->d_max <= CLASS_LO[k]) break;
                 hipLaunchKernelGGL(k_hub_partition<uint32_t>, dim3(512), dim3(HUB_TB), 0, st, lst[k], &L.cnt[k],
@@ -2226,14 +2377,11 @@ static ad_status rank_all(const ad_graph *g, const Tr *rho, const Emit &em, cons
         AD_RANK_D(512, 8, grid, 5);
         AD_RANK_D(256, 8, grid, 4);
         AD_RANK_D(256, 4, grid, 3);
-        AD_RANK_D(64, 8, grid_w, 2);
-        AD_RANK_D(64, 4, grid_w, 1);
-        AD_RANK_D(64, 2, grid_w, 0);
 #undef AD_RANK_D
+        hipLaunchKernelGGL((k_rank_radix_waves<double>), dim3(grid_w), dim3(WAVE), 0, st, L.cb, L.lists, L.cnt,
+                           g->row_ptr, g->col, g->eid, g->orig_id, g->col_orig, rd, (const double *)nullptr, em);
         AD_LAUNCH_CHECK("k_rank_radix");
         if (g->d_max > SORT_CAP) {
-            s = fill_i32((int32_t *)L.hub.nbk, 0, 1, st);
-            if (s != AD_OK) return s;
             hipLaunchKernelGGL((k_hub_partition<unsigned long long, double>), dim3(512), dim3(HUB_TB), 0, st,
                                lst[HUB_CLASS], &L.cnt[HUB_CLASS], g->row_ptr, g->col, g->eid, g->orig_id, g->col_orig,
                                rd, (const double *)nullptr, (const unsigned long long *)nullptr, em.orient, L.hub);
@@ -2243,6 +2391,15 @@ static ad_status rank_all(const ad_graph *g, const Tr *rho, const Emit &em, cons
             AD_LAUNCH_CHECK("k_hub_rank64");
         }
     }
+    return AD_OK;
+}
+
+// n_kept = sum(keep); counts[0] and counts[1] are zero before.
+static ad_status count_kept(int64_t m, const uint8_t *keep, unsigned long long *counts, int64_t *n_kept,
+                            hipStream_t st) {
+    hipLaunchKernelGGL(k_count_bytes, dim3((unsigned)std::min<int64_t>(SUM_BLOCKS, ceil_div(m, 16 * SBLOCK))),
+                       dim3(SBLOCK), 0, st, m, keep, counts, n_kept);
+    AD_LAUNCH_CHECK("k_count_bytes");
     return AD_OK;
 }
 
@@ -2356,7 +2513,7 @@ ad_status sparsify_fixed(const ad_graph *g, ad_dtype rho_dtype, const void *rho,
     SelLayout L;
     if (sel_layout(g, ws, ws_bytes, &L) == 0) return fail(AD_ERR_WORKSPACE, "workspace too small");
     if (g->m <= 0) return AD_OK;
-    ad_status s = fill_u8(keep, 0, g->m, stream);
+    ad_status s = rank_setup(g, L, keep, false, stream);
     if (s != AD_OK) return s;
     const Emit em = emit_single(MODE_FIXED, orient, budget, keep, nullptr);
     if (rho_dtype == AD_F32) return rank_all<float>(g, (const float *)rho, em, L, stream);
@@ -2441,25 +2598,20 @@ extern "C" size_t ad_sparsify_workspace_size(const ad_graph *g) {
 static ad_status sparsify_count(const ad_graph *g, ad_dtype rho_dtype, const void *rho, ad_orient orient,
                                 const int32_t *budget, uint8_t *keep, int64_t *n_kept, const SelLayout &L,
                                 hipStream_t stream, const float *rho_ent = nullptr) {
-    ad_status s = fill_u64(L.counts, 0, 1, stream);
-    if (s != AD_OK) return s;
-    if (g->m > 0) {
-        s = fill_u8(keep, 0, g->m, stream);
-        if (s != AD_OK) return s;
-        const Emit em = emit_single(MODE_FIXED, orient, budget, keep, nullptr);
-        if (rho_dtype == AD_F32)
-            s = rank_all<float>(g, (const float *)rho, em, L, stream, nullptr, rho_ent);
-        else
-            s = rank_all<double>(g, (const double *)rho, em, L, stream);
-        if (s != AD_OK) return s;
-        hipLaunchKernelGGL(k_count_bytes, dim3((unsigned)std::min<int64_t>(SUM_BLOCKS, ceil_div(g->m, SBLOCK))),
-                           dim3(SBLOCK), 0, stream, g->m, keep,
-                           L.counts);
-        AD_LAUNCH_CHECK("k_count_bytes");
+    ad_status s;
+    if (g->m <= 0) {
+        s = fill_u64((unsigned long long *)n_kept, 0, 1, stream);
+        return s;
     }
-    hipLaunchKernelGGL(k_store_count, dim3(1), dim3(1), 0, stream, L.counts, n_kept);
-    AD_LAUNCH_CHECK("k_store_count");
-    return AD_OK;
+    s = rank_setup(g, L, keep, false, stream);
+    if (s != AD_OK) return s;
+    const Emit em = emit_single(MODE_FIXED, orient, budget, keep, nullptr);
+    if (rho_dtype == AD_F32)
+        s = rank_all<float>(g, (const float *)rho, em, L, stream, nullptr, rho_ent);
+    else
+        s = rank_all<double>(g, (const double *)rho, em, L, stream);
+    if (s != AD_OK) return s;
+    return count_kept(g->m, keep, L.counts, n_kept, stream);
 }
 
 extern "C" ad_status ad_sparsify(const ad_graph *g, ad_dtype rho_dtype, const void *rho, ad_orient orient,
@@ -2697,15 +2849,14 @@ static ad_status sparsify_fit_impl(const ad_graph *g, ad_dtype rho_dtype, const 
         em.orient = AD_LOCAL;
         em.both = 1;
     }
+    s = rank_setup(g, L, nullptr, true, stream);
+    if (s != AD_OK) return s;
     if (rho_dtype == AD_F32)
         s = rank_all<float>(g, (const float *)rho, em, L, stream, nullptr, rho_ent);
     else
         s = rank_all<double>(g, (const double *)rho, em, L, stream);
     if (s != AD_OK) return s;
     TraceScope trace_fit("k_fit_select", stream);
-    hipLaunchKernelGGL(k_log_table, dim3(grid_for((int64_t)g->d_max + 2, SBLOCK)), dim3(SBLOCK), 0, stream,
-                       (int64_t)g->d_max + 2, L.logs);
-    AD_LAUNCH_CHECK("k_log_table");
     uint8_t *kp[2] = {keep, keep2};
     return fit_from_recs(g, L, nfit, K, kp, n_kept, e_used_host, stream);
 }
@@ -3124,6 +3275,8 @@ static ad_status sparsify_binned_impl(const ad_graph *g, ad_dtype rho_dtype, con
         AD_LAUNCH_CHECK("k_bin_keys");
     }
     // first ranking: (bin, priority); ranks into the side records
+    s = rank_setup(g, L, target > 0.0 ? nullptr : keep, target > 0.0, stream);
+    if (s != AD_OK) return s;
     s = rank_all<float>(g, nullptr, emit_single(MODE_REC, AD_LOCAL, nullptr, nullptr, L.recs), L, stream, B.keys);
     if (s != AD_OK) return s;
     {
@@ -3144,24 +3297,14 @@ static ad_status sparsify_binned_impl(const ad_graph *g, ad_dtype rho_dtype, con
                             B.keys);
         if (s != AD_OK) return s;
         TraceScope trace_fit("k_fit_select", stream);
-        hipLaunchKernelGGL(k_log_table, dim3(grid_for((int64_t)g->d_max + 2, SBLOCK)), dim3(SBLOCK), 0, stream,
-                           (int64_t)g->d_max + 2, L.logs);
-        AD_LAUNCH_CHECK("k_log_table");
         uint8_t *kp[1] = {keep};
         return fit_from_recs(g, L, 1, fit_count_target(m, target), kp, n_kept, e_used_host, stream);
     }
     // second ranking straight into keep at the fixed exponent
-    s = fill_u64(L.counts, 0, 1, stream);
-    if (s != AD_OK) return s;
-    s = fill_u8(keep, 0, m, stream);
-    if (s != AD_OK) return s;
     s = rank_all<float>(g, nullptr, emit_single(MODE_FIXED, AD_LOCAL, B.budget, keep, nullptr), L, stream, B.keys);
     if (s != AD_OK) return s;
-    hipLaunchKernelGGL(k_count_bytes, dim3((unsigned)std::min<int64_t>(SUM_BLOCKS, ceil_div(m, SBLOCK))),
-                       dim3(SBLOCK), 0, stream, m, keep, L.counts);
-    AD_LAUNCH_CHECK("k_count_bytes");
-    hipLaunchKernelGGL(k_store_count, dim3(1), dim3(1), 0, stream, L.counts, n_kept);
-    AD_LAUNCH_CHECK("k_store_count");
+    s = count_kept(m, keep, L.counts, n_kept, stream);
+    if (s != AD_OK) return s;
     // the host tables must outlive their copies
     AD_HIP(hipStreamSynchronize(stream));
     if (e_used_host) *e_used_host = e;

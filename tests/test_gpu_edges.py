@@ -144,3 +144,41 @@ def test_fp64_rows_of_every_length(api, values):
             ref[g.eid[p][rank < bud[p.stop - p.start]]] = 1
         np.testing.assert_array_equal(_np(keep), ref)
         assert int(nk.item()) == ref.sum()
+
+
+# ------------------------------------------------- plan of the short rows --
+
+@pytest.mark.parametrize("n", [1, 63, 64, 65, 1023, 1025, 70_000])
+def test_short_row_packing(api, n):
+    """Rows packed into waves at the edges of tiles: rows that fill a wave
+    exactly, rows closed by long ones, runs of isolated rows, and tiles
+    without any short row; the fit over both orders equals the oracle's."""
+    announce(f"short rows n={n}")
+    rng = np.random.default_rng(n)
+    hubs = max(1, n // 40)                             # long rows (above 64 where n allows) between short ones
+    u = rng.integers(0, hubs, 6 * n) * 40 % max(1, n)
+    v = rng.integers(0, n, 6 * n)
+    iso = (np.arange(n) // 64) % 5 == 3                # every fifth tile isolated
+    ok = (u != v) & ~iso[u] & ~iso[v]
+    key = np.unique(np.minimum(u, v)[ok] * np.int64(n) + np.maximum(u, v)[ok])
+    g = G.from_edges(n, key // max(n, 1), key % max(n, 1))
+    rho = np.round(rng.random(g.m), 3).astype(np.float32)
+    dg = api.DeviceGraph.from_host(g, "cuda")
+    if g.m == 0:
+        keep, nk = api.sparsify(dg, torch.empty(0, device="cuda"), 0, 0.5)
+        assert int(nk.item()) == 0
+        return
+    t = torch.from_numpy(rho).cuda()
+    kl, kg, nk, (el, eg) = api.sparsify_fit_both(dg, t, 0.4)
+    for o, (keep, e) in enumerate([(kl, el), (kg, eg)]):
+        e_o, keep_o, kept_o = oracle.fit_exponent(g, rho.astype(np.float64), o, 0.4)
+        assert e == e_o
+        np.testing.assert_array_equal(_np(keep), keep_o)
+        assert int(_np(nk)[o]) == kept_o
+        # a keep buffer that starts one byte past a 16-byte boundary
+        buf = torch.full((g.m + 32,), 7, dtype=torch.uint8, device="cuda")
+        k1, n1 = api.sparsify(dg, t, o, e, keep=buf[1:1 + g.m])
+        keep_f, kept_f = oracle.sparsify(g, rho.astype(np.float64), o, e)
+        np.testing.assert_array_equal(_np(k1), keep_f)
+        assert int(n1.item()) == kept_f
+        assert int(buf[0]) == 7 and bool((buf[1 + g.m:] == 7).all())
