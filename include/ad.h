@@ -39,9 +39,9 @@
  *   - Library-owned state: the selection calls on FP32 distances
  *     (ad_sparsify, ad_sparsify_fit, ad_sparsify_fit_both,
  *     ad_edge_dist_sparsify, ad_edge_dist_fit_both, ad_sparsify_binned)
- *     rank rows longer than 64 on three helper streams per device, of
- *     default priority, created on first use and kept until
- *     the process ends; they are forked from the caller's stream with an
+ *     rank rows longer than 64 of graphs with at least 2^21 stored entries on
+ *     three helper streams per device, of default priority, created on first
+ *     use and kept until the process ends; they are forked from the caller's stream with an
  *     event after the call's first kernels and joined back into it with
  *     events before the call returns, so the caller's stream orders all of
  *     the call's work, and a per-device mutex serialises the forks of calls

@@ -11,10 +11,9 @@
 // Keys are unique inside a row, so ranks are well defined.  Rows of degree
 // <= 64 are packed several to a wave, one entry per lane, and rank by
 // counting through shuffles.  Rows of degree <= 8192 sort in LDS, one
-// workgroup per row sized to the row: a radix sort of the distance bits, or,
-// for a caller's own 64-bit keys, counting inside one wave (<= 512) and a
-// bitonic network (<= 8192).  Longer rows are cut into buckets by a sorted
-// sample and rank inside their bucket.  FP64 distances take the same sorts
+// workgroup per row sized to the row: a radix sort of the distance bits.
+// Longer rows are cut into buckets by a sorted sample and rank inside their
+// bucket.  FP64 distances take the same sorts
 // and buckets on 64-bit codes.
 //
 // Selection at fixed e: entry (i, j) selects its edge when rank < budget[d_i];
@@ -309,7 +308,7 @@ __global__ __launch_bounds__(SBLOCK) void k_normalize(int64_t n, int64_t nnz, co
 
 // ------------------------------------------------------------------ ranking --
 
-enum { MODE_FIXED = 0, MODE_REC = 1, MODE_REC_L = 2, MODE_REC_G = 3 };
+enum { MODE_FIXED = 0, MODE_REC = 1 };
 
 // Original id of the neighbour of entry p (tie-break key): the per-entry
 // copy when the graph carries one, else a gather through orig_id.
@@ -323,34 +322,13 @@ __device__ __forceinline__ int32_t nbr_id(int64_t p, int32_t j, const int32_t *_
 // (budget2, keep2); otherwise the rank of `orient`).  MODE_REC stores the
 // side record {d, first rank, second rank, 0} at recs[2e + (row > j)]: with
 // `both` the LOCAL and the GLOBAL rank, otherwise the rank of `orient` in
-// both places; one 16-byte store per entry.  The bucketed rows rank one
-// orientation per pass: MODE_REC_L stores {d, rank} in words 0 and 1,
-// MODE_REC_G stores d and the rank in words 0 and 2.
+// both places; one 16-byte store per entry.
 struct Emit {
     int mode, orient, both;
     const int32_t *budget, *budget2;
     uint8_t *keep, *keep2;
     uint4 *recs;
 };
-
-// Order-preserving 64-bit key of (rho, orig_id) for the row's order
-// (FP32 distances); the GLOBAL key is the LOCAL key with the rho half
-// inverted, i.e. key ^ KEY_FLIP.
-constexpr unsigned long long KEY_FLIP = 0xffffffff00000000ull;
-__device__ __forceinline__ unsigned long long sort_key(float r, int32_t id, int orient) {
-    uint32_t b = __float_as_uint(r);                 // rho >= 0: bits are monotone
-    if (orient == AD_GLOBAL) b = ~b;
-    return ((unsigned long long)b << 32) | (unsigned long long)(uint32_t)id;
-}
-
-// Key of CSR entry p (edge e, neighbour id `id`): the caller's own 64-bit
-// key when `keys` is given (distinct within each row and below ~0; the row
-// order is then ascending keys), else the distance key above.
-__device__ __forceinline__ unsigned long long entry_key(const unsigned long long *__restrict__ keys,
-                                                        const float *__restrict__ rho, int64_t p, int32_t e,
-                                                        int32_t id, int orient) {
-    return keys ? keys[p] : sort_key(rho[e], id, orient);
-}
 
 // Rank of an entry in its row of d entries, in both orders of Algorithm 3:
 // LOCAL (rho ascending) and GLOBAL (rho descending), ties by neighbour id
@@ -369,16 +347,8 @@ __device__ __forceinline__ void emit_ranks(const Emit &em, int64_t row, int32_t 
         }
         return;
     }
-    uint4 *r = em.recs + 2 * (int64_t)e + (row > j ? 1 : 0);
-    if (em.mode == MODE_REC) {
-        *r = make_uint4((uint32_t)d, (uint32_t)(em.both ? rank_local : rank_o),
-                        (uint32_t)(em.both ? rank_global : rank_o), 0u);
-    } else if (em.mode == MODE_REC_L) {
-        *reinterpret_cast<uint2 *>(r) = make_uint2((uint32_t)d, (uint32_t)rank_o);
-    } else {
-        reinterpret_cast<uint32_t *>(r)[0] = (uint32_t)d;
-        reinterpret_cast<uint32_t *>(r)[2] = (uint32_t)rank_o;
-    }
+    em.recs[2 * (int64_t)e + (row > j ? 1 : 0)] =
+        make_uint4((uint32_t)d, (uint32_t)(em.both ? rank_local : rank_o), (uint32_t)(em.both ? rank_global : rank_o), 0u);
 }
 
 // Rows of degree <= 64, packed: a wave takes consecutive rows whose entries
@@ -393,8 +363,8 @@ __global__ __launch_bounds__(SBLOCK) void k_rank_packed(
     const long long *__restrict__ plan, const unsigned int *__restrict__ plan_count,
     const int64_t *__restrict__ row_ptr, const int32_t *__restrict__ col,
     const int32_t *__restrict__ eid, const int32_t *__restrict__ orig_id,
-    const int32_t *__restrict__ col_orig, const Tr *__restrict__ rho,
-    const unsigned long long *__restrict__ keys, Emit em, const float *__restrict__ rho_ent) {
+    const int32_t *__restrict__ col_orig, const Tr *__restrict__ rho, Emit em,
+    const float *__restrict__ rho_ent) {
     const int lane = threadIdx.x & (WAVE - 1);
     const unsigned int np = *plan_count;
     const unsigned int nwaves = gridDim.x * (SBLOCK / WAVE);
@@ -425,13 +395,13 @@ __global__ __launch_bounds__(SBLOCK) void k_rank_packed(
         if (on) {
             my_j = col[e];
             my_e = eid[e];
-            if (!keys) my_rho = rho_ent ? (Tr)rho_ent[e] : rho[my_e];
+            my_rho = rho_ent ? (Tr)rho_ent[e] : rho[my_e];
             my_id = nbr_id(e, my_j, col_orig, orig_id);
         }
         // every lane walks its own row: as many steps as the wave's longest row
         int dmax = d;
         for (int o = WAVE / 2; o >= 1; o >>= 1) dmax = max(dmax, __shfl_xor(dmax, o, WAVE));
-        if (sizeof(Tr) == 4 && !keys) {
+        if constexpr (sizeof(Tr) == 4) {
             // FP32 distances: count on the 32-bit distance bits (rho >= 0, so
             // the bits order as the values): lt = #{rho' < rho}, eq = #{rho' ==
             // rho}; only when some row of the wave has a tie, a second pass
@@ -454,28 +424,6 @@ __global__ __launch_bounds__(SBLOCK) void k_rank_packed(
                 }
             }
             if (on) emit_ranks(em, first + k, my_j, my_e, d, lt + eqlt, d - lt - eq + eqlt);
-        } else if constexpr (sizeof(Tr) == 4) {
-            // caller keys: the row orders are those of 64-bit keys
-            const unsigned long long key =
-                keys ? (on ? keys[e] : 0ull) : sort_key((float)my_rho, my_id, em.both ? AD_LOCAL : em.orient);
-            const unsigned long long keyg = key ^ KEY_FLIP;
-            int r1 = 0, r2 = 0;
-            if (em.both) {
-                for (int t = 0; t < dmax; ++t) {
-                    const unsigned long long k = shfl(key, min(s0 + t, WAVE - 1));
-                    if (t < d) {
-                        r1 += (k < key) ? 1 : 0;
-                        r2 += ((k ^ KEY_FLIP) < keyg) ? 1 : 0;
-                    }
-                }
-            } else {
-                for (int t = 0; t < dmax; ++t) {
-                    const unsigned long long k = shfl(key, min(s0 + t, WAVE - 1));
-                    if (t < d) r1 += (k < key) ? 1 : 0;
-                }
-                r2 = r1;
-            }
-            if (on) emit_ranks(em, first + k, my_j, my_e, d, r1, r2);
         } else {
             int lt = 0, eq = 0, eqlt = 0;
             for (int t = 0; t < dmax; ++t) {
@@ -552,13 +500,21 @@ __global__ __launch_bounds__(SBLOCK) void k_sel_init(SelInit in) {
 // twice, three scan launches between and a pass of its own for the classes
 // took 107 us before the first row was ranked (n = 2^20; 15 + 20 us of it in
 // the two plan passes of a 4,096-vertex graph), 15 us here (4.4 us).
+// For the selection with binning the rows' random keys K_i come from the same
+// pass (a lane per row), where they cost a Philox block per row instead of
+// one per entry.
+struct BinKey {
+    uint64_t seed, graph_id;
+    const int32_t *orig_id;
+    uint32_t *vkey;                        // [n], or NULL: none
+};
 constexpr int SETUP_TB = 1024;             // sixteen tiles at a time
 constexpr int SETUP_TILES = 4;             // tiles per wave, at most
 
 __global__ __launch_bounds__(SETUP_TB) void k_rank_setup(int64_t n, const int64_t *__restrict__ row_ptr,
                                                          ClassBounds cb, int tiles_per_wave,
                                                          unsigned int *__restrict__ cnt, int32_t *__restrict__ lists,
-                                                         long long *__restrict__ plan) {
+                                                         long long *__restrict__ plan, BinKey bk) {
     __shared__ unsigned int part[NCLASS + 1], base[NCLASS + 1];
     __shared__ int64_t off[NCLASS];
     const int lane = threadIdx.x & (WAVE - 1), wave = threadIdx.x >> 6;
@@ -578,6 +534,12 @@ __global__ __launch_bounds__(SETUP_TB) void k_rank_setup(int64_t n, const int64_
         const int64_t r =
             (((int64_t)blockIdx.x * tiles_per_wave + k) * (SETUP_TB / WAVE) + wave) * RANK_TILE + lane;
         deg[k] = k < tiles_per_wave && r < n ? row_ptr[r + 1] - row_ptr[r] : 0;
+        if (bk.vkey && k < tiles_per_wave && r < n) {
+            uint64_t words[4];
+            philox4x64_10((uint64_t)(uint32_t)(bk.orig_id ? bk.orig_id[r] : (int32_t)r), 0, 1, 0, bk.seed, bk.graph_id,
+                          words);
+            bk.vkey[r] = (uint32_t)words[0];
+        }
     }
 #pragma unroll
     for (int k = 0; k < SETUP_TILES; ++k) {
@@ -656,158 +618,7 @@ __global__ __launch_bounds__(SETUP_TB) void k_rank_setup(int64_t n, const int64_
 }
 
 
-// Listed rows with 32 * KPL < d <= 64 * KPL (FP32 distances): one wave per row,
-// KPL keys per lane; each key's rank counts the row's smaller keys (and,
-// for both orders, the smaller GLOBAL keys), broadcast one lane at a time.
-template <int KPL>
-__global__ __launch_bounds__(SBLOCK) void k_rank_wave(
-    const int32_t *__restrict__ list, const unsigned int *__restrict__ count,
-    const int64_t *__restrict__ row_ptr, const int32_t *__restrict__ col,
-    const int32_t *__restrict__ eid, const int32_t *__restrict__ orig_id,
-    const int32_t *__restrict__ col_orig, const float *__restrict__ rho,
-    const unsigned long long *__restrict__ keys, Emit em) {
-    const int lane = threadIdx.x & (WAVE - 1);
-    const unsigned int nr = *count;
-    const unsigned int waves = gridDim.x * (SBLOCK / WAVE);
-    const int orient = em.both ? AD_LOCAL : em.orient;
-    for (unsigned int h = blockIdx.x * (SBLOCK / WAVE) + (threadIdx.x >> 6); h < nr; h += waves) {
-        const int64_t row = list[h];
-        const int64_t beg = row_ptr[row];
-        const int d = (int)(row_ptr[row + 1] - beg);
-        unsigned long long key[KPL];
-        int32_t jj[KPL], ee[KPL];
-#pragma unroll
-        for (int t = 0; t < KPL; ++t) {
-            const int q = t * WAVE + lane;
-            if (q < d) {
-                jj[t] = col[beg + q];
-                ee[t] = eid[beg + q];
-                key[t] = entry_key(keys, rho, beg + q, ee[t], nbr_id(beg + q, jj[t], col_orig, orig_id), orient);
-            } else {
-                jj[t] = 0;
-                ee[t] = 0;
-                key[t] = ~0ull;
-            }
-        }
-        int r1[KPL], r2[KPL];
-#pragma unroll
-        for (int t = 0; t < KPL; ++t) r1[t] = r2[t] = 0;
-        if (em.both) {
-            unsigned long long keyg[KPL];
-#pragma unroll
-            for (int t = 0; t < KPL; ++t) keyg[t] = key[t] ^ KEY_FLIP;
-#pragma unroll
-            for (int ts = 0; ts < KPL; ++ts) {
-                if (ts * WAVE >= d) break;                 // uniform across the wave
-                const int lim = min(WAVE, d - ts * WAVE);
-                for (int src = 0; src < lim; ++src) {
-                    const unsigned long long k = shfl(key[ts], src);
-                    const unsigned long long kg = k ^ KEY_FLIP;
-#pragma unroll
-                    for (int t = 0; t < KPL; ++t) {
-                        r1[t] += (k < key[t]) ? 1 : 0;
-                        r2[t] += (kg < keyg[t]) ? 1 : 0;
-                    }
-                }
-            }
-        } else {
-#pragma unroll
-            for (int ts = 0; ts < KPL; ++ts) {
-                if (ts * WAVE >= d) break;
-                const int lim = min(WAVE, d - ts * WAVE);
-                for (int src = 0; src < lim; ++src) {
-                    const unsigned long long k = shfl(key[ts], src);
-#pragma unroll
-                    for (int t = 0; t < KPL; ++t) r1[t] += (k < key[t]) ? 1 : 0;
-                }
-            }
-#pragma unroll
-            for (int t = 0; t < KPL; ++t) r2[t] = r1[t];
-        }
-#pragma unroll
-        for (int t = 0; t < KPL; ++t) {
-            const int q = t * WAVE + lane;
-            if (q < d) emit_ranks(em, row, jj[t], ee[t], d, r1[t], r2[t]);
-        }
-    }
-}
-
-// Listed rows with P_MAX/2 < d <= P_MAX (FP32 distances): bitonic sort in
-// LDS by a TB-thread workgroup.
-template <int P_MAX, int TB>
-__global__ __launch_bounds__(TB) void k_rank_bitonic(
-    const int32_t *__restrict__ list, const unsigned int *__restrict__ count,
-    const int64_t *__restrict__ row_ptr, const int32_t *__restrict__ col,
-    const int32_t *__restrict__ eid, const int32_t *__restrict__ orig_id,
-    const int32_t *__restrict__ col_orig, const float *__restrict__ rho,
-    const unsigned long long *__restrict__ keys, Emit em) {
-    __shared__ unsigned long long key[P_MAX];
-    __shared__ uint16_t idx[P_MAX];
-    const unsigned int nr = *count;
-    const int orient = em.both ? AD_LOCAL : em.orient;
-    for (unsigned int h = blockIdx.x; h < nr; h += gridDim.x) {
-        const int64_t row = list[h];
-        const int64_t beg = row_ptr[row];
-        const int d = (int)(row_ptr[row + 1] - beg);
-        int P = 1;
-        while (P < d) P <<= 1;
-        for (int t = threadIdx.x; t < P; t += TB) {
-            if (t < d) {
-                int32_t j = col[beg + t];
-                key[t] = entry_key(keys, rho, beg + t, eid[beg + t], nbr_id(beg + t, j, col_orig, orig_id), orient);
-            } else {
-                key[t] = ~0ull;
-            }
-            idx[t] = (uint16_t)t;
-        }
-        __syncthreads();
-        for (int size = 2; size <= P; size <<= 1) {
-            for (int stride = size >> 1; stride > 0; stride >>= 1) {
-                for (int t = threadIdx.x; t < (P >> 1); t += TB) {
-                    int a = 2 * t - (t & (stride - 1));
-                    int b = a + stride;
-                    bool up = ((a & size) == 0);
-                    unsigned long long ka = key[a], kb = key[b];
-                    if ((ka > kb) == up) {
-                        key[a] = kb;
-                        key[b] = ka;
-                        uint16_t ia = idx[a];
-                        idx[a] = idx[b];
-                        idx[b] = ia;
-                    }
-                }
-                __syncthreads();
-            }
-        }
-        for (int t = threadIdx.x; t < d; t += TB) {
-            const int64_t p = beg + idx[t];
-            int64_t rank_global = t;
-            if (em.both) {
-                // sorted LOCAL: the run [a, b) of equal rho holds t; GLOBAL puts the
-                // d - b larger distances first, then the run in the same id order
-                const unsigned long long hb = key[t] >> 32;
-                int a = 0, hi = d;
-                while (a < hi) {
-                    const int mid = (a + hi) >> 1;
-                    if ((key[mid] >> 32) < hb) a = mid + 1;
-                    else hi = mid;
-                }
-                int b = a;
-                hi = d;
-                while (b < hi) {
-                    const int mid = (b + hi) >> 1;
-                    if ((key[mid] >> 32) <= hb) b = mid + 1;
-                    else hi = mid;
-                }
-                rank_global = (int64_t)(d - b) + (t - a);
-            }
-            emit_ranks(em, row, col[p], eid[p], d, t, rank_global);
-        }
-        __syncthreads();
-    }
-}
-
-// Listed rows with d <= TB * IPT (FP32 distances, no caller keys): one
+// Listed rows with d <= TB * IPT: one
 // workgroup per row sorts the row's distance bits (rho >= 0, so the bits
 // order as the values) with the entry's place in the row as payload, by a
 // block radix sort in LDS (8-bit digits, four passes).  A distance shared by
@@ -1069,27 +880,23 @@ __device__ __forceinline__ int hub_upper(const K *samp, int S, K k) {
     return lo;
 }
 
-// Key of entry p for the bucket partition: 64-bit (rho, id) or caller keys
-// of one orientation, or, with K = uint32_t, the 32-bit distance bits alone
-// (both orientations from one partition: equal distances share a bucket);
-// for FP64 distances (Tr double) their 64-bit codes, both orientations too.
+// Key of entry p for the bucket partition: the caller's own 64-bit key when
+// `keys` is given (distinct within each row; the row order is then ascending
+// keys), else the distance's code (both orientations from one partition:
+// equal distances share a bucket).
 template <typename K, typename Tr>
 __device__ __forceinline__ K hub_key(const unsigned long long *__restrict__ keys, const Tr *__restrict__ rho,
-                                     const Tr *__restrict__ rho_ent, int64_t p, const int32_t *__restrict__ eid,
-                                     const int32_t *__restrict__ col, const int32_t *__restrict__ col_orig,
-                                     const int32_t *__restrict__ orig_id, int orient) {
+                                     const Tr *__restrict__ rho_ent, int64_t p, const int32_t *__restrict__ eid) {
     if constexpr (sizeof(Tr) == 8) return rank_code(rho[eid[p]]);
     else if constexpr (sizeof(K) == 4) return __float_as_uint(rho_ent ? rho_ent[p] : rho[eid[p]]);
-    else return entry_key(keys, rho, p, eid[p], nbr_id(p, col[p], col_orig, orig_id), orient);
+    else return keys[p];
 }
 
 template <typename K, typename Tr = float>
 __global__ __launch_bounds__(HUB_TB) void k_hub_partition(
     const int32_t *__restrict__ list, const unsigned int *__restrict__ count,
-    const int64_t *__restrict__ row_ptr, const int32_t *__restrict__ col,
-    const int32_t *__restrict__ eid, const int32_t *__restrict__ orig_id,
-    const int32_t *__restrict__ col_orig, const Tr *__restrict__ rho, const Tr *__restrict__ rho_ent,
-    const unsigned long long *__restrict__ keys, int orient, HubScratch hs) {
+    const int64_t *__restrict__ row_ptr, const int32_t *__restrict__ eid, const Tr *__restrict__ rho,
+    const Tr *__restrict__ rho_ent, const unsigned long long *__restrict__ keys, HubScratch hs) {
     __shared__ K samp[HUB_SAMPLE];
     __shared__ uint32_t cnt[HUB_MAX_B];
     __shared__ uint32_t wsum[HUB_TB / WAVE];
@@ -1106,7 +913,7 @@ __global__ __launch_bounds__(HUB_TB) void k_hub_partition(
         const int B = (int)min((int64_t)(S / HUB_MIN_SP), (d + HUB_BUCKET - 1) / HUB_BUCKET);
         for (int t = threadIdx.x; t < S; t += HUB_TB) {
             const int64_t p = beg + ((int64_t)t * d) / S;
-            samp[t] = hub_key<K, Tr>(keys, rho, rho_ent, p, eid, col, col_orig, orig_id, orient);
+            samp[t] = hub_key<K, Tr>(keys, rho, rho_ent, p, eid);
         }
         for (int b = threadIdx.x; b < B; b += HUB_TB) cnt[b] = 0;
         __syncthreads();
@@ -1127,7 +934,7 @@ __global__ __launch_bounds__(HUB_TB) void k_hub_partition(
         }
         for (int64_t q = threadIdx.x; q < d; q += HUB_TB) {
             const int64_t p = beg + q;
-            const K k = hub_key<K, Tr>(keys, rho, rho_ent, p, eid, col, col_orig, orig_id, orient);
+            const K k = hub_key<K, Tr>(keys, rho, rho_ent, p, eid);
             atomicAdd(&cnt[min(B - 1, hub_upper(samp, S, k) * B / S)], 1u);
             // 32-bit keys: kept at the entry's own place for the scatter pass
             // (one gather of the distance per entry instead of two)
@@ -1158,7 +965,7 @@ __global__ __launch_bounds__(HUB_TB) void k_hub_partition(
                 const uint32_t at = atomicAdd(&cnt[min(B - 1, hub_upper(samp, S, k) * B / S)], 1u);
                 hs.key[beg + at] = ((unsigned long long)k << 32) | (uint32_t)q;
             } else {
-                const K k = hub_key<K, Tr>(keys, rho, rho_ent, p, eid, col, col_orig, orig_id, orient);
+                const K k = hub_key<K, Tr>(keys, rho, rho_ent, p, eid);
                 const uint32_t at = atomicAdd(&cnt[min(B - 1, hub_upper(samp, S, k) * B / S)], 1u);
                 hs.key[beg + at] = (unsigned long long)k;
                 hs.pos[beg + at] = (uint32_t)q;
@@ -1169,11 +976,12 @@ __global__ __launch_bounds__(HUB_TB) void k_hub_partition(
 }
 
 // One wave per bucket: each key's rank among the bucket's keys, counted
-// against all of them broadcast 64 at a time; HUB_KPL * 64 own keys per pass.
-// `em` names one orientation (the one the keys were built for).
+// against all of them broadcast 64 at a time; HUB_KPL * 64 own keys per pass
+// (a caller's own 64-bit keys, one order).  With rank_out every entry's rank goes
+// there, else it is emitted.
 __global__ __launch_bounds__(SBLOCK) void k_hub_rank(
     const int64_t *__restrict__ row_ptr, const int32_t *__restrict__ col, const int32_t *__restrict__ eid,
-    Emit em, HubScratch hs) {
+    Emit em, HubScratch hs, uint32_t *__restrict__ rank_out) {
     const int lane = threadIdx.x & (WAVE - 1);
     const unsigned int nb = (unsigned int)min((int64_t)(*hs.nbk), hs.cap);
     const unsigned int waves = gridDim.x * (SBLOCK / WAVE);
@@ -1208,7 +1016,8 @@ __global__ __launch_bounds__(SBLOCK) void k_hub_rank(
                 if (q < c) {
                     const int64_t p = beg + bp[q];
                     const int64_t r = (int64_t)off + rank[t];
-                    emit_ranks(em, row, col[p], eid[p], d, r, r);
+                    if (rank_out) rank_out[p] = (uint32_t)r;
+                    else emit_ranks(em, row, col[p], eid[p], d, r, r);
                 }
             }
         }
@@ -2023,8 +1832,8 @@ struct SelLayout {
     HubScratch hub;               // rows longer than SORT_CAP (d_max > SORT_CAP only)
 };
 
-// Degree classes above 64: wave counting with 2/4/8 keys per lane, bitonic
-// sorts in LDS of 1024/2048/4096/8192 keys, then the bucket partition.
+// Degree classes above 64: sorts by one wave (128, 256, 512 keys) and by
+// workgroups (1024 .. 8192), then the bucket partition.
 static const int64_t CLASS_LO[NCLASS + 1] = {64, 128, 256, 512, 1024, 2048, 4096, 8192, (int64_t)1 << 62};
 
 static size_t sel_layout(const ad_graph *g, void *ws, size_t ws_bytes, SelLayout *L, bool both = false) {
@@ -2167,7 +1976,8 @@ constexpr int64_t FORK_ENTRIES = (int64_t)1 << 21;
 
 // The launches every selection starts with: counters (with keep[] zeroed and
 // the log tables filled where asked), then the plan and the class lists.
-static ad_status rank_setup(const ad_graph *g, const SelLayout &L, uint8_t *zero_keep, bool logs, hipStream_t st) {
+static ad_status rank_setup(const ad_graph *g, const SelLayout &L, uint8_t *zero_keep, bool logs, hipStream_t st,
+                            const BinKey *bin = nullptr) {
     SelInit in;
     in.cnt = L.cnt;
     in.nbk = L.hub.nbk;
@@ -2185,43 +1995,66 @@ static ad_status rank_setup(const ad_graph *g, const SelLayout &L, uint8_t *zero
     const int64_t ntiles = ceil_div(g->n, RANK_TILE), per = SETUP_TB / WAVE;
     const int tpw = (int)std::min<int64_t>(SETUP_TILES, std::max<int64_t>(1, ceil_div(ntiles, 256 * per)));
     hipLaunchKernelGGL(k_rank_setup, dim3((unsigned)ceil_div(ntiles, tpw * per)), dim3(SETUP_TB), 0, st, g->n,
-                       g->row_ptr, L.cb, tpw, L.cnt, L.lists, L.plan);
+                       g->row_ptr, L.cb, tpw, L.cnt, L.lists, L.plan, bin ? *bin : BinKey{0, 0, nullptr, nullptr});
     AD_LAUNCH_CHECK("k_rank_setup");
     return AD_OK;
 }
 
-// Rank every entry of every row and emit per `em`, after rank_setup.
-template <typename Tr>
-static ad_status rank_all(const ad_graph *g, const Tr *rho, const Emit &em, const SelLayout &L, hipStream_t st,
-                          const unsigned long long *keys = nullptr, const float *rho_ent = nullptr) {
-    const int64_t n = g->n;
-    if (n <= 0 || g->m <= 0) return AD_OK;
-    TraceScope trace("k_rank", st);
-    ad_status s;
-    // FP32 rows above 64 of larger graphs: fork the classes off
+// A selection's streams for the row classes: three helper streams forked from
+// the caller's (rule above), or the caller's own.
+struct ClassFork {
     RankFork *fk = nullptr;
     std::unique_lock<std::mutex> hold;
-    hipStream_t cls[3] = {st, st, st};
-    if (sizeof(Tr) == 4 && g->d_max > 64 && 2 * g->m >= FORK_ENTRIES) {
+    hipStream_t cls[3];
+    ad_status open(const ad_graph *g, hipStream_t st) {
+        cls[0] = cls[1] = cls[2] = st;
+        if (g->d_max <= 64 || 2 * g->m < FORK_ENTRIES) return AD_OK;
         hipStreamCaptureStatus cap = hipStreamCaptureStatusNone;
         if (hipStreamIsCapturing(st, &cap) == hipSuccess && cap == hipStreamCaptureStatusNone) fk = rank_fork();
         else (void)hipGetLastError();
-        if (fk) {
-            hold = std::unique_lock<std::mutex>(fk->mu);
-            AD_HIP(hipEventRecord(fk->fork, st));
-            for (int h = 0; h < 3; ++h) {
-                AD_HIP(hipStreamWaitEvent(fk->side[h], fk->fork, 0));
-                cls[h] = fk->side[h];
-            }
+        if (!fk) return AD_OK;
+        hold = std::unique_lock<std::mutex>(fk->mu);
+        AD_HIP(hipEventRecord(fk->fork, st));
+        for (int h = 0; h < 3; ++h) {
+            AD_HIP(hipStreamWaitEvent(fk->side[h], fk->fork, 0));
+            cls[h] = fk->side[h];
         }
+        return AD_OK;
     }
+    // the caller's stream waits for the three class streams
+    ad_status join(hipStream_t st) {
+        if (!fk) return AD_OK;
+        for (int h = 0; h < 3; ++h) {
+            AD_HIP(hipEventRecord(fk->join[h], fk->side[h]));
+            AD_HIP(hipStreamWaitEvent(st, fk->join[h], 0));
+        }
+        return AD_OK;
+    }
+};
+
+// Rank every entry of every row and emit per `em`, after rank_setup.
+template <typename Tr>
+static ad_status rank_all(const ad_graph *g, const Tr *rho, const Emit &em, const SelLayout &L, hipStream_t st,
+                          const float *rho_ent = nullptr) {
+    const int64_t n = g->n;
+    if (n <= 0 || g->m <= 0) return AD_OK;
+    TraceScope trace("k_rank", st);
+    // FP32 rows above 64 of larger graphs: fork the classes off
+    ClassFork cf;
+    hipStream_t *const cls = cf.cls;
+    cls[0] = cls[1] = cls[2] = st;
+    if (sizeof(Tr) == 4) {
+        const ad_status s = cf.open(g, st);
+        if (s != AD_OK) return s;
+    }
+    const bool fk = cf.fk != nullptr;
     // rows of degree <= 64, packed into waves: after the longest rows' launches
     // where those run on their own streams (their large workgroups would wait
     // for room behind the packed waves), else first
     auto rank_packed = [&]() {
         const unsigned blocks = (unsigned)std::min<int64_t>(4096, ceil_div(n, SBLOCK / WAVE));
         hipLaunchKernelGGL((k_rank_packed<Tr>), dim3(blocks), dim3(SBLOCK), 0, st, L.plan, L.cnt + NCLASS, g->row_ptr,
-                           g->col, g->eid, g->orig_id, g->col_orig, rho, keys, em, rho_ent);
+                           g->col, g->eid, g->orig_id, g->col_orig, rho, em, rho_ent);
     };
     if (!fk) rank_packed();
     AD_LAUNCH_CHECK("k_rank_packed");
@@ -2232,11 +2065,8 @@ static ad_status rank_all(const ad_graph *g, const Tr *rho, const Emit &em, cons
     for (int k = 0; k < NCLASS; ++k) lst[k] = L.lists + L.cb.off[k];
     if (sizeof(Tr) == 4) {
         const float *rf = (const float *)rho;
-#define AD_RANK_ARGS_F g->row_ptr, g->col, g->eid, g->orig_id, g->col_orig, rf, keys, em
-        // the longest rows first on their streams: their latency is the tail.
-        // Distance keys: radix sorts of the 32-bit distance bits; the caller's
-        // own 64-bit keys: bitonic sorts of the keys.
-        if (!keys) {
+        // the longest rows first on their streams: their latency is the tail
+        {
             // one-wave workgroups for rows up to 512: more of them in flight
             const unsigned grid_w = (unsigned)std::min<int64_t>(8192, n);
 #define AD_RANK_ARGS_R g->row_ptr, g->col, g->eid, g->orig_id, g->col_orig, rf, rho_ent, em
@@ -2281,43 +2111,15 @@ static ad_status rank_all(const ad_graph *g, const Tr *rho, const Emit &em, cons
                                    AD_RANK_ARGS_R);
             AD_LAUNCH_CHECK("k_rank_radix");
 #undef AD_RANK_ARGS_R
-        } else {
-            if (g->d_max > 4096)
-                hipLaunchKernelGGL((k_rank_bitonic<8192, 1024>), dim3(grid), dim3(1024), 0, cls[0], lst[6], &L.cnt[6],
-                                   AD_RANK_ARGS_F);
-            if (g->d_max > 2048)
-                hipLaunchKernelGGL((k_rank_bitonic<4096, 512>), dim3(grid), dim3(512), 0, cls[1], lst[5], &L.cnt[5],
-                                   AD_RANK_ARGS_F);
-            if (fk) rank_packed();
-            if (g->d_max > 1024)
-                hipLaunchKernelGGL((k_rank_bitonic<2048, 256>), dim3(grid), dim3(256), 0, cls[2], lst[4], &L.cnt[4],
-                                   AD_RANK_ARGS_F);
-            if (g->d_max > 512)
-                hipLaunchKernelGGL((k_rank_bitonic<1024, 256>), dim3(grid), dim3(256), 0, cls[1], lst[3], &L.cnt[3],
-                                   AD_RANK_ARGS_F);
-            AD_LAUNCH_CHECK("k_rank_bitonic");
-            if (g->d_max > 256)
-                hipLaunchKernelGGL((k_rank_wave<8>), dim3(grid), dim3(SBLOCK), 0, cls[2], lst[2], &L.cnt[2],
-                                   AD_RANK_ARGS_F);
-            if (g->d_max > 128)
-                hipLaunchKernelGGL((k_rank_wave<4>), dim3(grid), dim3(SBLOCK), 0, cls[0], lst[1], &L.cnt[1],
-                                   AD_RANK_ARGS_F);
-            if (g->d_max > 64)
-                hipLaunchKernelGGL((k_rank_wave<2>), dim3(grid), dim3(SBLOCK), 0, cls[2], lst[0], &L.cnt[0],
-                                   AD_RANK_ARGS_F);
-            AD_LAUNCH_CHECK("k_rank_wave");
         }
-        // rows above SORT_CAP: the bucket partition (for caller keys once per
-        // orientation, on a helper stream; for distance keys once, on the caller's stream)
-        static_assert(HUB_CLASS == 7 && SORT_CAP == 8192, "bitonic classes end where the bucket partition starts");
-#undef AD_RANK_ARGS_F
-        if (g->d_max > SORT_CAP && !keys) {
+        // rows above SORT_CAP: the bucket partition, on the caller's stream
+        static_assert(HUB_CLASS == 7 && SORT_CAP == 8192, "the sorts end where the bucket partition starts");
+        if (g->d_max > SORT_CAP) {
             // distance keys: one partition on the 32-bit distance bits serves both orders
             for (int k = HUB_CLASS; k < NCLASS; ++k) {
                 if (g->d_max <= CLASS_LO[k]) break;
                 hipLaunchKernelGGL(k_hub_partition<uint32_t>, dim3(512), dim3(HUB_TB), 0, st, lst[k], &L.cnt[k],
-                                   g->row_ptr, g->col, g->eid, g->orig_id, g->col_orig, rf, rho_ent, keys, em.orient,
-                                   L.hub);
+                                   g->row_ptr, g->eid, rf, rho_ent, (const unsigned long long *)nullptr, L.hub);
                 AD_LAUNCH_CHECK("k_hub_partition");
             }
             // buckets of up to 256 / 512 entries by sorts, larger ones by counting
@@ -2331,40 +2133,9 @@ static ad_status rank_all(const ad_graph *g, const Tr *rho, const Emit &em, cons
             AD_LAUNCH_CHECK("k_hub_rank32");
             hipLaunchKernelGGL(k_hub_emit, dim3(2048), dim3(SBLOCK), 0, st, g->row_ptr, g->col, g->eid, em, L.hub);
             AD_LAUNCH_CHECK("k_hub_emit");
-        } else if (g->d_max > SORT_CAP) {
-            // caller keys carry one orientation: one partition per orientation asked for
-            for (int pass = 0; pass < (em.both ? 2 : 1); ++pass) {
-                Emit one = em;
-                one.both = 0;
-                if (em.both) {
-                    one.orient = pass == 0 ? AD_LOCAL : AD_GLOBAL;
-                    if (pass == 1) {
-                        one.budget = em.budget2;
-                        one.keep = em.keep2;
-                    }
-                }
-                if (em.mode != MODE_FIXED) one.mode = (em.both && pass == 1) ? MODE_REC_G : MODE_REC_L;
-                s = fill_i32((int32_t *)L.hub.nbk, 0, 1, cls[2]);
-                if (s != AD_OK) return s;
-                for (int k = HUB_CLASS; k < NCLASS; ++k) {
-                    if (g->d_max <= CLASS_LO[k]) break;
-                    hipLaunchKernelGGL(k_hub_partition<unsigned long long>, dim3(512), dim3(HUB_TB), 0, cls[2], lst[k], &L.cnt[k],
-                                       g->row_ptr, g->col, g->eid, g->orig_id, g->col_orig, rf, (const float *)nullptr, keys,
-                                       one.orient, L.hub);
-                    AD_LAUNCH_CHECK("k_hub_partition");
-                }
-                hipLaunchKernelGGL(k_hub_rank, dim3(2048), dim3(SBLOCK), 0, cls[2], g->row_ptr, g->col, g->eid, one,
-                                   L.hub);
-                AD_LAUNCH_CHECK("k_hub_rank");
-            }
         }
-        if (fk) {
-            // join: the caller's stream waits for the three class streams
-            for (int h = 0; h < 3; ++h) {
-                AD_HIP(hipEventRecord(fk->join[h], fk->side[h]));
-                AD_HIP(hipStreamWaitEvent(st, fk->join[h], 0));
-            }
-        }
+        const ad_status s = cf.join(st);
+        if (s != AD_OK) return s;
     } else {
         // FP64 rows: the same sorts on 64-bit codes, every class on the caller's stream
         const double *rd = (const double *)rho;
@@ -2383,8 +2154,8 @@ static ad_status rank_all(const ad_graph *g, const Tr *rho, const Emit &em, cons
         AD_LAUNCH_CHECK("k_rank_radix");
         if (g->d_max > SORT_CAP) {
             hipLaunchKernelGGL((k_hub_partition<unsigned long long, double>), dim3(512), dim3(HUB_TB), 0, st,
-                               lst[HUB_CLASS], &L.cnt[HUB_CLASS], g->row_ptr, g->col, g->eid, g->orig_id, g->col_orig,
-                               rd, (const double *)nullptr, (const unsigned long long *)nullptr, em.orient, L.hub);
+                               lst[HUB_CLASS], &L.cnt[HUB_CLASS], g->row_ptr, g->eid, rd, (const double *)nullptr,
+                               (const unsigned long long *)nullptr, L.hub);
             AD_LAUNCH_CHECK("k_hub_partition");
             hipLaunchKernelGGL(k_hub_rank64, dim3(2048), dim3(SBLOCK), 0, st, g->row_ptr, g->col, g->eid, g->orig_id,
                                g->col_orig, em, L.hub);
@@ -2607,7 +2378,7 @@ static ad_status sparsify_count(const ad_graph *g, ad_dtype rho_dtype, const voi
     if (s != AD_OK) return s;
     const Emit em = emit_single(MODE_FIXED, orient, budget, keep, nullptr);
     if (rho_dtype == AD_F32)
-        s = rank_all<float>(g, (const float *)rho, em, L, stream, nullptr, rho_ent);
+        s = rank_all<float>(g, (const float *)rho, em, L, stream, rho_ent);
     else
         s = rank_all<double>(g, (const double *)rho, em, L, stream);
     if (s != AD_OK) return s;
@@ -2852,7 +2623,7 @@ static ad_status sparsify_fit_impl(const ad_graph *g, ad_dtype rho_dtype, const 
     s = rank_setup(g, L, nullptr, true, stream);
     if (s != AD_OK) return s;
     if (rho_dtype == AD_F32)
-        s = rank_all<float>(g, (const float *)rho, em, L, stream, nullptr, rho_ent);
+        s = rank_all<float>(g, (const float *)rho, em, L, stream, rho_ent);
     else
         s = rank_all<double>(g, (const double *)rho, em, L, stream);
     if (s != AD_OK) return s;
@@ -3002,13 +2773,19 @@ extern "C" ad_status ad_edge_dist_fit_both(const ad_graph *g, int32_t R, ad_dtyp
 //     edge of smallest priority, until c_i = budget(d_i, e) edges are taken;
 //     an edge is kept when either endpoint takes it.
 //
-// On the device the rounds become two rankings of 64-bit keys per row: first
-// (bin, priority), whose rank p of an entry minus the rank of its bin's
-// first entry is the entry's round r (the bins' first entries are read off
-// the row laid out in that order); then (r, smallest priority of the bin),
-// whose rank is the entry's place in the selection order.  The rank
-// kernels of Algorithm 3 do both; the budget and the retention fit then
-// apply unchanged (the selected sets grow with e).
+// On the device an entry's round r is the number of entries of its bin with a
+// smaller priority, and its place in the selection order is its rank by
+// (r, smallest priority of its bin).  Rows of degree <= 64 find both by
+// counting inside their packed wave; rows up to SORT_CAP by two sorts in LDS,
+// one workgroup per row ((bin, priority), whose places give the rounds, then
+// (r, the bin's rank by its smallest priority)); longer rows by two rankings
+// of 64-bit keys in memory (the bucket partition).  The place goes where
+// Algorithm 3's rank goes, so budgets and the retention fit apply unchanged
+// (the selected sets grow with e).
+// What bounds it: gathers of rho by edge id and the scattered records, as in
+// the ranking of distances.  Before, the keys, both rankings and three passes
+// between them went through memory: n = 2^20, m = 16M, fitted to 30%: 4.45 ms
+// a call, 1.75 ms here.
 // ---------------------------------------------------------------------------
 
 namespace ad {
@@ -3022,152 +2799,420 @@ __device__ __forceinline__ uint32_t fmix32(uint32_t h) {
     return h;
 }
 
-// Rows of degree <= BIN_SHORT_ROW are handled by groups of BIN_SHORT_G
-// consecutive lanes (neighbouring lanes read neighbouring entries), longer
-// rows by one wave each: every kernel below runs its row body over the
-// short rows with groups of BIN_SHORT_G lanes, then over the long rows with
-// groups of WAVE lanes (rows strided over the grid's groups, then its waves).
-constexpr int64_t BIN_SHORT_ROW = 32;
-constexpr int BIN_SHORT_G = 16;
-
-template <int G>
-__device__ __forceinline__ double group_sum(double v) {
-    for (int o = G / 2; o >= 1; o >>= 1) v += __shfl_xor(v, o, WAVE);
-    return __shfl(v, (int)(threadIdx.x & (WAVE - 1)) & ~(G - 1), WAVE);   // one value for the group
-}
-template <int G>
-__device__ __forceinline__ double group_min(double v) {
-    for (int o = G / 2; o >= 1; o >>= 1) v = fmin(v, __shfl_xor(v, o, WAVE));
-    return v;
-}
-template <int G>
-__device__ __forceinline__ double group_max(double v) {
-    for (int o = G / 2; o >= 1; o >>= 1) v = fmax(v, __shfl_xor(v, o, WAVE));
-    return v;
-}
-
-// Runs body.template run<G>(row, lane in group) for every row with d >= 1:
-// short rows with G = BIN_SHORT_G, long rows with G = WAVE.  All lanes of a
-// wave take part in both passes (rows past n or of the other kind idle
-// through the group's loops), so the group shuffles see full waves.
-template <typename Body>
-__device__ __forceinline__ void for_bin_rows(int64_t n, const int64_t *__restrict__ row_ptr, const Body &body) {
-    constexpr int GS = BIN_SHORT_G;
-    const int64_t tid = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    const int64_t nt = (int64_t)gridDim.x * blockDim.x;
-    const int lane = threadIdx.x & (WAVE - 1);
-    // short rows: the wave's groups take rows g, g + ngroups, ... in lockstep
-    for (int64_t base = (tid / WAVE) * (WAVE / GS); base < n; base += (nt / WAVE) * (WAVE / GS)) {
-        const int64_t i = base + lane / GS;
-        const int64_t d = i < n ? row_ptr[i + 1] - row_ptr[i] : 0;
-        body.template run<GS>(i, lane % GS, d >= 1 && d <= BIN_SHORT_ROW);
-    }
-    for (int64_t i = tid / WAVE; i < n; i += nt / WAVE) {
-        const int64_t d = row_ptr[i + 1] - row_ptr[i];
-        if (d > BIN_SHORT_ROW) body.template run<WAVE>(i, lane, true);
-    }
-}
-
-// Per row: bins by Scott's rule and the first key (bin << 32 | priority) of
-// every entry.
+// What the bin kernels read.
 template <typename Tr>
-struct BinKeys {
+struct BinIn {
     const int64_t *row_ptr;
     const int32_t *col, *eid, *orig_id, *col_orig;
     const Tr *rho;
-    const double *cbrt_tab;
+    const double *cbrt_tab;               // [d_max + 1], the host's
     int64_t d_max;
-    uint64_t seed, graph_id;
-    unsigned long long *keys;
-    template <int G>
-    __device__ __forceinline__ void run(int64_t i, int lane, bool on) const {
-        const int64_t beg = on ? row_ptr[i] : 0, d = on ? row_ptr[i + 1] - beg : 0;
-        double mn = INFINITY, mx = -INFINITY, sum = 0.0;
-        for (int64_t q = lane; q < d; q += G) {
-            const double v = (double)rho[eid[beg + q]];
+    const uint32_t *vkey;                 // K_i
+};
+
+// Bins of a row: width and count by Scott's rule from sigma (already rounded
+// to single precision), the smallest and the largest value.
+struct BinRule {
+    double mn, h;
+    int64_t nb;
+    __device__ __forceinline__ int64_t bin(double v) const {
+        if (!(h > 0.0)) return 0;
+        const int64_t b = (int64_t)floor((v - mn) / h);
+        return b > nb - 1 ? nb - 1 : b;
+    }
+};
+__device__ __forceinline__ BinRule bin_rule(int64_t d, double mn, double mx, double ss,
+                                            const double *__restrict__ cbrt_tab, int64_t d_max) {
+    BinRule r;
+    const double sigma = (double)(float)sqrt(ss / (double)d);
+    // (rows longer than d_max break the graph's contract; they are kept in bounds)
+    r.h = (3.5 * sigma) / (d <= d_max ? cbrt_tab[d] : cbrt((double)d));
+    r.mn = mn;
+    r.nb = 1;
+    if (r.h > 0.0) {
+        const double k = ceil((mx - mn) / r.h);
+        r.nb = k < 1.0 ? 1 : (int64_t)k;
+        if (r.nb > d) r.nb = d;    // never binds: (max - min) / sigma <= sqrt(2 d)
+    }
+    return r;
+}
+
+// Sums over a row are taken in one order wherever the row is handled: rows of
+// up to 32 entries as 16 strided partial sums, longer rows as 64, partial
+// sums combined by halving the distance 32, 16, ..., 1.
+
+// Rows of degree <= 64, packed (k_rank_setup's plan): one entry per lane.
+template <typename Tr>
+__global__ __launch_bounds__(SBLOCK) void k_bin_packed(const long long *__restrict__ plan,
+                                                       const unsigned int *__restrict__ plan_count, BinIn<Tr> in,
+                                                       Emit em) {
+    const int lane = threadIdx.x & (WAVE - 1);
+    const unsigned int np = *plan_count;
+    const unsigned int nwaves = gridDim.x * (SBLOCK / WAVE);
+    for (unsigned int pi = blockIdx.x * (SBLOCK / WAVE) + (threadIdx.x >> 6); pi < np; pi += nwaves) {
+        const long long pe = plan[pi];
+        const int64_t first = pe >> 8;
+        const int nrows = (int)(pe & 0xff);
+        const int64_t e0 = in.row_ptr[first];
+        const int cnt = (int)(in.row_ptr[first + nrows] - e0);
+        const int st = lane < nrows ? (int)(in.row_ptr[first + lane] - e0) : cnt;
+        const uint32_t vk = lane < nrows ? in.vkey[first + lane] : 0u;
+        const bool on = lane < cnt;
+        const int64_t p = e0 + lane;
+        int32_t my_j = 0, my_e = 0;
+        double v = 0.0;
+        uint32_t u = 0u;
+        if (on) {
+            my_j = in.col[p];
+            my_e = in.eid[p];
+            v = (double)in.rho[my_e];
+            u = (uint32_t)nbr_id(p, my_j, in.col_orig, in.orig_id);
+        }
+        // my row: the last row of the wave that starts at or before my entry
+        int k = 0;
+        for (int step = WAVE / 2; step >= 1; step >>= 1) {
+            const int cand = k + step;
+            const int sc = shfl(st, cand < WAVE ? cand : WAVE - 1);
+            if (cand < nrows && sc <= lane) k = cand;
+        }
+        const int s0 = shfl(st, k);
+        const int s1 = shfl(st, k + 1 < WAVE ? k + 1 : WAVE - 1);
+        const int d = on ? ((k + 1 < nrows) ? s1 : cnt) - s0 : 0;
+        const int q = lane - s0;                                     // my place in the row
+        u = fmix32(u ^ (uint32_t)shfl((int)vk, k));
+        // the row's sums, smallest and largest value end at its first lane
+        double sum = v, mn = on ? v : INFINITY, mx = on ? v : -INFINITY;
+#pragma unroll
+        for (int o = WAVE / 2; o >= 1; o >>= 1) {
+            const double a = shfl_down(sum, o), lo = shfl_down(mn, o), hi = shfl_down(mx, o);
+            if (q + o < d) {
+                sum += a;
+                mn = fmin(mn, lo);
+                mx = fmax(mx, hi);
+            }
+        }
+        const double mean = d > 0 ? shfl(sum, s0) / (double)d : 0.0;
+        const double t = v - mean;
+        double ss = t * t;
+#pragma unroll
+        for (int o = WAVE / 2; o >= 1; o >>= 1) {
+            const double a = shfl_down(ss, o);
+            if (q + o < d) ss += a;
+        }
+        const BinRule rule =
+            bin_rule(d > 0 ? d : 1, shfl(mn, s0), shfl(mx, s0), shfl(ss, s0), in.cbrt_tab, in.d_max);
+        const int b = on ? (int)rule.bin(v) : 0;
+        // round and bin-first priority, then the place in the selection order,
+        // by counting over the row (as many steps as the wave's longest row)
+        int dmax = d;
+        for (int o = WAVE / 2; o >= 1; o >>= 1) dmax = max(dmax, __shfl_xor(dmax, o, WAVE));
+        uint32_t f = u;
+        int r = 0;
+        for (int i = 0; i < dmax; ++i) {
+            const int src = min(s0 + i, WAVE - 1);
+            const int bi = shfl(b, src);
+            const uint32_t ui = (uint32_t)shfl((int)u, src);
+            if (i < d && bi == b) {
+                r += ui < u ? 1 : 0;
+                f = min(f, ui);
+            }
+        }
+        const unsigned long long key = ((unsigned long long)(unsigned)r << 32) | f;
+        int rank = 0;
+        for (int i = 0; i < dmax; ++i) {
+            const int src = min(s0 + i, WAVE - 1);
+            const unsigned long long ki = ((unsigned long long)(unsigned)shfl(r, src) << 32) | (uint32_t)shfl((int)f, src);
+            if (i < d) rank += ki < key ? 1 : 0;
+        }
+        if (on) emit_ranks(em, first + k, my_j, my_e, d, rank, rank);
+    }
+}
+
+__device__ __forceinline__ int bits_of(unsigned int v) { return v ? 32 - __clz((int)v) : 0; }
+
+// Bins of a row in LDS: B_i <= 2 sqrt(2 d) cbrt(d) / 3.5 ((max - min) / sigma is
+// at most sqrt(2 d), and rounding sigma to single precision at most halves
+// it), 1,475 for the longest row; so the arrays leave room for two workgroups
+// per compute unit beside the sorts.
+constexpr int BINS_MAX = 2048;
+
+template <int TB, int IPT, typename Tr>
+union BinShared {
+    static constexpr int P = TB * IPT;
+    static constexpr int B = P < BINS_MAX ? P : BINS_MAX;
+    typename rocprim::block_radix_sort<uint32_t, TB, IPT, uint16_t>::storage_type sort;
+    Tr val[P];                            // the row's values
+    struct {
+        uint32_t key[P];                  // sorted keys and the entries' places in the row
+        uint16_t place[P];
+        uint32_t f[B], rank[B];           // per bin: smallest priority, the bin's rank by it
+        uint16_t first[B];                // place of the bin's first entry (0xffff: empty)
+    } bins;
+    uint16_t place[P];                    // selection order, by place in the row
+};
+struct BinStats {
+    double mn, mx, ss;
+    unsigned int r_max;
+};
+
+// One row of at most TB * IPT entries by a workgroup of TB threads.
+template <int TB, int IPT, typename Tr>
+__device__ __forceinline__ void bin_row(BinShared<TB, IPT, Tr> &sh, BinStats &st, int64_t row, const BinIn<Tr> &in,
+                                        const Emit &em) {
+    static_assert(TB * IPT <= 8192, "places and bins are 16-bit, 0xffff marks an empty bin");
+    using Sorter = rocprim::block_radix_sort<uint32_t, TB, IPT, uint16_t>;
+    const int tid = (int)threadIdx.x;
+    const int64_t beg = in.row_ptr[row];
+    const int d = (int)(in.row_ptr[row + 1] - beg);
+    {
+        int32_t e[IPT];
+#pragma unroll
+        for (int s = 0; s < IPT; ++s) {
+            const int q = s * TB + tid;
+            e[s] = q < d ? in.eid[beg + q] : 0;
+        }
+#pragma unroll
+        for (int s = 0; s < IPT; ++s) {
+            const int q = s * TB + tid;
+            if (q < d) sh.val[q] = in.rho[e[s]];
+        }
+    }
+    if (tid == 0) st.r_max = 0u;
+    __syncthreads();
+    if (tid < WAVE) {                                // one wave: 64 strided partial sums
+        double sum = 0.0, mn = INFINITY, mx = -INFINITY;
+#pragma unroll 4
+        for (int q = tid; q < d; q += WAVE) {
+            const double v = (double)sh.val[q];
             mn = fmin(mn, v);
             mx = fmax(mx, v);
             sum += v;
         }
-        mn = group_min<G>(mn);
-        mx = group_max<G>(mx);
-        sum = group_sum<G>(sum);
-        const double mean = d > 0 ? sum / (double)d : 0.0;
+        for (int o = WAVE / 2; o >= 1; o >>= 1) {
+            sum += __shfl_xor(sum, o, WAVE);
+            mn = fmin(mn, __shfl_xor(mn, o, WAVE));
+            mx = fmax(mx, __shfl_xor(mx, o, WAVE));
+        }
+        const double mean = shfl(sum, 0) / (double)d;
         double ss = 0.0;
-        for (int64_t q = lane; q < d; q += G) {
-            const double t = (double)rho[eid[beg + q]] - mean;
+#pragma unroll 4
+        for (int q = tid; q < d; q += WAVE) {
+            const double t = (double)sh.val[q] - mean;
             ss += t * t;
         }
-        ss = group_sum<G>(ss);
-        if (!on) return;
-        const double sigma = (double)(float)sqrt(ss / (double)d);
-        // (rows longer than d_max break the graph's contract; they are kept in bounds)
-        const double h = (3.5 * sigma) / (d <= d_max ? cbrt_tab[d] : cbrt((double)d));
-        int64_t nb = 1;
-        if (h > 0.0) {
-            const double k = ceil((mx - mn) / h);
-            nb = k < 1.0 ? 1 : (int64_t)k;
-            if (nb > d) nb = d;    // never binds: (max - min) / sigma <= sqrt(2 d)
-        }
-        uint64_t words[4];
-        philox4x64_10((uint64_t)(uint32_t)(orig_id ? orig_id[i] : (int32_t)i), 0, 1, 0, seed, graph_id, words);
-        const uint32_t K = (uint32_t)words[0];
-        for (int64_t q = lane; q < d; q += G) {
-            const int64_t p = beg + q;
-            const double v = (double)rho[eid[p]];
-            int64_t b = 0;
-            if (h > 0.0) {
-                b = (int64_t)floor((v - mn) / h);
-                if (b > nb - 1) b = nb - 1;
-            }
-            const uint32_t u = fmix32((uint32_t)nbr_id(p, col[p], col_orig, orig_id) ^ K);
-            keys[p] = ((unsigned long long)b << 32) | u;
+        for (int o = WAVE / 2; o >= 1; o >>= 1) ss += __shfl_xor(ss, o, WAVE);
+        if (tid == 0) {
+            st.mn = mn;
+            st.mx = mx;
+            st.ss = ss;
         }
     }
-};
+    __syncthreads();
+    BinRule rule = bin_rule(d, st.mn, st.mx, st.ss, in.cbrt_tab, in.d_max);
+    rule.nb = min(rule.nb, (int64_t)BinShared<TB, IPT, Tr>::B);       // never binds (BINS_MAX)
+    const int nb = (int)rule.nb;
+    const uint32_t K = in.vkey[row];
+    auto priority = [&](int q) {
+        const int64_t p = beg + q;
+        return fmix32((uint32_t)nbr_id(p, in.col[p], in.col_orig, in.orig_id) ^ K);
+    };
+    // sort by (bin, the priority's upper bits): 24 bits in all for up to 63 bins,
+    // three digits; entries that agree in them, a few per row, are told apart
+    // by their whole priorities afterwards
+    const int bb = bits_of((unsigned)nb);            // bin nb: padding, behind every entry
+    const int ub = min(32 - bb, 18);
+    uint32_t k[IPT];
+    uint16_t v[IPT];
+#pragma unroll
+    for (int s = 0; s < IPT; ++s) {
+        const int q = s * TB + tid;
+        k[s] = (uint32_t)nb << ub;
+        v[s] = (uint16_t)q;
+        if (q < d) k[s] = ((uint32_t)rule.bin((double)sh.val[q]) << ub) | (priority(q) >> (32 - ub));
+    }
+    __syncthreads();
+    Sorter().sort(k, v, sh.sort, 0u, (unsigned)(bb + ub));
+    __syncthreads();
+    // thread t holds sorted places t * IPT + s
+    for (int b = tid; b < nb; b += TB) {
+        sh.bins.first[b] = 0xffffu;
+        sh.bins.rank[b] = 0u;
+    }
+#pragma unroll
+    for (int s = 0; s < IPT; ++s) {
+        const int q = tid * IPT + s;
+        sh.bins.key[q] = k[s];
+        sh.bins.place[q] = v[s];
+    }
+    __syncthreads();
+    uint16_t at[IPT];                                // place by (bin, whole priority)
+#pragma unroll
+    for (int s = 0; s < IPT; ++s) {
+        const int q = tid * IPT + s;
+        at[s] = (uint16_t)q;
+        if (q >= d) continue;
+        const uint32_t key = k[s];
+        const bool head = q == 0 || sh.bins.key[q - 1] != key;
+        if (head && (q == 0 || (sh.bins.key[q - 1] >> ub) != (key >> ub))) sh.bins.first[key >> ub] = (uint16_t)q;
+        if (!head || (q + 1 < d && sh.bins.key[q + 1] == key)) {
+            int a = q, e = q + 1;                    // the run [a, e) of this key
+            while (a > 0 && sh.bins.key[a - 1] == key) --a;
+            while (e < d && sh.bins.key[e] == key) ++e;
+            const uint32_t u = priority(v[s]);
+            int before = 0;
+            for (int i = a; i < e; ++i) before += priority(sh.bins.place[i]) < u ? 1 : 0;
+            at[s] = (uint16_t)(a + before);
+        }
+    }
+    __syncthreads();
+#pragma unroll
+    for (int s = 0; s < IPT; ++s) {
+        const int q = tid * IPT + s;
+        if (q < d && at[s] == sh.bins.first[k[s] >> ub]) sh.bins.f[k[s] >> ub] = priority(v[s]);
+    }
+    __syncthreads();
+    // the bins' ranks by smallest priority (distinct): all pairs, spread over
+    // the workgroup
+    for (int i = tid; i < nb * nb; i += TB) {
+        const int b = i / nb, c = i - b * nb;
+        if (sh.bins.first[b] != 0xffffu && sh.bins.first[c] != 0xffffu && sh.bins.f[c] < sh.bins.f[b])
+            atomicAdd(&sh.bins.rank[b], 1u);
+    }
+    unsigned int r_max = 0u;
+#pragma unroll
+    for (int s = 0; s < IPT; ++s)
+        if (tid * IPT + s < d) r_max = max(r_max, (unsigned int)(at[s] - sh.bins.first[k[s] >> ub]));
+    for (int o = WAVE / 2; o >= 1; o >>= 1) r_max = max(r_max, (unsigned int)__shfl_xor((int)r_max, o, WAVE));
+    if ((tid & (WAVE - 1)) == 0) atomicMax(&st.r_max, r_max);
+    __syncthreads();
+    r_max = st.r_max;
+    // sort by (round, the bin's rank): r < 2^13 and nb <= 2^11, at most 25 bits
+#pragma unroll
+    for (int s = 0; s < IPT; ++s) {
+        const uint32_t b = k[s] >> ub;
+        k[s] = tid * IPT + s < d ? ((uint32_t)(at[s] - sh.bins.first[b]) << bb) | sh.bins.rank[b] : (r_max + 1u) << bb;
+    }
+    __syncthreads();
+    Sorter().sort(k, v, sh.sort, 0u, (unsigned)(bb + bits_of(r_max + 1u)));
+    __syncthreads();
+#pragma unroll
+    for (int s = 0; s < IPT; ++s) {
+        const int q = tid * IPT + s;
+        if (q < d) sh.place[v[s]] = (uint16_t)q;
+    }
+    __syncthreads();
+#pragma unroll 2
+    for (int s = 0; s < IPT; ++s) {
+        const int q = s * TB + tid;
+        if (q < d) {
+            const int64_t r = sh.place[q];
+            emit_ranks(em, row, in.col[beg + q], in.eid[beg + q], d, r, r);
+        }
+    }
+    __syncthreads();
+}
+
+template <int TB, int IPT, typename Tr>
+__global__ __launch_bounds__(TB) void k_bin_rows(const int32_t *__restrict__ list,
+                                                 const unsigned int *__restrict__ count, BinIn<Tr> in, Emit em) {
+    __shared__ BinShared<TB, IPT, Tr> sh;
+    __shared__ BinStats st;
+    const unsigned int nr = *count;
+    for (unsigned int h = blockIdx.x; h < nr; h += gridDim.x) bin_row<TB, IPT, Tr>(sh, st, list[h], in, em);
+}
+
+// Listed rows longer than SORT_CAP: the first key (bin << 32 | priority) of
+// every entry, a workgroup per row.  The values pass through LDS in chunks, so
+// that one wave can add them in the rows' common order at LDS speed.
+constexpr int BIN_HUB_CHUNK = 8192;
 
 template <typename Tr>
-__global__ __launch_bounds__(SBLOCK) void k_bin_keys(int64_t n, BinKeys<Tr> body) {
-    for_bin_rows(n, body.row_ptr, body);
-}
-
-// Rank in the (bin, priority) order of an entry, from the side records
-// written by the first ranking (word 1 of recs[2e + (i > j)]).
-__device__ __forceinline__ uint32_t side_rank(const uint4 *__restrict__ recs, int32_t e, int64_t i, int32_t j) {
-    return recs[2 * (int64_t)e + (i > j ? 1 : 0)].y;
-}
-
-// The row in (bin, priority) order: order[beg + rank] = entry offset, and
-// every entry's rank.
-struct BinOrder {
-    const int64_t *row_ptr;
-    const int32_t *col, *eid;
-    const uint4 *recs;
-    uint32_t *order, *rank;
-    template <int G>
-    __device__ __forceinline__ void run(int64_t i, int lane, bool on) const {
-        if (!on) return;
-        const int64_t beg = row_ptr[i], d = row_ptr[i + 1] - beg;
-        for (int64_t q = lane; q < d; q += G) {
-            const uint32_t r = side_rank(recs, eid[beg + q], i, col[beg + q]);
-            order[beg + r] = (uint32_t)q;
-            rank[beg + q] = r;
+__global__ __launch_bounds__(HUB_TB) void k_bin_hub_keys(const int32_t *__restrict__ list,
+                                                         const unsigned int *__restrict__ count, BinIn<Tr> in,
+                                                         unsigned long long *__restrict__ keys) {
+    __shared__ Tr val[BIN_HUB_CHUNK];
+    __shared__ BinStats st;
+    __shared__ double mean_s;
+    const int tid = (int)threadIdx.x;
+    const unsigned int nr = *count;
+    for (unsigned int h = blockIdx.x; h < nr; h += gridDim.x) {
+        const int64_t row = list[h];
+        const int64_t beg = in.row_ptr[row], d = in.row_ptr[row + 1] - beg;
+        double sum = 0.0, mn = INFINITY, mx = -INFINITY, ss = 0.0;
+        for (int pass = 0; pass < 2; ++pass) {
+            for (int64_t c0 = 0; c0 < d; c0 += BIN_HUB_CHUNK) {
+                const int c = (int)min((int64_t)BIN_HUB_CHUNK, d - c0);
+                __syncthreads();
+                for (int q = tid; q < c; q += HUB_TB) val[q] = in.rho[in.eid[beg + c0 + q]];
+                __syncthreads();
+                if (tid < WAVE) {                    // BIN_HUB_CHUNK is a multiple of 64: the stride goes on
+                    const double mean = pass ? mean_s : 0.0;
+#pragma unroll 4
+                    for (int q = tid; q < c; q += WAVE) {
+                        const double v = (double)val[q];
+                        if (pass == 0) {
+                            mn = fmin(mn, v);
+                            mx = fmax(mx, v);
+                            sum += v;
+                        } else {
+                            const double t = v - mean;
+                            ss += t * t;
+                        }
+                    }
+                }
+            }
+            if (tid < WAVE) {
+                for (int o = WAVE / 2; o >= 1; o >>= 1) {
+                    if (pass == 0) {
+                        sum += __shfl_xor(sum, o, WAVE);
+                        mn = fmin(mn, __shfl_xor(mn, o, WAVE));
+                        mx = fmax(mx, __shfl_xor(mx, o, WAVE));
+                    } else {
+                        ss += __shfl_xor(ss, o, WAVE);
+                    }
+                }
+                if (tid == 0) {
+                    if (pass == 0) {
+                        mean_s = sum / (double)d;
+                    } else {
+                        st.mn = mn;
+                        st.mx = mx;
+                        st.ss = ss;
+                    }
+                }
+            }
+            __syncthreads();
         }
+        const BinRule rule = bin_rule(d, st.mn, st.mx, st.ss, in.cbrt_tab, in.d_max);
+        const uint32_t K = in.vkey[row];
+        for (int64_t q = tid; q < d; q += HUB_TB) {
+            const int64_t p = beg + q;
+            const uint32_t u = fmix32((uint32_t)nbr_id(p, in.col[p], in.col_orig, in.orig_id) ^ K);
+            keys[p] = ((unsigned long long)rule.bin((double)in.rho[in.eid[p]]) << 32) | u;
+        }
+        __syncthreads();
     }
-};
+}
 
-// Each bin's first entry in that order: its rank (first_pos) and priority
-// (first_u), at the row's bin slots [beg, beg + B_i).
-struct BinFirsts {
-    const int64_t *row_ptr;
-    const unsigned long long *keys;
-    const uint32_t *order;
-    uint32_t *first_u, *first_pos;
-    template <int G>
-    __device__ __forceinline__ void run(int64_t i, int lane, bool on) const {
-        if (!on) return;
-        const int64_t beg = row_ptr[i], d = row_ptr[i + 1] - beg;
-        for (int64_t t = lane; t < d; t += G) {
+// The same rows' second keys from the ranks by the first: the row in that
+// order, each bin's first entry (place and priority, at the row's slots [beg,
+// beg + B_i)), then (round << 32 | the bin's smallest priority) in place of the
+// first key.
+__global__ __launch_bounds__(HUB_TB) void k_bin_hub_rounds(const int32_t *__restrict__ list,
+                                                           const unsigned int *__restrict__ count,
+                                                           const int64_t *__restrict__ row_ptr,
+                                                           const uint32_t *__restrict__ rank,
+                                                           uint32_t *__restrict__ order,
+                                                           uint32_t *__restrict__ first_u,
+                                                           uint32_t *__restrict__ first_pos,
+                                                           unsigned long long *__restrict__ keys) {
+    const unsigned int nr = *count;
+    for (unsigned int h = blockIdx.x; h < nr; h += gridDim.x) {
+        const int64_t row = list[h];
+        const int64_t beg = row_ptr[row], d = row_ptr[row + 1] - beg;
+        for (int64_t q = threadIdx.x; q < d; q += HUB_TB) order[beg + rank[beg + q]] = (uint32_t)q;
+        __syncthreads();
+        for (int64_t t = threadIdx.x; t < d; t += HUB_TB) {
             const unsigned long long k = keys[beg + order[beg + t]];
             const uint32_t b = (uint32_t)(k >> 32);
             if (t == 0 || (uint32_t)(keys[beg + order[beg + t - 1]] >> 32) != b) {
@@ -3175,40 +3220,25 @@ struct BinFirsts {
                 first_u[beg + b] = (uint32_t)k;
             }
         }
-    }
-};
-
-// Per entry: its round r (rank minus the rank of its bin's first entry) and
-// the second key (r << 32 | the bin's smallest priority), in place of the first.
-struct BinRounds {
-    const int64_t *row_ptr;
-    unsigned long long *keys;
-    const uint32_t *rank, *first_u, *first_pos;
-    template <int G>
-    __device__ __forceinline__ void run(int64_t i, int lane, bool on) const {
-        if (!on) return;
-        const int64_t beg = row_ptr[i], d = row_ptr[i + 1] - beg;
-        for (int64_t q = lane; q < d; q += G) {
+        __syncthreads();
+        for (int64_t q = threadIdx.x; q < d; q += HUB_TB) {
             const int64_t p = beg + q;
             const int64_t b = (int64_t)(keys[p] >> 32);
-            const uint32_t r = rank[p] - first_pos[beg + b];
-            keys[p] = ((unsigned long long)r << 32) | first_u[beg + b];
+            keys[p] = ((unsigned long long)(rank[p] - first_pos[beg + b]) << 32) | first_u[beg + b];
         }
+        __syncthreads();
     }
-};
-
-template <typename Body>
-__global__ __launch_bounds__(SBLOCK) void k_bin_rows(int64_t n, Body body) {
-    for_bin_rows(n, body.row_ptr, body);
 }
 
 struct BinLayout {
-    SelLayout sel;                // recs hold the first ranking's ranks, then the second's
-    unsigned long long *keys;     // [2m]
-    uint32_t *first_u, *first_pos;  // [2m]: per-row bin slots
-    uint32_t *order, *rank;         // [2m]: the row in the first order, and each entry's rank in it
-    double *cbrt_tab;             // [d_max + 1]
-    int32_t *budget;              // [d_max + 1]
+    SelLayout sel;
+    uint32_t *vkey;                 // [n]
+    double *cbrt_tab;               // [d_max + 1]
+    int32_t *budget;                // [d_max + 1]
+    // rows longer than SORT_CAP (d_max > SORT_CAP only), [2m] each
+    unsigned long long *keys;
+    uint32_t *first_u, *first_pos;  // per-row bin slots
+    uint32_t *order, *rank;         // the row in the first order, and each entry's rank in it
 };
 
 static size_t bin_layout(const ad_graph *g, void *ws, size_t ws_bytes, BinLayout *B) {
@@ -3216,15 +3246,18 @@ static size_t bin_layout(const ad_graph *g, void *ws, size_t ws_bytes, BinLayout
     if (ws && sel == 0) return 0;
     const size_t sel_bytes = sel_layout(g, nullptr, 0, nullptr, true);
     Carver c(ws ? (char *)ws + sel_bytes : nullptr, ws ? ws_bytes - std::min(ws_bytes, sel_bytes) : 0);
-    const int64_t nnz = std::max<int64_t>(1, 2 * g->m);
-    BinLayout l;
-    l.keys = c.take<unsigned long long>(nnz);
-    l.first_u = c.take<uint32_t>(nnz);
-    l.first_pos = c.take<uint32_t>(nnz);
-    l.order = c.take<uint32_t>(nnz);
-    l.rank = c.take<uint32_t>(nnz);
+    BinLayout l{};
+    l.vkey = c.take<uint32_t>((size_t)std::max<int64_t>(1, g->n));
     l.cbrt_tab = c.take<double>((size_t)g->d_max + 1);
     l.budget = c.take<int32_t>((size_t)g->d_max + 1);
+    if (g->d_max > SORT_CAP) {
+        const int64_t nnz = std::max<int64_t>(1, 2 * g->m);
+        l.keys = c.take<unsigned long long>(nnz);
+        l.first_u = c.take<uint32_t>(nnz);
+        l.first_pos = c.take<uint32_t>(nnz);
+        l.order = c.take<uint32_t>(nnz);
+        l.rank = c.take<uint32_t>(nnz);
+    }
     if (B) {
         l.sel = B->sel;
         *B = l;
@@ -3233,11 +3266,62 @@ static size_t bin_layout(const ad_graph *g, void *ws, size_t ws_bytes, BinLayout
     return sel_bytes + c.used;
 }
 
+// Every row's selection order, emitted per `em`, after rank_setup.
+template <typename Tr>
+static ad_status bin_all(const ad_graph *g, const Tr *rho, const Emit &em, const BinLayout &B, hipStream_t st) {
+    const SelLayout &L = B.sel;
+    const int64_t n = g->n;
+    TraceScope trace("k_bin", st);
+    const BinIn<Tr> in{g->row_ptr, g->col, g->eid, g->orig_id, g->col_orig, rho, B.cbrt_tab, (int64_t)g->d_max, B.vkey};
+    ClassFork cf;
+    ad_status s = cf.open(g, st);
+    if (s != AD_OK) return s;
+    const unsigned grid = (unsigned)std::min<int64_t>(2048, n), grid_w = (unsigned)std::min<int64_t>(8192, n);
+    // the longest rows first on their streams, the packed rows after them
+#define AD_BIN_ROWS(TB, IPT, GRID, K, STREAM)                                                                  \
+    if (g->d_max > CLASS_LO[K])                                                                                \
+    hipLaunchKernelGGL((k_bin_rows<TB, IPT, Tr>), dim3(GRID), dim3(TB), 0, STREAM, L.lists + L.cb.off[K], &L.cnt[K], in, em)
+    AD_BIN_ROWS(512, 16, grid, 6, cf.cls[0]);
+    AD_BIN_ROWS(512, 8, grid, 5, cf.cls[1]);
+    AD_BIN_ROWS(256, 8, grid, 4, cf.cls[2]);
+    const unsigned blocks = (unsigned)std::min<int64_t>(4096, ceil_div(n, SBLOCK / WAVE));
+    hipLaunchKernelGGL((k_bin_packed<Tr>), dim3(blocks), dim3(SBLOCK), 0, st, L.plan, L.cnt + NCLASS, in, em);
+    AD_LAUNCH_CHECK("k_bin_packed");
+    AD_BIN_ROWS(256, 4, grid, 3, cf.cls[1]);
+    AD_BIN_ROWS(64, 8, grid_w, 2, cf.cls[2]);
+    AD_BIN_ROWS(64, 4, grid_w, 1, st);
+    AD_BIN_ROWS(64, 2, grid_w, 0, cf.cls[2]);
+#undef AD_BIN_ROWS
+    AD_LAUNCH_CHECK("k_bin_rows");
+    if (g->d_max > SORT_CAP) {
+        const int32_t *list = L.lists + L.cb.off[HUB_CLASS];
+        const unsigned int *count = &L.cnt[HUB_CLASS];
+        hipLaunchKernelGGL((k_bin_hub_keys<Tr>), dim3(512), dim3(HUB_TB), 0, st, list, count, in, B.keys);
+        AD_LAUNCH_CHECK("k_bin_hub_keys");
+        for (int pass = 0; pass < 2; ++pass) {
+            if (pass) {
+                hipLaunchKernelGGL(k_bin_hub_rounds, dim3(512), dim3(HUB_TB), 0, st, list, count, g->row_ptr, B.rank,
+                                   B.order, B.first_u, B.first_pos, B.keys);
+                AD_LAUNCH_CHECK("k_bin_hub_rounds");
+                s = fill_i32((int32_t *)L.hub.nbk, 0, 1, st);
+                if (s != AD_OK) return s;
+            }
+            hipLaunchKernelGGL((k_hub_partition<unsigned long long>), dim3(512), dim3(HUB_TB), 0, st, list, count,
+                               g->row_ptr, g->eid, (const float *)nullptr, (const float *)nullptr, B.keys, L.hub);
+            AD_LAUNCH_CHECK("k_hub_partition");
+            hipLaunchKernelGGL(k_hub_rank, dim3(2048), dim3(SBLOCK), 0, st, g->row_ptr, g->col, g->eid, em, L.hub,
+                               pass ? nullptr : B.rank);
+            AD_LAUNCH_CHECK("k_hub_rank");
+        }
+    }
+    return cf.join(st);
+}
+
 static ad_status sparsify_binned_impl(const ad_graph *g, ad_dtype rho_dtype, const void *rho, uint64_t seed,
                                       uint64_t graph_id, double e, double target, uint8_t *keep, int64_t *n_kept,
                                       double *e_used_host, const BinLayout &B, hipStream_t stream) {
     const SelLayout &L = B.sel;
-    const int64_t n = g->n, m = g->m;
+    const int64_t m = g->m;
     ad_status s;
     if (m == 0) {
         s = fill_u64(L.counts, 0, 1, stream);
@@ -3250,59 +3334,29 @@ static ad_status sparsify_binned_impl(const ad_graph *g, ad_dtype rho_dtype, con
         }
         return AD_OK;
     }
+    const bool fit = target > 0.0;
+    const BinKey bk{seed, graph_id, g->orig_id, B.vkey};
+    s = rank_setup(g, L, fit ? nullptr : keep, fit, stream, &bk);
+    if (s != AD_OK) return s;
     // host tables by degree (the C library's cbrt and pow), copied to the device
     std::vector<double> cb((size_t)g->d_max + 1);
     for (int64_t d = 0; d <= g->d_max; ++d) cb[(size_t)d] = cbrt((double)d);
     AD_HIP(hipMemcpyAsync(B.cbrt_tab, cb.data(), cb.size() * sizeof(double), hipMemcpyHostToDevice, stream));
     std::vector<int32_t> bt;
-    if (!(target > 0.0)) {
+    if (!fit) {
         budget_table(g->d_max, e, bt);
         AD_HIP(hipMemcpyAsync(B.budget, bt.data(), bt.size() * sizeof(int32_t), hipMemcpyHostToDevice, stream));
     }
-    // a group of lanes per short row, a wave per long row
-    const unsigned grid = (unsigned)std::max<int64_t>(1, std::min<int64_t>(4096, ceil_div(n, SBLOCK / BIN_SHORT_G)));
-    {
-        TraceScope trace("k_bin", stream);
-        if (rho_dtype == AD_F32) {
-            const BinKeys<float> bk{g->row_ptr, g->col, g->eid, g->orig_id, g->col_orig, (const float *)rho,
-                                    B.cbrt_tab, (int64_t)g->d_max, seed, graph_id, B.keys};
-            hipLaunchKernelGGL((k_bin_keys<float>), dim3(grid), dim3(SBLOCK), 0, stream, n, bk);
-        } else {
-            const BinKeys<double> bk{g->row_ptr, g->col, g->eid, g->orig_id, g->col_orig, (const double *)rho,
-                                     B.cbrt_tab, (int64_t)g->d_max, seed, graph_id, B.keys};
-            hipLaunchKernelGGL((k_bin_keys<double>), dim3(grid), dim3(SBLOCK), 0, stream, n, bk);
-        }
-        AD_LAUNCH_CHECK("k_bin_keys");
-    }
-    // first ranking: (bin, priority); ranks into the side records
-    s = rank_setup(g, L, target > 0.0 ? nullptr : keep, target > 0.0, stream);
+    const Emit em = fit ? emit_single(MODE_REC, AD_LOCAL, nullptr, nullptr, L.recs)
+                        : emit_single(MODE_FIXED, AD_LOCAL, B.budget, keep, nullptr);
+    if (rho_dtype == AD_F32) s = bin_all<float>(g, (const float *)rho, em, B, stream);
+    else s = bin_all<double>(g, (const double *)rho, em, B, stream);
     if (s != AD_OK) return s;
-    s = rank_all<float>(g, nullptr, emit_single(MODE_REC, AD_LOCAL, nullptr, nullptr, L.recs), L, stream, B.keys);
-    if (s != AD_OK) return s;
-    {
-        TraceScope trace("k_bin", stream);
-        hipLaunchKernelGGL(k_bin_rows<BinOrder>, dim3(grid), dim3(SBLOCK), 0, stream, n,
-                           BinOrder{g->row_ptr, g->col, g->eid, L.recs, B.order, B.rank});
-        AD_LAUNCH_CHECK("k_bin_order");
-        hipLaunchKernelGGL(k_bin_rows<BinFirsts>, dim3(grid), dim3(SBLOCK), 0, stream, n,
-                           BinFirsts{g->row_ptr, B.keys, B.order, B.first_u, B.first_pos});
-        AD_LAUNCH_CHECK("k_bin_firsts");
-        hipLaunchKernelGGL(k_bin_rows<BinRounds>, dim3(grid), dim3(SBLOCK), 0, stream, n,
-                           BinRounds{g->row_ptr, B.keys, B.rank, B.first_u, B.first_pos});
-        AD_LAUNCH_CHECK("k_bin_rounds");
-    }
-    if (target > 0.0) {
-        // second ranking (round, bin order) over the first's records, then the retention fit
-        s = rank_all<float>(g, nullptr, emit_single(MODE_REC, AD_LOCAL, nullptr, nullptr, L.recs), L, stream,
-                            B.keys);
-        if (s != AD_OK) return s;
+    if (fit) {
         TraceScope trace_fit("k_fit_select", stream);
         uint8_t *kp[1] = {keep};
         return fit_from_recs(g, L, 1, fit_count_target(m, target), kp, n_kept, e_used_host, stream);
     }
-    // second ranking straight into keep at the fixed exponent
-    s = rank_all<float>(g, nullptr, emit_single(MODE_FIXED, AD_LOCAL, B.budget, keep, nullptr), L, stream, B.keys);
-    if (s != AD_OK) return s;
     s = count_kept(m, keep, L.counts, n_kept, stream);
     if (s != AD_OK) return s;
     // the host tables must outlive their copies

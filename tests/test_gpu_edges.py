@@ -182,3 +182,43 @@ def test_short_row_packing(api, n):
         np.testing.assert_array_equal(_np(k1), keep_f)
         assert int(n1.item()) == kept_f
         assert int(buf[0]) == 7 and bool((buf[1 + g.m:] == 7).all())
+
+
+# --------------------------------------------------- selection with binning --
+
+@pytest.mark.parametrize("values", ["f32", "f64", "one-bin", "many-bins"])
+def test_binned_rows_of_every_length(api, values):
+    """Rows at the bounds of the packed waves, of every sort and of the bucket
+    partition; all values of a row in one bin, and rows whose one outlier
+    gives them as many bins as their length allows."""
+    announce(f"binned rows {values}")
+    rng = np.random.default_rng(9)
+    degs = [1, 2, 31, 32, 33, 63, 64, 65, 128, 129, 256, 257, 512, 513, 1024, 1025, 2048, 2049, 4096, 4097, 8192, 8193, 20_000]
+    us, vs = [], []
+    leaf = len(degs)
+    for q, d in enumerate(degs):
+        us.append(np.full(d, q))
+        vs.append(np.arange(leaf, leaf + d))
+        leaf += d
+    chain = np.arange(len(degs), leaf - 1)
+    chain = chain[chain % 3 != 0]
+    g = G.from_edges(leaf, np.concatenate(us + [chain]), np.concatenate(vs + [chain + 1]))
+    rho = rng.random(g.m) + 0.1
+    if values == "one-bin":
+        rho[:] = 0.7
+    elif values == "many-bins":
+        rho = 0.5 + 1e-4 * rng.random(g.m)
+        for q in range(len(degs)):
+            rho[g.eid[g.row_ptr[q]]] = 40.0
+    rho = rho if values == "f64" else rho.astype(np.float32)
+    dg = api.DeviceGraph.from_host(g, "cuda")
+    t = torch.from_numpy(rho).cuda()
+    for e in (0.35, 0.8):
+        keep, nk, _ = api.sparsify_binned(dg, t, seed=5, e=e)
+        keep_o, kept_o = oracle.sparsify_binned(g, rho.astype(np.float64), e, 5)
+        np.testing.assert_array_equal(_np(keep), keep_o)
+        assert int(nk.item()) == kept_o
+    keep, nk, e_fit = api.sparsify_binned(dg, t, seed=6, target=0.4)
+    e_o, keep_o, kept_o = oracle.fit_exponent_binned(g, rho.astype(np.float64), 0.4, 6)
+    assert e_fit == e_o
+    np.testing.assert_array_equal(_np(keep), keep_o)
