@@ -18,7 +18,6 @@ namespace ad {
 
 constexpr int PBLOCK = 256;
 constexpr int PREDUCE_BLOCKS = 1024;     // fixed grid: reductions in a fixed order
-constexpr int64_t TRI_LANE = 64;         // pairs whose shorter row fits this are counted by one lane
 
 static unsigned pgrid(int64_t count) { return grid_for(std::max<int64_t>(1, count), PBLOCK); }
 
@@ -72,228 +71,351 @@ __global__ void k_compact_entries(int64_t nnz, const int32_t *__restrict__ col, 
 
 // ------------------------------------------------------------ triangles --
 
-// |N_a ∩ N_b| for sorted rows, by binary searches of the shorter row's
-// entries [s0 + first, s1) (stepping by `step`) in the longer one.
-__device__ __forceinline__ int64_t common_count(const int32_t *__restrict__ col, int64_t s0, int64_t s1,
-                                                int64_t l0, int64_t l1, int64_t first, int64_t step) {
-    int64_t t = 0;
-    for (int64_t q = s0 + first; q < s1; q += step) {
-        const int32_t x = col[q];
-        int64_t lo = l0, hi = l1;
-        while (lo < hi) {
-            const int64_t mid = (lo + hi) >> 1;
-            if (col[mid] < x) lo = mid + 1;
-            else hi = mid;
+// Triangles, each found once: with the vertices ordered by (degree, id), the
+// triangle a < b < c is found at b, where c of a's upper neighbours N+(a), a in
+// N-(b), is looked up among b's own, N+(b).  |N+(b)| is at most sqrt(2m) (each
+// member has at least as many neighbours as b), so N+(b) fits a small table in LDS,
+// with a count per entry for c's share; a's share is the walk's hits and b's
+// their total.  Lookups: the sum over edges (a, b) of |N+(a)|.
+// The table has 4-entry buckets at a load of a quarter or less, so that one
+// 16-byte LDS read answers almost every lookup, hits included.
+// What bounds it: the line requests of the walked rows and, for each edge, of
+// the row's place and the share's atomic.  A search of one end's whole row
+// per edge (3.6e9 lookups at n = 2^20, m = 16M, against 0.92e9 here, in a bitmap
+// that left one workgroup per compute unit): 17.2 ms for that graph and
+// its 30% selection together; 4.3 ms here.
+constexpr int TRI_SMALL = 64;            // rows up to here: 16 lanes each; longer: a workgroup
+constexpr int TRI_HUB = 4096;            // rows from here: TRI_SLICES workgroups
+constexpr int TRI_SLICES = 16;
+constexpr int TRI_CAP = 512;             // N+ entries in a workgroup's table (1,024: 10% slower, fewer
+                                         // workgroups fit); more take further passes
+constexpr int TRI_U = 8;                 // loads in flight per lane (4: 25% slower)
+constexpr int TRI_TEAM = 16;
+constexpr int32_t TRI_EMPTY = -1;
+
+// Where N+(i) starts (below 2m < 2^32) and its length (below 2^16).
+__device__ __forceinline__ uint64_t tri_place(int64_t start, int len) { return ((uint64_t)start << 16) | (uint64_t)len; }
+__device__ __forceinline__ int64_t tri_start(uint64_t p) { return (int64_t)(p >> 16); }
+__device__ __forceinline__ int tri_len(uint64_t p) { return (int)(p & 0xffffu); }
+
+template <int SLOTS>
+__device__ __forceinline__ int tri_bucket(int32_t x) {
+    return (int)(((uint32_t)x * 0x9E3779B1u) >> 8) & (SLOTS / 4 - 1);
+}
+
+// Puts x, absent so far, into the table and returns its slot.  A bucket's
+// slots fill in order.
+template <int SLOTS>
+__device__ __forceinline__ int tri_put(int32_t *key, int32_t x) {
+    for (int s = 4 * tri_bucket<SLOTS>(x);; s = (s + 1) & (SLOTS - 1))
+        if (atomicCAS(&key[s], TRI_EMPTY, x) == TRI_EMPTY) return s;
+}
+
+// The slot of x, or -1.  Some bucket always has room, so the search ends.
+template <int SLOTS>
+__device__ __forceinline__ int tri_find(const int32_t *key, int32_t x) {
+    int b = tri_bucket<SLOTS>(x);
+    for (;;) {
+        const int4 k = *(const int4 *)(key + 4 * b);
+        const int at = k.x == x ? 0 : (k.y == x ? 1 : (k.z == x ? 2 : (k.w == x ? 3 : -1)));
+        if (at >= 0) return 4 * b + at;
+        if (k.w == TRI_EMPTY) return -1;
+        b = (b + 1) & (SLOTS / 4 - 1);
+    }
+}
+
+// Walks dir[q0], dir[q0 + step], ... < q1, counting each entry found; returns the hits.
+template <int SLOTS>
+__device__ __forceinline__ unsigned int tri_walk(const int32_t *__restrict__ dir, int64_t q0, int64_t q1, int step,
+                                                 const int32_t *key, unsigned int *cnt) {
+    unsigned int t = 0;
+    for (; q0 < q1; q0 += (int64_t)TRI_U * step) {
+        int32_t x[TRI_U];
+#pragma unroll
+        for (int u = 0; u < TRI_U; ++u) x[u] = q0 + u * step < q1 ? dir[q0 + u * step] : TRI_EMPTY;
+#pragma unroll
+        for (int u = 0; u < TRI_U; ++u) {
+            if (x[u] == TRI_EMPTY) continue;
+            const int at = tri_find<SLOTS>(key, x[u]);
+            if (at >= 0) {
+                atomicAdd(&cnt[at], 1u);
+                ++t;
+            }
         }
-        t += (lo < l1 && col[lo] == x) ? 1 : 0;
     }
     return t;
 }
 
-// Every edge (i, j), i < j, adds |N_i ∩ N_j| to both ends (each triangle at i
-// is then counted once through each of its two edges at i).  Pairs whose
-// shorter row exceeds TRI_LANE are left to k_triangles_hub(_bits), and with
-// both_short also those whose longer row does (k_triangles_hub_bits takes
-// them from the long row's bitmap).
-__global__ void k_triangles_lane(int64_t n, const int64_t *__restrict__ row_ptr, const int32_t *__restrict__ col,
-                                 int both_short, unsigned long long *__restrict__ lam2) {
-    const int lane = threadIdx.x & (WAVE - 1);
-    const int64_t nw = (int64_t)gridDim.x * (PBLOCK / WAVE);
-    for (int64_t i = (int64_t)blockIdx.x * (PBLOCK / WAVE) + (threadIdx.x >> 6); i < n; i += nw) {
-        const int64_t b0 = row_ptr[i], b1 = row_ptr[i + 1];
-        unsigned long long own = 0;
-        for (int64_t base = b0; base < b1; base += WAVE) {
-            const int64_t p = base + lane;
-            const int32_t j = p < b1 ? col[p] : -1;
-            const bool up = j > i;
-            int64_t c0 = 0, c1 = 0;
-            if (up) {
-                c0 = row_ptr[j];
-                c1 = row_ptr[j + 1];
-            }
-            const bool i_short = (b1 - b0) <= (c1 - c0);
-            const int64_t shorter = i_short ? b1 - b0 : c1 - c0;
-            const int64_t longer = i_short ? c1 - c0 : b1 - b0;
-            const bool is_big = up && (shorter > TRI_LANE || (both_short && longer > TRI_LANE));
-            if (up && !is_big) {
-                const int64_t t =
-                    i_short ? common_count(col, b0, b1, c0, c1, 0, 1) : common_count(col, c0, c1, b0, b1, 0, 1);
-                own += (unsigned long long)t;
-                if (t) atomicAdd(&lam2[j], (unsigned long long)t);
-            }
-        }
-        for (int o = WAVE / 2; o >= 1; o >>= 1) own += __shfl_xor(own, o, WAVE);
-        if (lane == 0 && own) atomicAdd(&lam2[i], own);
-    }
+// Degrees, and the rows longer than TRI_SMALL: rows[0 ..] up to TRI_HUB entries
+// (count[0]), rows[n ..] longer (count[1]).  One append per workgroup and list.
+constexpr int TRI_LIST_B = 1024;
+
+__global__ __launch_bounds__(TRI_LIST_B) void k_triangles_lists(int64_t n, const int64_t *__restrict__ row_ptr,
+                                                                int32_t *__restrict__ deg, int32_t *__restrict__ rows,
+                                                                unsigned int *__restrict__ count) {
+    __shared__ unsigned int have[2], base[2];
+    if (threadIdx.x < 2) have[threadIdx.x] = 0u;
+    __syncthreads();
+    const int64_t i = (int64_t)blockIdx.x * TRI_LIST_B + threadIdx.x;
+    const int64_t d = i < n ? row_ptr[i + 1] - row_ptr[i] : 0;
+    if (i < n) deg[i] = (int32_t)d;
+    const int c = d > TRI_HUB ? 1 : (d > TRI_SMALL ? 0 : -1);
+    unsigned int at = 0;
+    if (c >= 0) at = atomicAdd(&have[c], 1u);
+    __syncthreads();
+    if (threadIdx.x < 2 && have[threadIdx.x]) base[threadIdx.x] = atomicAdd(&count[threadIdx.x], have[threadIdx.x]);
+    __syncthreads();
+    if (c >= 0) rows[c * n + base[c] + at] = (int32_t)i;
 }
 
-// Pairs of rows both longer than TRI_LANE, each counted by the endpoint of
-// larger (degree, id): one workgroup per such row L holds N_L in LDS (when
-// it has at most TRI_LDS entries, else it is searched in memory) for all of
-// its pairs; each wave takes a neighbour j and its lanes, striding over
-// N_j, binary-search N_L.
-constexpr int TRI_LDS = 8192;
-
-__global__ __launch_bounds__(PBLOCK) void k_triangles_hub(int64_t n, const int64_t *__restrict__ row_ptr,
-                                                          const int32_t *__restrict__ col,
-                                                          unsigned long long *__restrict__ lam2) {
-    __shared__ int32_t lrow[TRI_LDS];
-    __shared__ unsigned long long wsum[PBLOCK / WAVE];
-    const int lane = threadIdx.x & (WAVE - 1), wv = threadIdx.x >> 6;
-    for (int64_t L = blockIdx.x; L < n; L += gridDim.x) {
-        const int64_t l0 = row_ptr[L], l1 = row_ptr[L + 1], dl = l1 - l0;
-        if (dl <= TRI_LANE) continue;                       // uniform over the workgroup
-        const bool in_lds = dl <= TRI_LDS;
-        if (in_lds)
-            for (int64_t q = threadIdx.x; q < dl; q += PBLOCK) lrow[q] = col[l0 + q];
-        __syncthreads();
-        unsigned long long own = 0;
-        for (int64_t p = l0 + wv; p < l1; p += PBLOCK / WAVE) {
-            const int32_t j = col[p];
-            const int64_t c0 = row_ptr[j], c1 = row_ptr[j + 1], dj = c1 - c0;
-            if (dj <= TRI_LANE || dj > dl || (dj == dl && j > L)) continue;     // uniform over the wave
-            int64_t t = 0;
-            for (int64_t q = c0 + lane; q < c1; q += WAVE) {
-                const int32_t x = col[q];
-                if (in_lds) {
-                    int lo = 0, hi = (int)dl;
-                    while (lo < hi) {
-                        const int mid = (lo + hi) >> 1;
-                        if (lrow[mid] < x) lo = mid + 1;
-                        else hi = mid;
+// dir: every row with N+ first and N- after it, either in any order; place[i]:
+// where N+(i) lies.  Bound by the gathers of the neighbours' degrees.
+__global__ __launch_bounds__(PBLOCK) void k_triangles_orient(int64_t n, const int64_t *__restrict__ row_ptr,
+                                                             const int32_t *__restrict__ col,
+                                                             const int32_t *__restrict__ deg,
+                                                             const int32_t *__restrict__ rows,
+                                                             const unsigned int *__restrict__ count,
+                                                             int32_t *__restrict__ dir, uint64_t *__restrict__ place) {
+    __shared__ unsigned int n_up, n_down;
+    const int lane = threadIdx.x & (WAVE - 1);
+    for (int c = 0; c < 2; ++c) {
+        const unsigned int nr = count[c];
+        for (unsigned int h = blockIdx.x; h < nr; h += gridDim.x) {
+            const int64_t i = rows[c * n + h];
+            const int64_t b0 = row_ptr[i], b1 = row_ptr[i + 1];
+            const int32_t di = (int32_t)(b1 - b0);
+            if (threadIdx.x == 0) n_up = n_down = 0u;
+            __syncthreads();
+            for (int64_t q0 = b0; q0 < b1; q0 += 4 * PBLOCK) {
+                int32_t j[4], dj[4];
+#pragma unroll
+                for (int u = 0; u < 4; ++u) {
+                    const int64_t q = q0 + u * PBLOCK + threadIdx.x;
+                    j[u] = q < b1 ? col[q] : -1;
+                }
+#pragma unroll
+                for (int u = 0; u < 4; ++u) dj[u] = j[u] >= 0 ? deg[j[u]] : 0;
+#pragma unroll
+                for (int u = 0; u < 4; ++u) {
+                    const bool up = j[u] >= 0 && (dj[u] > di || (dj[u] == di && j[u] > i));
+                    const bool down = j[u] >= 0 && !up;
+                    const unsigned long long mu = __ballot(up), md = __ballot(down);
+                    unsigned int au = 0, ad = 0;
+                    if (lane == 0) {
+                        if (mu) au = atomicAdd(&n_up, (unsigned int)__popcll(mu));
+                        if (md) ad = atomicAdd(&n_down, (unsigned int)__popcll(md));
                     }
-                    t += (lo < dl && lrow[lo] == x) ? 1 : 0;
-                } else {
-                    int64_t lo = l0, hi = l1;
-                    while (lo < hi) {
-                        const int64_t mid = (lo + hi) >> 1;
-                        if (col[mid] < x) lo = mid + 1;
-                        else hi = mid;
-                    }
-                    t += (lo < l1 && col[lo] == x) ? 1 : 0;
+                    au = __shfl(au, 0, WAVE);
+                    ad = __shfl(ad, 0, WAVE);
+                    const unsigned long long below = ((unsigned long long)1 << lane) - 1;
+                    if (up) dir[b0 + au + __popcll(mu & below)] = j[u];
+                    if (down) dir[b1 - 1 - ad - __popcll(md & below)] = j[u];
                 }
             }
-            for (int o = WAVE / 2; o >= 1; o >>= 1) t += __shfl_xor(t, o, WAVE);
-            if (lane == 0 && t) {
-                atomicAdd(&lam2[j], (unsigned long long)t);
-                own += (unsigned long long)t;
-            }
+            __syncthreads();
+            if (threadIdx.x == 0) place[i] = tri_place(b0, (int)n_up);
+            __syncthreads();
         }
-        if (lane == 0) wsum[wv] = own;
-        __syncthreads();
-        if (threadIdx.x == 0) {
-            unsigned long long tot = 0;
-            for (int q = 0; q < PBLOCK / WAVE; ++q) tot += wsum[q];
-            if (tot) atomicAdd(&lam2[L], tot);
+    }
+    const int sub = threadIdx.x % TRI_TEAM, shift = lane - sub;      // the team's first lane
+    const unsigned long long below = ((unsigned long long)1 << sub) - 1;
+    const int64_t teams = (int64_t)gridDim.x * (PBLOCK / TRI_TEAM);
+    const int64_t n_pad = ceil_div_dev(n, teams) * teams;            // whole waves reach the ballots
+    for (int64_t i = (int64_t)blockIdx.x * (PBLOCK / TRI_TEAM) + threadIdx.x / TRI_TEAM; i < n_pad; i += teams) {
+        const int64_t b0 = i < n ? row_ptr[i] : 0, b1 = i < n ? row_ptr[i + 1] : 0;
+        const int64_t d = b1 - b0;
+        const bool mine = i < n && d <= TRI_SMALL;
+        const int di = mine ? (int)d : 0;
+        int32_t j[TRI_SMALL / TRI_TEAM], dj[TRI_SMALL / TRI_TEAM];
+#pragma unroll
+        for (int u = 0; u < TRI_SMALL / TRI_TEAM; ++u) {
+            const int q = u * TRI_TEAM + sub;
+            j[u] = q < di ? col[b0 + q] : -1;
         }
-        __syncthreads();     // lrow and wsum are reused by the next row
+#pragma unroll
+        for (int u = 0; u < TRI_SMALL / TRI_TEAM; ++u) dj[u] = j[u] >= 0 ? deg[j[u]] : 0;
+        int au = 0, ad = 0;
+#pragma unroll
+        for (int u = 0; u < TRI_SMALL / TRI_TEAM; ++u) {
+            const bool up = j[u] >= 0 && (dj[u] > di || (dj[u] == di && j[u] > i));
+            const bool down = j[u] >= 0 && !up;
+            const unsigned long long mu = (__ballot(up) >> shift) & 0xffffull;
+            const unsigned long long md = (__ballot(down) >> shift) & 0xffffull;
+            if (up) dir[b0 + au + __popcll(mu & below)] = j[u];
+            if (down) dir[b1 - 1 - ad - __popcll(md & below)] = j[u];
+            au += __popcll(mu);
+            ad += __popcll(md);
+        }
+        if (mine && sub == 0) place[i] = tri_place(b0, au);
     }
 }
 
-// The pairs of a long row L with every neighbour of no larger (degree, id),
-// short neighbours included, with N_L held as a bitmap over its id range [lo, hi]
-// (rows are sorted, so lo and hi are its first and last entries) when that
-// range has at most TRI_BITS ids: a lookup is one LDS read instead of a
-// binary search (used for graphs of at most TRI_BITS vertices; a row with
-// a wider range would search N_L in memory).  The bitmap
-// is cleared once per workgroup and, after each row, only in the words that
-// row set.  Needs TRI_BITS / 8 bytes of LDS per workgroup.
-constexpr int TRI_BT = 1024;
-constexpr int64_t TRI_BITS = (int64_t)1 << 20;
+// Rows of up to TRI_SMALL entries, 16 lanes each; a lane per lower neighbour
+// (whose row is no longer than b's).
+__global__ __launch_bounds__(PBLOCK) void k_triangles_small(int64_t n, const int64_t *__restrict__ row_ptr,
+                                                            const int32_t *__restrict__ dir,
+                                                            const uint64_t *__restrict__ place,
+                                                            unsigned long long *__restrict__ lam) {
+    constexpr int TEAMS = PBLOCK / TRI_TEAM, SLOTS = 4 * TRI_SMALL, K = TRI_SMALL / TRI_TEAM;
+    __shared__ int4 keys[TEAMS][SLOTS / 4];
+    __shared__ unsigned int cnts[TEAMS][SLOTS];
+    const int team = threadIdx.x / TRI_TEAM, lane = threadIdx.x % TRI_TEAM;
+    int32_t *key = (int32_t *)keys[team];
+    unsigned int *cnt = cnts[team];
+    for (int s = lane; s < SLOTS; s += TRI_TEAM) {
+        key[s] = TRI_EMPTY;
+        cnt[s] = 0u;
+    }
+    // a team's lanes are lanes of one wave: fences order their LDS accesses
+    __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+    __builtin_amdgcn_wave_barrier();
+    for (int64_t b = (int64_t)blockIdx.x * TEAMS + team; b < n; b += (int64_t)gridDim.x * TEAMS) {
+        const int64_t b0 = row_ptr[b], b1 = row_ptr[b + 1];
+        const int up = tri_len(place[b]);
+        if (b1 - b0 > TRI_SMALL || up == 0 || up == b1 - b0) continue;      // uniform over the team
+        int32_t x[K];
+        int slot[K];
+#pragma unroll
+        for (int u = 0; u < K; ++u) x[u] = u * TRI_TEAM + lane < up ? dir[b0 + u * TRI_TEAM + lane] : TRI_EMPTY;
+#pragma unroll
+        for (int u = 0; u < K; ++u) slot[u] = x[u] != TRI_EMPTY ? tri_put<SLOTS>(key, x[u]) : -1;
+        __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+        __builtin_amdgcn_wave_barrier();
+        unsigned int own = 0;
+        for (int64_t q = b0 + up + lane; q < b1; q += TRI_TEAM) {
+            const int32_t a = dir[q];
+            const uint64_t p = place[a];
+            if (tri_len(p) < 2) continue;                            // N+(a) = {b}
+            const unsigned int t = tri_walk<SLOTS>(dir, tri_start(p), tri_start(p) + tri_len(p), 1, key, cnt);
+            if (t) atomicAdd(&lam[a], (unsigned long long)t);
+            own += t;
+        }
+        for (int o = TRI_TEAM / 2; o >= 1; o >>= 1) own += __shfl_xor(own, o, WAVE);
+        if (lane == 0 && own) atomicAdd(&lam[b], (unsigned long long)own);
+        __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+        __builtin_amdgcn_wave_barrier();
+#pragma unroll
+        for (int u = 0; u < K; ++u)
+            if (slot[u] >= 0) {
+                if (cnt[slot[u]]) atomicAdd(&lam[x[u]], (unsigned long long)cnt[slot[u]]);
+                key[slot[u]] = TRI_EMPTY;
+                cnt[slot[u]] = 0u;
+            }
+        __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+        __builtin_amdgcn_wave_barrier();
+    }
+}
 
-__global__ __launch_bounds__(TRI_BT) void k_triangles_hub_bits(int64_t n, const int64_t *__restrict__ row_ptr,
-                                                               const int32_t *__restrict__ col,
-                                                               unsigned long long *__restrict__ lam2) {
-    extern __shared__ uint32_t bm[];                       // TRI_BITS / 32 words
-    __shared__ unsigned long long wsum[TRI_BT / WAVE];
+// Listed rows, a workgroup each, or TRI_SLICES (grid y) for the rows from TRI_HUB
+// entries, each with every TRI_SLICES-th block of PBLOCK lower neighbours.
+// Lower neighbours a are read 64 to a wave, then their rows walked
+// with 4, 16 or 64 lanes each by length, TRI_U loads in flight per lane.
+__global__ __launch_bounds__(PBLOCK) void k_triangles_rows(const int32_t *__restrict__ rows,
+                                                           const unsigned int *__restrict__ count,
+                                                           const int64_t *__restrict__ row_ptr,
+                                                           const int32_t *__restrict__ dir,
+                                                           const uint64_t *__restrict__ place,
+                                                           unsigned long long *__restrict__ lam) {
+    constexpr int SLOTS = 4 * TRI_CAP, K = TRI_CAP / PBLOCK;
+    __shared__ int4 keys[SLOTS / 4];
+    __shared__ unsigned int cnt[SLOTS];
+    __shared__ unsigned long long wsum[PBLOCK / WAVE];
+    int32_t *key = (int32_t *)keys;
     const int lane = threadIdx.x & (WAVE - 1), wv = threadIdx.x >> 6;
-    for (int64_t q = threadIdx.x; q < TRI_BITS / 32; q += TRI_BT) bm[q] = 0u;
+    for (int s = threadIdx.x; s < SLOTS; s += PBLOCK) {
+        key[s] = TRI_EMPTY;
+        cnt[s] = 0u;
+    }
     __syncthreads();
-    for (int64_t L = blockIdx.x; L < n; L += gridDim.x) {
-        const int64_t l0 = row_ptr[L], l1 = row_ptr[L + 1], dl = l1 - l0;
-        if (dl <= TRI_LANE) continue;                       // uniform over the workgroup
-        const int64_t lo = col[l0], span = (int64_t)col[l1 - 1] - lo + 1;
-        const bool bits = span <= TRI_BITS;
-        if (bits) {
-            for (int64_t q = threadIdx.x; q < dl; q += TRI_BT) {
-                const int64_t r = (int64_t)col[l0 + q] - lo;
-                atomicOr(&bm[r >> 5], 1u << (r & 31));
-            }
-        }
-        __syncthreads();
-        // whether id x is in N_L
-        auto in_l = [&](int32_t x) -> int64_t {
-            if (bits) {
-                const int64_t r = (int64_t)x - lo;
-                return (r >= 0 && r < span) ? (int64_t)((bm[r >> 5] >> (r & 31)) & 1u) : 0;
-            }
-            int64_t a = l0, b = l1;
-            while (a < b) {
-                const int64_t mid = (a + b) >> 1;
-                if (col[mid] < x) a = mid + 1;
-                else b = mid;
-            }
-            return (a < l1 && col[a] == x) ? 1 : 0;
-        };
+    const unsigned int nr = *count;
+    for (unsigned int h = blockIdx.x; h < nr; h += gridDim.x) {
+        const int64_t b = rows[h];
+        const int64_t b0 = row_ptr[b], b1 = row_ptr[b + 1];
+        const int up = tri_len(place[b]);
+        const int64_t first = b0 + up + (int64_t)blockIdx.y * PBLOCK;
+        if (up == 0 || first >= b1) continue;                        // uniform over the workgroup
         unsigned long long own = 0;
-        // short neighbours: one lane each, over the whole of N_j
-        for (int64_t p0 = l0 + (int64_t)wv * WAVE; p0 < l1; p0 += TRI_BT) {
-            const int64_t p = p0 + lane;
-            if (p >= l1) continue;
-            const int32_t j = col[p];
-            const int64_t c0 = row_ptr[j], c1 = row_ptr[j + 1];
-            if (c1 - c0 > TRI_LANE) continue;
-            int64_t t = 0;
-            for (int64_t q0 = c0; q0 < c1; q0 += 8) {                  // eight loads in flight
-                int32_t x[8];
+        for (int c0 = 0; c0 < up; c0 += TRI_CAP) {
+            int32_t x[K];
+            int slot[K];
 #pragma unroll
-                for (int u = 0; u < 8; ++u) x[u] = q0 + u < c1 ? col[q0 + u] : -1;
+            for (int u = 0; u < K; ++u) {
+                const int q = c0 + u * PBLOCK + (int)threadIdx.x;
+                x[u] = q < up ? dir[b0 + q] : TRI_EMPTY;
+            }
 #pragma unroll
-                for (int u = 0; u < 8; ++u) t += x[u] >= 0 ? in_l(x[u]) : 0;
+            for (int u = 0; u < K; ++u) slot[u] = x[u] != TRI_EMPTY ? tri_put<SLOTS>(key, x[u]) : -1;
+            __syncthreads();
+            for (int64_t q0 = first + wv * WAVE; q0 < b1; q0 += (int64_t)gridDim.y * PBLOCK) {
+                const bool have = q0 + lane < b1;
+                const int32_t a = have ? dir[q0 + lane] : 0;
+                const uint64_t p = have ? place[a] : 0;
+                const int len = tri_len(p);
+                const unsigned long long m4 = __ballot(len >= 2 && len <= 4 * TRI_U);
+                const unsigned long long m16 = __ballot(len > 4 * TRI_U && len <= 16 * TRI_U);
+                unsigned long long m64 = __ballot(len > 16 * TRI_U);
+                unsigned int mine = 0;                               // hits of this lane's a
+#pragma unroll
+                for (int r = 0; r < 4; ++r) {
+                    if (!((m4 >> (16 * r)) & 0xffffull)) continue;
+                    const int s = 16 * r + (lane >> 2);
+                    const int64_t e0 = tri_start(__shfl(p, s, WAVE));
+                    const int l = __shfl(len, s, WAVE);
+                    const int n_e = (m4 >> s) & 1 ? l : 0;
+                    unsigned int t = tri_walk<SLOTS>(dir, e0 + (lane & 3), e0 + n_e, 4, key, cnt);
+                    t += __shfl_xor(t, 1, WAVE);
+                    t += __shfl_xor(t, 2, WAVE);
+                    const unsigned int got = __shfl(t, (lane & 15) * 4, WAVE);
+                    if ((lane >> 4) == r && ((m4 >> lane) & 1)) mine = got;
+                }
+                for (int r = 0; r < 16; ++r) {
+                    if (!((m16 >> (4 * r)) & 0xfull)) continue;
+                    const int s = 4 * r + (lane >> 4);
+                    const int64_t e0 = tri_start(__shfl(p, s, WAVE));
+                    const int l = __shfl(len, s, WAVE);
+                    const int n_e = (m16 >> s) & 1 ? l : 0;
+                    unsigned int t = tri_walk<SLOTS>(dir, e0 + (lane & 15), e0 + n_e, 16, key, cnt);
+                    for (int o = 8; o >= 1; o >>= 1) t += __shfl_xor(t, o, WAVE);
+                    const unsigned int got = __shfl(t, (lane & 3) * 16, WAVE);
+                    if ((lane >> 2) == r && ((m16 >> lane) & 1)) mine = got;
+                }
+                while (m64) {
+                    const int s = __ffsll((long long)m64) - 1;
+                    m64 &= m64 - 1;
+                    const int64_t e0 = tri_start(__shfl(p, s, WAVE));
+                    const int n_e = __shfl(len, s, WAVE);
+                    unsigned int t = tri_walk<SLOTS>(dir, e0 + lane, e0 + n_e, WAVE, key, cnt);
+                    for (int o = WAVE / 2; o >= 1; o >>= 1) t += __shfl_xor(t, o, WAVE);
+                    if (lane == s) mine = t;
+                }
+                if (mine) atomicAdd(&lam[a], (unsigned long long)mine);
+                own += mine;
             }
-            if (t) {
-                atomicAdd(&lam2[j], (unsigned long long)t);
-                own += (unsigned long long)t;
-            }
-        }
-        // long neighbours: one wave each, lanes striding over N_j
-        for (int64_t p = l0 + wv; p < l1; p += TRI_BT / WAVE) {
-            const int32_t j = col[p];
-            const int64_t c0 = row_ptr[j], c1 = row_ptr[j + 1], dj = c1 - c0;
-            if (dj <= TRI_LANE || dj > dl || (dj == dl && j > L)) continue;     // uniform over the wave
-            int64_t t = 0;
-            for (int64_t q = c0 + lane; q < c1; q += WAVE) t += in_l(col[q]);
-            for (int o = WAVE / 2; o >= 1; o >>= 1) t += __shfl_xor(t, o, WAVE);
-            if (lane == 0 && t) {
-                atomicAdd(&lam2[j], (unsigned long long)t);
-                own += (unsigned long long)t;
-            }
+            __syncthreads();
+#pragma unroll
+            for (int u = 0; u < K; ++u)
+                if (slot[u] >= 0) {
+                    if (cnt[slot[u]]) atomicAdd(&lam[x[u]], (unsigned long long)cnt[slot[u]]);
+                    key[slot[u]] = TRI_EMPTY;
+                    cnt[slot[u]] = 0u;
+                }
+            __syncthreads();
         }
         for (int o = WAVE / 2; o >= 1; o >>= 1) own += __shfl_xor(own, o, WAVE);
         if (lane == 0) wsum[wv] = own;
         __syncthreads();
         if (threadIdx.x == 0) {
             unsigned long long tot = 0;
-            for (int q = 0; q < TRI_BT / WAVE; ++q) tot += wsum[q];
-            if (tot) atomicAdd(&lam2[L], tot);
+            for (int w = 0; w < PBLOCK / WAVE; ++w) tot += wsum[w];
+            if (tot) atomicAdd(&lam[b], tot);
         }
-        if (bits)
-            for (int64_t q = threadIdx.x; q < dl; q += TRI_BT) bm[((int64_t)col[l0 + q] - lo) >> 5] = 0u;
-        __syncthreads();     // bm and wsum are reused by the next row
+        // wsum is written again only after the next row's barriers
     }
-}
-
-// Whether the current device gives a workgroup the bitmap's LDS.
-static bool tri_bits_fit() {
-    int dev = 0, lds = 0;
-    if (hipGetDevice(&dev) != hipSuccess) return false;
-    if (hipDeviceGetAttribute(&lds, hipDeviceAttributeMaxSharedMemoryPerBlock, dev) != hipSuccess) return false;
-    return (int64_t)lds >= TRI_BITS / 8 + (int64_t)sizeof(unsigned long long) * (TRI_BT / WAVE);
 }
 
 // lambda_i and c_i; per-block partial sums of c_i over d_i > 1 (and their
 // count), in a fixed order for the host to finish.
-__global__ void k_clustering(int64_t n, const int64_t *__restrict__ row_ptr, const unsigned long long *__restrict__ lam2,
+__global__ void k_clustering(int64_t n, const int64_t *__restrict__ row_ptr, const unsigned long long *__restrict__ lam,
                              int64_t *__restrict__ lambda, double *__restrict__ c, double *__restrict__ part_sum,
                              unsigned long long *__restrict__ part_cnt) {
     __shared__ double ssum[PBLOCK];
@@ -301,7 +423,7 @@ __global__ void k_clustering(int64_t n, const int64_t *__restrict__ row_ptr, con
     double s = 0.0;
     unsigned long long k = 0;
     for (int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; i < n; i += (int64_t)gridDim.x * blockDim.x) {
-        const int64_t l = (int64_t)(lam2[i] / 2);
+        const int64_t l = (int64_t)lam[i];
         const int64_t d = row_ptr[i + 1] - row_ptr[i];
         double ci = 0.0;
         if (d > 1) {
@@ -591,8 +713,12 @@ static size_t sub_layout(const ad_graph *g, void *ws, size_t ws_bytes, SubLayout
 }
 
 struct PropLayout {
-    unsigned long long *lam2;     // [n]
-    unsigned int *flags;          // [4]: listed pairs, changed
+    unsigned long long *lam;      // [n]
+    unsigned int *flags;          // [4]: rows per list of long rows
+    int32_t *tri_rows;            // [2][n]: the long rows
+    int32_t *deg;                 // [n]
+    int32_t *dir;                 // [2m]: rows, upper neighbours first
+    uint64_t *place;              // [n]: upper neighbours' places in dir
     unsigned long long *roots;    // [1]
     double *part_sum;             // [PREDUCE_BLOCKS]
     unsigned long long *part_cnt; // [PREDUCE_BLOCKS]
@@ -603,8 +729,12 @@ static size_t prop_layout(const ad_graph *g, void *ws, size_t ws_bytes, PropLayo
     Carver c(ws, ws_bytes);
     const size_t m = (size_t)std::max<int64_t>(1, g->m), n = (size_t)std::max<int64_t>(1, g->n);
     PropLayout l;
-    l.lam2 = c.take<unsigned long long>(n);
+    l.lam = c.take<unsigned long long>(n);
     l.flags = c.take<unsigned int>(4);
+    l.tri_rows = c.take<int32_t>(2 * n);
+    l.deg = c.take<int32_t>(n);
+    l.dir = c.take<int32_t>(2 * m);
+    l.place = c.take<uint64_t>(n);
     l.roots = c.take<unsigned long long>(1);
     l.part_sum = c.take<double>(PREDUCE_BLOCKS);
     l.part_cnt = c.take<unsigned long long>(PREDUCE_BLOCKS);
@@ -798,29 +928,33 @@ extern "C" ad_status ad_graph_properties(const ad_graph *g, int64_t *lambda, dou
     summary_host[0] = 0.0;
     summary_host[1] = 0.0;
     if (n == 0) return AD_OK;
-    const unsigned wgrid = (unsigned)std::max<int64_t>(1, std::min<int64_t>(4096, ceil_div(n, PBLOCK / WAVE)));
     // triangles and clustering
-    s = fill_u64(L.lam2, 0, n, stream);
+    s = fill_u64(L.lam, 0, n, stream);
     if (s != AD_OK) return s;
     s = fill_i32((int32_t *)L.flags, 0, 4, stream);
     if (s != AD_OK) return s;
     if (g->m > 0) {
-        // with at most TRI_BITS vertices every row's id range fits the bitmap
-        const bool use_bits = n <= TRI_BITS && tri_bits_fit();
-        hipLaunchKernelGGL(k_triangles_lane, dim3(wgrid), dim3(PBLOCK), 0, stream, n, g->row_ptr, g->col,
-                           use_bits ? 1 : 0, L.lam2);
-        AD_LAUNCH_CHECK("k_triangles_lane");
-        if (use_bits) {
-            hipLaunchKernelGGL(k_triangles_hub_bits, dim3((unsigned)std::min<int64_t>(4096, n)), dim3(TRI_BT),
-                               (size_t)(TRI_BITS / 8), stream, n, g->row_ptr, g->col, L.lam2);
-            AD_LAUNCH_CHECK("k_triangles_hub_bits");
-        } else {
-            hipLaunchKernelGGL(k_triangles_hub, dim3((unsigned)std::min<int64_t>(4096, n)), dim3(PBLOCK), 0, stream,
-                               n, g->row_ptr, g->col, L.lam2);
-            AD_LAUNCH_CHECK("k_triangles_hub");
-        }
+        hipLaunchKernelGGL(k_triangles_lists, dim3((unsigned)ceil_div(n, TRI_LIST_B)), dim3(TRI_LIST_B), 0, stream, n,
+                           g->row_ptr, L.deg, L.tri_rows, L.flags);
+        AD_LAUNCH_CHECK("k_triangles_lists");
+        const unsigned teams = (unsigned)std::min<int64_t>(4096, ceil_div(n, PBLOCK / TRI_TEAM));
+        hipLaunchKernelGGL(k_triangles_orient, dim3(teams), dim3(PBLOCK), 0, stream, n, g->row_ptr, g->col, L.deg,
+                           L.tri_rows, L.flags, L.dir, L.place);
+        AD_LAUNCH_CHECK("k_triangles_orient");
+        // a listed row has more than TRI_HUB (TRI_SMALL) of the 2m entries
+        const int64_t hubs = 2 * g->m / (TRI_HUB + 1), longs = 2 * g->m / (TRI_SMALL + 1);
+        if (hubs > 0)
+            hipLaunchKernelGGL(k_triangles_rows, dim3((unsigned)std::min<int64_t>(512, hubs), TRI_SLICES),
+                               dim3(PBLOCK), 0, stream, L.tri_rows + n, L.flags + 1, g->row_ptr, L.dir, L.place, L.lam);
+        if (longs > 0)
+            hipLaunchKernelGGL(k_triangles_rows, dim3((unsigned)std::min<int64_t>(4096, longs), 1), dim3(PBLOCK), 0,
+                               stream, L.tri_rows, L.flags, g->row_ptr, L.dir, L.place, L.lam);
+        AD_LAUNCH_CHECK("k_triangles_rows");
+        hipLaunchKernelGGL(k_triangles_small, dim3(teams), dim3(PBLOCK), 0, stream, n, g->row_ptr, L.dir, L.place,
+                           L.lam);
+        AD_LAUNCH_CHECK("k_triangles_small");
     }
-    hipLaunchKernelGGL(k_clustering, dim3(PREDUCE_BLOCKS), dim3(PBLOCK), 0, stream, n, g->row_ptr, L.lam2, lambda, c,
+    hipLaunchKernelGGL(k_clustering, dim3(PREDUCE_BLOCKS), dim3(PBLOCK), 0, stream, n, g->row_ptr, L.lam, lambda, c,
                        L.part_sum, L.part_cnt);
     AD_LAUNCH_CHECK("k_clustering");
     // components: hook and jump until no hook changes a parent

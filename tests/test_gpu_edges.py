@@ -25,6 +25,69 @@ def _np(t):
     return t.detach().cpu().numpy()
 
 
+# -------------------------------------------------------------- triangles --
+
+@pytest.mark.parametrize("edge", [2, 15, 16, 31, 32, 63, 1023, 8191])
+def test_triangles_at_class_edges(api, edge):
+    """Six mutually joined vertices of exactly edge .. edge + 3 and 64, 65
+    entries (at least) around an edge of a row class, their other neighbours drawn from one
+    pool, so that most triangles lie on two of them; the pool's own rows stay
+    short.  Counts are whole numbers."""
+    announce(f"triangles at rows of {edge}")
+    rng = np.random.default_rng(edge)
+    k = 6
+    degs = [max(k, d) for d in (edge, edge + 1, edge + 2, edge + 3, 64, 65)]
+    pool = max(degs) + 40
+    hubs = rng.choice(pool + k, size=k, replace=False)
+    rest = np.setdiff1d(np.arange(pool + k), hubs)
+    us, vs = [], []
+    a, b = np.triu_indices(k, 1)
+    us.append(hubs[a])
+    vs.append(hubs[b])
+    for h, d in zip(hubs, degs):
+        x = rng.choice(rest, size=d - (k - 1), replace=False)
+        us.append(np.full(x.size, h))
+        vs.append(x)
+    ring = rng.permutation(rest)
+    us.append(ring)
+    vs.append(np.roll(ring, 1))
+    g = G.from_edges(pool + k, np.concatenate(us), np.concatenate(vs))
+    np.testing.assert_array_equal(np.diff(g.row_ptr)[hubs], degs)
+    pr = api.graph_properties(api.DeviceGraph.from_host(g, "cuda"))
+    ref = oracle.properties(g.n, g.row_ptr, g.col)
+    assert ref["lambda"].sum() > 0
+    np.testing.assert_array_equal(_np(pr["lambda"]), ref["lambda"])
+    np.testing.assert_array_equal(_np(pr["c"]), ref["c"])
+
+
+@pytest.mark.parametrize("k", [2, 3, 17, 65, 66, 513, 514, 1025, 1026, 1600])
+def test_triangles_of_cliques(api, k):
+    """Every length of upper-neighbour list up to k - 1 at once: below, at and
+    above one table, and several tables.  k vertices have C(k - 1, 2) triangles
+    each, a pendant vertex none."""
+    announce(f"triangles of a clique of {k}")
+    a, b = np.triu_indices(k, 1)
+    g = G.from_edges(k + 1, np.append(a, 0), np.append(b, k))
+    pr = api.graph_properties(api.DeviceGraph.from_host(g, "cuda"))
+    lam = _np(pr["lambda"])
+    np.testing.assert_array_equal(lam[:k], np.full(k, (k - 1) * (k - 2) // 2))
+    assert lam[k] == 0
+
+
+def test_triangles_of_hubs(api):
+    """Rows beyond one workgroup: two joined hubs that share 9,000 neighbours,
+    consecutive ones of which are joined."""
+    announce("triangles of hubs")
+    n = 9_002
+    leaf = np.arange(2, n)
+    u = np.concatenate([[0], np.zeros(leaf.size, int), np.ones(leaf.size, int), leaf[:-1]])
+    v = np.concatenate([[1], leaf, leaf, leaf[1:]])
+    g = G.from_edges(n, u, v)
+    pr = api.graph_properties(api.DeviceGraph.from_host(g, "cuda"))
+    ref = oracle.properties(g.n, g.row_ptr, g.col)
+    np.testing.assert_array_equal(_np(pr["lambda"]), ref["lambda"])
+
+
 # ------------------------------------------------------------- components --
 
 def _component_graph(kind):
