@@ -15,11 +15,11 @@
 // neighbours of a dequeued vertex queued by increasing (degree, id), the
 // whole order reversed.
 //
-// The pipeline: canonical 64-bit pair keys, a stable radix sort (rocPRIM) of
-// (key, list index), run heads and their scan (edge ids), run bounds, and
+// The pipeline: canonical pair keys of 2 log2(n) bits, a radix sort (rocPRIM) of
+// (key, weight), a scan of the run heads (edge ids), and
 // the exact weight sum of every run (one thread per short run, one wave per
 // long run); for
-// the degree order a sort of (degree, id) vertex keys and a second pair sort
+// the degree order a stable sort of the vertices by degree and a second pair sort
 // under the new labels (for reverse Cuthill-McKee, the graph placed under
 // the listed ids, its components, and a level-by-level search with two
 // sorts per level, then the same relabelling); then per-row counts from the run lengths of the
@@ -39,52 +39,69 @@
 namespace ad {
 
 constexpr int IBLOCK = 256;
-constexpr unsigned long long NO_PAIR = ~0ull;
-
 static unsigned bits_for(int64_t n) {
     unsigned b = 1;
     while (b < 32 && ((int64_t)1 << b) < n) ++b;
     return b;
 }
 
-// Pair key (smaller << 32 | larger), NO_PAIR for self-loops; endpoints out
+// Pair keys hold both ids in 2b bits, b = bits_for(n), smaller id above: the
+// radix sorts take a pass per 8 bits, 140 us for 16M keys with weights (n = 2^20:
+// five passes; 64-bit keys with list indices took eight and a gather of the
+// weights after them: 16M pairs stored by degree, with their components, 6.0 ms;
+// 4.4 ms here).
+// All ones, the pair of the largest id with itself, stands for no pair and sorts last.
+struct PairCode {
+    unsigned b;
+    unsigned long long none;
+    explicit PairCode(int64_t n) : b(bits_for(n)), none((1ull << (2 * b)) - 1) {}
+};
+__device__ __forceinline__ unsigned long long pair_key(PairCode c, uint64_t lo, uint64_t hi) { return (lo << c.b) | hi; }
+__device__ __forceinline__ int32_t pair_lo(PairCode c, unsigned long long k) { return (int32_t)(k >> c.b); }
+__device__ __forceinline__ int32_t pair_hi(PairCode c, unsigned long long k) {
+    return (int32_t)(k & ((1ull << c.b) - 1));
+}
+
+// Key of every listed pair, none for self-loops; endpoints out
 // of [0, n) raise the error flag (and sort last).
-__global__ void k_pair_keys(int64_t m_in, int64_t n, const int32_t *__restrict__ u, const int32_t *__restrict__ v,
-                            const float *__restrict__ w, unsigned long long *__restrict__ key,
-                            uint32_t *__restrict__ idx, unsigned int *__restrict__ err) {
+__global__ void k_pair_keys(int64_t m_in, int64_t n, PairCode code, const int32_t *__restrict__ u,
+                            const int32_t *__restrict__ v, const float *__restrict__ w,
+                            unsigned long long *__restrict__ key, unsigned int *__restrict__ err) {
     for (int64_t q = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; q < m_in; q += (int64_t)gridDim.x * blockDim.x) {
         const int64_t a = u[q], b = v[q];
-        unsigned long long k = NO_PAIR;
+        unsigned long long k = code.none;
         if (w && !(w[q] > 0.0f && w[q] <= FLT_MAX)) atomicOr(err, 2u);
         if (a < 0 || a >= n || b < 0 || b >= n) {
             atomicOr(err, 1u);
         } else if (a != b) {
-            const uint64_t lo = (uint64_t)(a < b ? a : b), hi = (uint64_t)(a < b ? b : a);
-            k = (lo << 32) | hi;
+            k = pair_key(code, (uint64_t)(a < b ? a : b), (uint64_t)(a < b ? b : a));
         }
         key[q] = k;
-        idx[q] = (uint32_t)q;
     }
 }
 
-// 1 at the first entry of every run of equal pair keys.
-__global__ void k_run_heads(int64_t count, const unsigned long long *__restrict__ key, uint32_t *__restrict__ head) {
-    for (int64_t q = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; q < count; q += (int64_t)gridDim.x * blockDim.x)
-        head[q] = (key[q] != NO_PAIR && (q == 0 || key[q] != key[q - 1])) ? 1u : 0u;
+// 1 at the first entry of every run of equal pair keys, as an iterator for the scan.
+struct RunHead {
+    const unsigned long long *key;
+    unsigned long long none;
+    __device__ __host__ uint32_t operator()(int64_t q) const {
+        return (key[q] != none && (q == 0 || key[q] != key[q - 1])) ? 1u : 0u;
+    }
+};
+using RunHeadIt = rocprim::transform_iterator<rocprim::counting_iterator<int64_t>, RunHead, uint32_t>;
+static RunHeadIt run_heads(const unsigned long long *key, unsigned long long none) {
+    return RunHeadIt(rocprim::counting_iterator<int64_t>(0), RunHead{key, none});
 }
 
-// Bounds [start, end) of every run of equal pair keys, by edge id (edge_of
-// is the exclusive scan of the run heads).
-__global__ void k_run_bounds(int64_t count, const unsigned long long *__restrict__ key,
-                             const uint32_t *__restrict__ head, const uint32_t *__restrict__ edge_of,
-                             uint2 *__restrict__ bounds) {
-    for (int64_t q = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; q < count; q += (int64_t)gridDim.x * blockDim.x) {
-        const unsigned long long k = key[q];
-        if (k == NO_PAIR) continue;
-        const uint32_t e = head[q] ? edge_of[q] : edge_of[q] - 1u;
-        if (head[q]) bounds[e].x = (uint32_t)q;
-        if (q + 1 == count || key[q + 1] != k) bounds[e].y = (uint32_t)(q + 1);
-    }
+// Counts as 64-bit numbers, 0 from index n on.
+struct CountAt {
+    const uint32_t *cnt;
+    int64_t n;
+    __device__ __host__ uint64_t operator()(int64_t i) const { return i < n ? (uint64_t)cnt[i] : 0ull; }
+};
+using CountIt = rocprim::transform_iterator<rocprim::counting_iterator<int64_t>, CountAt, uint64_t>;
+static CountIt counts_of(const uint32_t *cnt, int64_t n) {
+    return CountIt(rocprim::counting_iterator<int64_t>(0), CountAt{cnt, n});
 }
 
 // Merged weights: the exact sum of a run's listed weights, rounded once to
@@ -168,32 +185,41 @@ __device__ float digits_round(const unsigned long long (&acc)[XDIG]) {
     return ldexpf((float)mant, top - 23 - 149);
 }
 
-// One thread per run: the edge's endpoints and, for a short run, its
-// weight.  Longer runs go to lists for k_merge_long and k_merge_big.
-__global__ void k_merge_runs(int64_t m, const uint2 *__restrict__ bounds, const unsigned long long *__restrict__ key,
-                             const uint32_t *__restrict__ idx, const float *__restrict__ w, int32_t *__restrict__ ea,
-                             int32_t *__restrict__ eb, float *__restrict__ ew, uint32_t *__restrict__ long_list,
+// One thread per sorted pair; the first of a run writes the edge's endpoints and, for
+// a short run, its weight (w: the weights in the keys' order).  Longer runs get
+// bounds and go to lists for k_merge_long and k_merge_big.  total: the edges.
+__global__ void k_merge_runs(int64_t count, PairCode code, const unsigned long long *__restrict__ key,
+                             const uint32_t *__restrict__ edge_of, const float *__restrict__ w,
+                             int32_t *__restrict__ ea, int32_t *__restrict__ eb, float *__restrict__ ew,
+                             uint2 *__restrict__ bounds, uint32_t *__restrict__ long_list,
                              unsigned int *__restrict__ long_count, uint32_t *__restrict__ big_list,
-                             unsigned int *__restrict__ big_count) {
+                             unsigned int *__restrict__ big_count, unsigned int *__restrict__ total) {
     // the loop bound is uniform per wave (blocks are whole waves), so every
     // lane reaches the wave-wide append
     const int64_t stride = (int64_t)gridDim.x * blockDim.x;
-    const int64_t m_pad = ceil_div_dev(m, stride) * stride;
-    for (int64_t e = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; e < m_pad; e += stride) {
+    const int64_t n_pad = ceil_div_dev(count, stride) * stride;
+    for (int64_t q = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; q < n_pad; q += stride) {
         bool defer = false, big = false;
-        if (e < m) {
-            const uint2 b = bounds[e];
-            const unsigned long long k = key[b.x];
-            ea[e] = (int32_t)(k >> 32);
-            eb[e] = (int32_t)(k & 0xffffffffull);
-            const uint32_t len = b.y - b.x;
-            if (w && len == 1) {
-                ew[e] = w[idx[b.x]];
-            } else if (w && len <= MERGE_SHORT) {
+        uint32_t e = 0;
+        const unsigned long long k = q < count ? key[q] : code.none;
+        const bool first = k != code.none && (q == 0 || key[q - 1] != k);
+        if (q == count - 1) *total = edge_of[q] + (first ? 1u : 0u);
+        if (first) {
+            e = edge_of[q];
+            ea[e] = pair_lo(code, k);
+            eb[e] = pair_hi(code, k);
+        }
+        if (first && w) {
+            int64_t end = q + 1;
+            while (end < count && end - q <= (int64_t)MERGE_SHORT && key[end] == k) ++end;
+            const uint32_t len = (uint32_t)(end - q);
+            if (len == 1) {
+                ew[e] = w[q];
+            } else if (len <= MERGE_SHORT) {
                 int lo = 1 << 20, hi = -1;
                 double sum = 0.0;
-                for (uint32_t r = b.x; r < b.y; ++r) {
-                    const float x = w[idx[r]];
+                for (int64_t r = q; r < end; ++r) {
+                    const float x = w[r];
                     uint32_t mant;
                     int shift;
                     f32_split(x, mant, shift);
@@ -205,19 +231,27 @@ __global__ void k_merge_runs(int64_t m, const uint2 *__restrict__ bounds, const 
                     ew[e] = (float)sum;
                 } else {
                     unsigned long long acc[XDIG] = {};
-                    for (uint32_t r = b.x; r < b.y; ++r) digits_add(acc, w[idx[r]]);
+                    for (int64_t r = q; r < end; ++r) digits_add(acc, w[r]);
                     ew[e] = digits_round(acc);
                 }
-            } else if (w) {
+            } else {
+                int64_t past = count;                        // first key above k in (end, count]
+                while (end < past) {
+                    const int64_t mid = (end + past) >> 1;
+                    if (key[mid] > k) past = mid;
+                    else end = mid + 1;
+                }
+                bounds[e] = make_uint2((uint32_t)q, (uint32_t)past);
                 defer = true;
-                big = len > MERGE_WAVE;
+                big = past - q > (int64_t)MERGE_WAVE;
             }
         }
         const bool to_long = defer && !big, to_big = defer && big;
+        if (!__any(defer)) continue;
         const unsigned int at = wave_append(to_long, long_count);
-        if (to_long) long_list[at] = (uint32_t)e;
+        if (to_long) long_list[at] = e;
         const unsigned int bt = wave_append(to_big, big_count);
-        if (to_big) big_list[bt] = (uint32_t)e;
+        if (to_big) big_list[bt] = e;
     }
 }
 
@@ -230,8 +264,7 @@ constexpr int MERGE_LOADS = 4;           // weights each lane loads per step
 __global__ __launch_bounds__(IBLOCK) void k_merge_long(const unsigned int *__restrict__ long_count,
                                                        const uint32_t *__restrict__ long_list,
                                                        const uint2 *__restrict__ bounds,
-                                                       const uint32_t *__restrict__ idx, const float *__restrict__ w,
-                                                       float *__restrict__ ew) {
+                                                       const float *__restrict__ w, float *__restrict__ ew) {
     const int lane = threadIdx.x & (WAVE - 1);
     const int64_t nw = (int64_t)gridDim.x * (IBLOCK / WAVE);
     const int64_t count = *long_count;
@@ -245,7 +278,7 @@ __global__ __launch_bounds__(IBLOCK) void k_merge_long(const unsigned int *__res
 #pragma unroll
             for (int t = 0; t < MERGE_LOADS; ++t) {
                 const uint32_t r = base + (uint32_t)(t * WAVE + lane);
-                x[t] = r < b.y ? w[idx[r]] : 0.0f;
+                x[t] = r < b.y ? w[r] : 0.0f;
             }
 #pragma unroll
             for (int t = 0; t < MERGE_LOADS; ++t) {
@@ -268,7 +301,7 @@ __global__ __launch_bounds__(IBLOCK) void k_merge_long(const unsigned int *__res
             continue;
         }
         unsigned long long acc[XDIG] = {};
-        for (uint32_t r = b.x + (uint32_t)lane; r < b.y; r += WAVE) digits_add(acc, w[idx[r]]);
+        for (uint32_t r = b.x + (uint32_t)lane; r < b.y; r += WAVE) digits_add(acc, w[r]);
 #pragma unroll
         for (int d = 0; d < XDIG; ++d)
             for (int o = WAVE / 2; o >= 1; o >>= 1) acc[d] += __shfl_xor(acc[d], o, WAVE);
@@ -281,8 +314,7 @@ __global__ __launch_bounds__(IBLOCK) void k_merge_long(const unsigned int *__res
 __global__ __launch_bounds__(MERGE_TB) void k_merge_big(const unsigned int *__restrict__ big_count,
                                                         const uint32_t *__restrict__ big_list,
                                                         const uint2 *__restrict__ bounds,
-                                                        const uint32_t *__restrict__ idx, const float *__restrict__ w,
-                                                        float *__restrict__ ew) {
+                                                        const float *__restrict__ w, float *__restrict__ ew) {
     __shared__ unsigned long long part[MERGE_TB / WAVE][XDIG];
     const int lane = threadIdx.x & (WAVE - 1), wv = threadIdx.x >> 6;
     const unsigned int count = *big_count;
@@ -295,7 +327,7 @@ __global__ __launch_bounds__(MERGE_TB) void k_merge_big(const unsigned int *__re
 #pragma unroll
             for (int t = 0; t < MERGE_LOADS; ++t) {
                 const uint32_t r = base + (uint32_t)(t * MERGE_TB) + threadIdx.x;
-                x[t] = r < b.y ? w[idx[r]] : 0.0f;
+                x[t] = r < b.y ? w[r] : 0.0f;
             }
 #pragma unroll
             for (int t = 0; t < MERGE_LOADS; ++t) digits_add(acc, x[t]);     // a zero adds nothing
@@ -348,13 +380,12 @@ __global__ void k_degree_max(int64_t n, const uint32_t *__restrict__ deg, unsign
     if ((threadIdx.x & (WAVE - 1)) == 0) atomicMax(dmax, mx);
 }
 
-// Storage-order key of vertex i: decreasing degree, then increasing listed id.
-__global__ void k_vertex_keys(int64_t n, const uint32_t *__restrict__ deg, unsigned long long *__restrict__ vkey,
-                              uint32_t *__restrict__ vid) {
-    for (int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; i < n; i += (int64_t)gridDim.x * blockDim.x) {
-        vkey[i] = ((unsigned long long)(0xffffffffu - deg[i]) << 32) | (unsigned long long)i;
-        vid[i] = (uint32_t)i;
-    }
+// Storage-order key of vertex i: decreasing degree; the stable sort keeps equal
+// ones by increasing listed id.  top: the largest key.
+__global__ void k_vertex_keys(int64_t n, const uint32_t *__restrict__ deg, uint32_t top,
+                              uint32_t *__restrict__ vkey) {
+    for (int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; i < n; i += (int64_t)gridDim.x * blockDim.x)
+        vkey[i] = top - deg[i];
 }
 
 __global__ void k_new_ids(int64_t n, const uint32_t *__restrict__ vid_sorted, uint32_t *__restrict__ new_of,
@@ -371,24 +402,21 @@ __global__ void k_orig_identity(int64_t n, const int32_t *__restrict__ orig_in, 
         orig_out[i] = orig_in ? orig_in[i] : (int32_t)i;
 }
 
-// Edge keys under the new labels (no repeats remain), payload the old edge id.
-__global__ void k_relabel_keys(int64_t m, const int32_t *__restrict__ ea, const int32_t *__restrict__ eb,
-                               const uint32_t *__restrict__ new_of, unsigned long long *__restrict__ key,
-                               uint32_t *__restrict__ idx) {
+// Edge keys under the new labels (no repeats remain).
+__global__ void k_relabel_keys(int64_t m, PairCode code, const int32_t *__restrict__ ea,
+                               const int32_t *__restrict__ eb, const uint32_t *__restrict__ new_of,
+                               unsigned long long *__restrict__ key) {
     for (int64_t e = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; e < m; e += (int64_t)gridDim.x * blockDim.x) {
         const uint64_t x = new_of[ea[e]], y = new_of[eb[e]];
-        key[e] = ((x < y ? x : y) << 32) | (x < y ? y : x);
-        idx[e] = (uint32_t)e;
+        key[e] = pair_key(code, x < y ? x : y, x < y ? y : x);
     }
 }
 
-__global__ void k_unpack_edges(int64_t m, const unsigned long long *__restrict__ key,
-                               const uint32_t *__restrict__ idx, const float *__restrict__ ew_old,
-                               int32_t *__restrict__ ea, int32_t *__restrict__ eb, float *__restrict__ ew) {
+__global__ void k_unpack_edges(int64_t m, PairCode code, const unsigned long long *__restrict__ key,
+                               int32_t *__restrict__ ea, int32_t *__restrict__ eb) {
     for (int64_t e = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; e < m; e += (int64_t)gridDim.x * blockDim.x) {
-        ea[e] = (int32_t)(key[e] >> 32);
-        eb[e] = (int32_t)(key[e] & 0xffffffffull);
-        if (ew_old) ew[e] = ew_old[idx[e]];
+        ea[e] = pair_lo(code, key[e]);
+        eb[e] = pair_hi(code, key[e]);
     }
 }
 
@@ -422,17 +450,11 @@ __global__ void k_place_lower(int64_t m, const uint32_t *__restrict__ b_sorted, 
     }
 }
 
-__global__ void k_edge_b(int64_t m, const int32_t *__restrict__ eb, uint32_t *__restrict__ bkey,
-                         uint32_t *__restrict__ eidx) {
-    for (int64_t e = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; e < m; e += (int64_t)gridDim.x * blockDim.x) {
-        bkey[e] = (uint32_t)eb[e];
-        eidx[e] = (uint32_t)e;
-    }
-}
-
-__global__ void k_u32_to_u64(int64_t n, const uint32_t *__restrict__ a, uint64_t *__restrict__ b) {
+// Zeroes four arrays of n.
+__global__ void k_zero_counts(int64_t n, uint32_t *__restrict__ a, uint32_t *__restrict__ b, uint32_t *__restrict__ c,
+                              uint32_t *__restrict__ d) {
     for (int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; i < n; i += (int64_t)gridDim.x * blockDim.x)
-        b[i] = a[i];
+        a[i] = b[i] = c[i] = d[i] = 0u;
 }
 
 // ------------------------------------------------ reverse Cuthill-McKee --
@@ -537,17 +559,21 @@ __global__ void k_rc_order(int64_t n, const uint32_t *__restrict__ pos, uint32_t
         vid_sorted[n - 1 - (int64_t)pos[v]] = (uint32_t)v;
 }
 
+constexpr int INGEST_FLAGS = 5;
+
 struct IngestLayout {
     unsigned long long *key0, *key1;     // [m_in] pair keys (sort double buffer)
-    uint32_t *idx0, *idx1;               // [m_in] list indices / edge ids
-    uint32_t *head, *edge_of;            // [m_in]
+    uint32_t *list;                      // [m_in] long runs
+    uint32_t *b_sorted;                  // [m_in] larger endpoints, sorted
+    uint32_t *edge_of;                   // [m_in] edge of a sorted pair; edges by larger endpoint
+    float *w_sorted;                     // [m_in] weights in the order of the sorted pairs
     int32_t *ea, *eb;                    // [m_in] edges (a < b)
     float *ew, *ew2;                     // [m_in]
     uint32_t *deg, *lower_cnt, *upper_cnt, *new_of;   // [n]
-    uint64_t *lower_start, *upper_start, *deg64;      // [n]
-    unsigned long long *vkey0, *vkey1;   // [n]
+    uint64_t *lower_start, *upper_start; // [n]
+    uint32_t *vkey0, *vkey1;             // [n]
     uint32_t *vid0, *vid1;               // [n]
-    unsigned int *flags;                 // [4]: error bits, d_max, runs for a workgroup, runs for a wave
+    unsigned int *flags;                 // [INGEST_FLAGS]: error bits, d_max, runs for a workgroup, runs for a wave, edges
     // reverse Cuthill-McKee order ([n] each)
     int32_t *rc_root;                    // component of every vertex (its smallest id)
     uint32_t *rc_pos;                    // place in the Cuthill-McKee order (RC_UNSET before)
@@ -568,19 +594,27 @@ static size_t rocprim_temp_bytes(int64_t m_in, int64_t n) {
     size_t need = 0, t = 0;
     hipError_t e = hipSuccess;
     const size_t mm = (size_t)std::max<int64_t>(1, m_in), nn = (size_t)std::max<int64_t>(1, n);
+    const rocprim::counting_iterator<uint32_t> ids(0);
     e = rocprim::radix_sort_pairs(nullptr, t, (unsigned long long *)nullptr, (unsigned long long *)nullptr,
-                                  (uint32_t *)nullptr, (uint32_t *)nullptr, mm, 0, 64);
+                                  (const float *)nullptr, (float *)nullptr, mm, 0, 64);
+    need = std::max(need, e == hipSuccess ? t : 0);
+    e = rocprim::radix_sort_keys(nullptr, t, (unsigned long long *)nullptr, (unsigned long long *)nullptr, mm, 0, 64);
     need = std::max(need, e == hipSuccess ? t : 0);
     e = rocprim::radix_sort_pairs(nullptr, t, (unsigned long long *)nullptr, (unsigned long long *)nullptr,
                                   (uint32_t *)nullptr, (uint32_t *)nullptr, nn, 0, 64);
     need = std::max(need, e == hipSuccess ? t : 0);
-    e = rocprim::radix_sort_pairs(nullptr, t, (uint32_t *)nullptr, (uint32_t *)nullptr, (uint32_t *)nullptr,
-                                  (uint32_t *)nullptr, mm, 0, 32);
+    e = rocprim::radix_sort_pairs(nullptr, t, (const uint32_t *)nullptr, (uint32_t *)nullptr, ids, (uint32_t *)nullptr,
+                                  mm, 0, 32);
     need = std::max(need, e == hipSuccess ? t : 0);
-    e = rocprim::exclusive_scan(nullptr, t, (uint32_t *)nullptr, (uint32_t *)nullptr, 0u, mm,
+    e = rocprim::radix_sort_keys(nullptr, t, (const uint32_t *)nullptr, (uint32_t *)nullptr, mm, 0, 32);
+    need = std::max(need, e == hipSuccess ? t : 0);
+    e = rocprim::radix_sort_pairs(nullptr, t, (const uint32_t *)nullptr, (uint32_t *)nullptr, ids, (uint32_t *)nullptr,
+                                  nn, 0, 32);
+    need = std::max(need, e == hipSuccess ? t : 0);
+    e = rocprim::exclusive_scan(nullptr, t, run_heads(nullptr, 0), (uint32_t *)nullptr, 0u, mm,
                                 rocprim::plus<uint32_t>());
     need = std::max(need, e == hipSuccess ? t : 0);
-    e = rocprim::exclusive_scan(nullptr, t, (uint64_t *)nullptr, (uint64_t *)nullptr, (uint64_t)0, nn + 1,
+    e = rocprim::exclusive_scan(nullptr, t, counts_of(nullptr, 0), (uint64_t *)nullptr, (uint64_t)0, nn + 1,
                                 rocprim::plus<uint64_t>());
     need = std::max(need, e == hipSuccess ? t : 0);
     e = rocprim::exclusive_scan(nullptr, t, (uint32_t *)nullptr, (uint32_t *)nullptr, 0u, nn,
@@ -597,10 +631,10 @@ static size_t ingest_layout(int64_t n, int64_t m_in, void *ws, size_t ws_bytes, 
     IngestLayout l;
     l.key0 = c.take<unsigned long long>(mm);
     l.key1 = c.take<unsigned long long>(mm);
-    l.idx0 = c.take<uint32_t>(mm);
-    l.idx1 = c.take<uint32_t>(mm);
-    l.head = c.take<uint32_t>(mm);
+    l.list = c.take<uint32_t>(mm);
+    l.b_sorted = c.take<uint32_t>(mm);
     l.edge_of = c.take<uint32_t>(mm);
+    l.w_sorted = c.take<float>(mm);
     l.ea = c.take<int32_t>(mm);
     l.eb = c.take<int32_t>(mm);
     l.ew = c.take<float>(mm);
@@ -611,12 +645,11 @@ static size_t ingest_layout(int64_t n, int64_t m_in, void *ws, size_t ws_bytes, 
     l.new_of = c.take<uint32_t>(nn);
     l.lower_start = c.take<uint64_t>(nn);
     l.upper_start = c.take<uint64_t>(nn);
-    l.deg64 = c.take<uint64_t>(nn);
-    l.vkey0 = c.take<unsigned long long>(nn);
-    l.vkey1 = c.take<unsigned long long>(nn);
+    l.vkey0 = c.take<uint32_t>(nn);
+    l.vkey1 = c.take<uint32_t>(nn);
     l.vid0 = c.take<uint32_t>(nn);
     l.vid1 = c.take<uint32_t>(nn);
-    l.flags = c.take<unsigned int>(4);
+    l.flags = c.take<unsigned int>(INGEST_FLAGS);
     l.rc_root = c.take<int32_t>(nn);
     l.rc_pos = c.take<uint32_t>(nn);
     l.rc_par = c.take<uint32_t>(nn);
@@ -647,24 +680,24 @@ static unsigned igrid(int64_t count) { return grid_for(std::max<int64_t>(1, coun
     } while (0)
 
 // Degrees of the m edges (ea < eb, sorted by (ea, eb)) without atomics:
-// upper_cnt from the runs of ea, lower_cnt from the runs of eb after a
-// stable sort of the edge ids by eb (left in idx1 / edge_of for the lower
-// placement), deg = upper + lower.  deg, upper_cnt, lower_cnt: [n];
+// upper_cnt from the runs of ea, lower_cnt from the runs of the sorted eb
+// (left in b_sorted; with_edges: the edge ids, stably sorted by eb, in edge_of for
+// the lower placement), deg = upper + lower.  deg, upper_cnt, lower_cnt: [n];
 // vid0 / vid1 serve as scratch.
-static ad_status edge_counts(int64_t n, int64_t m, const int32_t *ea, const int32_t *eb, const IngestLayout &L,
-                             hipStream_t st) {
-    ad_status s;
-    for (uint32_t *p : {L.upper_cnt, L.lower_cnt, L.vid0, L.vid1}) {
-        s = fill_i32((int32_t *)p, 0, n, st);
-        if (s != AD_OK) return s;
-    }
+static ad_status edge_counts(int64_t n, int64_t m, const int32_t *ea, const int32_t *eb, bool with_edges,
+                             const IngestLayout &L, hipStream_t st) {
+    hipLaunchKernelGGL(k_zero_counts, dim3(igrid(n)), dim3(IBLOCK), 0, st, n, L.upper_cnt, L.lower_cnt, L.vid0, L.vid1);
+    AD_LAUNCH_CHECK("k_zero_counts");
     hipLaunchKernelGGL(k_count_marks, dim3(igrid(m)), dim3(IBLOCK), 0, st, m, ea, L.vid0, L.upper_cnt);
     AD_LAUNCH_CHECK("k_count_marks");
-    hipLaunchKernelGGL(k_edge_b, dim3(igrid(m)), dim3(IBLOCK), 0, st, m, eb, L.idx0, L.head);
-    AD_LAUNCH_CHECK("k_edge_b");
     size_t tb = L.temp_bytes;
-    AD_RP(rocprim::radix_sort_pairs(L.temp, tb, L.idx0, L.idx1, L.head, L.edge_of, (size_t)m, 0, bits_for(n), st));
-    hipLaunchKernelGGL(k_count_marks, dim3(igrid(m)), dim3(IBLOCK), 0, st, m, (const int32_t *)L.idx1, L.vid1,
+    const uint32_t *b = (const uint32_t *)eb;
+    if (with_edges)
+        AD_RP(rocprim::radix_sort_pairs(L.temp, tb, b, L.b_sorted, rocprim::counting_iterator<uint32_t>(0), L.edge_of,
+                                        (size_t)m, 0, bits_for(n), st));
+    else
+        AD_RP(rocprim::radix_sort_keys(L.temp, tb, b, L.b_sorted, (size_t)m, 0, bits_for(n), st));
+    hipLaunchKernelGGL(k_count_marks, dim3(igrid(m)), dim3(IBLOCK), 0, st, m, (const int32_t *)L.b_sorted, L.vid1,
                        L.lower_cnt);
     AD_LAUNCH_CHECK("k_count_marks");
     hipLaunchKernelGGL(k_count_finish, dim3(igrid(n)), dim3(IBLOCK), 0, st, n, L.vid0, L.upper_cnt,
@@ -679,54 +712,41 @@ static ad_status edge_counts(int64_t n, int64_t m, const int32_t *ea, const int3
 // The edges (ea < eb, sorted by (ea, eb); weights ew or NULL) as the
 // symmetric CSR: per-row counts (upper_cnt: edges whose smaller endpoint is
 // the row, lower_cnt: larger), the edges sorted by larger endpoint
-// (idx1 / edge_of), the degrees and their maximum (flags[1]), row_ptr, then
+// (b_sorted / edge_of), the degrees and their maximum (flags[1]), row_ptr, then
 // the upper entries in edge order and the lower ones.  w_out NULL: no weights.
 static ad_status place_csr(int64_t n, int64_t m, const int32_t *ea, const int32_t *eb, const float *ew,
                            int64_t *row_ptr, int32_t *col, float *w_out, int32_t *eid, const IngestLayout &L,
                            hipStream_t st) {
     ad_status s;
     if (n > 0) {
-        s = fill_i32((int32_t *)L.deg, 0, n, st);
-        if (s != AD_OK) return s;
         if (m > 0) {
-            s = edge_counts(n, m, ea, eb, L, st);
+            s = edge_counts(n, m, ea, eb, true, L, st);
             if (s != AD_OK) return s;
         } else {
-            s = fill_i32((int32_t *)L.lower_cnt, 0, n, st);
-            if (s != AD_OK) return s;
-            s = fill_i32((int32_t *)L.upper_cnt, 0, n, st);
-            if (s != AD_OK) return s;
+            hipLaunchKernelGGL(k_zero_counts, dim3(igrid(n)), dim3(IBLOCK), 0, st, n, L.upper_cnt, L.lower_cnt, L.deg,
+                               L.vid0);
+            AD_LAUNCH_CHECK("k_zero_counts");
         }
         hipLaunchKernelGGL(k_degree_max, dim3(std::min<unsigned>(256, igrid(n))), dim3(IBLOCK), 0, st, n, L.deg,
                            L.flags + 1);
         AD_LAUNCH_CHECK("k_degree_max");
     }
     // row_ptr = exclusive scan of the degrees over n + 1 entries (the last one 0)
-    s = fill_i32((int32_t *)(L.deg64 + n), 0, 2, st);
-    if (s != AD_OK) return s;
-    if (n > 0) {
-        hipLaunchKernelGGL(k_u32_to_u64, dim3(igrid(n)), dim3(IBLOCK), 0, st, n, L.deg, L.deg64);
-        AD_LAUNCH_CHECK("k_u32_to_u64");
-    }
     size_t tb = L.temp_bytes;
-    AD_RP(rocprim::exclusive_scan(L.temp, tb, L.deg64, (uint64_t *)row_ptr, (uint64_t)0, (size_t)n + 1,
+    AD_RP(rocprim::exclusive_scan(L.temp, tb, counts_of(L.deg, n), (uint64_t *)row_ptr, (uint64_t)0, (size_t)n + 1,
                                   rocprim::plus<uint64_t>(), st));
     if (m > 0) {
-        hipLaunchKernelGGL(k_u32_to_u64, dim3(igrid(n)), dim3(IBLOCK), 0, st, n, L.upper_cnt, L.deg64);
-        AD_LAUNCH_CHECK("k_u32_to_u64");
         tb = L.temp_bytes;
-        AD_RP(rocprim::exclusive_scan(L.temp, tb, L.deg64, L.upper_start, (uint64_t)0, (size_t)n,
+        AD_RP(rocprim::exclusive_scan(L.temp, tb, counts_of(L.upper_cnt, n), L.upper_start, (uint64_t)0, (size_t)n,
                                       rocprim::plus<uint64_t>(), st));
-        hipLaunchKernelGGL(k_u32_to_u64, dim3(igrid(n)), dim3(IBLOCK), 0, st, n, L.lower_cnt, L.deg64);
-        AD_LAUNCH_CHECK("k_u32_to_u64");
         tb = L.temp_bytes;
-        AD_RP(rocprim::exclusive_scan(L.temp, tb, L.deg64, L.lower_start, (uint64_t)0, (size_t)n,
+        AD_RP(rocprim::exclusive_scan(L.temp, tb, counts_of(L.lower_cnt, n), L.lower_start, (uint64_t)0, (size_t)n,
                                       rocprim::plus<uint64_t>(), st));
         hipLaunchKernelGGL(k_place_upper, dim3(igrid(m)), dim3(IBLOCK), 0, st, m, ea, eb, ew, row_ptr, L.lower_cnt,
                            L.upper_start, col, w_out, eid);
         AD_LAUNCH_CHECK("k_place_upper");
         // lower entries from the edges sorted (stably) by their larger endpoint
-        hipLaunchKernelGGL(k_place_lower, dim3(igrid(m)), dim3(IBLOCK), 0, st, m, L.idx1, L.edge_of, ea, ew, row_ptr,
+        hipLaunchKernelGGL(k_place_lower, dim3(igrid(m)), dim3(IBLOCK), 0, st, m, L.b_sorted, L.edge_of, ea, ew, row_ptr,
                            L.lower_start, col, w_out, eid);
         AD_LAUNCH_CHECK("k_place_lower");
     }
@@ -735,15 +755,18 @@ static ad_status place_csr(int64_t n, int64_t m, const int32_t *ea, const int32_
 
 // Relabel the edges by new_of and number them again in (smaller, larger)
 // order: ea, eb rewritten, the weights (when given) permuted into ew2.
-static ad_status relabel_edges(int64_t m, const int32_t *ea, const int32_t *eb, const float *ew,
+static ad_status relabel_edges(int64_t n, int64_t m, const int32_t *ea, const int32_t *eb, const float *ew,
                                const IngestLayout &L, hipStream_t st) {
     if (m <= 0) return AD_OK;
-    hipLaunchKernelGGL(k_relabel_keys, dim3(igrid(m)), dim3(IBLOCK), 0, st, m, ea, eb, L.new_of, L.key0, L.idx0);
+    const PairCode code(n);
+    hipLaunchKernelGGL(k_relabel_keys, dim3(igrid(m)), dim3(IBLOCK), 0, st, m, code, ea, eb, L.new_of, L.key0);
     AD_LAUNCH_CHECK("k_relabel_keys");
     size_t tb = L.temp_bytes;
-    AD_RP(rocprim::radix_sort_pairs(L.temp, tb, L.key0, L.key1, L.idx0, L.idx1, (size_t)m, 0, 64, st));
-    hipLaunchKernelGGL(k_unpack_edges, dim3(igrid(m)), dim3(IBLOCK), 0, st, m, L.key1, L.idx1, ew, L.ea, L.eb,
-                       L.ew2);
+    if (ew)
+        AD_RP(rocprim::radix_sort_pairs(L.temp, tb, L.key0, L.key1, ew, L.ew2, (size_t)m, 0, 2 * code.b, st));
+    else
+        AD_RP(rocprim::radix_sort_keys(L.temp, tb, L.key0, L.key1, (size_t)m, 0, 2 * code.b, st));
+    hipLaunchKernelGGL(k_unpack_edges, dim3(igrid(m)), dim3(IBLOCK), 0, st, m, code, L.key1, L.ea, L.eb);
     AD_LAUNCH_CHECK("k_unpack_edges");
     return AD_OK;
 }
@@ -822,49 +845,41 @@ static ad_status ingest_impl(int64_t n, int64_t m_in, const int32_t *u, const in
                              int32_t *eid, int32_t *orig_out, int64_t *m_host, int32_t *d_max_host,
                              int64_t *n_dropped_host, const IngestLayout &L, hipStream_t st) {
     TraceScope trace("k_ingest", st);
-    ad_status s = fill_i32((int32_t *)L.flags, 0, 4, st);
+    ad_status s = fill_i32((int32_t *)L.flags, 0, INGEST_FLAGS, st);
     if (s != AD_OK) return s;
     int64_t m = 0;
     if (m_in > 0) {
-        hipLaunchKernelGGL(k_pair_keys, dim3(igrid(m_in)), dim3(IBLOCK), 0, st, m_in, n, u, v, w, L.key0, L.idx0,
+        const PairCode code(n);
+        hipLaunchKernelGGL(k_pair_keys, dim3(igrid(m_in)), dim3(IBLOCK), 0, st, m_in, n, code, u, v, w, L.key0,
                            L.flags);
         AD_LAUNCH_CHECK("k_pair_keys");
         size_t tb = L.temp_bytes;
-        AD_RP(rocprim::radix_sort_pairs(L.temp, tb, L.key0, L.key1, L.idx0, L.idx1, (size_t)m_in, 0, 64, st));
-        hipLaunchKernelGGL(k_run_heads, dim3(igrid(m_in)), dim3(IBLOCK), 0, st, m_in, L.key1, L.head);
-        AD_LAUNCH_CHECK("k_run_heads");
+        if (w)
+            AD_RP(rocprim::radix_sort_pairs(L.temp, tb, L.key0, L.key1, w, L.w_sorted, (size_t)m_in, 0, 2 * code.b, st));
+        else
+            AD_RP(rocprim::radix_sort_keys(L.temp, tb, L.key0, L.key1, (size_t)m_in, 0, 2 * code.b, st));
         tb = L.temp_bytes;
-        AD_RP(rocprim::exclusive_scan(L.temp, tb, L.head, L.edge_of, 0u, (size_t)m_in, rocprim::plus<uint32_t>(),
-                                      st));
-        unsigned int hflags[2];
-        uint32_t last[2];
+        AD_RP(rocprim::exclusive_scan(L.temp, tb, run_heads(L.key1, code.none), L.edge_of, 0u, (size_t)m_in,
+                                      rocprim::plus<uint32_t>(), st));
+        // long runs' bounds in key0 and the list of a workgroup's runs in ew2 (both free here)
+        uint2 *bounds = reinterpret_cast<uint2 *>(L.key0);
+        uint32_t *big_list = reinterpret_cast<uint32_t *>(L.ew2);
+        const float *ws = w ? L.w_sorted : nullptr;
+        hipLaunchKernelGGL(k_merge_runs, dim3(igrid(m_in)), dim3(IBLOCK), 0, st, m_in, code, L.key1, L.edge_of, ws,
+                           L.ea, L.eb, L.ew, bounds, L.list, L.flags + 3, big_list, L.flags + 2, L.flags + 4);
+        AD_LAUNCH_CHECK("k_merge_runs");
+        if (w) {
+            hipLaunchKernelGGL(k_merge_long, dim3(1024), dim3(IBLOCK), 0, st, L.flags + 3, L.list, bounds, ws, L.ew);
+            AD_LAUNCH_CHECK("k_merge_long");
+            hipLaunchKernelGGL(k_merge_big, dim3(1024), dim3(MERGE_TB), 0, st, L.flags + 2, big_list, bounds, ws, L.ew);
+            AD_LAUNCH_CHECK("k_merge_big");
+        }
+        unsigned int hflags[INGEST_FLAGS];
         AD_HIP(hipMemcpyAsync(hflags, L.flags, sizeof(hflags), hipMemcpyDeviceToHost, st));
-        AD_HIP(hipMemcpyAsync(&last[0], L.edge_of + (m_in - 1), sizeof(uint32_t), hipMemcpyDeviceToHost, st));
-        AD_HIP(hipMemcpyAsync(&last[1], L.head + (m_in - 1), sizeof(uint32_t), hipMemcpyDeviceToHost, st));
         AD_HIP(hipStreamSynchronize(st));
         if (hflags[0] & 1u) return fail(AD_ERR_GRAPH, "edge list names a vertex outside [0, n)");
         if (hflags[0] & 2u) return fail(AD_ERR_GRAPH, "a listed weight is not finite and positive");
-        m = (int64_t)last[0] + (int64_t)last[1];
-        if (m > 0) {
-            // run bounds in key0 (free after the sort), long runs listed in idx0
-            uint2 *bounds = reinterpret_cast<uint2 *>(L.key0);
-            hipLaunchKernelGGL(k_run_bounds, dim3(igrid(m_in)), dim3(IBLOCK), 0, st, m_in, L.key1, L.head, L.edge_of,
-                               bounds);
-            AD_LAUNCH_CHECK("k_run_bounds");
-            // runs for a wave listed in idx0, runs for a workgroup in ew2 (both free here)
-            uint32_t *big_list = reinterpret_cast<uint32_t *>(L.ew2);
-            hipLaunchKernelGGL(k_merge_runs, dim3(igrid(m)), dim3(IBLOCK), 0, st, m, bounds, L.key1, L.idx1, w, L.ea,
-                               L.eb, L.ew, L.idx0, L.flags + 3, big_list, L.flags + 2);
-            AD_LAUNCH_CHECK("k_merge_runs");
-            if (w) {
-                hipLaunchKernelGGL(k_merge_long, dim3(1024), dim3(IBLOCK), 0, st, L.flags + 3, L.idx0, bounds, L.idx1,
-                                   w, L.ew);
-                AD_LAUNCH_CHECK("k_merge_long");
-                hipLaunchKernelGGL(k_merge_big, dim3(1024), dim3(MERGE_TB), 0, st, L.flags + 2, big_list, bounds,
-                                   L.idx1, w, L.ew);
-                AD_LAUNCH_CHECK("k_merge_big");
-            }
-        }
+        m = (int64_t)hflags[4];
     }
     const int32_t *ea = L.ea, *eb = L.eb;
     const float *ew = L.ew;
@@ -873,16 +888,20 @@ static ad_status ingest_impl(int64_t n, int64_t m_in, const int32_t *u, const in
         if (s != AD_OK) return s;
         if (m > 0) {
             // degrees before relabelling: run lengths of the sorted smaller and larger endpoints
-            s = edge_counts(n, m, ea, eb, L, st);
+            s = edge_counts(n, m, ea, eb, false, L, st);
             if (s != AD_OK) return s;
         }
-        hipLaunchKernelGGL(k_vertex_keys, dim3(igrid(n)), dim3(IBLOCK), 0, st, n, L.deg, L.vkey0, L.vid0);
+        // degrees are below n, so the keys fill bits_for(n) bits
+        const unsigned b = bits_for(n);
+        hipLaunchKernelGGL(k_vertex_keys, dim3(igrid(n)), dim3(IBLOCK), 0, st, n, L.deg, (uint32_t)((1ull << b) - 1),
+                           L.vkey0);
         AD_LAUNCH_CHECK("k_vertex_keys");
         size_t tb = L.temp_bytes;
-        AD_RP(rocprim::radix_sort_pairs(L.temp, tb, L.vkey0, L.vkey1, L.vid0, L.vid1, (size_t)n, 0, 64, st));
+        AD_RP(rocprim::radix_sort_pairs(L.temp, tb, (const uint32_t *)L.vkey0, L.vkey1,
+                                        rocprim::counting_iterator<uint32_t>(0), L.vid1, (size_t)n, 0, b, st));
         hipLaunchKernelGGL(k_new_ids, dim3(igrid(n)), dim3(IBLOCK), 0, st, n, L.vid1, L.new_of, orig_in, orig_out);
         AD_LAUNCH_CHECK("k_new_ids");
-        s = relabel_edges(m, ea, eb, w ? ew : nullptr, L, st);
+        s = relabel_edges(n, m, ea, eb, w ? ew : nullptr, L, st);
         if (s != AD_OK) return s;
         if (m > 0) ew = L.ew2;
     } else if (order == 2 && n > 0) {
@@ -893,7 +912,7 @@ static ad_status ingest_impl(int64_t n, int64_t m_in, const int32_t *u, const in
         if (s != AD_OK) return s;
         hipLaunchKernelGGL(k_new_ids, dim3(igrid(n)), dim3(IBLOCK), 0, st, n, L.vid1, L.new_of, orig_in, orig_out);
         AD_LAUNCH_CHECK("k_new_ids");
-        s = relabel_edges(m, ea, eb, w ? ew : nullptr, L, st);
+        s = relabel_edges(n, m, ea, eb, w ? ew : nullptr, L, st);
         if (s != AD_OK) return s;
         if (m > 0) ew = L.ew2;
     } else if (n > 0) {

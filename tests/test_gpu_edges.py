@@ -285,3 +285,30 @@ def test_binned_rows_of_every_length(api, values):
     e_o, keep_o, kept_o = oracle.fit_exponent_binned(g, rho.astype(np.float64), 0.4, 6)
     assert e_fit == e_o
     np.testing.assert_array_equal(_np(keep), keep_o)
+
+
+# ----------------------------------------------------------------- ingest --
+
+@pytest.mark.parametrize("n", [2, 3, 4, 255, 256, 257, 4096, 4097, 65536, 65537, 1 << 22, (1 << 22) + 1])
+@pytest.mark.parametrize("order", [0, 1])
+def test_ingest_at_id_widths(api, n, order):
+    """Ids that fill their key bits: the largest ids joined to each other, to 0 and
+    looped (the largest id's loop has the code of no pair), each pair listed once, twice or 17
+    times."""
+    announce(f"ingest n={n} order={order}")
+    rng = np.random.default_rng(n)
+    top = np.arange(max(0, n - 12), n)
+    u = np.concatenate([top, np.repeat(top, 17), rng.integers(0, n, 300), top])
+    v = np.concatenate([top, np.repeat(top[::-1], 17), rng.integers(0, n, 300), np.zeros(top.size, int)])
+    p = rng.permutation(u.size)
+    u, v = u[p].astype(np.int32), v[p].astype(np.int32)
+    w = rng.lognormal(0.0, 1.0, u.size).astype(np.float32)
+    cu = lambda a: torch.from_numpy(np.ascontiguousarray(a)).cuda()
+    for ww in (None, w):
+        dg = api.ingest(n, cu(u), cu(v), None if ww is None else cu(ww), by_degree=order == 1)
+        row_ptr, col, we, eid, orig, m, dropped = oracle.ingest(n, u, v, ww, order=order)
+        assert dg.m == m and dg.n_dropped == dropped
+        for got, want in ((dg.row_ptr, row_ptr), (dg.col, col), (dg.eid, eid), (dg.orig_id, orig)):
+            np.testing.assert_array_equal(_np(got), want)
+        if ww is not None:
+            np.testing.assert_array_equal(_np(dg.w), we)
