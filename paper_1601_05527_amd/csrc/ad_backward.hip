@@ -28,7 +28,8 @@
 namespace ad {
 
 constexpr int BB = 256;
-constexpr int PART_ROWS = 1024;
+constexpr int PART_ROWS = 256;           // rows per workgroup of k_adj_rescale (1,024: too few workgroups
+                                         // in flight, 39 us at n = 2^18, R = 8; 256: 15 us)
 
 static int lanes_for(double avg) {
     int lpr = 1;
@@ -175,52 +176,30 @@ __global__ __launch_bounds__(BB) void k_adj_rescale(int64_t n, int R, const int6
     }
 }
 
-__global__ void k_adj_corner(int R, int64_t nblocks, const double *__restrict__ part,
-                             const unsigned long long *__restrict__ arg, const double *__restrict__ minmax,
-                             float *__restrict__ lam) {
-    const int r = threadIdx.x;
-    if (r >= R) return;
+// The rows attaining min and max, a wave per vector (a thread per vector read
+// 256 workgroups' sums one after another: 64 us; 8 us).
+__global__ __launch_bounds__(WAVE) void k_adj_corner(int R, int64_t nblocks, const double *__restrict__ part,
+                                                     const unsigned long long *__restrict__ arg,
+                                                     const double *__restrict__ minmax, float *__restrict__ lam) {
+    const int r = blockIdx.x;
     if (!(minmax[R + r] > minmax[r])) return;
     double sa = 0.0, sb = 0.0;
-    for (int64_t b = 0; b < nblocks; ++b) {
+    for (int64_t b = threadIdx.x; b < nblocks; b += WAVE) {
         sa += part[b * 2 * R + r];
         sb += part[b * 2 * R + R + r];
     }
+    for (int o = WAVE / 2; o >= 1; o >>= 1) {
+        sa += __shfl_xor(sa, o, WAVE);
+        sb += __shfl_xor(sb, o, WAVE);
+    }
+    if (threadIdx.x != 0) return;
     const unsigned long long imin = arg[r], imax = arg[R + r];
-    // one thread per vector: the two updates of column r never race
+    // one wave per vector: the two updates of column r never race
     lam[imin * R + r] = (float)((double)lam[imin * R + r] + sa);
     lam[imax * R + r] = (float)((double)lam[imax * R + r] + sb);
 }
 
-// g[p] += omega * inv_s_i * sum_r lambda_i,r (x_j,r - y_i,r)
-template <int RB>
-__global__ __launch_bounds__(BB) void k_adj_grad(int64_t n, const int64_t *__restrict__ row_ptr,
-                                                 const int32_t *__restrict__ col, const float *__restrict__ inv_s,
-                                                 float omega, const float *__restrict__ xprev,
-                                                 const float *__restrict__ y, const float *__restrict__ lam,
-                                                 float *__restrict__ g, int R, int LPR) {
-    const int64_t row = (int64_t)blockIdx.x * (BB / LPR) + threadIdx.x / LPR;
-    const int lane = threadIdx.x % LPR;
-    if (row >= n) return;
-    const int64_t beg = row_ptr[row], end = row_ptr[row + 1];
-    if (beg == end) return;
-    float li[RB], yi[RB];
-#pragma unroll
-    for (int r = 0; r < RB; ++r) {
-        li[r] = r < R ? lam[row * R + r] : 0.f;
-        yi[r] = r < R ? y[row * R + r] : 0.f;
-    }
-    const float sc = omega * inv_s[row];
-    for (int64_t p = beg + lane; p < end; p += LPR) {
-        const float *xj = xprev + (int64_t)col[p] * R;
-        float dot = 0.f;
-#pragma unroll
-        for (int r = 0; r < RB; ++r)
-            if (r < R) dot = fmaf(li[r], xj[r] - yi[r], dot);
-        g[p] = fmaf(sc, dot, g[p]);
-    }
-}
-
+// mu = lambda / s of the first reverse step.
 __global__ void k_adj_scale_rows(int64_t n, int R, const float *__restrict__ a, const float *__restrict__ s,
                                  float *__restrict__ out) {
     const int64_t total = n * R;
@@ -229,12 +208,181 @@ __global__ void k_adj_scale_rows(int64_t n, int R, const float *__restrict__ a, 
         out[idx] = a[idx] * s[idx / R];
 }
 
-// out = (1 - omega) a + omega b
-__global__ void k_adj_axpby(int64_t total, float omega, const float *__restrict__ a, const float *__restrict__ b,
-                            float *__restrict__ out) {
-    for (int64_t idx = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; idx < total;
-         idx += (int64_t)gridDim.x * blockDim.x)
-        out[idx] = fmaf(omega, b[idx], (1.f - omega) * a[idx]);
+// One reverse step, a row per group of CP * S lanes (CP: a power of two not below the
+// C = R / VEC lanes that hold a row of R values; S slots share the row's entries):
+//   y_i = sum_j w_ij x_j / s_i,  W_i = sum_j w_ij mu_j
+//   g_p += omega / s_i * lambda_i . (x_j - y_i) for every entry p = (i, j)
+//   lambda'_i = (1 - omega) lambda_i + omega W_i,  mu'_i = lambda'_i / s_i
+// Both gathers of a row are issued together and the gathered x_j kept for g
+// where the row fits ADJ_U entries per slot; longer rows gather x_j twice.  Rows
+// beyond hub_d are listed, and the first hub_blocks workgroups take one each.
+// Bound by the gathers.  As five launches (two sweeps, the gradient with a third
+// gather, two passes over n x R for the scale and the sum) a step took
+// 52 us at n = 2^18, m = 526K, R = 8 and a gradient through 20 sweeps 1.68 ms;
+// 19.4 us and 0.95 ms here.
+constexpr int ADJ_U = 4;                 // entries per slot and chunk
+
+template <int VEC>
+struct AdjRow {
+    int64_t beg, end;
+    float is;
+    int off, slot, step;          // of R values, of entries
+    bool on;                      // this lane holds values
+};
+
+// Entries p, p + step, ... of one chunk: x_j (and mu_j into am).
+template <int VEC, bool SUMS>
+__device__ __forceinline__ void adj_gather(const AdjRow<VEC> &a, int64_t p, const int32_t *__restrict__ col,
+                                           const float *__restrict__ w, const float *__restrict__ x,
+                                           const float *__restrict__ mu, int R, float (&xv)[ADJ_U][VEC],
+                                           float (&ay)[VEC], float (&am)[VEC]) {
+    int32_t jj[ADJ_U];
+    float ww[ADJ_U];
+#pragma unroll
+    for (int u = 0; u < ADJ_U; ++u) {
+        const int64_t q = p + (int64_t)u * a.step;
+        const bool ok = a.on && q < a.end;
+        jj[u] = ok ? col[q] : -1;
+        if (SUMS) ww[u] = ok ? (w ? w[q] : 1.f) : 0.f;
+    }
+    float mv[ADJ_U][VEC];
+#pragma unroll
+    for (int u = 0; u < ADJ_U; ++u) {
+#pragma unroll
+        for (int q = 0; q < VEC; ++q) {
+            xv[u][q] = 0.f;
+            if (SUMS) mv[u][q] = 0.f;
+        }
+        if (jj[u] >= 0) {
+            load_vec<VEC>(x + (int64_t)jj[u] * R + a.off, xv[u]);
+            if (SUMS) load_vec<VEC>(mu + (int64_t)jj[u] * R + a.off, mv[u]);
+        }
+    }
+    if (SUMS) {
+#pragma unroll
+        for (int u = 0; u < ADJ_U; ++u) {
+#pragma unroll
+            for (int q = 0; q < VEC; ++q) {
+                ay[q] = fmaf(ww[u], xv[u][q], ay[q]);
+                am[q] = fmaf(ww[u], mv[u][q], am[q]);
+            }
+        }
+    }
+}
+
+template <int VEC>
+__device__ __forceinline__ void adj_grad(const AdjRow<VEC> &a, int64_t p, int CP, float sc, const float (&li)[VEC],
+                                         const float (&y)[VEC], const float (&xv)[ADJ_U][VEC], float *__restrict__ g) {
+    float dot[ADJ_U];
+#pragma unroll
+    for (int u = 0; u < ADJ_U; ++u) {
+        dot[u] = 0.f;
+#pragma unroll
+        for (int q = 0; q < VEC; ++q) dot[u] = fmaf(li[q], xv[u][q] - y[q], dot[u]);     // li is 0 off the row
+    }
+    for (int o = 1; o < CP; o <<= 1) {
+#pragma unroll
+        for (int u = 0; u < ADJ_U; ++u) dot[u] += __shfl_xor(dot[u], o, WAVE);
+    }
+#pragma unroll
+    for (int u = 0; u < ADJ_U; ++u) {
+        const int64_t q = p + (int64_t)u * a.step;
+        if (a.off == 0 && q < a.end) g[q] = fmaf(sc, dot[u], g[q]);
+    }
+}
+
+template <int VEC>
+__global__ __launch_bounds__(BB) void k_adj_step(int64_t n, const int64_t *__restrict__ row_ptr,
+                                                 const int32_t *__restrict__ col, const float *__restrict__ w,
+                                                 const float *__restrict__ inv_s, float omega,
+                                                 const float *__restrict__ x, const float *__restrict__ lam,
+                                                 const float *__restrict__ mu, float *__restrict__ g,
+                                                 float *__restrict__ lam_out, float *__restrict__ mu_out, int R,
+                                                 int CP, int S, int64_t hub_d, const int32_t *__restrict__ hubs,
+                                                 const unsigned int *__restrict__ hub_count, unsigned int hub_blocks) {
+    constexpr int NW = BB / WAVE;
+    __shared__ float part[NW][WAVE][2 * VEC];
+    const int c = threadIdx.x % CP;
+    AdjRow<VEC> a;
+    a.off = c * VEC;
+    a.on = a.off < R;
+    const bool hub = blockIdx.x < hub_blocks;
+    const unsigned int nh = hub ? *hub_count : 1u;
+    for (unsigned int h = hub ? blockIdx.x : 0u; h < nh; h += hub ? hub_blocks : 1u) {
+        int64_t row;
+        if (hub) {
+            row = hubs[h];
+            a.slot = threadIdx.x / CP;
+            a.step = BB / CP;
+        } else {
+            const int group = CP * S;
+            row = (int64_t)(blockIdx.x - hub_blocks) * (BB / group) + threadIdx.x / group;
+            a.slot = (threadIdx.x % group) / CP;
+            a.step = S;
+            if (row >= n) return;                                    // uniform over the group
+        }
+        a.beg = row_ptr[row];
+        a.end = row_ptr[row + 1];
+        if (!hub && a.end - a.beg > hub_d) return;                   // uniform over the group
+        a.is = inv_s[row];
+        float li[VEC], ay[VEC], am[VEC], xv[ADJ_U][VEC];
+#pragma unroll
+        for (int q = 0; q < VEC; ++q) li[q] = ay[q] = am[q] = 0.f;
+        if (a.on) load_vec<VEC>(lam + row * R + a.off, li);
+        const int64_t chunk = (int64_t)ADJ_U * a.step;
+        for (int64_t p = a.beg + a.slot; p < a.end; p += chunk)
+            adj_gather<VEC, true>(a, p, col, w, x, mu, R, xv, ay, am);
+        // the slots' sums, over the wave's slots and then over the workgroup's waves
+        const int span = hub ? WAVE : CP * S;
+        for (int o = CP; o < span; o <<= 1) {
+#pragma unroll
+            for (int q = 0; q < VEC; ++q) {
+                ay[q] += __shfl_xor(ay[q], o, WAVE);
+                am[q] += __shfl_xor(am[q], o, WAVE);
+            }
+        }
+        if (hub) {
+            const int wv = threadIdx.x / WAVE;
+            if ((int)(threadIdx.x % WAVE) < CP) {
+#pragma unroll
+                for (int q = 0; q < VEC; ++q) {
+                    part[wv][c][q] = ay[q];
+                    part[wv][c][VEC + q] = am[q];
+                }
+            }
+            __syncthreads();
+#pragma unroll
+            for (int q = 0; q < VEC; ++q) {
+                ay[q] = am[q] = 0.f;
+                for (int v = 0; v < NW; ++v) {
+                    ay[q] += part[v][c][q];
+                    am[q] += part[v][c][VEC + q];
+                }
+            }
+            __syncthreads();
+        }
+#pragma unroll
+        for (int q = 0; q < VEC; ++q) ay[q] *= a.is;
+        const float sc = omega * a.is;
+        if (a.end - a.beg <= chunk) {
+            if (a.beg + a.slot < a.end) adj_grad<VEC>(a, a.beg + a.slot, CP, sc, li, ay, xv, g);
+        } else {
+            for (int64_t p = a.beg + a.slot; p < a.end; p += chunk) {
+                adj_gather<VEC, false>(a, p, col, w, x, mu, R, xv, ay, am);
+                adj_grad<VEC>(a, p, CP, sc, li, ay, xv, g);
+            }
+        }
+        if (a.slot == 0 && a.on) {
+            float nl[VEC], nm[VEC];
+#pragma unroll
+            for (int q = 0; q < VEC; ++q) {
+                nl[q] = fmaf(omega, am[q], (1.f - omega) * li[q]);
+                nm[q] = nl[q] * a.is;
+            }
+            store_vec<VEC>(lam_out + row * R + a.off, nl);
+            store_vec<VEC>(mu_out + row * R + a.off, nm);
+        }
+    }
 }
 
 __global__ void k_edge_to_entries(int64_t nnz, const int32_t *__restrict__ eid, const float *__restrict__ we,
@@ -253,9 +401,9 @@ __global__ void k_adj_fold(int64_t nnz, const int32_t *__restrict__ eid, const f
 }
 
 struct BwdLayout {
-    float *inv_s, *sdeg, *ones;
+    float *inv_s, *sdeg;
     SweepPlan plan;
-    float *xbh, *lam, *lam2, *mu, *y, *seg, *g;
+    float *xbh, *lam, *lam2, *mu, *mu2, *seg, *g;
     double *part;
     unsigned long long *arg;
 };
@@ -269,13 +417,12 @@ static size_t bwd_layout(const ad_graph *g, const ad_relax_opts *o, void *ws, si
     BwdLayout l;
     l.inv_s = c.take<float>(n);
     l.sdeg = c.take<float>(n);
-    l.ones = c.take<float>(n);
     sweep_plan_carve(c, n, ceil_div(n, PLAN_TILE), l.plan);
     l.xbh = c.take<float>(nR);
     l.lam = c.take<float>(nR);
     l.lam2 = c.take<float>(nR);
     l.mu = c.take<float>(nR);
-    l.y = c.take<float>(nR);
+    l.mu2 = c.take<float>(nR);
     l.seg = c.take<float>(nR * (size_t)std::max(1, o->ckpt_every));
     l.g = c.take<float>(nnz);
     l.part = c.take<double>(nb * 2 * o->R);
@@ -304,13 +451,25 @@ static ad_status launch_rb(const ad_graph *g, const ad_relax_opts *o, const floa
     return AD_OK;
 }
 
-template <int RB>
-static ad_status launch_grad(const ad_graph *g, const BwdLayout &L, float omega, const float *xprev,
-                             const float *lam, int R, int lpr, hipStream_t st) {
-    const unsigned nb = (unsigned)ceil_div(g->n, BB / lpr);
-    hipLaunchKernelGGL((k_adj_grad<RB>), dim3(nb), dim3(BB), 0, st, g->n, g->row_ptr, g->col, L.inv_s, omega,
-                       xprev, L.y, lam, L.g, R, lpr);
-    AD_LAUNCH_CHECK("k_adj_grad");
+template <int VEC>
+static ad_status launch_step(const ad_graph *g, const BwdLayout &L, const SweepPlan &plan, float omega,
+                             const float *xprev, const float *lam, const float *mu, float *lam_out, float *mu_out,
+                             int R, hipStream_t st) {
+    int cp = 1;
+    while (cp * VEC < R) cp *= 2;
+    // slots: a chunk holds 1.5 times the average row, so that most rows need one.  Average
+    // 4, R = 8, entries per slot x slots: 4 x 2 19.4 us a step, 4 x 1 21.4, 2 x 2 22.1,
+    // 2 x 4 25.1, 8 x 1 22.7, 8 x 2 32.1
+    const double avg = 2.0 * (double)g->m / (double)g->n;
+    int slots = 1;
+    while (2 * cp * slots <= WAVE && 2 * slots * ADJ_U < 3 * avg) slots *= 2;
+    // a listed row has more than hub_d of the 2m entries
+    const unsigned hub_blocks = (unsigned)std::min<int64_t>(512, 2 * g->m / (plan.sh.hub_d + 1));
+    const int64_t blocks = ceil_div(g->n, BB / (cp * slots));
+    hipLaunchKernelGGL((k_adj_step<VEC>), dim3((unsigned)(hub_blocks + blocks)), dim3(BB), 0, st, g->n, g->row_ptr,
+                       g->col, g->w, L.inv_s, omega, xprev, lam, mu, L.g, lam_out, mu_out, R, cp, slots,
+                       plan.sh.hub_d, plan.hub_list, plan.hub_count, hub_blocks);
+    AD_LAUNCH_CHECK("k_adj_step");
     return AD_OK;
 }
 
@@ -375,8 +534,6 @@ extern "C" ad_status ad_relax_backward(const ad_graph *g, const ad_relax_opts *o
     if (s != AD_OK) return s;
     s = weighted_degree_f32(g, L.inv_s, L.sdeg, plan, stream);
     if (s != AD_OK) return s;
-    s = fill_i32((int32_t *)L.ones, 0x3f800000, n, stream);   // 1.0f
-    if (s != AD_OK) return s;
     s = fill_i32((int32_t *)L.g, 0, nnz, stream);
     if (s != AD_OK) return s;
     s = fill_i32((int32_t *)grad_w, 0, g->m, stream);
@@ -399,13 +556,15 @@ extern "C" ad_status ad_relax_backward(const ad_graph *g, const ad_relax_opts *o
     hipLaunchKernelGGL(k_adj_rescale, dim3((unsigned)nb), dim3(BB), 0, stream, n, R, g->row_ptr, xk, shift,
                        comp_of, minmax, L.xbh, L.lam, L.part);
     AD_LAUNCH_CHECK("k_adj_rescale");
-    hipLaunchKernelGGL(k_adj_corner, dim3(1), dim3(64), 0, stream, R, nb, L.part, L.arg, minmax, L.lam);
+    hipLaunchKernelGGL(k_adj_corner, dim3((unsigned)R), dim3(WAVE), 0, stream, R, nb, L.part, L.arg, minmax, L.lam);
     AD_LAUNCH_CHECK("k_adj_corner");
 
     // reverse sweeps, one checkpoint segment at a time
     const int c = o->ckpt_every;
     const int nseg = ad_relax_num_checkpoints(o);
-    float *lam = L.lam, *lam_next = L.lam2;
+    float *lam = L.lam, *lam_next = L.lam2, *mu = L.mu, *mu_next = L.mu2;
+    hipLaunchKernelGGL(k_adj_scale_rows, dim3(grid_for((int64_t)nR, BB)), dim3(BB), 0, stream, n, R, lam, L.inv_s, mu);
+    AD_LAUNCH_CHECK("k_adj_scale_rows");
     for (int q = nseg - 1; q >= 0; --q) {
         const int t0 = q * c;
         const int t1 = std::min(o->k, (q + 1) * c);
@@ -419,23 +578,14 @@ extern "C" ad_status ad_relax_backward(const ad_graph *g, const ad_relax_opts *o
         for (int t = t1; t > t0; --t) {
             const int u = t - 1 - t0;
             const float *xprev = u == 0 ? base : L.seg + (size_t)u * nR;
-            // y = S^-1 W x^(t-1): the sweep kernel with omega = 1
-            s = sweep_f32(g, L.inv_s, 1.0f, xprev, L.y, R, plan, stream);
+            if (plan.sh.vec == 4)
+                s = launch_step<4>(g, L, plan, omega, xprev, lam, mu, lam_next, mu_next, R, stream);
+            else if (plan.sh.vec == 2)
+                s = launch_step<2>(g, L, plan, omega, xprev, lam, mu, lam_next, mu_next, R, stream);
+            else
+                s = launch_step<1>(g, L, plan, omega, xprev, lam, mu, lam_next, mu_next, R, stream);
             if (s != AD_OK) return s;
-            if (R <= 8) s = launch_grad<8>(g, L, omega, xprev, lam, R, lpr, stream);
-            else if (R <= 16) s = launch_grad<16>(g, L, omega, xprev, lam, R, lpr, stream);
-            else if (R <= 32) s = launch_grad<32>(g, L, omega, xprev, lam, R, lpr, stream);
-            else s = launch_grad<64>(g, L, omega, xprev, lam, R, lpr, stream);
-            if (s != AD_OK) return s;
-            // lambda^(t-1) = (1 - omega) lambda + omega W (lambda / s)
-            hipLaunchKernelGGL(k_adj_scale_rows, dim3(grid_for((int64_t)nR, BB)), dim3(BB), 0, stream, n, R, lam,
-                               L.inv_s, L.mu);
-            AD_LAUNCH_CHECK("k_adj_scale_rows");
-            s = sweep_f32(g, L.ones, 1.0f, L.mu, L.y, R, plan, stream);
-            if (s != AD_OK) return s;
-            hipLaunchKernelGGL(k_adj_axpby, dim3(grid_for((int64_t)nR, BB)), dim3(BB), 0, stream, (int64_t)nR,
-                               omega, lam, L.y, lam_next);
-            AD_LAUNCH_CHECK("k_adj_axpby");
+            std::swap(mu, mu_next);
             std::swap(lam, lam_next);
         }
     }

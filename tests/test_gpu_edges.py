@@ -312,3 +312,42 @@ def test_ingest_at_id_widths(api, n, order):
             np.testing.assert_array_equal(_np(got), want)
         if ww is not None:
             np.testing.assert_array_equal(_np(dg.w), we)
+
+
+# ---------------------------------------------------------------- adjoint --
+
+@pytest.mark.parametrize("R", [1, 2, 4, 6, 8, 12, 24, 33, 64])
+@pytest.mark.parametrize("kind", ["rows", "sparse"])
+def test_adjoint_rows_of_every_kind(api, R, kind):
+    """The reverse step's vector widths and lanes per row, on rows of one chunk, of
+    several and of a workgroup (the two hubs, 300 and 700 entries), and
+    isolated vertices.  Bounds: those of the adjoint tests on grids, which are k
+    FP32 roundings on the scale of the largest gradients."""
+    announce(f"adjoint {kind} R={R}")
+    rng = np.random.default_rng(7)
+    n, k = 1500, 6
+    if kind == "rows":
+        us, vs = [np.arange(n - 3)], [np.arange(1, n - 2)]
+        for h, d in ((3, 300), (700, 700), (11, 64), (12, 65), (13, 40), (14, 17)):
+            us.append(np.full(d, h))
+            vs.append(rng.choice(np.setdiff1d(np.arange(n - 3), [h - 1, h, h + 1]), size=d, replace=False))
+        u, v = np.concatenate(us), np.concatenate(vs)
+        key = np.unique(np.minimum(u, v) * n + np.maximum(u, v))
+        g = G.from_edges(n, key // n, key % n)
+    else:
+        g = G.from_edges(n, np.arange(0, n - 2, 2), np.arange(1, n - 1, 2))
+        g = G.from_edges(n, np.concatenate([g.edge_u, np.arange(0, n - 4, 4)]),
+                         np.concatenate([g.edge_v, np.arange(2, n - 2, 4)]))
+    g = G.with_weights(g, rng.uniform(0.5, 2.0, g.m).astype(np.float32))
+    c = rng.normal(size=g.m)
+    dg = api.DeviceGraph.from_host(g, "cuda")
+    w = torch.from_numpy(g.edge_w.astype(np.float32)).cuda().requires_grad_(True)
+    rho = api.AlgDist.apply(w, dg, R, k, 0.5, 3, 4)
+    (torch.from_numpy(c.astype(np.float32)).cuda() * rho).sum().backward()
+    got = _np(w.grad).astype(np.float64)
+    want = oracle.grad_weights(g, c, R, k, 0.5, x0=oracle.start_vectors(g.n, R, 3, 0, g.orig_id))
+    err = np.linalg.norm(got - want) / np.linalg.norm(want)
+    per = np.abs(got - want) / (np.abs(want) + 1e-3 * np.abs(want).max())
+    print(f"rel L2 {err:.3e}  max per-edge {per.max():.3e}")
+    assert err <= 1e-4
+    assert per.max() <= 1e-3
