@@ -35,7 +35,6 @@ namespace ad {
 
 constexpr int BLOCK = 256;
 constexpr int MM_SLOTS = 16;       // copies of each graph's min / max codes (k_minmax)
-constexpr int MM_SPLIT = 4;        // k_minmax blocks per CENTRE_ROWS chunk
 constexpr int SWEEP_UNROLL = 8;     // row gathers in flight per lane
 
 // s_i = sum_j w_ij in FP64 (LPR lanes per row, strided partial sums combined
@@ -249,6 +248,9 @@ __device__ __forceinline__ double wave_sum(double v) {
     return v;
 }
 
+// A wave takes four vectors (one Philox block's words) of a chunk; the first also
+// sums s_i.  All of a chunk's vectors on one wave left the chip idle on small
+// graphs: 20 us at n = 2,000, R = 12, 8.5 here.
 template <typename T>
 __global__ __launch_bounds__(BLOCK) void k_comp_partials(int R, int64_t n_comp, int64_t n_chunks,
                                                         const int32_t *__restrict__ members,
@@ -260,7 +262,10 @@ __global__ __launch_bounds__(BLOCK) void k_comp_partials(int R, int64_t n_comp, 
                                                         const int32_t *__restrict__ row_graph,
                                                         double *__restrict__ part, double *__restrict__ part_s) {
     const int lane = threadIdx.x & (WAVE - 1);
-    const int64_t ch = (int64_t)blockIdx.x * (BLOCK / WAVE) + (threadIdx.x >> 6);
+    const int nq = (R + 3) >> 2;
+    const int64_t wv = (int64_t)blockIdx.x * (BLOCK / WAVE) + (threadIdx.x >> 6);
+    const int64_t ch = wv / nq;
+    const int q = (int)(wv - ch * nq);
     if (ch >= n_chunks) return;                      // uniform across the wave
     int64_t lo = 0, hi = n_comp - 1;                 // last component starting at or before ch
     while (lo < hi) {
@@ -271,33 +276,32 @@ __global__ __launch_bounds__(BLOCK) void k_comp_partials(int R, int64_t n_comp, 
     const int64_t p0 = comp_start[lo] + (ch - chunk_start[lo]) * COMP_CHUNK;
     const int64_t p1 = min(comp_start[lo + 1], p0 + COMP_CHUNK);
     double sacc = 0.0;
-    for (int64_t p = p0 + lane; p < p1; p += WAVE) sacc += (double)sdeg[members[p]];
-    sacc = wave_sum(sacc);
-    if (lane == 0) part_s[ch] = sacc;
-    const int nq = (R + 3) >> 2;
-    for (int q = 0; q < nq; ++q) {
-        double acc[4] = {0.0, 0.0, 0.0, 0.0};
-        for (int64_t p = p0 + lane; p < p1; p += WAVE) {
-            const int32_t i = members[p];
-            const double s = (double)sdeg[i];
-            if (x0) {
+    double acc[4] = {0.0, 0.0, 0.0, 0.0};
+    for (int64_t p = p0 + lane; p < p1; p += WAVE) {
+        const int32_t i = members[p];
+        const double s = (double)sdeg[i];
+        sacc += s;
+        if (x0) {
 #pragma unroll
-                for (int c = 0; c < 4; ++c)
-                    if (4 * q + c < R) acc[c] += s * (double)x0[(int64_t)i * R + 4 * q + c];
-            } else {
-                uint64_t words[4];
-                const int32_t key = orig_id ? orig_id[i] : i;
-                const uint64_t g = row_graph ? (uint64_t)row_graph[i] : 0ull;
-                philox4x64_10((uint64_t)(uint32_t)key, (uint64_t)q, 0, 0, seed, gid + g, words);
+            for (int c = 0; c < 4; ++c)
+                if (4 * q + c < R) acc[c] += s * (double)x0[(int64_t)i * R + 4 * q + c];
+        } else {
+            uint64_t words[4];
+            const int32_t key = orig_id ? orig_id[i] : i;
+            const uint64_t g = row_graph ? (uint64_t)row_graph[i] : 0ull;
+            philox4x64_10((uint64_t)(uint32_t)key, (uint64_t)q, 0, 0, seed, gid + g, words);
 #pragma unroll
-                for (int c = 0; c < 4; ++c) acc[c] += s * start_from_word(words[c]);
-            }
+            for (int c = 0; c < 4; ++c) acc[c] += s * start_from_word(words[c]);
         }
+    }
+    if (q == 0) {
+        sacc = wave_sum(sacc);
+        if (lane == 0) part_s[ch] = sacc;
+    }
 #pragma unroll
-        for (int c = 0; c < 4; ++c) {
-            const double v = wave_sum(acc[c]);
-            if (lane == 0 && 4 * q + c < R) part[ch * R + 4 * q + c] = v;
-        }
+    for (int c = 0; c < 4; ++c) {
+        const double v = wave_sum(acc[c]);
+        if (lane == 0 && 4 * q + c < R) part[ch * R + 4 * q + c] = v;
     }
 }
 
@@ -334,11 +338,15 @@ __device__ __forceinline__ void comp_chunk_sums(int64_t c0, int64_t c1, int R, i
 }
 
 // shift[c][r] = the weighted mean of component c rounded to the 2^-24 grid:
-// one wave per (component, vector).
+// one wave per (component, vector).  Also empties the running min / max codes
+// of every graph (MM_SLOTS copies, mm_count words).
 __global__ __launch_bounds__(BLOCK) void k_comp_finalize(int R, int64_t n_comp, const int64_t *__restrict__ chunk_start,
                                                         const double *__restrict__ part,
                                                         const double *__restrict__ part_s, int centre,
-                                                        double *__restrict__ shift) {
+                                                        double *__restrict__ shift, int64_t mm_count,
+                                                        unsigned long long *__restrict__ mm) {
+    for (int64_t i = (int64_t)blockIdx.x * BLOCK + threadIdx.x; i < mm_count; i += (int64_t)gridDim.x * BLOCK)
+        mm[i] = ((i / R) % 2 == 0) ? ~0ull : 0ull;
     const int64_t pairs = n_comp * R;
     for (int64_t idx = (int64_t)blockIdx.x * (BLOCK / WAVE) + (threadIdx.x >> 6); idx < pairs;
          idx += (int64_t)gridDim.x * (BLOCK / WAVE)) {     // uniform across the wave
@@ -412,13 +420,6 @@ __global__ __launch_bounds__(BLOCK) void k_comp_drift(int R, int64_t n_comp, con
             shift[idx] += (double)d;
         }
     }
-}
-
-// The running min / max codes of every graph (MM_SLOTS copies) start empty.
-__global__ void k_mm_reset(int64_t count, int R, unsigned long long *__restrict__ mm) {
-    const int64_t idx = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (idx >= count) return;
-    mm[idx] = ((idx / R) % 2 == 0) ? ~0ull : 0ull;
 }
 
 // x^(0) - shift into the start buffer.  One Philox block feeds 4 vectors.
@@ -934,6 +935,13 @@ __global__ __launch_bounds__(BLOCK) __attribute__((amdgpu_waves_per_eu(sweep_wav
 // longest upper suffix), so that one round of
 // SWEEP_UNROLL gathers per slot covers it (short rows share a wave, long
 // rows get more slots).  A fixed rows-per-wave request overrides this.
+__device__ __forceinline__ int tile_lg_of(int64_t dm, int spr_max, int rpw_fixed) {
+    if (rpw_fixed > 0) return 31 - __clz(rpw_fixed);
+    int spr = 1;
+    while (spr < spr_max && (int64_t)spr * SWEEP_UNROLL < dm) spr <<= 1;
+    return 31 - __clz(spr_max / spr);
+}
+
 __global__ __launch_bounds__(BLOCK) void k_plan_tiles(int64_t n, const int64_t *__restrict__ row_ptr,
                                                       const int32_t *__restrict__ col, int upper_only,
                                                       int64_t hub_d, int spr_max, int rpw_fixed,
@@ -959,15 +967,7 @@ __global__ __launch_bounds__(BLOCK) void k_plan_tiles(int64_t n, const int64_t *
             dm = max(dm, (int64_t)__shfl_xor(dm, o, WAVE));
             ds += (int64_t)__shfl_xor(ds, o, WAVE);
         }
-        int lg;
-        if (rpw_fixed > 0) {
-            lg = 31 - __clz(rpw_fixed);
-        } else {
-            int spr = 1;
-            while (spr < spr_max && (int64_t)spr * SWEEP_UNROLL < dm) spr <<= 1;
-            const int rpw = spr_max / spr;
-            lg = 31 - __clz(rpw);
-        }
+        const int lg = tile_lg_of(dm, spr_max, rpw_fixed);
         if (lane == 0) {
             tile_lg[t] = lg;
             tile_waves[t] = (unsigned int)ceil_div_dev(r1 - r0, (int64_t)1 << lg);
@@ -992,16 +992,88 @@ __global__ void k_plan_fill(int64_t n, const int *__restrict__ tile_lg, const un
     }
 }
 
+// The plan and the hub list (hub_list not NULL) of one graph in a single launch: a
+// wave per tile, one append per workgroup of PLAN_WG tiles to the plan and to
+// the list; with one workgroup the counts start in LDS, otherwise they are zeroed
+// before.  The plan's order is then that of the workgroups' appends, which a static
+// walk does not mind.  For up to PLAN_ONCE tiles: the appends of one address
+// are served one by one, 45 ns each, and beyond 256 of them cost what
+// the tiles, three scans and the fill take in launches (seven with the hub list, 27 us
+// at any size up to there; 6.8 us here at n = 2,000).
+constexpr int PLAN_WG = 16;
+constexpr int64_t PLAN_ONCE = 4096, PLAN_SOLO = 32;     // tiles; one workgroup up to PLAN_SOLO
+
+__global__ __launch_bounds__(PLAN_WG * WAVE) void k_plan_once(int64_t n, const int64_t *__restrict__ row_ptr,
+                                                              const int32_t *__restrict__ col, int upper_only,
+                                                              int64_t hub_d, int spr_max, int rpw_fixed,
+                                                              long long *__restrict__ plan,
+                                                              unsigned int *__restrict__ plan_count,
+                                                              int32_t *__restrict__ hub_list,
+                                                              unsigned int *__restrict__ hub_count, int64_t ntiles) {
+    __shared__ unsigned int waves[PLAN_WG], hubs[PLAN_WG], base[2], count[2];
+    const int lane = threadIdx.x & (WAVE - 1), wv = threadIdx.x >> 6;
+    const bool solo = gridDim.x == 1;
+    if (threadIdx.x < 2) count[threadIdx.x] = 0u;
+    for (int64_t t0 = (int64_t)blockIdx.x * PLAN_WG; t0 < ntiles; t0 += (int64_t)gridDim.x * PLAN_WG) {
+        const int64_t r0 = (t0 + wv) * PLAN_TILE, r1 = min(n, r0 + PLAN_TILE);   // r1 <= r0: no tile
+        const int64_t i = r0 + lane;
+        int64_t d = 0;
+        bool hub = false;
+        if (i < r1) {
+            const int64_t beg = row_ptr[i], end = row_ptr[i + 1];
+            hub = end - beg > hub_d;
+            if (!hub) d = upper_only ? end - upper_start(col, beg, end, i) : end - beg;
+        }
+        int64_t dm = d;
+        for (int o = WAVE / 2; o >= 1; o >>= 1) dm = max(dm, (int64_t)__shfl_xor(dm, o, WAVE));
+        const int lg = tile_lg_of(dm, spr_max, rpw_fixed);
+        const unsigned int nw = r1 > r0 ? (unsigned int)ceil_div_dev(r1 - r0, (int64_t)1 << lg) : 0u;
+        const unsigned long long hm = hub_list ? __ballot(hub) : 0ull;
+        if (lane == 0) {
+            waves[wv] = nw;
+            hubs[wv] = (unsigned int)__popcll(hm);
+        }
+        __syncthreads();
+        if (threadIdx.x < 2) {
+            const unsigned int *of = threadIdx.x == 0 ? waves : hubs;
+            unsigned int tot = 0;
+            for (int w = 0; w < PLAN_WG; ++w) tot += of[w];
+            unsigned int b = count[threadIdx.x];
+            if (solo) count[threadIdx.x] = b + tot;
+            else if (tot) b = atomicAdd(threadIdx.x == 0 ? plan_count : hub_count, tot);
+            base[threadIdx.x] = b;
+        }
+        __syncthreads();
+        unsigned int po = base[0], ho = base[1];
+        for (int w = 0; w < wv; ++w) {
+            po += waves[w];
+            ho += hubs[w];
+        }
+        if ((unsigned int)lane < nw) {
+            const int64_t r = r0 + ((int64_t)lane << lg);
+            plan[po + lane] = ((long long)r << 16) | ((long long)min((int64_t)1 << lg, r1 - r) << 8) | lg;
+        }
+        if ((hm >> lane) & 1) hub_list[ho + __popcll(hm & (((unsigned long long)1 << lane) - 1))] = (int32_t)i;
+        __syncthreads();                                             // waves, hubs and base are written again
+    }
+    if (solo && threadIdx.x == 0) {
+        *plan_count = count[0];
+        if (hub_list) *hub_count = count[1];
+    }
+}
+
 // Per-vector min and max of x^(k) = x + shift over non-isolated rows
-// (ordered-integer atomics); MM_SPLIT blocks per chunk of CENTRE_ROWS rows of
-// one graph, each taking 1 / MM_SPLIT of the chunk's rows.  Block b updates copy
+// (ordered-integer atomics); `split` blocks per chunk of CENTRE_ROWS rows of
+// one graph, each taking its share of the chunk's rows: 4, or 32 where that still
+// leaves at most 1,024 blocks (a block's rows are a chain of dependent loads: n = 2,000,
+// R = 12 11.3 us with 4, 5.5 with 32).  Block b updates copy
 // b % MM_SLOTS of the codes: atomics on one address from many blocks
 // serialise at the memory side.
 template <typename T>
 __global__ __launch_bounds__(BLOCK) void k_minmax(int64_t n, int R, const int64_t *__restrict__ row_ptr,
                                                  const T *__restrict__ x, const double *__restrict__ shift,
                                                  const int32_t *__restrict__ comp_of,
-                                                 unsigned long long *__restrict__ mm, Segs sg) {
+                                                 unsigned long long *__restrict__ mm, Segs sg, int split) {
     __shared__ double lo_l[BLOCK];
     __shared__ double hi_l[BLOCK];
     const int t = threadIdx.x;
@@ -1010,10 +1082,10 @@ __global__ __launch_bounds__(BLOCK) void k_minmax(int64_t n, int R, const int64_
     const int row_off = t / R;
     int g;
     int64_t r0, r1;
-    seg_span(sg, sg.chunk_off, n, blockIdx.x / MM_SPLIT, CENTRE_ROWS, g, r0, r1);
+    seg_span(sg, sg.chunk_off, n, blockIdx.x / split, CENTRE_ROWS, g, r0, r1);
     {
-        const int64_t q = (r1 - r0 + MM_SPLIT - 1) / MM_SPLIT;
-        r0 += (int64_t)(blockIdx.x % MM_SPLIT) * q;
+        const int64_t q = (r1 - r0 + split - 1) / split;
+        r0 += (int64_t)(blockIdx.x % split) * q;
         r1 = min(r1, r0 + q);
     }
     double lo = INFINITY, hi = -INFINITY;
@@ -1115,9 +1187,9 @@ void sweep_plan_carve(Carver &c, int64_t n, int64_t ntiles_cap, SweepPlan &p) {
     const int64_t nn = std::max<int64_t>(1, n);
     const int64_t ntiles = std::max<int64_t>(1, ntiles_cap);
     p.hub_list = c.take<int32_t>(nn);
-    p.hub_count = c.take<unsigned int>(1);
+    p.hub_count = c.take<unsigned int>(2);
+    p.plan_count = p.hub_count + 1;                      // zeroed together
     p.plan = c.take<long long>(nn + ntiles);
-    p.plan_count = c.take<unsigned int>(1);
     p.tile_lg = c.take<int>(ntiles);
     p.tile_waves = c.take<unsigned int>(ntiles);
     p.tile_nnz = c.take<unsigned long long>(ntiles);
@@ -1132,6 +1204,21 @@ void sweep_plan_carve(Carver &c, int64_t n, int64_t ntiles_cap, SweepPlan &p) {
 ad_status sweep_plan_build(const ad_graph *g, SweepPlan &p, bool build_hubs, const Segs &sg, hipStream_t st) {
     ad_status s;
     p.xcd_groups = (sg.tile_off && sg.G > 1) ? (int)XCDS : 1;
+    const int64_t ntiles = sg.tile_off ? sg.ntiles : ceil_div(g->n, PLAN_TILE);
+    if (p.xcd_groups <= 1 && !sg.tile_off && ntiles > 0 && ntiles <= PLAN_ONCE) {
+        p.turn = 0;
+        if (ntiles > PLAN_SOLO) {
+            // hub_count is another plan's when the hubs are not built here
+            s = fill_i32((int32_t *)(build_hubs ? p.hub_count : p.plan_count), 0, build_hubs ? 2 : 1, st);
+            if (s != AD_OK) return s;
+        }
+        hipLaunchKernelGGL(k_plan_once, dim3(ntiles <= PLAN_SOLO ? 1u : (unsigned)ceil_div(ntiles, PLAN_WG)),
+                           dim3(PLAN_WG * WAVE), 0, st, g->n, g->row_ptr, g->col, p.sh.upper_only, p.sh.hub_d,
+                           p.sh.SPRW, p.sh.rpw_fixed, p.plan, p.plan_count, build_hubs ? p.hub_list : nullptr,
+                           p.hub_count, ntiles);
+        AD_LAUNCH_CHECK("k_plan_once");
+        return AD_OK;
+    }
     // every queue set starts at zero; each launch then clears the set the launch after next uses
     p.turn = 0;
     s = fill_i32((int32_t *)p.queue, 0, (int64_t)QUEUE_SLOTS * QUEUE_SET, st);
@@ -1142,7 +1229,6 @@ ad_status sweep_plan_build(const ad_graph *g, SweepPlan &p, bool build_hubs, con
         s = collect_rows(g, p.sh.hub_d, (int64_t)1 << 62, p.hub_list, p.hub_count, st);
         if (s != AD_OK) return s;
     }
-    const int64_t ntiles = sg.tile_off ? sg.ntiles : ceil_div(g->n, PLAN_TILE);
     if (ntiles <= 0) {
         ad_status s0 = fill_i32((int32_t *)p.splits, 0, XCDS + 1, st);
         if (s0 != AD_OK) return s0;
@@ -1442,21 +1528,17 @@ static ad_status relax_impl(const ad_graph *g, const ad_relax_opts *o, const voi
     }
     if (comp) {
         if (n > 0 && comp->n_chunks > 0) {
-            hipLaunchKernelGGL((k_comp_partials<T>), dim3((unsigned)ceil_div(comp->n_chunks, BLOCK / WAVE)),
+            hipLaunchKernelGGL((k_comp_partials<T>), dim3((unsigned)ceil_div(comp->n_chunks * ((R + 3) / 4), BLOCK / WAVE)),
                                dim3(BLOCK), 0, st, R, comp->n_comp, comp->n_chunks, comp->members, comp->comp_start,
                                comp->chunk_start, L.sdeg, g->orig_id, o->seed, o->graph_id, (const T *)x0,
                                sg.row_graph, L.part, L.part_s);
             AD_LAUNCH_CHECK("k_comp_partials");
         }
-        const int64_t cr = comp->n_comp * R;
-        if (cr > 0) {
-            hipLaunchKernelGGL(k_comp_finalize, dim3((unsigned)std::min<int64_t>(ceil_div(cr, BLOCK / WAVE), 1 << 16)), dim3(BLOCK), 0, st, R,
-                               comp->n_comp, comp->chunk_start, L.part, L.part_s, 1, shift);
-            AD_LAUNCH_CHECK("k_comp_finalize");
-        }
+        const int64_t cr = std::max<int64_t>(1, comp->n_comp * R);
         const int64_t mmc = (int64_t)MM_SLOTS * sg.G * 2 * R;
-        hipLaunchKernelGGL(k_mm_reset, dim3((unsigned)ceil_div(mmc, BLOCK)), dim3(BLOCK), 0, st, mmc, R, L.mm);
-        AD_LAUNCH_CHECK("k_mm_reset");
+        hipLaunchKernelGGL(k_comp_finalize, dim3((unsigned)std::min<int64_t>(ceil_div(cr, BLOCK / WAVE), 1 << 16)), dim3(BLOCK), 0, st, R,
+                           comp->n_comp, comp->chunk_start, L.part, L.part_s, 1, shift, mmc, L.mm);
+        AD_LAUNCH_CHECK("k_comp_finalize");
     } else {
         if (n > 0 && nb > 0) {
             hipLaunchKernelGGL((k_centre_partials<T>), dim3((unsigned)nb), dim3(BLOCK), 0, st, n, R, L.sdeg,
@@ -1539,12 +1621,13 @@ static ad_status relax_impl(const ad_graph *g, const ad_relax_opts *o, const voi
     }
 
     if (n > 0 && nb > 0) {
+        const int split = nb * 32 <= 1024 ? 32 : 4;
         if (out64)
-            hipLaunchKernelGGL((k_minmax<double>), dim3((unsigned)(nb * MM_SPLIT)), dim3(BLOCK), 0, st, n, R, g->row_ptr,
-                               (const double *)x_out, shift, comp_of, L.mm, sg);
+            hipLaunchKernelGGL((k_minmax<double>), dim3((unsigned)(nb * split)), dim3(BLOCK), 0, st, n, R, g->row_ptr,
+                               (const double *)x_out, shift, comp_of, L.mm, sg, split);
         else
-            hipLaunchKernelGGL((k_minmax<float>), dim3((unsigned)(nb * MM_SPLIT)), dim3(BLOCK), 0, st, n, R, g->row_ptr,
-                               (const float *)x_out, shift, comp_of, L.mm, sg);
+            hipLaunchKernelGGL((k_minmax<float>), dim3((unsigned)(nb * split)), dim3(BLOCK), 0, st, n, R, g->row_ptr,
+                               (const float *)x_out, shift, comp_of, L.mm, sg, split);
         AD_LAUNCH_CHECK("k_minmax");
     }
     const int64_t gr = (int64_t)sg.G * R;

@@ -170,13 +170,10 @@ __device__ __forceinline__ void dist_span(const int32_t *__restrict__ col, const
     }
 }
 
-// Entries per wave work item of a long row in the distance pass.
-constexpr int64_t DIST_SEG = 4096;
-
 // rho for every edge, visited from its upper entry (j > i; the suffix of the
 // row after upper_start); with ALL, from both of its entries (whole rows),
 // every entry's value also in rho_ent in CSR order.  The first hub_blocks workgroups take the rows
-// longer than hub_d, their upper suffix cut into work items of DIST_SEG
+// longer than hub_d, their upper suffix cut into work items of hub_d
 // entries (row h of the hub list, segment s < hub_segs; items past the row's
 // end are skipped), one wave per item.  The other waves walk the launch plan (first row, rows in the tile,
 // log2 rows per wave) as the sweep does, with SPRW / rpw slots per row.
@@ -201,11 +198,12 @@ __global__ __launch_bounds__(SBLOCK) void k_edge_dist(
         for (unsigned long long it = (unsigned long long)blockIdx.x * (SBLOCK / WAVE) + wave; it < items;
              it += stride) {
             const int64_t row = hub_list[it / hub_segs];
-            const int64_t re = row_ptr[row + 1];
-            const int64_t rb = ALL ? row_ptr[row] : upper_start(col, row_ptr[row], re, row);
-            const int64_t b0 = rb + (int64_t)(it % hub_segs) * DIST_SEG;
-            if (b0 >= re) continue;                       // uniform across the wave
-            const int64_t e0 = min(re, b0 + DIST_SEG);
+            const int64_t re = row_ptr[row + 1], r0 = row_ptr[row];
+            const int64_t skip = (int64_t)(it % hub_segs) * hub_d;
+            if (skip >= re - r0) continue;                // uniform across the wave, as below
+            const int64_t b0 = (ALL ? r0 : upper_start(col, r0, re, row)) + skip;
+            if (b0 >= re) continue;
+            const int64_t e0 = min(re, b0 + hub_d);
             const int64_t gb = (int64_t)(row_graph ? row_graph[row] : 0) * 2 * R;
             dist_span<Tx, Tr, VEC, U, ALL>(col, eid, x, minmax, rho, rho_ent, R, C, SPRW, slot, chunk,
                                            lane - chunk, active, row, b0, e0, e0 - b0, gb);
@@ -2207,15 +2205,23 @@ using namespace ad;
 
 namespace ad {
 
-// Rows longer than this are cut into DIST_SEG-entry work items.
-constexpr int64_t DIST_HUB = 4096;
+// Rows longer than this are cut into work items of as many entries: a
+// 8,192nd of the stored entries (about a wave's share with the chip full) as a power
+// of two, from 256 to 4,096.  A row of 1,800 upper entries on one wave was the tail of
+// the pass at n = 65,000, m = 1M (FP64, R = 16): 146 us, 42 at 256.
+static int64_t dist_hub(int64_t m) {
+    int64_t d = 256;
+    while (d < 4096 && d * 8192 < 2 * m) d *= 2;
+    return d;
+}
 
-static SweepShape dist_shape(int R, ad_dtype x_dtype, int64_t d_max, bool whole_rows) {
+static SweepShape dist_shape(int R, ad_dtype x_dtype, int64_t m, int64_t d_max, bool whole_rows) {
     // the sweep's lane layout for this vector width, rows per wave sized by
-    // the upper entries (or the whole rows); rows longer than DIST_HUB (when
+    // the upper entries (or the whole rows); rows longer than dist_hub(m) (when
     // the graph has any) go to the hub workgroups
     SweepShape sh = sweep_shape(R, x_dtype == AD_F64 ? 8 : 4, 0, 0);
-    sh.hub_d = (d_max > DIST_HUB) ? DIST_HUB : ((int64_t)1 << 62);
+    const int64_t hub = dist_hub(m);
+    sh.hub_d = d_max > hub ? hub : ((int64_t)1 << 62);
     sh.upper_only = whole_rows ? 0 : 1;
     return sh;
 }
@@ -2235,15 +2241,16 @@ ad_status edge_dist_segs(const ad_graph *g, int32_t R, ad_dtype x_dtype, const v
     // FP64 vectors with FP32 distances (the FP64 tail of FP32 storage) take
     // the FP32 lane layout: four values, 32 bytes, per lane
     if (rho_ent && rho_dtype != AD_F32) return fail(AD_ERR_INTERNAL, "entry-ordered distances are FP32");
-    pl.sh = dist_shape(R, (x_dtype == AD_F64 && rho_dtype == AD_F32) ? AD_F32 : x_dtype, g->d_max, rho_ent != nullptr);
-    const bool hubs = g->d_max > DIST_HUB;
+    pl.sh = dist_shape(R, (x_dtype == AD_F64 && rho_dtype == AD_F32) ? AD_F32 : x_dtype, g->m, g->d_max, rho_ent != nullptr);
+    const int64_t hub = dist_hub(g->m);
+    const bool hubs = g->d_max > hub;
     ad_status s = sweep_plan_build(g, pl, hubs, sg, stream);
     if (s != AD_OK) return s;
-    // hub work items: (rows longer than DIST_HUB) x (segments of the longest row)
+    // hub work items: (rows longer than hub) x (segments of the longest row)
     int64_t hub_segs = 1, hub_blocks = 0;
     if (hubs) {
-        hub_segs = ceil_div(g->d_max, DIST_SEG);
-        const int64_t busy = ceil_div(2 * g->m, DIST_SEG) + ceil_div(2 * g->m, DIST_HUB + 1);
+        hub_segs = ceil_div(g->d_max, hub);
+        const int64_t busy = ceil_div(2 * g->m, hub) + ceil_div(2 * g->m, hub + 1);
         hub_blocks = round_up_xcds(std::min<int64_t>(1024, std::max<int64_t>(1, ceil_div(busy, SBLOCK / WAVE))));
     }
     const unsigned nb = (unsigned)(std::min<int64_t>(4096, ceil_div(g->n, SBLOCK / WAVE)) + hub_blocks);

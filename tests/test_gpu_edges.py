@@ -351,3 +351,32 @@ def test_adjoint_rows_of_every_kind(api, R, kind):
     print(f"rel L2 {err:.3e}  max per-edge {per.max():.3e}")
     assert err <= 1e-4
     assert per.max() <= 1e-3
+
+
+# ------------------------------------------- launch plans and set-up passes --
+
+@pytest.mark.parametrize("n", [3, 64, 65, 1024, 1025, 2048, 2049, 32_768, 32_769, 262_144, 262_145])
+@pytest.mark.parametrize("R", [2, 7])
+def test_plans_at_their_sizes(api, n, R):
+    """Graphs at the tile counts where the launch plan, its single workgroup, the
+    min / max split and the two plan forms change over; rows of a workgroup (300
+    and 600 entries; the last vertex is one) where they fit, and hub
+    bounds that make every row one.  FP64 storage: the values are the oracle's up
+    to the summation order of a row (600 terms of 1.1e-16) over 3 sweeps."""
+    announce(f"plans n={n} R={R}")
+    rng = np.random.default_rng(n)
+    us, vs = [np.arange(n - 1)], [np.arange(1, n)]
+    if n > 1000:
+        for h, d in ((n - 1, 600), (7, 300), (n // 2, 600)):
+            us.append(np.full(d, h))
+            vs.append(rng.choice(n, size=d, replace=False))
+    u, v = np.concatenate(us), np.concatenate(vs)
+    lo, hi = np.minimum(u, v), np.maximum(u, v)
+    key = np.unique((lo * n + hi)[lo != hi])
+    g = G.from_edges(n, key // n, key % n)
+    dg = api.DeviceGraph.from_host(g, "cuda")
+    want = oracle.algebraic_distance(g, R, 3, 0.5, seed=4)
+    for hub in (0, 1):
+        res = api.relax(dg, R, 3, omega=0.5, seed=4, store="f64", hub_degree=hub)
+        rho = _np(api.edge_dist(dg, res.x, res.minmax))
+        np.testing.assert_allclose(rho, want, rtol=1e-11, atol=1e-12)
