@@ -458,7 +458,10 @@ struct SelInit {
     int64_t m = 0;
     uint8_t *keep = nullptr;               // [m] zeroed, or NULL
     int64_t nlogs = 0;
-    double *logs = nullptr;                // [2 * nlogs], or NULL
+    double *logs = nullptr;                // [2 * nlogs], or NULL: a fit follows, and clears
+    int nhist = 0;                         // its histograms
+    unsigned int *hist = nullptr;
+    unsigned long long *cand_n = nullptr;  // and its candidate counts ([2])
 };
 constexpr int COUNT_WORDS = 8;
 
@@ -473,6 +476,8 @@ __global__ __launch_bounds__(SBLOCK) void k_sel_init(SelInit in) {
             in.logs[v] = l;
             in.logs[in.nlogs + v] = v > 1 ? 1.0 / l : 0.0;
         }
+        for (int64_t b = idx; b < in.nhist; b += step) in.hist[b] = 0u;
+        if (idx < 2) in.cand_n[idx] = 0ull;
     }
     if (in.keep) {
         // bytes up to the first 16-byte boundary, whole words, the remaining bytes
@@ -1396,7 +1401,7 @@ __device__ __forceinline__ unsigned long long side_grid(uint32_t d, uint32_t r, 
 __device__ __forceinline__ uint32_t rec_rank(const uint4 &v, int o) { return o == 0 ? v.y : v.z; }
 
 // Per fitted orientation (at most two): the edges' grid indices and the
-// current radix histogram.
+// first digit's histogram (digit p's: p * 2 * NBINS further on).
 struct FitArrays {
     unsigned long long *G[2];
     unsigned int *hist[2];
@@ -1485,20 +1490,47 @@ struct CandArrays {
     int64_t cap;
 };
 
-// Zero the histograms, the candidate counts and the first check's six
-// counters; state[2o] = prefix of selected digits, state[2o + 1] = rank
-// still to skip (1-based inside the prefix), for o < nfit.  One block.
-__global__ __launch_bounds__(SBLOCK) void k_select_init(unsigned long long *state, unsigned long long K, int nfit,
-                                                       unsigned int *hist, unsigned long long *cand_n,
-                                                       unsigned long long *counts) {
-    for (int b = threadIdx.x; b < 2 * NBINS; b += SBLOCK) hist[b] = 0;
-    if (threadIdx.x < 2) cand_n[threadIdx.x] = 0;
-    if (threadIdx.x < 6) counts[threadIdx.x] = 0;
-    if (threadIdx.x == 0)
-        for (int o = 0; o < nfit; ++o) {
-            state[2 * o] = 0;
-            state[2 * o + 1] = K;
+// The digit that holds the rank still to skip (1-based inside the prefix) in a
+// complete histogram, appended to the prefix.  Every thread of the block calls it
+// and gets the result.  Each kernel of the select finds the digit before it
+// this way for itself: a kernel of one workgroup between every two passes, its
+// first thread walking the 256 partial sums, took 7 to 13 us each.
+struct Digits {
+    unsigned long long prefix, need;
+};
+__device__ __forceinline__ Digits digit_pick(const unsigned int *__restrict__ hist, Digits d, int width) {
+    constexpr int PER = NBINS / SBLOCK;
+    __shared__ unsigned long long wsum[SBLOCK / WAVE];
+    __shared__ Digits out;
+    const int lane = threadIdx.x & (WAVE - 1), wv = threadIdx.x >> 6;
+    unsigned int c[PER];
+    unsigned long long mine = 0;
+#pragma unroll
+    for (int q = 0; q < PER; ++q) {
+        c[q] = hist[threadIdx.x * PER + q];
+        mine += c[q];
+    }
+    unsigned long long incl = mine;
+    for (int o = 1; o < WAVE; o <<= 1) {
+        const unsigned long long t = __shfl_up(incl, o, WAVE);
+        if (lane >= o) incl += t;
+    }
+    if (lane == WAVE - 1) wsum[wv] = incl;
+    __syncthreads();
+    for (int w = 0; w < wv; ++w) incl += wsum[w];
+    unsigned long long before = incl - mine;
+    if ((before < d.need && d.need <= incl) || (threadIdx.x == SBLOCK - 1 && d.need > incl)) {
+        int bin = PER - 1;
+#pragma unroll
+        for (int q = 0; q < PER - 1; ++q) {
+            if (bin == PER - 1 && before + c[q] >= d.need) bin = q;
+            if (bin == PER - 1) before += c[q];
         }
+        out.prefix = (d.prefix << width) | (unsigned long long)(threadIdx.x * PER + bin);
+        out.need = d.need - before;
+    }
+    __syncthreads();
+    return out;
 }
 
 constexpr int STAGE = 2048;   // LDS staging of a block's candidates (entries)
@@ -1526,10 +1558,12 @@ __device__ __forceinline__ void stage_flush(const T *stage, unsigned int *n_stag
 // whose higher digits equal the selected prefix; orientation o = blockIdx.y.
 // COMPACT (the second digit's pass) also appends those values to the
 // candidate list; the later passes read the list instead of G_o when it is
-// complete.
+// complete.  state: [pass][orientation], written here for the digit before
+// (`before_width` bits) and read for those before it; K: the rank to select.
 template <bool COMPACT>
-__global__ __launch_bounds__(SBLOCK) void k_radix_hist(int64_t m, FitArrays fa, CandArrays cs, int shift,
-                                                      int width, const unsigned long long *__restrict__ state) {
+__global__ __launch_bounds__(SBLOCK) void k_radix_hist(int64_t m, FitArrays fa, CandArrays cs, int pass, int shift,
+                                                      int width, int before_width, unsigned long long K,
+                                                      Digits *__restrict__ state) {
     __shared__ unsigned int h[NBINS];
     __shared__ unsigned long long stage[COMPACT ? STAGE : 1];
     __shared__ unsigned int n_stage;
@@ -1544,14 +1578,17 @@ __global__ __launch_bounds__(SBLOCK) void k_radix_hist(int64_t m, FitArrays fa, 
             count = (int64_t)nc;
         }
     }
+    constexpr int64_t STEP = (int64_t)SBLOCK * FIT_U;
+    if (blockIdx.x > 0 && (int64_t)blockIdx.x * STEP >= count) return;
     for (int b = threadIdx.x; b < NBINS; b += SBLOCK) h[b] = 0;
     if (threadIdx.x == 0) n_stage = 0;
-    __syncthreads();
-    const unsigned long long prefix = state[2 * o];
+    const Digits sel = digit_pick(fa.hist[o] + (size_t)(pass - 1) * 2 * NBINS,
+                                  pass > 1 ? state[2 * (pass - 2) + o] : Digits{0ull, K}, before_width);
+    if (blockIdx.x == 0 && threadIdx.x == 0) state[2 * (pass - 1) + o] = sel;
+    const unsigned long long prefix = sel.prefix;
     const int lane = threadIdx.x & (WAVE - 1);
     const unsigned long long below = lane ? (~0ull >> (WAVE - lane)) : 0ull;
     BinRun run;
-    constexpr int64_t STEP = (int64_t)SBLOCK * FIT_U;
     for (int64_t b0 = (int64_t)blockIdx.x * STEP; b0 < count; b0 += (int64_t)gridDim.x * STEP) {
         unsigned long long v[FIT_U];
 #pragma unroll
@@ -1586,32 +1623,18 @@ __global__ __launch_bounds__(SBLOCK) void k_radix_hist(int64_t m, FitArrays fa, 
     }
     __syncthreads();
     for (int b = threadIdx.x; b < NBINS; b += SBLOCK)
-        if (h[b]) atomicAdd(&fa.hist[o][b], h[b]);
+        if (h[b]) atomicAdd(&fa.hist[o][(size_t)pass * 2 * NBINS + b], h[b]);
 }
 
-// The bin holding the state's rank, appended (`width` bits) to the prefix,
-// and the histogram cleared for the next pass; orientation o = blockIdx.x.
-__global__ __launch_bounds__(SBLOCK) void k_radix_pick(FitArrays fa, unsigned long long *state_all, int width) {
-    __shared__ unsigned long long part[SBLOCK];
-    constexpr int PER = NBINS / SBLOCK;
-    unsigned int *hist = fa.hist[blockIdx.x];
-    unsigned long long *state = state_all + 2 * blockIdx.x;
-    unsigned long long c = 0;
-    for (int q = 0; q < PER; ++q) c += hist[threadIdx.x * PER + q];
-    part[threadIdx.x] = c;
-    __syncthreads();
-    if (threadIdx.x == 0) {
-        unsigned long long need = state[1];   // 1-based rank inside the current prefix
-        unsigned long long run = 0;
-        int chunk = 0;
-        while (chunk < SBLOCK - 1 && run + part[chunk] < need) run += part[chunk++];
-        int bin = chunk * PER;
-        while (bin < chunk * PER + PER - 1 && run + hist[bin] < need) run += hist[bin++];
-        state[0] = (state[0] << width) | (unsigned long long)bin;
-        state[1] = need - run;
-    }
-    __syncthreads();
-    for (int b = threadIdx.x; b < NBINS; b += SBLOCK) hist[b] = 0;
+// The last digit: the selected value of orientation o = blockIdx.x, to the host
+// (out: mapped host memory, read after the stream is synchronised; a copy's
+// launch and its pageable path took 25 us).
+__global__ __launch_bounds__(SBLOCK) void k_radix_last(FitArrays fa, const Digits *__restrict__ state,
+                                                      unsigned long long *__restrict__ out) {
+    const int o = blockIdx.x;
+    const Digits sel = digit_pick(fa.hist[o] + (size_t)(NPASS - 1) * 2 * NBINS, state[2 * (NPASS - 2) + o],
+                                  DIGIT_WIDTH[NPASS - 1]);
+    if (threadIdx.x == 0) out[2 * o] = sel.prefix;
 }
 
 // The exact check of a candidate grid point g_hi per orientation (and of
@@ -1636,7 +1659,7 @@ struct CountArgs {
 constexpr unsigned long long FIT_MARGIN = 1ull << 16;
 
 // Exact kept counts at the two grid points of every active orientation (per
-// block, into part[4 * block ..]), and keep[] at the upper point.  A thread takes four consecutive edges at a
+// block, into part[4 * block ..], added up by k_fit_margin), and keep[] at the upper point.  A thread takes four consecutive edges at a
 // time (two 16-byte loads of G per orientation, one 4-byte store of keep when
 // keep is 4-byte aligned).  LIST form (launched before the budget tables
 // reach the device): an edge whose estimate does not settle it is not counted
@@ -1750,7 +1773,7 @@ __global__ __launch_bounds__(SBLOCK) void k_fit_count(int64_t m, const uint4 *__
             if (o < nfit && ca.active[o])
                 stage_flush(stage[LIST ? o : 0], &n_stage[o], &base_sh, ca.list[o], &ca.list_n[o], ca.list_cap);
     }
-    // the block's four counts to its own slots (k_sum_counts adds them up)
+    // the block's four counts to its own slots
 #pragma unroll
     for (int k = 0; k < 4; ++k) {
         const unsigned long long t = block_sum(c[k >> 1][k & 1]);
@@ -1759,42 +1782,63 @@ __global__ __launch_bounds__(SBLOCK) void k_fit_count(int64_t m, const uint4 *__
     }
 }
 
-// counts[k] += the sum over nblocks blocks of part[4 * b + k], k < 4.  One
-// block; wave k sums count k.
-static_assert(SBLOCK / WAVE == 4, "one wave per count");
-__global__ __launch_bounds__(SBLOCK) void k_sum_counts(const unsigned long long *__restrict__ part, int nblocks,
-                                                      unsigned long long *__restrict__ counts) {
-    const int k = threadIdx.x / WAVE, lane = threadIdx.x & (WAVE - 1);
-    unsigned long long c = 0;
-    for (int b = lane; b < nblocks; b += WAVE) c += part[4 * (int64_t)b + k];
-    for (int d = WAVE / 2; d >= 1; d >>= 1) c += shfl_down(c, d);
-    if (lane == 0) counts[k] += c;
-}
-
 // The listed edges of orientation o = blockIdx.y against the budget tables:
-// counts added, keep flags stored.  Does nothing for an orientation whose
-// list overflowed (the host then counts it again in one full pass).
+// counts added, keep flags stored (none for an orientation whose
+// list overflowed; the host then counts it again in one full pass).  The last
+// workgroup of an orientation to arrive (counts[6 + o]: its tickets) adds the
+// count pass's per-block counts (nblocks of them) and gives the totals and the list's
+// length to the host (out, mapped: [2o], [2o + 1], [4 + o]) and the upper
+// total to n_kept[o]; the launches that did so took 4 us each.
 __global__ __launch_bounds__(SBLOCK) void k_fit_margin(const uint4 *__restrict__ recs, CountArgs ca,
-                                                      unsigned long long *__restrict__ counts) {
+                                                      const unsigned long long *__restrict__ part, int nblocks,
+                                                      unsigned long long *__restrict__ counts,
+                                                      unsigned long long *__restrict__ out,
+                                                      int64_t *__restrict__ n_kept) {
+    __shared__ bool last;
     const int o = blockIdx.y;
     if (!ca.active[o]) return;
     const unsigned long long n = ca.list_n[o];
-    if (n > (unsigned long long)ca.list_cap) return;
     unsigned long long c_hi = 0, c_lo = 0;
-    for (int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; i < (int64_t)n;
-         i += (int64_t)gridDim.x * blockDim.x) {
-        const int64_t e = ca.list[o][i];
-        const uint4 a = recs[2 * e], b = recs[2 * e + 1];
-        const uint32_t ra = rec_rank(a, o), rb = rec_rank(b, o);
-        const bool k_hi = ra < (uint32_t)ca.tab_hi[o][a.x] || rb < (uint32_t)ca.tab_hi[o][b.x];
-        const bool k_lo = ca.use_lo[o] && (ra < (uint32_t)ca.tab_lo[o][a.x] || rb < (uint32_t)ca.tab_lo[o][b.x]);
-        ca.keep[o][e] = k_hi ? 1 : 0;
-        c_hi += k_hi;
-        c_lo += k_lo;
+    if (n <= (unsigned long long)ca.list_cap) {
+        for (int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; i < (int64_t)n;
+             i += (int64_t)gridDim.x * blockDim.x) {
+            const int64_t e = ca.list[o][i];
+            const uint4 a = recs[2 * e], b = recs[2 * e + 1];
+            const uint32_t ra = rec_rank(a, o), rb = rec_rank(b, o);
+            const bool k_hi = ra < (uint32_t)ca.tab_hi[o][a.x] || rb < (uint32_t)ca.tab_hi[o][b.x];
+            const bool k_lo =
+                ca.use_lo[o] && (ra < (uint32_t)ca.tab_lo[o][a.x] || rb < (uint32_t)ca.tab_lo[o][b.x]);
+            ca.keep[o][e] = k_hi ? 1 : 0;
+            c_hi += k_hi;
+            c_lo += k_lo;
+        }
     }
     block_add(c_hi, &counts[2 * o]);
     __syncthreads();
     block_add(c_lo, &counts[2 * o + 1]);
+    if (threadIdx.x == 0) {
+        __threadfence();
+        last = atomicAdd(&counts[6 + o], 1ull) == gridDim.x - 1;
+        __threadfence();
+    }
+    __syncthreads();
+    if (!last) return;
+    c_hi = c_lo = 0;
+    for (int b = threadIdx.x; b < nblocks; b += SBLOCK) {
+        c_hi += part[4 * (int64_t)b + 2 * o];
+        c_lo += part[4 * (int64_t)b + 2 * o + 1];
+    }
+    const unsigned long long hi = block_sum(c_hi);
+    __syncthreads();
+    const unsigned long long lo = block_sum(c_lo);
+    if (threadIdx.x == 0) {
+        const unsigned long long t_hi = hi + __hip_atomic_load(&counts[2 * o], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        const unsigned long long t_lo = lo + __hip_atomic_load(&counts[2 * o + 1], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        out[2 * o] = t_hi;
+        out[2 * o + 1] = t_lo;
+        out[4 + o] = n;
+        n_kept[o] = (int64_t)t_hi;
+    }
 }
 
 // dst[i] = src[i] for i < count; src is host memory mapped for the device.
@@ -1803,10 +1847,6 @@ __global__ __launch_bounds__(SBLOCK) void k_copy_mapped(int32_t *__restrict__ ds
     for (int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; i < count;
          i += (int64_t)gridDim.x * blockDim.x)
         dst[i] = src[i];
-}
-
-__global__ void k_store_count(const unsigned long long *__restrict__ c, int64_t *__restrict__ out) {
-    *out = (int64_t)c[0];
 }
 
 // ------------------------------------------------------------------- host --
@@ -1821,10 +1861,10 @@ struct SelLayout {
     unsigned long long *cand, *cand2, *cand_n;   // select candidates (CandArrays), per orientation
     unsigned long long *fit_part;                // [COUNT_BLOCKS][4]: the count pass's per-block counts
     int64_t cand_cap;
-    unsigned int *hist;           // [2][NBINS]
-    unsigned long long *state;    // [4]: two words per fitted orientation
+    unsigned int *hist;           // [NPASS][2][NBINS]
+    unsigned long long *state;    // [NPASS][2][2]: prefix and rank left after each digit, per fitted orientation
     unsigned long long *counts;   // [COUNT_WORDS]: counts at the upper and lower grid point per orientation,
-                                  // the listed edges per orientation (k_fit_count LIST form), a ticket
+                                  // the listed edges per orientation (k_fit_count LIST form), tickets
     int32_t *tabs;                // [4][d_max + 1]: upper and lower budget tables, per orientation
     double *logs;                 // [2][d_max + 2]: log(v), then 1 / log(v)
     HubScratch hub;               // rows longer than SORT_CAP (d_max > SORT_CAP only)
@@ -1857,8 +1897,8 @@ static size_t sel_layout(const ad_graph *g, void *ws, size_t ws_bytes, SelLayout
     l.cand2 = both ? c.take<unsigned long long>(l.cand_cap) : nullptr;
     l.cand_n = c.take<unsigned long long>(2);
     l.fit_part = c.take<unsigned long long>(4 * (size_t)COUNT_BLOCKS);
-    l.hist = c.take<unsigned int>(2 * NBINS);
-    l.state = c.take<unsigned long long>(4);
+    l.hist = c.take<unsigned int>(NPASS * 2 * NBINS);
+    l.state = c.take<unsigned long long>(4 * NPASS);
     l.counts = c.take<unsigned long long>(COUNT_WORDS);
     l.tabs = c.take<int32_t>(4 * ((size_t)g->d_max + 1));
     l.logs = c.take<double>(2 * ((size_t)g->d_max + 2));
@@ -1984,7 +2024,11 @@ static ad_status rank_setup(const ad_graph *g, const SelLayout &L, uint8_t *zero
     in.keep = zero_keep;
     in.nlogs = (int64_t)g->d_max + 2;
     in.logs = logs ? L.logs : nullptr;
-    const int64_t items = std::max<int64_t>(zero_keep ? ceil_div(g->m, 16) : 1, logs ? in.nlogs : 1);
+    in.nhist = NPASS * 2 * NBINS;
+    in.hist = L.hist;
+    in.cand_n = L.cand_n;
+    const int64_t items =
+        std::max<int64_t>(zero_keep ? ceil_div(g->m, 16) : 1, logs ? std::max<int64_t>(in.nlogs, in.nhist / 8) : 1);
     hipLaunchKernelGGL(k_sel_init, dim3((unsigned)std::min<int64_t>(2048, ceil_div(items, SBLOCK))), dim3(SBLOCK), 0, st,
                        in);
     AD_LAUNCH_CHECK("k_sel_init");
@@ -2458,9 +2502,8 @@ static ad_status fit_from_recs(const ad_graph *g, const SelLayout &L, int nfit, 
     int32_t *stage_dev = nullptr;
     AD_HIP(hipHostGetDevicePointer((void **)&stage_dev, g_stage, 0));
     const int32_t *const tabs_mapped = stage_dev + STAGE_RB;   // tabs_h as the device sees it
-    hipLaunchKernelGGL(k_select_init, dim3(1), dim3(SBLOCK), 0, stream, L.state, (unsigned long long)K, nfit,
-                       L.hist, L.cand_n, L.counts);
-    AD_LAUNCH_CHECK("k_select_init");
+    unsigned long long *const rb_mapped = reinterpret_cast<unsigned long long *>(stage_dev);
+    Digits *const state = reinterpret_cast<Digits *>(L.state);
     const int64_t nlogs = (int64_t)g->d_max + 2;
     int dev = 0, lds_max = 0, n_cu = 0;
     const bool lds_tab = hipGetDevice(&dev) == hipSuccess &&
@@ -2477,20 +2520,19 @@ static ad_status fit_from_recs(const ad_graph *g, const SelLayout &L, int nfit, 
                            L.logs, nlogs, nfit, fa);
     }
     AD_LAUNCH_CHECK("k_fit_grid");
-    hipLaunchKernelGGL(k_radix_pick, dim3(nfit), dim3(SBLOCK), 0, stream, fa, L.state, DIGIT_WIDTH[0]);
-    AD_LAUNCH_CHECK("k_radix_pick");
     for (int pass = 1; pass < NPASS; ++pass) {
         if (pass == 1)
-            hipLaunchKernelGGL(k_radix_hist<true>, dim3(hist_blocks, nfit), dim3(SBLOCK), 0, stream, m, fa, cs,
-                               DIGIT_SHIFT[pass], DIGIT_WIDTH[pass], L.state);
+            hipLaunchKernelGGL(k_radix_hist<true>, dim3(hist_blocks, nfit), dim3(SBLOCK), 0, stream, m, fa, cs, pass,
+                               DIGIT_SHIFT[pass], DIGIT_WIDTH[pass], DIGIT_WIDTH[pass - 1], (unsigned long long)K,
+                               state);
         else
-            hipLaunchKernelGGL(k_radix_hist<false>, dim3(hist_blocks, nfit), dim3(SBLOCK), 0, stream, m, fa, cs,
-                               DIGIT_SHIFT[pass], DIGIT_WIDTH[pass], L.state);
+            hipLaunchKernelGGL(k_radix_hist<false>, dim3(hist_blocks, nfit), dim3(SBLOCK), 0, stream, m, fa, cs, pass,
+                               DIGIT_SHIFT[pass], DIGIT_WIDTH[pass], DIGIT_WIDTH[pass - 1], (unsigned long long)K,
+                               state);
         AD_LAUNCH_CHECK("k_radix_hist");
-        hipLaunchKernelGGL(k_radix_pick, dim3(nfit), dim3(SBLOCK), 0, stream, fa, L.state, DIGIT_WIDTH[pass]);
-        AD_LAUNCH_CHECK("k_radix_pick");
     }
-    AD_HIP(hipMemcpyAsync(rb, L.state, 4 * sizeof(unsigned long long), hipMemcpyDeviceToHost, stream));
+    hipLaunchKernelGGL(k_radix_last, dim3(nfit), dim3(SBLOCK), 0, stream, fa, state, rb_mapped);
+    AD_LAUNCH_CHECK("k_radix_last");
     AD_HIP(hipStreamSynchronize(stream));
     const unsigned long long GMAX = 1ull << 40;
     long long g_try[2];
@@ -2501,7 +2543,7 @@ static ad_status fit_from_recs(const ad_graph *g, const SelLayout &L, int nfit, 
     // the tables arrive.  Later checks (a moved grid point, or a list that
     // overflowed) count in one pass with the tables.
     bool split = true;
-    const unsigned margin_blocks = (unsigned)std::min<int64_t>(64, ceil_div(2 * L.cand_cap, SBLOCK));
+    const unsigned margin_blocks = (unsigned)std::min<int64_t>(32, ceil_div(2 * L.cand_cap, SBLOCK));
     for (int attempt = 0; attempt < 64; ++attempt) {
         // budget tables at the candidate grid point and one step below, filled
         // in the pinned staging buffer (one host thread per table for long rows)
@@ -2523,17 +2565,14 @@ static ad_status fit_from_recs(const ad_graph *g, const SelLayout &L, int nfit, 
         }
         ca.list_n = L.counts + 4;
         ca.list_cap = 2 * L.cand_cap;
-        if (!split) {                        // the first check's counts were zeroed by k_select_init
-            s = fill_u64(L.counts, 0, 6, stream);
+        if (!split) {                        // the first check's counts were zeroed by k_sel_init
+            s = fill_u64(L.counts, 0, COUNT_WORDS, stream);
             if (s != AD_OK) return s;
         }
         if (split) {
             hipLaunchKernelGGL(k_fit_count<true>, dim3(count_blocks), dim3(SBLOCK), 0, stream, m, L.recs, nfit, ca,
                                L.fit_part);
             AD_LAUNCH_CHECK("k_fit_count");
-            hipLaunchKernelGGL(k_sum_counts, dim3(1), dim3(SBLOCK), 0, stream, L.fit_part, (int)count_blocks,
-                               L.counts);
-            AD_LAUNCH_CHECK("k_sum_counts");
         }
         std::vector<std::thread> th;
         size_t started = 0;                  // tables 1 .. started on their own threads
@@ -2556,20 +2595,15 @@ static ad_status fit_from_recs(const ad_graph *g, const SelLayout &L, int nfit, 
         hipLaunchKernelGGL(k_copy_mapped, dim3(grid_for(tab_words, SBLOCK)), dim3(SBLOCK), 0, stream, L.tabs,
                            tabs_mapped, tab_words);
         AD_LAUNCH_CHECK("k_copy_mapped");
-        if (split) {
-            hipLaunchKernelGGL(k_fit_margin, dim3(margin_blocks, nfit), dim3(SBLOCK), 0, stream, L.recs, ca,
-                               L.counts);
-            AD_LAUNCH_CHECK("k_fit_margin");
-        } else {
+        if (!split) {                        // lists nothing: the kernel after it only adds up
             hipLaunchKernelGGL(k_fit_count<false>, dim3(count_blocks), dim3(SBLOCK), 0, stream, m, L.recs, nfit, ca,
                                L.fit_part);
             AD_LAUNCH_CHECK("k_fit_count");
-            hipLaunchKernelGGL(k_sum_counts, dim3(1), dim3(SBLOCK), 0, stream, L.fit_part, (int)count_blocks,
-                               L.counts);
-            AD_LAUNCH_CHECK("k_sum_counts");
         }
+        hipLaunchKernelGGL(k_fit_margin, dim3(margin_blocks, nfit), dim3(SBLOCK), 0, stream, L.recs, ca, L.fit_part,
+                           (int)count_blocks, L.counts, rb_mapped + 4, n_kept);
+        AD_LAUNCH_CHECK("k_fit_margin");
         unsigned long long *const hc = rb + 4;
-        AD_HIP(hipMemcpyAsync(hc, L.counts, 6 * sizeof(unsigned long long), hipMemcpyDeviceToHost, stream));
         AD_HIP(hipStreamSynchronize(stream));
         bool overflow = false;
         for (int o = 0; o < nfit; ++o)
@@ -2582,8 +2616,6 @@ static ad_status fit_from_recs(const ad_graph *g, const SelLayout &L, int nfit, 
             const bool hi_ok = (int64_t)hc[2 * o] >= K;
             const bool lo_ok = g_try[o] == 0 || (int64_t)hc[2 * o + 1] < K;
             if (hi_ok && lo_ok) {
-                hipLaunchKernelGGL(k_store_count, dim3(1), dim3(1), 0, stream, L.counts + 2 * o, n_kept + o);
-                AD_LAUNCH_CHECK("k_store_count");
                 e_used_host[o] = (double)g_try[o] / GRID;
                 done[o] = true;
                 continue;
@@ -2611,13 +2643,9 @@ static ad_status sparsify_fit_impl(const ad_graph *g, ad_dtype rho_dtype, const 
     const int nfit = both ? 2 : 1;
     ad_status s;
     if (m == 0) {
-        s = fill_u64(L.counts, 0, 4, stream);
+        s = fill_u64((unsigned long long *)n_kept, 0, nfit, stream);
         if (s != AD_OK) return s;
-        for (int o = 0; o < nfit; ++o) {
-            hipLaunchKernelGGL(k_store_count, dim3(1), dim3(1), 0, stream, L.counts, n_kept + o);
-            AD_LAUNCH_CHECK("k_store_count");
-            e_used_host[o] = 0.0;
-        }
+        for (int o = 0; o < nfit; ++o) e_used_host[o] = 0.0;
         AD_HIP(hipStreamSynchronize(stream));
         return AD_OK;
     }
@@ -3331,10 +3359,8 @@ static ad_status sparsify_binned_impl(const ad_graph *g, ad_dtype rho_dtype, con
     const int64_t m = g->m;
     ad_status s;
     if (m == 0) {
-        s = fill_u64(L.counts, 0, 1, stream);
+        s = fill_u64((unsigned long long *)n_kept, 0, 1, stream);
         if (s != AD_OK) return s;
-        hipLaunchKernelGGL(k_store_count, dim3(1), dim3(1), 0, stream, L.counts, n_kept);
-        AD_LAUNCH_CHECK("k_store_count");
         if (e_used_host) {
             *e_used_host = target > 0.0 ? 0.0 : e;
             AD_HIP(hipStreamSynchronize(stream));

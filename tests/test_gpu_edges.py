@@ -380,3 +380,32 @@ def test_plans_at_their_sizes(api, n, R):
         res = api.relax(dg, R, 3, omega=0.5, seed=4, store="f64", hub_degree=hub)
         rho = _np(api.edge_dist(dg, res.x, res.minmax))
         np.testing.assert_allclose(rho, want, rtol=1e-11, atol=1e-12)
+
+
+# ------------------------------------------------------------ retention fit --
+
+@pytest.mark.parametrize("target", [1e-9, 0.34, 0.999999, 1.0])
+@pytest.mark.parametrize("kind", ["edge", "three", "star", "cycle", "equal"])
+def test_fit_at_extreme_ranks(api, kind, target):
+    """The select's digits at the first and the last rank, on graphs whose threshold
+    indices are all equal, all distinct or one number apart.  Exponents and
+    masks equal the oracle's."""
+    announce(f"fit {kind} target={target}")
+    rng = np.random.default_rng(2)
+    if kind == "edge":
+        g = G.from_edges(2, np.array([0]), np.array([1]))
+    elif kind == "three":
+        g = G.from_edges(5, np.array([0, 0, 2]), np.array([1, 2, 4]))
+    elif kind == "star":
+        g = G.from_edges(5000, np.zeros(4999, int), np.arange(1, 5000))
+    elif kind == "cycle":
+        g = G.from_edges(3000, np.arange(3000), np.roll(np.arange(3000), -1))
+    else:
+        g = G.chung_lu(800, 9000, seed=6)
+    rho = np.full(g.m, 0.5, np.float32) if kind == "equal" else rng.uniform(0.1, 1.0, g.m).astype(np.float32)
+    dg = api.DeviceGraph.from_host(g, "cuda")
+    for o in (0, 1):
+        keep, n_kept, e = api.sparsify_fit(dg, torch.from_numpy(rho).cuda(), o, target)
+        e_o, keep_o, kept_o = oracle.fit_exponent(g, rho.astype(np.float64), o, target)
+        assert e == e_o and int(_np(n_kept)[0]) == kept_o
+        np.testing.assert_array_equal(_np(keep), keep_o)
