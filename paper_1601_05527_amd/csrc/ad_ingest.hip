@@ -186,9 +186,16 @@ __device__ float digits_round(const unsigned long long (&acc)[XDIG]) {
 }
 
 // One thread per sorted pair; the first of a run writes the edge's endpoints and, for
-// a short run, its weight (w: the weights in the keys' order).  Longer runs get
-// bounds and go to lists for k_merge_long and k_merge_big.  total: the edges.
-__global__ void k_merge_runs(int64_t count, PairCode code, const unsigned long long *__restrict__ key,
+// a short run, its weight (w: the weights in the keys' order), which the wave's lanes
+// sum together.  Longer runs get bounds and go to lists for k_merge_long and
+// k_merge_big, the first by way of LDS (a reservation per wave, on one address, was
+// most of the 570 us that merging a coarse graph's 16M pairs in runs of all
+// lengths took; 200 us here).  total: the edges.
+constexpr int MERGE_STAGE = 1024;        // staged long runs
+constexpr int MERGE_ROUNDS = 32;         // steps between flushes: at most IBLOCK / (MERGE_SHORT + 1) + 1 start in each
+static_assert(MERGE_ROUNDS * (IBLOCK / ((int)MERGE_SHORT + 1) + 2) <= MERGE_STAGE, "the stage holds every round's runs");
+
+__global__ __launch_bounds__(IBLOCK) void k_merge_runs(int64_t count, PairCode code, const unsigned long long *__restrict__ key,
                              const uint32_t *__restrict__ edge_of, const float *__restrict__ w,
                              int32_t *__restrict__ ea, int32_t *__restrict__ eb, float *__restrict__ ew,
                              uint2 *__restrict__ bounds, uint32_t *__restrict__ long_list,
@@ -198,6 +205,22 @@ __global__ void k_merge_runs(int64_t count, PairCode code, const unsigned long l
     // lane reaches the wave-wide append
     const int64_t stride = (int64_t)gridDim.x * blockDim.x;
     const int64_t n_pad = ceil_div_dev(count, stride) * stride;
+    const int lane = threadIdx.x & (WAVE - 1);
+    __shared__ uint32_t stage[MERGE_STAGE];
+    __shared__ unsigned int n_stage, base_s;
+    if (threadIdx.x == 0) n_stage = 0u;
+    __syncthreads();
+    auto flush = [&] {                   // by the whole workgroup
+        __syncthreads();
+        const unsigned int ns = n_stage;
+        if (threadIdx.x == 0 && ns) base_s = atomicAdd(long_count, ns);
+        __syncthreads();
+        for (unsigned int i = threadIdx.x; i < ns; i += IBLOCK) long_list[base_s + i] = stage[i];
+        __syncthreads();
+        if (threadIdx.x == 0) n_stage = 0u;
+        __syncthreads();
+    };
+    int round = 0;
     for (int64_t q = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; q < n_pad; q += stride) {
         bool defer = false, big = false;
         uint32_t e = 0;
@@ -209,24 +232,93 @@ __global__ void k_merge_runs(int64_t count, PairCode code, const unsigned long l
             ea[e] = pair_lo(code, k);
             eb[e] = pair_hi(code, k);
         }
+        // the run's end: the wave's next run, or for the last run of the wave a
+        // search by all its lanes (64 keys on, then 64 probes at a time)
+        const int64_t base = q - lane;
+        const unsigned long long starts = __ballot(q >= count || q == 0 || key[q - 1] != k);
+        const unsigned long long heads = __ballot(first);
+        const unsigned long long after = lane == WAVE - 1 ? 0ull : starts >> (lane + 1);
+        const int stop = after ? lane + __ffsll((long long)after) : WAVE;   // first lane past this one's run
+        int64_t end = base + stop;
+        const int tail = heads ? 63 - __clzll((long long)heads) : -1;    // its run passes the wave's end unless `after`
+        if (w && tail >= 0 && (tail == WAVE - 1 || !(starts >> (tail + 1)))) {
+            const unsigned long long kt = __shfl(k, tail, WAVE);
+            int64_t at = base + WAVE;                                    // key[at - 1] == kt throughout
+            unsigned long long past = __ballot(at + lane >= count || key[min(at + lane, count - 1)] != kt);
+            if (past) {
+                at += __ffsll((long long)past) - 1;
+            } else {
+                at += WAVE;
+                int64_t top = count;                                     // the end is at most top
+                while (at < top) {
+                    const int64_t step = ceil_div_dev(top - at, WAVE), p = at + lane * step;
+                    past = __ballot(p >= top || key[p] != kt);
+                    if (past & 1ull) break;
+                    const int f = past ? __ffsll((long long)past) - 1 : WAVE;
+                    top = min(top, at + f * step);
+                    at += (f - 1) * step + 1;
+                }
+            }
+            if (lane == tail) end = at;
+        }
+        // span and sum of every short run at its first lane: its lanes' values by
+        // doubling, and the lanes past the wave's end for the last one
+        float x = 0.0f;
+        int lo = 1 << 20, hi = -1;
+        double sum = 0.0;
+        if (w) {
+            uint32_t mant;
+            int shift;
+            if (q < count) {
+                x = w[q];
+                f32_split(x, mant, shift);
+                lo = shift;
+                hi = shift + 24;
+                sum = (double)x;
+            }
+            static_assert(MERGE_SHORT == 16, "four doublings and 16 lanes cover a short run");
+#pragma unroll
+            for (int o = 1; o < (int)MERGE_SHORT; o <<= 1) {
+                const int lo_o = __shfl_down(lo, o, WAVE), hi_o = __shfl_down(hi, o, WAVE);
+                const double sum_o = __shfl_down(sum, o, WAVE);
+                if (lane + o < stop) {
+                    lo = min(lo, lo_o);
+                    hi = max(hi, hi_o);
+                    sum += sum_o;
+                }
+            }
+            const int64_t tail_q = base + tail, tail_end = tail >= 0 ? __shfl(end, tail, WAVE) : 0;
+            if (tail >= 0 && tail_end > base + WAVE && tail_end - tail_q <= (int64_t)MERGE_SHORT) {
+                int lo2 = 1 << 20, hi2 = -1;
+                double sum2 = 0.0;
+                if (base + WAVE + lane < tail_end) {
+                    const float y = w[base + WAVE + lane];
+                    f32_split(y, mant, shift);
+                    lo2 = shift;
+                    hi2 = shift + 24;
+                    sum2 = (double)y;
+                }
+#pragma unroll
+                for (int o = (int)MERGE_SHORT / 2; o >= 1; o >>= 1) {
+                    lo2 = min(lo2, __shfl_xor(lo2, o, WAVE));
+                    hi2 = max(hi2, __shfl_xor(hi2, o, WAVE));
+                    sum2 += __shfl_xor(sum2, o, WAVE);
+                }
+                lo2 = __shfl(lo2, 0, WAVE);
+                hi2 = __shfl(hi2, 0, WAVE);
+                sum2 = __shfl(sum2, 0, WAVE);
+                if (lane == tail) {
+                    lo = min(lo, lo2);
+                    hi = max(hi, hi2);
+                    sum += sum2;
+                }
+            }
+        }
         if (first && w) {
-            int64_t end = q + 1;
-            while (end < count && end - q <= (int64_t)MERGE_SHORT && key[end] == k) ++end;
             const uint32_t len = (uint32_t)(end - q);
             if (len == 1) {
-                ew[e] = w[q];
+                ew[e] = x;
             } else if (len <= MERGE_SHORT) {
-                int lo = 1 << 20, hi = -1;
-                double sum = 0.0;
-                for (int64_t r = q; r < end; ++r) {
-                    const float x = w[r];
-                    uint32_t mant;
-                    int shift;
-                    f32_split(x, mant, shift);
-                    lo = min(lo, shift);
-                    hi = max(hi, shift + 24);
-                    sum += (double)x;
-                }
                 if (hi + ceil_log2_u32(len) - lo <= 53) {
                     ew[e] = (float)sum;
                 } else {
@@ -235,24 +327,22 @@ __global__ void k_merge_runs(int64_t count, PairCode code, const unsigned long l
                     ew[e] = digits_round(acc);
                 }
             } else {
-                int64_t past = count;                        // first key above k in (end, count]
-                while (end < past) {
-                    const int64_t mid = (end + past) >> 1;
-                    if (key[mid] > k) past = mid;
-                    else end = mid + 1;
-                }
-                bounds[e] = make_uint2((uint32_t)q, (uint32_t)past);
+                bounds[e] = make_uint2((uint32_t)q, (uint32_t)end);
                 defer = true;
-                big = past - q > (int64_t)MERGE_WAVE;
+                big = len > MERGE_WAVE;
             }
         }
-        const bool to_long = defer && !big, to_big = defer && big;
-        if (!__any(defer)) continue;
-        const unsigned int at = wave_append(to_long, long_count);
-        if (to_long) long_list[at] = e;
-        const unsigned int bt = wave_append(to_big, big_count);
-        if (to_big) big_list[bt] = e;
+        if (defer && !big) stage[atomicAdd(&n_stage, 1u)] = e;
+        if (__any(big)) {
+            const unsigned int bt = wave_append(big, big_count);
+            if (big) big_list[bt] = e;
+        }
+        if (++round == MERGE_ROUNDS) {   // uniform: every thread takes as many steps
+            flush();
+            round = 0;
+        }
     }
+    flush();
 }
 
 // One wave per run of MERGE_SHORT < length <= MERGE_WAVE: every lane sums
@@ -865,7 +955,7 @@ static ad_status ingest_impl(int64_t n, int64_t m_in, const int32_t *u, const in
         uint2 *bounds = reinterpret_cast<uint2 *>(L.key0);
         uint32_t *big_list = reinterpret_cast<uint32_t *>(L.ew2);
         const float *ws = w ? L.w_sorted : nullptr;
-        hipLaunchKernelGGL(k_merge_runs, dim3(igrid(m_in)), dim3(IBLOCK), 0, st, m_in, code, L.key1, L.edge_of, ws,
+        hipLaunchKernelGGL(k_merge_runs, dim3(std::min<unsigned>(2048, igrid(m_in))), dim3(IBLOCK), 0, st, m_in, code, L.key1, L.edge_of, ws,
                            L.ea, L.eb, L.ew, bounds, L.list, L.flags + 3, big_list, L.flags + 2, L.flags + 4);
         AD_LAUNCH_CHECK("k_merge_runs");
         if (w) {

@@ -409,3 +409,55 @@ def test_fit_at_extreme_ranks(api, kind, target):
         e_o, keep_o, kept_o = oracle.fit_exponent(g, rho.astype(np.float64), o, target)
         assert e == e_o and int(_np(n_kept)[0]) == kept_o
         np.testing.assert_array_equal(_np(keep), keep_o)
+
+
+# --------------------------------------------------- merging and coarsening --
+
+@pytest.mark.parametrize("spread", [1.0, 1e30])
+def test_merged_runs_across_waves(api, spread):
+    """Runs of 1 to 40 listed copies of a pair, so that runs of every length up to and past
+    the short ones start at every lane and cross waves and workgroups; with the large
+    spread most sums need the exact digits.  Weights equal the oracle's."""
+    announce(f"merged runs spread={spread}")
+    rng = np.random.default_rng(3)
+    lens = np.concatenate([np.arange(1, 41), rng.integers(1, 41, 4000)])
+    n = 3000
+    key = np.sort(rng.choice(n * n, size=3 * lens.size, replace=False))
+    key = key[key // n < key % n][:lens.size]
+    u, v = np.repeat(key // n, lens[:key.size]), np.repeat(key % n, lens[:key.size])
+    w = np.exp(rng.uniform(-np.log(spread), np.log(spread), u.size) + rng.normal(size=u.size)).astype(np.float32)
+    p = rng.permutation(u.size)
+    u, v, w = u[p].astype(np.int32), v[p].astype(np.int32), w[p]
+    cu = lambda a: torch.from_numpy(np.ascontiguousarray(a)).cuda()
+    dg = api.ingest(n, cu(u), cu(v), cu(w), by_degree=False)
+    row_ptr, col, we, eid, orig, m, dropped = oracle.ingest(n, u, v, w, order=0)
+    assert dg.m == m
+    np.testing.assert_array_equal(_np(dg.col), col)
+    np.testing.assert_array_equal(_np(dg.w), we)
+
+
+@pytest.mark.parametrize("prec", ["f32", "f64"])
+@pytest.mark.parametrize("edge", [15, 63, 255, 2047])
+def test_coarsening_at_row_classes(api, edge, prec):
+    """Rows of edge .. edge + 3 entries around the lengths where a row goes from
+    one step to several, from 16 lanes to a wave and from a wave to a workgroup,
+    with distances in steps so that ties occur.  Seeds and aggregates equal the oracle's."""
+    announce(f"coarsening rows of {edge} {prec}")
+    rng = np.random.default_rng(edge)
+    n = max(400, 2 * edge)
+    us, vs = [np.arange(8, n - 1)], [np.arange(9, n)]
+    for h, d in enumerate((edge, edge + 1, edge + 2, edge + 3)):
+        us.append(np.full(d, h))
+        vs.append(rng.choice(np.arange(8, n), size=d, replace=False))
+    u, v = np.concatenate(us), np.concatenate(vs)
+    g = G.relabel(G.from_edges(n, u, v), rng.permutation(n)) if edge == 63 else G.from_edges(n, u, v)
+    rho = rng.integers(1, 40, g.m) / 64.0
+    rho = rho.astype(np.float32 if prec == "f32" else np.float64)
+    dg = api.DeviceGraph.from_host(g, "cuda")
+    for theta in (0.3, 0.9):
+        agg, is_seed, nc = api.ml_aggregate(dg, torch.from_numpy(rho).cuda(), 1e-12, theta)
+        seeds_o = oracle.ml_seeds(g, rho.astype(np.float64), 1e-12, theta)
+        agg_o, nc_o = oracle.ml_aggregates(g, rho.astype(np.float64), seeds_o, 1e-12)
+        assert nc == nc_o
+        np.testing.assert_array_equal(_np(is_seed), seeds_o)
+        np.testing.assert_array_equal(_np(agg), agg_o)
