@@ -90,72 +90,212 @@ struct __align__(16) MlVert {
     int32_t key;
 };
 
-template <typename Tr>
-__global__ __launch_bounds__(MBLOCK) void k_ml_smax(int64_t n, const int64_t *__restrict__ row_ptr,
-                                                     const int32_t *__restrict__ eid,
-                                                     const int32_t *__restrict__ orig_id, const Tr *__restrict__ rho,
-                                                     double eps, double theta, MlVert *__restrict__ vert) {
-    const int lane = threadIdx.x & (WAVE - 1);
-    const int64_t nw = (int64_t)gridDim.x * (MBLOCK / WAVE);
-    for (int64_t i = (int64_t)blockIdx.x * (MBLOCK / WAVE) + (threadIdx.x >> 6); i < n; i += nw) {
-        const int64_t b0 = row_ptr[i], b1 = row_ptr[i + 1];
-        double mx = 0.0;
-        for (int64_t p = b0 + lane; p < b1; p += WAVE) mx = fmax(mx, ml_strength(rho[eid[p]], eps));
-        for (int o = WAVE / 2; o >= 1; o >>= 1) mx = fmax(mx, __shfl_xor(mx, o, WAVE));
-        if (lane == 0) vert[i] = MlVert{theta * mx, (uint32_t)(b1 - b0), orig_id ? orig_id[i] : (int32_t)i};
+// Rows dealt to the passes over whole rows below: 16 lanes a row, four rows to a
+// wave, rows longer than ML_LONG then by the whole wave, and the listed rows longer than
+// ML_HUB by the first hub_blocks workgroups, one each; ML_U entries per lane in
+// flight.  Wave gw takes rows gw + k nw (the high-degree rows, stored first, spread over
+// the waves).  K: bool begin(i, sub) (whether the row's entries are wanted),
+// chunk(i, q0, b1, sub, T, shift) for entries q0 .. q0 + ML_U T - 1 below b1 (lane
+// `sub` of T takes q0 + u T + sub; shift: the team's first lane), end(i, b0, b1, sub, T),
+// and for a workgroup's row share(wave, lane) (this wave's part into LDS) and, past a barrier
+// and on one wave, gather() (all parts) before end.  Bound by the gathers and, on coarse
+// graphs, by the longest rows.  A wave per row of any length with one entry per lane in
+// flight and rho read through eid in three passes took, in sparsify_multilevel at
+// n = 2^20, m = 16M, levels 0 / 1 / 2: k_ml_smax 367 / 502 / 730 us, k_ml_strong with the
+// lists of vertices ahead by passes of their own 870 / 1050 / 1220, k_ml_aggregate
+// 534 / 715 / 1070, k_ml_pairs 395 / 730 / 1170; 335 / 310 / 190, 340 / 296 / 210,
+// 288 / 248 / 196 and 278 / 245 / 213 here.
+constexpr int ML_TEAM = 16;
+constexpr int ML_U = 4;
+constexpr int64_t ML_LONG = 256, ML_HUB = 2048;
+constexpr int ML_WAVES = MBLOCK / WAVE;
+static unsigned mrgrid(int64_t rows) {
+    return (unsigned)std::max<int64_t>(1, std::min<int64_t>(4096, ceil_div(rows, MBLOCK / ML_TEAM)));
+}
+
+struct MlHubs {
+    const int32_t *list = nullptr;        // rows longer than ML_HUB (NULL: there are none)
+    const unsigned int *count = nullptr;
+    unsigned int blocks = 0;
+};
+
+template <typename K>
+__device__ __forceinline__ void ml_rows(int64_t n, const int64_t *__restrict__ row_ptr, MlHubs hubs, K &k) {
+    constexpr int TEAMS = WAVE / ML_TEAM;
+    const int lane = threadIdx.x & (WAVE - 1), wave = threadIdx.x >> 6;
+    if (blockIdx.x < hubs.blocks) {
+        const unsigned int nh = *hubs.count;
+        for (unsigned int h = blockIdx.x; h < nh; h += hubs.blocks) {
+            const int64_t i = hubs.list[h];
+            const int64_t b0 = row_ptr[i], b1 = row_ptr[i + 1];
+            if (!k.begin(i, (int)threadIdx.x)) continue;             // uniform over the workgroup
+            k.hub_begin();
+            for (int64_t q0 = b0 + (int64_t)wave * ML_U * WAVE; q0 < b1; q0 += (int64_t)ML_WAVES * ML_U * WAVE)
+                k.chunk(i, q0, b1, lane, WAVE, 0);
+            k.share(wave, lane);
+            __syncthreads();
+            if (wave == 0) {
+                k.gather();
+                k.end(i, b0, b1, lane, WAVE);
+            }
+            __syncthreads();                                         // the parts are read
+        }
+        return;
+    }
+    const int team = lane / ML_TEAM, sub = lane % ML_TEAM;
+    const int64_t nw = (int64_t)(gridDim.x - hubs.blocks) * ML_WAVES;
+    const int64_t gw = (int64_t)(blockIdx.x - hubs.blocks) * ML_WAVES + wave;
+    const int64_t longest = hubs.blocks ? ML_HUB : ((int64_t)1 << 62);
+    for (int64_t r0 = gw; r0 < n; r0 += TEAMS * nw) {
+        const int64_t i = r0 + team * nw;
+        int64_t b0 = 0, b1 = 0;
+        if (i < n) {
+            b0 = row_ptr[i];
+            b1 = row_ptr[i + 1];
+        }
+        const bool is_long = b1 - b0 > ML_LONG;
+        if (i < n && !is_long) {
+            if (k.begin(i, sub)) {
+                for (int64_t q0 = b0; q0 < b1; q0 += ML_U * ML_TEAM) k.chunk(i, q0, b1, sub, ML_TEAM, lane - sub);
+                k.end(i, b0, b1, sub, ML_TEAM);
+            }
+        }
+        unsigned long long todo = __ballot(is_long && b1 - b0 <= longest && sub == 0);
+        while (todo) {
+            const int s = __ffsll((long long)todo) - 1;
+            todo &= todo - 1;
+            const int64_t il = r0 + (s / ML_TEAM) * nw;
+            const int64_t c0 = __shfl(b0, s, WAVE), c1 = __shfl(b1, s, WAVE);
+            if (k.begin(il, lane)) {
+                for (int64_t q0 = c0; q0 < c1; q0 += ML_U * WAVE) k.chunk(il, q0, c1, lane, WAVE, 0);
+                k.end(il, c0, c1, lane, WAVE);
+            }
+        }
     }
 }
 
-// Coupling of every stored entry (i, j): 0 not strong, 1 strong with j
-// after i in the traversal, 2 strong with j ahead of i; acnt[i] = the number
-// of entries of row i coupled strongly to a vertex ahead.
+// Every vertex's largest strength, and rho in entry order for the passes after it.
+template <typename Tr>
+struct MlSmax {
+    const int32_t *eid, *orig_id;
+    const Tr *rho;
+    Tr *rho_ent;
+    double eps, theta;
+    MlVert *vert;
+    double mx;
+    double *part;                         // LDS, [ML_WAVES]
+    __device__ bool begin(int64_t, int) {
+        mx = 0.0;
+        return true;
+    }
+    __device__ void hub_begin() {}
+    __device__ void share(int wave, int lane) {
+        for (int o = WAVE / 2; o >= 1; o >>= 1) mx = fmax(mx, __shfl_xor(mx, o, WAVE));
+        if (lane == 0) part[wave] = mx;
+    }
+    __device__ void gather() {
+        for (int w = 0; w < ML_WAVES; ++w) mx = fmax(mx, part[w]);
+    }
+    __device__ void chunk(int64_t, int64_t q0, int64_t b1, int sub, int T, int) {
+        int32_t e[ML_U];
+        Tr r[ML_U];
+#pragma unroll
+        for (int u = 0; u < ML_U; ++u) e[u] = q0 + u * T + sub < b1 ? eid[q0 + u * T + sub] : -1;
+#pragma unroll
+        for (int u = 0; u < ML_U; ++u) r[u] = e[u] >= 0 ? rho[e[u]] : (Tr)0;
+#pragma unroll
+        for (int u = 0; u < ML_U; ++u) {
+            if (e[u] < 0) continue;
+            rho_ent[q0 + u * T + sub] = r[u];
+            mx = fmax(mx, ml_strength(r[u], eps));
+        }
+    }
+    __device__ void end(int64_t i, int64_t b0, int64_t b1, int sub, int T) {
+        for (int o = T / 2; o >= 1; o >>= 1) mx = fmax(mx, __shfl_xor(mx, o, WAVE));
+        if (sub == 0) vert[i] = MlVert{theta * mx, (uint32_t)(b1 - b0), orig_id ? orig_id[i] : (int32_t)i};
+    }
+};
+
+template <typename Tr>
+__global__ __launch_bounds__(MBLOCK) void k_ml_smax(int64_t n, const int64_t *__restrict__ row_ptr, MlHubs hubs,
+                                                    MlSmax<Tr> k) {
+    __shared__ double part[ML_WAVES];
+    k.part = part;
+    ml_rows(n, row_ptr, hubs, k);
+}
+
+// The strongly coupled neighbours ahead of each vertex, in any order: alist from
+// row_ptr[i] on, acnt[i] of them.
+template <typename Tr>
+struct MlStrong {
+    const int32_t *col;
+    const Tr *rho_ent;
+    double eps;
+    const MlVert *vert;
+    int32_t *alist;
+    uint32_t *acnt;
+    const int64_t *row_ptr;
+    unsigned int *taken;                  // LDS: places handed out of a workgroup's row
+    MlVert vi;
+    int64_t out;
+    bool hub;
+    __device__ bool begin(int64_t i, int) {
+        vi = vert[i];
+        out = row_ptr[i];
+        hub = false;
+        return true;
+    }
+    __device__ void hub_begin() {
+        hub = true;
+        if (threadIdx.x == 0) *taken = 0u;
+        __syncthreads();
+    }
+    __device__ void share(int, int) {}
+    __device__ void gather() { out += *taken; }
+    __device__ void chunk(int64_t, int64_t q0, int64_t b1, int sub, int T, int shift) {
+        int32_t j[ML_U];
+        Tr r[ML_U];
+        MlVert vj[ML_U];
+#pragma unroll
+        for (int u = 0; u < ML_U; ++u) {
+            const bool ok = q0 + u * T + sub < b1;
+            j[u] = ok ? col[q0 + u * T + sub] : -1;
+            r[u] = ok ? rho_ent[q0 + u * T + sub] : (Tr)0;
+        }
+#pragma unroll
+        for (int u = 0; u < ML_U; ++u)
+            if (j[u] >= 0) vj[u] = vert[j[u]];
+        const unsigned long long mine = T == WAVE ? ~0ull : 0xffffull;
+#pragma unroll
+        for (int u = 0; u < ML_U; ++u) {
+            bool ahead = false;
+            if (j[u] >= 0) {
+                const double d = ml_strength(r[u], eps);
+                ahead = (d >= vi.tsmax || d >= vj[u].tsmax) && ml_ahead(vi.deg, vi.key, vj[u].deg, vj[u].key);
+            }
+            const unsigned long long m = (__ballot(ahead) >> shift) & mine;
+            int64_t at = out;
+            if (hub) {                                               // uniform over the workgroup
+                unsigned int t = 0;
+                if (sub == 0 && m) t = atomicAdd(taken, (unsigned int)__popcll(m));
+                at += __shfl(t, 0, WAVE);
+            } else {
+                out += __popcll(m);
+            }
+            if (ahead) alist[at + __popcll(m & ((1ull << sub) - 1ull))] = j[u];
+        }
+    }
+    __device__ void end(int64_t i, int64_t b0, int64_t, int sub, int) {
+        if (sub == 0) acnt[i] = (uint32_t)(out - b0);
+    }
+};
+
 template <typename Tr>
 __global__ __launch_bounds__(MBLOCK) void k_ml_strong(int64_t n, const int64_t *__restrict__ row_ptr,
-                                                      const int32_t *__restrict__ col, const int32_t *__restrict__ eid,
-                                                      const Tr *__restrict__ rho, double eps,
-                                                      const MlVert *__restrict__ vert,
-                                                      uint8_t *__restrict__ sflag, uint32_t *__restrict__ acnt) {
-    const int lane = threadIdx.x & (WAVE - 1);
-    const int64_t nw = (int64_t)gridDim.x * (MBLOCK / WAVE);
-    for (int64_t i = (int64_t)blockIdx.x * (MBLOCK / WAVE) + (threadIdx.x >> 6); i < n; i += nw) {
-        const int64_t b0 = row_ptr[i], b1 = row_ptr[i + 1];
-        const MlVert vi = vert[i];
-        int ahead = 0;
-        for (int64_t p = b0 + lane; p < b1; p += WAVE) {
-            const int32_t j = col[p];
-            const double d = ml_strength(rho[eid[p]], eps);
-            const MlVert vj = vert[j];
-            uint8_t f = 0;
-            if (d >= vi.tsmax || d >= vj.tsmax) f = ml_ahead(vi.deg, vi.key, vj.deg, vj.key) ? 2 : 1;
-            sflag[p] = f;
-            ahead += f == 2;
-        }
-        for (int o = WAVE / 2; o >= 1; o >>= 1) ahead += __shfl_xor(ahead, o, WAVE);
-        if (lane == 0) acnt[i] = (uint32_t)ahead;
-    }
-}
-
-// The strongly coupled neighbours ahead of each vertex, in row order:
-// alist[aoff[i], aoff[i + 1]).
-__global__ __launch_bounds__(MBLOCK) void k_ml_ahead_list(int64_t n, const int64_t *__restrict__ row_ptr,
-                                                          const int32_t *__restrict__ col,
-                                                          const uint8_t *__restrict__ sflag,
-                                                          const uint32_t *__restrict__ aoff,
-                                                          int32_t *__restrict__ alist) {
-    const int lane = threadIdx.x & (WAVE - 1);
-    const int64_t nw = (int64_t)gridDim.x * (MBLOCK / WAVE);
-    const unsigned long long below = (1ull << lane) - 1ull;
-    for (int64_t i = (int64_t)blockIdx.x * (MBLOCK / WAVE) + (threadIdx.x >> 6); i < n; i += nw) {
-        const int64_t b0 = row_ptr[i], b1 = row_ptr[i + 1];
-        uint32_t o = aoff[i];
-        for (int64_t p0 = b0; p0 < b1; p0 += WAVE) {            // the bound is the same for the whole wave
-            const int64_t p = p0 + lane;
-            const bool f2 = p < b1 && sflag[p] == 2;
-            const unsigned long long bal = __ballot(f2);
-            if (f2) alist[o + (uint32_t)__popcll(bal & below)] = col[p];
-            o += (uint32_t)__popcll(bal);
-        }
-    }
+                                                      MlHubs hubs, MlStrong<Tr> k) {
+    __shared__ unsigned int taken;
+    k.taken = &taken;
+    ml_rows(n, row_ptr, hubs, k);
 }
 
 // One round of the seed traversal over the undecided vertices (state 0;
@@ -173,8 +313,10 @@ __global__ __launch_bounds__(MBLOCK) void k_ml_ahead_list(int64_t n, const int64
 // no shorter).
 constexpr uint32_t SEED_LANE_MAX = 32;   // lists up to this length: one lane per vertex, longer: one wave
 constexpr int SEED_LOADS = 8;            // list entries a lane reads per step
+constexpr int SEED_RUN = 8;              // consecutive rows of a wave
 
-__global__ __launch_bounds__(MBLOCK) void k_ml_seed_round(int64_t n, const uint32_t *__restrict__ aoff,
+__global__ __launch_bounds__(MBLOCK) void k_ml_seed_round(int64_t n, const int64_t *__restrict__ aoff,
+                                                          const uint32_t *__restrict__ acnt,
                                                           const int32_t *__restrict__ alist,
                                                           uint8_t *__restrict__ state,
                                                           uint32_t *__restrict__ resume,
@@ -182,19 +324,19 @@ __global__ __launch_bounds__(MBLOCK) void k_ml_seed_round(int64_t n, const uint3
     const int lane = threadIdx.x & (WAVE - 1);
     const int64_t nw = (int64_t)gridDim.x * (MBLOCK / WAVE);
     unsigned long long waiting = 0;
-    // wave gw owns rows gw + k nw (the high-degree rows, stored first, spread
-    // over the waves), 64 at a time: short lists by their own lane, then
+    // wave gw owns runs of SEED_RUN rows gw + k nw (the high-degree rows, stored first,
+    // spread over the waves; single rows spread so cost a request per row
+    // and array), 64 rows at a time: short lists by their own lane, then
     // long ones by the whole wave, one at a time
     const int64_t gw = (int64_t)blockIdx.x * (MBLOCK / WAVE) + (threadIdx.x >> 6);
-    for (int64_t base = gw; base < n; base += nw * WAVE) {
-        const int64_t mine = base + (int64_t)lane * nw;
-        // the row's state (only this wave writes its rows' states), list
-        // bounds and resume point, loaded together
-        const bool in = mine < n;
-        const uint8_t own = in ? state[mine] : (uint8_t)1;
-        const uint32_t a = in ? aoff[mine] : 0u, len = in ? aoff[mine + 1] - a : 0u;
-        const uint32_t from = in ? resume[mine] : 0u;
-        const bool undecided = own == 0;
+    const int64_t nruns = ceil_div_dev(n, SEED_RUN);
+    for (int64_t base = gw; base < nruns; base += nw * (WAVE / SEED_RUN)) {
+        const int64_t mine = (base + (int64_t)(lane / SEED_RUN) * nw) * SEED_RUN + lane % SEED_RUN;
+        // the row's state: only this wave writes its rows' states
+        const bool undecided = mine < n && state[mine] == 0;
+        const int64_t a = undecided ? aoff[mine] : 0;
+        const uint32_t len = undecided ? acnt[mine] : 0u;
+        const uint32_t from = undecided ? resume[mine] : 0u;
         if (undecided && len <= SEED_LANE_MAX) {
             bool seed_nb = false;
             uint32_t wait_at = len;
@@ -226,8 +368,9 @@ __global__ __launch_bounds__(MBLOCK) void k_ml_seed_round(int64_t n, const uint3
         while (todo) {
             const int t = __ffsll((long long)todo) - 1;
             todo &= todo - 1;
-            const int64_t i = base + (int64_t)t * nw;
-            const uint32_t ai = aoff[i], li = aoff[i + 1] - ai;
+            const int64_t i = (base + (int64_t)(t / SEED_RUN) * nw) * SEED_RUN + t % SEED_RUN;
+            const int64_t ai = aoff[i];
+            const uint32_t li = acnt[i];
             bool seed_nb = false;
             uint32_t wait_at = li;
             for (uint32_t q = resume[i] + (uint32_t)lane; q < li; q += WAVE) {
@@ -277,65 +420,131 @@ __global__ void k_ml_degree_max(int64_t n, const int64_t *__restrict__ row_ptr, 
 // Aggregates (Eq. P): a seed's own rank; otherwise the rank of the seed
 // neighbour of largest strength, ties by smaller name (-1 if none).
 template <typename Tr>
-__global__ __launch_bounds__(MBLOCK) void k_ml_aggregate(int64_t n, const int64_t *__restrict__ row_ptr,
-                                                         const int32_t *__restrict__ col,
-                                                         const int32_t *__restrict__ eid,
-                                                         const int32_t *__restrict__ orig_id,
-                                                         const Tr *__restrict__ rho, double eps,
-                                                         const uint8_t *__restrict__ state,
-                                                         const uint32_t *__restrict__ rank, int32_t *__restrict__ agg) {
-    const int lane = threadIdx.x & (WAVE - 1);
-    const int64_t nw = (int64_t)gridDim.x * (MBLOCK / WAVE);
-    for (int64_t i = (int64_t)blockIdx.x * (MBLOCK / WAVE) + (threadIdx.x >> 6); i < n; i += nw) {
-        if (state[i] == 1) {
-            if (lane == 0) agg[i] = (int32_t)rank[i];
-            continue;
+struct MlAggregate {
+    const int32_t *col, *orig_id;
+    const Tr *rho_ent;
+    double eps;
+    const uint8_t *state;
+    const uint32_t *rank;
+    int32_t *agg;
+    double bd;
+    int32_t bk, bj;
+    struct Best {
+        double d;
+        int32_t k, j;
+    };
+    Best *part;                           // LDS, [ML_WAVES]
+    __device__ void take(double od, int32_t ok, int32_t oj) {
+        if (od > bd || (od == bd && ok < bk)) {
+            bd = od;
+            bk = ok;
+            bj = oj;
         }
-        double bd = -1.0;
-        int32_t bk = 0x7fffffff, bj = -1;
-        for (int64_t p = row_ptr[i] + lane; p < row_ptr[i + 1]; p += WAVE) {
-            const int32_t j = col[p];
-            if (state[j] != 1) continue;
-            const double d = ml_strength(rho[eid[p]], eps);
-            const int32_t k = orig_id ? orig_id[j] : j;
-            if (d > bd || (d == bd && k < bk)) {
-                bd = d;
-                bk = k;
-                bj = j;
-            }
-        }
+    }
+    __device__ void hub_begin() {}
+    __device__ void share(int wave, int lane) {
         for (int o = WAVE / 2; o >= 1; o >>= 1) {
             const double od = __shfl_xor(bd, o, WAVE);
             const int32_t ok = __shfl_xor(bk, o, WAVE), oj = __shfl_xor(bj, o, WAVE);
-            if (od > bd || (od == bd && ok < bk)) {
-                bd = od;
-                bk = ok;
-                bj = oj;
+            take(od, ok, oj);
+        }
+        if (lane == 0) part[wave] = Best{bd, bk, bj};
+    }
+    __device__ void gather() {
+        for (int w = 0; w < ML_WAVES; ++w) take(part[w].d, part[w].k, part[w].j);
+    }
+    __device__ bool begin(int64_t i, int sub) {
+        bd = -1.0;
+        bk = 0x7fffffff;
+        bj = -1;
+        if (state[i] != 1) return true;
+        if (sub == 0) agg[i] = (int32_t)rank[i];
+        return false;
+    }
+    __device__ void chunk(int64_t, int64_t q0, int64_t b1, int sub, int T, int) {
+        int32_t j[ML_U];
+        Tr r[ML_U];
+        uint8_t sj[ML_U];
+#pragma unroll
+        for (int u = 0; u < ML_U; ++u) {
+            const bool ok = q0 + u * T + sub < b1;
+            j[u] = ok ? col[q0 + u * T + sub] : -1;
+            r[u] = ok ? rho_ent[q0 + u * T + sub] : (Tr)0;
+        }
+#pragma unroll
+        for (int u = 0; u < ML_U; ++u) sj[u] = j[u] >= 0 ? state[j[u]] : (uint8_t)0;
+#pragma unroll
+        for (int u = 0; u < ML_U; ++u) {
+            if (sj[u] != 1) continue;
+            const double d = ml_strength(r[u], eps);
+            if (d < bd) continue;
+            const int32_t k = orig_id ? orig_id[j[u]] : j[u];
+            if (d > bd || k < bk) {
+                bd = d;
+                bk = k;
+                bj = j[u];
             }
         }
-        if (lane == 0) agg[i] = bj >= 0 ? (int32_t)rank[bj] : -1;
     }
+    __device__ void end(int64_t i, int64_t, int64_t, int sub, int T) {
+        for (int o = T / 2; o >= 1; o >>= 1) {
+            const double od = __shfl_xor(bd, o, WAVE);
+            const int32_t ok = __shfl_xor(bk, o, WAVE), oj = __shfl_xor(bj, o, WAVE);
+            take(od, ok, oj);
+        }
+        if (sub == 0) agg[i] = bj >= 0 ? (int32_t)rank[bj] : -1;
+    }
+};
+
+template <typename Tr>
+__global__ __launch_bounds__(MBLOCK) void k_ml_aggregate(int64_t n, const int64_t *__restrict__ row_ptr,
+                                                         MlHubs hubs, MlAggregate<Tr> k) {
+    __shared__ typename MlAggregate<Tr>::Best part[ML_WAVES];
+    k.part = part;
+    ml_rows(n, row_ptr, hubs, k);
 }
 
 // The fine edges' aggregate pairs (edge id order) and weights (1 when unweighted).
-__global__ __launch_bounds__(MBLOCK) void k_ml_pairs(int64_t n, const int64_t *__restrict__ row_ptr,
-                                                     const int32_t *__restrict__ col, const float *__restrict__ w,
-                                                     const int32_t *__restrict__ eid, const int32_t *__restrict__ agg,
-                                                     int32_t *__restrict__ cu, int32_t *__restrict__ cv,
-                                                     float *__restrict__ cw) {
-    const int lane = threadIdx.x & (WAVE - 1);
-    const int64_t nw = (int64_t)gridDim.x * (MBLOCK / WAVE);
-    for (int64_t i = (int64_t)blockIdx.x * (MBLOCK / WAVE) + (threadIdx.x >> 6); i < n; i += nw) {
-        const int32_t ai = agg[i];
-        for (int64_t p = row_ptr[i] + lane; p < row_ptr[i + 1]; p += WAVE) {
-            const int32_t j = col[p];
-            if (j <= i) continue;
-            const int32_t e = eid[p];
-            cu[e] = ai;
-            cv[e] = agg[j];
-            cw[e] = w ? w[p] : 1.0f;
+struct MlPairs {
+    const int32_t *col;
+    const float *w;
+    const int32_t *eid, *agg;
+    int32_t *cu, *cv;
+    float *cw;
+    int32_t ai;
+    __device__ void hub_begin() {}
+    __device__ void share(int, int) {}
+    __device__ void gather() {}
+    __device__ bool begin(int64_t i, int) {
+        ai = agg[i];
+        return true;
+    }
+    __device__ void chunk(int64_t i, int64_t q0, int64_t b1, int sub, int T, int) {
+        int32_t j[ML_U], e[ML_U], aj[ML_U];
+        float ww[ML_U];
+#pragma unroll
+        for (int u = 0; u < ML_U; ++u) j[u] = q0 + u * T + sub < b1 ? col[q0 + u * T + sub] : -1;
+#pragma unroll
+        for (int u = 0; u < ML_U; ++u) {
+            const bool up = j[u] > i;
+            e[u] = up ? eid[q0 + u * T + sub] : -1;
+            ww[u] = up && w ? w[q0 + u * T + sub] : 1.0f;
+            aj[u] = up ? agg[j[u]] : 0;
+        }
+#pragma unroll
+        for (int u = 0; u < ML_U; ++u) {
+            if (e[u] < 0) continue;
+            cu[e[u]] = ai;
+            cv[e[u]] = aj[u];
+            cw[e[u]] = ww[u];
         }
     }
+    __device__ void end(int64_t, int64_t, int64_t, int, int) {}
+};
+
+__global__ __launch_bounds__(MBLOCK) void k_ml_pairs(int64_t n, const int64_t *__restrict__ row_ptr, MlHubs hubs,
+                                                     MlPairs k) {
+    ml_rows(n, row_ptr, hubs, k);
 }
 
 __global__ void k_ml_names(int64_t n, const uint8_t *__restrict__ state, const int32_t *__restrict__ agg,
@@ -344,7 +553,10 @@ __global__ void k_ml_names(int64_t n, const uint8_t *__restrict__ state, const i
         if (state[i] == 1) names[agg[i]] = orig_id ? orig_id[i] : (int32_t)i;
 }
 
-// Inherited state of every fine edge from the coarse keep.
+// Inherited state of every fine edge from the coarse keep.  Consecutive edges start
+// at one fine vertex, so their searches are in one coarse row and share its
+// lines (in the row of the smaller of the two ids 813 and 1,350 us for the two
+// largest levels of n = 2^20, m = 16M; 517 and 472 here; in the shorter one 990 and 1,700).
 __global__ void k_ml_inherit(int64_t m, const int32_t *__restrict__ cu, const int32_t *__restrict__ cv,
                              const int64_t *__restrict__ crp, const int32_t *__restrict__ ccol,
                              const int32_t *__restrict__ ceid, const uint8_t *__restrict__ ckeep,
@@ -355,8 +567,8 @@ __global__ void k_ml_inherit(int64_t m, const int32_t *__restrict__ cu, const in
             inh[e] = 1;
             continue;
         }
-        const int32_t x = a < b ? a : b, y = a < b ? b : a;
-        int64_t lo = crp[x], hi = crp[x + 1];
+        const int32_t y = b;
+        int64_t lo = crp[a], hi = crp[a + 1];
         const int64_t end = hi;
         while (lo < hi) {
             const int64_t mid = (lo + hi) >> 1;
@@ -391,9 +603,11 @@ struct AggLayout {
     MlVert *vert;                 // [n] theta * largest strength, degree and name of every vertex
     uint8_t *state;               // [n]
     uint32_t *resume;             // [n] where a waiting vertex's next seed round reads its row from
-    uint8_t *sflag;               // [nnz] coupling of every entry
-    uint32_t *aoff;               // [n + 1] offsets of the lists of strongly coupled neighbours ahead
-    int32_t *alist;               // [nnz / 2] those lists (a strong edge is ahead from one end only)
+    uint32_t *acnt;               // [n] strongly coupled neighbours ahead
+    int32_t *alist;               // [nnz] their lists, from row_ptr[i] on
+    double *rho_ent;              // [nnz] distances in entry order (FP32 ones fill half of it)
+    int32_t *hubs;                // [n] rows longer than ML_HUB
+    unsigned int *hub_count;      // [1]
     unsigned int *rank;           // [n] seed flags, scanned in place into aggregate ids
     unsigned int *total;          // [1] number of seeds
     unsigned long long *left;     // [SEED_BATCH] 1 when a vertex is still undecided after a round of a batch
@@ -407,9 +621,11 @@ static size_t agg_layout(int64_t n, int64_t nnz, void *ws, size_t ws_bytes, AggL
     l.vert = c.take<MlVert>(nn);
     l.state = c.take<uint8_t>(nn);
     l.resume = c.take<uint32_t>(nn);
-    l.sflag = c.take<uint8_t>((size_t)std::max<int64_t>(1, nnz));
-    l.aoff = c.take<uint32_t>(nn + 1);
-    l.alist = c.take<int32_t>((size_t)std::max<int64_t>(1, nnz / 2));
+    l.acnt = c.take<uint32_t>(nn);
+    l.alist = c.take<int32_t>((size_t)std::max<int64_t>(1, nnz));
+    l.rho_ent = c.take<double>((size_t)std::max<int64_t>(1, nnz));
+    l.hubs = c.take<int32_t>(nn);
+    l.hub_count = c.take<unsigned int>(1);
     l.rank = c.take<unsigned int>(nn);
     l.total = c.take<unsigned int>(1);
     l.left = c.take<unsigned long long>(SEED_BATCH);
@@ -428,6 +644,17 @@ static ad_status ml_check_ws(void *ws, size_t need, size_t ws_bytes) {
     return AD_OK;
 }
 
+// The hub rows listed in L, for the launches after; none are listed when the graph
+// has none (d_max 0: not known).
+static MlHubs ml_hubs(const ad_graph *g, const AggLayout &L) {
+    MlHubs h;
+    if (g->d_max != 0 && g->d_max <= ML_HUB) return h;
+    h.list = L.hubs;
+    h.count = L.hub_count;
+    h.blocks = (unsigned)std::min<int64_t>(1024, 2 * g->m / (ML_HUB + 1));
+    return h;
+}
+
 // Seeds and aggregates of one coarsening step; *nc_host = number of seeds.
 // Synchronises the stream (the rounds read a count back).
 template <typename Tr>
@@ -436,17 +663,36 @@ static ad_status aggregate_impl(const ad_graph *g, const Tr *rho, double eps, do
     const int64_t n = g->n;
     *nc_host = 0;
     if (n == 0) return AD_OK;
-    hipLaunchKernelGGL(k_ml_smax<Tr>, dim3(mwgrid(n)), dim3(MBLOCK), 0, st, n, g->row_ptr, g->eid, g->orig_id, rho,
-                       eps, theta, L.vert);
+    Tr *rho_ent = reinterpret_cast<Tr *>(L.rho_ent);
+    const MlHubs hubs = ml_hubs(g, L);
+    ad_status s;
+    if (hubs.blocks) {
+        s = fill_i32((int32_t *)L.hub_count, 0, 1, st);
+        if (s != AD_OK) return s;
+        s = collect_rows(g, ML_HUB, (int64_t)1 << 62, L.hubs, L.hub_count, st);
+        if (s != AD_OK) return s;
+    }
+    const dim3 rgrid(mrgrid(n) + hubs.blocks);
+    MlSmax<Tr> ks{};
+    ks.eid = g->eid;
+    ks.orig_id = g->orig_id;
+    ks.rho = rho;
+    ks.rho_ent = rho_ent;
+    ks.eps = eps;
+    ks.theta = theta;
+    ks.vert = L.vert;
+    hipLaunchKernelGGL(k_ml_smax<Tr>, rgrid, dim3(MBLOCK), 0, st, n, g->row_ptr, hubs, ks);
     AD_LAUNCH_CHECK("k_ml_smax");
-    hipLaunchKernelGGL(k_ml_strong<Tr>, dim3(mwgrid(n)), dim3(MBLOCK), 0, st, n, g->row_ptr, g->col, g->eid,
-                       rho, eps, L.vert, L.sflag, L.aoff);
+    MlStrong<Tr> kt{};
+    kt.col = g->col;
+    kt.rho_ent = rho_ent;
+    kt.eps = eps;
+    kt.vert = L.vert;
+    kt.alist = L.alist;
+    kt.acnt = L.acnt;
+    kt.row_ptr = g->row_ptr;
+    hipLaunchKernelGGL(k_ml_strong<Tr>, rgrid, dim3(MBLOCK), 0, st, n, g->row_ptr, hubs, kt);
     AD_LAUNCH_CHECK("k_ml_strong");
-    ad_status s = scan_exclusive(n, L.aoff, nullptr, L.aoff + n, nullptr, L.scan, st);
-    if (s != AD_OK) return s;
-    hipLaunchKernelGGL(k_ml_ahead_list, dim3(mwgrid(n)), dim3(MBLOCK), 0, st, n, g->row_ptr, g->col, L.sflag,
-                       L.aoff, L.alist);
-    AD_LAUNCH_CHECK("k_ml_ahead_list");
     s = fill_u8(L.state, 0, n, st);
     if (s != AD_OK) return s;
     s = fill_i32((int32_t *)L.resume, 0, n, st);
@@ -459,7 +705,7 @@ static ad_status aggregate_impl(const ad_graph *g, const Tr *rho, double eps, do
         s = fill_u64(L.left, 0, SEED_BATCH, st);
         if (s != AD_OK) return s;
         for (int b = 0; b < SEED_BATCH; ++b) {
-            hipLaunchKernelGGL(k_ml_seed_round, dim3(mwgrid(n)), dim3(MBLOCK), 0, st, n, L.aoff, L.alist, L.state,
+            hipLaunchKernelGGL(k_ml_seed_round, dim3(mwgrid(n)), dim3(MBLOCK), 0, st, n, g->row_ptr, L.acnt, L.alist, L.state,
                                L.resume, L.left + b);
             AD_LAUNCH_CHECK("k_ml_seed_round");
         }
@@ -472,8 +718,15 @@ static ad_status aggregate_impl(const ad_graph *g, const Tr *rho, double eps, do
     AD_LAUNCH_CHECK("k_ml_seed_flags");
     s = scan_exclusive(n, L.rank, nullptr, L.total, nullptr, L.scan, st);
     if (s != AD_OK) return s;
-    hipLaunchKernelGGL(k_ml_aggregate<Tr>, dim3(mwgrid(n)), dim3(MBLOCK), 0, st, n, g->row_ptr, g->col, g->eid,
-                       g->orig_id, rho, eps, L.state, L.rank, agg);
+    MlAggregate<Tr> ka{};
+    ka.col = g->col;
+    ka.orig_id = g->orig_id;
+    ka.rho_ent = rho_ent;
+    ka.eps = eps;
+    ka.state = L.state;
+    ka.rank = L.rank;
+    ka.agg = agg;
+    hipLaunchKernelGGL(k_ml_aggregate<Tr>, rgrid, dim3(MBLOCK), 0, st, n, g->row_ptr, hubs, ka);
     AD_LAUNCH_CHECK("k_ml_aggregate");
     unsigned int nc = 0;
     AD_HIP(hipMemcpyAsync(&nc, L.total, sizeof(nc), hipMemcpyDeviceToHost, st));
@@ -711,11 +964,19 @@ static ad_status ml_level(const ad_graph *g, const ad_ml_opts *o, int l, uint8_t
     ML_TRY(dev_alloc(cv, (size_t)m * sizeof(int32_t)));
     ML_TRY(dev_alloc(cw, (size_t)m * sizeof(float)));
     ML_TRY(dev_alloc(names, (size_t)nc * sizeof(int32_t)));
-    hipLaunchKernelGGL(k_ml_pairs, dim3(mwgrid(n)), dim3(MBLOCK), 0, st, n, g->row_ptr, g->col, g->w, g->eid,
-                       agg.get<const int32_t>(), cu.get<int32_t>(), cv.get<int32_t>(), cw.get<float>());
-    AD_LAUNCH_CHECK("k_ml_pairs");
-    AggLayout L;
+    AggLayout L;                          // still holds the hub rows and the states
     agg_layout(n, 2 * m, aws.p, aws.bytes, &L);
+    MlPairs kp{};
+    kp.col = g->col;
+    kp.w = g->w;
+    kp.eid = g->eid;
+    kp.agg = agg.get<const int32_t>();
+    kp.cu = cu.get<int32_t>();
+    kp.cv = cv.get<int32_t>();
+    kp.cw = cw.get<float>();
+    const MlHubs hubs = ml_hubs(g, L);
+    hipLaunchKernelGGL(k_ml_pairs, dim3(mrgrid(n) + hubs.blocks), dim3(MBLOCK), 0, st, n, g->row_ptr, hubs, kp);
+    AD_LAUNCH_CHECK("k_ml_pairs");
     hipLaunchKernelGGL(k_ml_names, dim3(mgrid(n)), dim3(MBLOCK), 0, st, n, L.state, agg.get<const int32_t>(),
                        g->orig_id, names.get<int32_t>());
     AD_LAUNCH_CHECK("k_ml_names");
