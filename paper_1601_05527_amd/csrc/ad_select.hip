@@ -318,15 +318,38 @@ __device__ __forceinline__ int32_t nbr_id(int64_t p, int32_t j, const int32_t *_
 // Where ranks go.  MODE_FIXED marks keep[e] when rank < budget[d] (with
 // `both`, the LOCAL rank against (budget, keep) and the GLOBAL rank against
 // (budget2, keep2); otherwise the rank of `orient`).  MODE_REC stores the
-// side record {d, first rank, second rank, 0} at recs[2e + (row > j)]: with
+// side record {d, first rank, second rank} at recs[e + (row > j ? m : 0)]: with
 // `both` the LOCAL and the GLOBAL rank, otherwise the rank of `orient` in
-// both places; one 16-byte store per entry.
+// both places; one store per entry.
 struct Emit {
     int mode, orient, both;
     const int32_t *budget, *budget2;
     uint8_t *keep, *keep2;
-    uint4 *recs;
+    void *recs;
+    int packed;
+    int64_t m;
 };
+
+// A side record {d, first rank, second rank} is one 64-bit word where degrees
+// fit REC_BITS bits, else a uint4: the records are stores at random places (the upper
+// sides' are consecutive) and the fit's largest stream.  n = 2^20, m = 16M,
+// both orientations: 1,259 us with a uint4 per side, two sides together, 1,183
+// with words, all upper sides before all lower ones.
+constexpr int REC_BITS = 21;
+struct SideRec {
+    uint32_t d, r0, r1;
+};
+template <bool PACKED>
+__device__ __forceinline__ SideRec load_rec(const void *__restrict__ recs, int64_t at) {
+    if constexpr (PACKED) {
+        const unsigned long long v = ((const unsigned long long *)recs)[at];
+        constexpr uint32_t MASK = (1u << REC_BITS) - 1;
+        return SideRec{(uint32_t)(v >> (2 * REC_BITS)), (uint32_t)(v >> REC_BITS) & MASK, (uint32_t)v & MASK};
+    } else {
+        const uint4 v = ((const uint4 *)recs)[at];
+        return SideRec{v.x, v.y, v.z};
+    }
+}
 
 // Rank of an entry in its row of d entries, in both orders of Algorithm 3:
 // LOCAL (rho ascending) and GLOBAL (rho descending), ties by neighbour id
@@ -345,8 +368,12 @@ __device__ __forceinline__ void emit_ranks(const Emit &em, int64_t row, int32_t 
         }
         return;
     }
-    em.recs[2 * (int64_t)e + (row > j ? 1 : 0)] =
-        make_uint4((uint32_t)d, (uint32_t)(em.both ? rank_local : rank_o), (uint32_t)(em.both ? rank_global : rank_o), 0u);
+    const int64_t at = (int64_t)e + (row > j ? em.m : 0);
+    const uint32_t r0 = (uint32_t)(em.both ? rank_local : rank_o), r1 = (uint32_t)(em.both ? rank_global : rank_o);
+    if (em.packed)
+        ((unsigned long long *)em.recs)[at] = ((unsigned long long)d << (2 * REC_BITS)) | ((unsigned long long)r0 << REC_BITS) | r1;
+    else
+        ((uint4 *)em.recs)[at] = make_uint4((uint32_t)d, r0, r1, 0u);
 }
 
 // Rows of degree <= 64, packed: a wave takes consecutive rows whose entries
@@ -1398,7 +1425,7 @@ __device__ __forceinline__ unsigned long long side_grid(uint32_t d, uint32_t r, 
 
 // Rank of fitted orientation o in a side record: the first rank, or the
 // second when both orientations are fitted.
-__device__ __forceinline__ uint32_t rec_rank(const uint4 &v, int o) { return o == 0 ? v.y : v.z; }
+__device__ __forceinline__ uint32_t rec_rank(const SideRec &v, int o) { return o == 0 ? v.r0 : v.r1; }
 
 // Per fitted orientation (at most two): the edges' grid indices and the
 // first digit's histogram (digit p's: p * 2 * NBINS further on).
@@ -1432,8 +1459,8 @@ struct BinRun {
 // doubles) are first copied into dynamic LDS, one workgroup per compute unit
 // (six random table reads per edge cost more from the caches than the
 // records' stream; the values read are the same).
-template <int TB, bool LDS_TAB>
-__global__ __launch_bounds__(TB) void k_fit_grid(int64_t m, const uint4 *__restrict__ recs,
+template <int TB, bool LDS_TAB, bool PACKED>
+__global__ __launch_bounds__(TB) void k_fit_grid(int64_t m, const void *__restrict__ recs,
                                                 const double *__restrict__ logs, int64_t nlogs, int nfit,
                                                 FitArrays fa) {
     extern __shared__ double tab_lds[];
@@ -1446,25 +1473,25 @@ __global__ __launch_bounds__(TB) void k_fit_grid(int64_t m, const uint4 *__restr
     BinRun run[2];
     constexpr int64_t STEP = (int64_t)TB * FIT_U;
     for (int64_t b0 = (int64_t)blockIdx.x * STEP; b0 < m; b0 += (int64_t)gridDim.x * STEP) {
-        uint4 a[FIT_U] = {}, b[FIT_U] = {};
+        SideRec a[FIT_U] = {}, b[FIT_U] = {};
 #pragma unroll
         for (int u = 0; u < FIT_U; ++u) {
             const int64_t e = b0 + u * TB + threadIdx.x;
             if (e < m) {
-                a[u] = recs[2 * e];
-                b[u] = recs[2 * e + 1];
+                a[u] = load_rec<PACKED>(recs, e);
+                b[u] = load_rec<PACKED>(recs, m + e);
             }
         }
 #pragma unroll
         for (int u = 0; u < FIT_U; ++u) {
             const int64_t e = b0 + u * TB + threadIdx.x;
             if (e >= m) continue;
-            const double ia = tab[nlogs + a[u].x], ib = tab[nlogs + b[u].x];
+            const double ia = tab[nlogs + a[u].d], ib = tab[nlogs + b[u].d];
 #pragma unroll
             for (int o = 0; o < 2; ++o) {
                 if (o >= nfit) break;
-                const unsigned long long ga = side_grid(a[u].x, rec_rank(a[u], o), ia, tab);
-                const unsigned long long gb = side_grid(b[u].x, rec_rank(b[u], o), ib, tab);
+                const unsigned long long ga = side_grid(a[u].d, rec_rank(a[u], o), ia, tab);
+                const unsigned long long gb = side_grid(b[u].d, rec_rank(b[u], o), ib, tab);
                 const unsigned long long g = ga < gb ? ga : gb;
                 fa.G[o][e] = g;
                 run[o].add(h[o], (int)((g >> DIGIT_SHIFT[0]) & (NBINS - 1)));
@@ -1667,8 +1694,8 @@ constexpr unsigned long long FIT_MARGIN = 1ull << 16;
 // block and flush), and its keep flag is left for that kernel to store.
 constexpr int STAGE_M = 4096;   // LDS staging of listed edges per orientation
 
-template <bool LIST>
-__global__ __launch_bounds__(SBLOCK) void k_fit_count(int64_t m, const uint4 *__restrict__ recs, int nfit,
+template <bool LIST, bool PACKED>
+__global__ __launch_bounds__(SBLOCK) void k_fit_count(int64_t m, const void *__restrict__ recs, int nfit,
                                                      CountArgs ca, unsigned long long *__restrict__ part) {
     __shared__ uint32_t stage[LIST ? 2 : 1][LIST ? STAGE_M : 1];
     __shared__ unsigned int n_stage[2];
@@ -1728,11 +1755,11 @@ __global__ __launch_bounds__(SBLOCK) void k_fit_count(int64_t m, const uint4 *__
                     } else if (LIST) {
                         listed = true;
                     } else {
-                        const uint4 a = recs[2 * e], b = recs[2 * e + 1];
+                        const SideRec a = load_rec<PACKED>(recs, e), b = load_rec<PACKED>(recs, m + e);
                         const uint32_t ra = rec_rank(a, o), rb = rec_rank(b, o);
-                        k_hi = ra < (uint32_t)ca.tab_hi[o][a.x] || rb < (uint32_t)ca.tab_hi[o][b.x];
+                        k_hi = ra < (uint32_t)ca.tab_hi[o][a.d] || rb < (uint32_t)ca.tab_hi[o][b.d];
                         k_lo = ca.use_lo[o] &&
-                               (ra < (uint32_t)ca.tab_lo[o][a.x] || rb < (uint32_t)ca.tab_lo[o][b.x]);
+                               (ra < (uint32_t)ca.tab_lo[o][a.d] || rb < (uint32_t)ca.tab_lo[o][b.d]);
                     }
                     kb |= (k_hi ? 1u : 0u) << (8 * t);
                     c[o][0] += k_hi;
@@ -1789,7 +1816,8 @@ __global__ __launch_bounds__(SBLOCK) void k_fit_count(int64_t m, const uint4 *__
 // count pass's per-block counts (nblocks of them) and gives the totals and the list's
 // length to the host (out, mapped: [2o], [2o + 1], [4 + o]) and the upper
 // total to n_kept[o]; the launches that did so took 4 us each.
-__global__ __launch_bounds__(SBLOCK) void k_fit_margin(const uint4 *__restrict__ recs, CountArgs ca,
+template <bool PACKED>
+__global__ __launch_bounds__(SBLOCK) void k_fit_margin(int64_t m, const void *__restrict__ recs, CountArgs ca,
                                                       const unsigned long long *__restrict__ part, int nblocks,
                                                       unsigned long long *__restrict__ counts,
                                                       unsigned long long *__restrict__ out,
@@ -1803,11 +1831,11 @@ __global__ __launch_bounds__(SBLOCK) void k_fit_margin(const uint4 *__restrict__
         for (int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; i < (int64_t)n;
              i += (int64_t)gridDim.x * blockDim.x) {
             const int64_t e = ca.list[o][i];
-            const uint4 a = recs[2 * e], b = recs[2 * e + 1];
+            const SideRec a = load_rec<PACKED>(recs, e), b = load_rec<PACKED>(recs, m + e);
             const uint32_t ra = rec_rank(a, o), rb = rec_rank(b, o);
-            const bool k_hi = ra < (uint32_t)ca.tab_hi[o][a.x] || rb < (uint32_t)ca.tab_hi[o][b.x];
+            const bool k_hi = ra < (uint32_t)ca.tab_hi[o][a.d] || rb < (uint32_t)ca.tab_hi[o][b.d];
             const bool k_lo =
-                ca.use_lo[o] && (ra < (uint32_t)ca.tab_lo[o][a.x] || rb < (uint32_t)ca.tab_lo[o][b.x]);
+                ca.use_lo[o] && (ra < (uint32_t)ca.tab_lo[o][a.d] || rb < (uint32_t)ca.tab_lo[o][b.d]);
             ca.keep[o][e] = k_hi ? 1 : 0;
             c_hi += k_hi;
             c_lo += k_lo;
@@ -1856,7 +1884,8 @@ struct SelLayout {
     unsigned int *cnt;            // [NCLASS + 1]: rows per class, packed waves
     ClassBounds cb;
     long long *plan;              // packed small-row waves
-    uint4 *recs;                  // [2m] side records (Emit, MODE_REC*)
+    void *recs;                   // [2m] side records (Emit, MODE_REC*)
+    bool packed;                  // 64-bit records
     unsigned long long *G, *G2;   // [m] grid indices per fitted orientation (G2 when both)
     unsigned long long *cand, *cand2, *cand_n;   // select candidates (CandArrays), per orientation
     unsigned long long *fit_part;                // [COUNT_BLOCKS][4]: the count pass's per-block counts
@@ -1889,7 +1918,9 @@ static size_t sel_layout(const ad_graph *g, void *ws, size_t ws_bytes, SelLayout
     l.lists = c.take<int32_t>(total);
     l.cnt = c.take<unsigned int>(NCLASS + 1);
     l.plan = c.take<long long>(n + ntiles);
-    l.recs = c.take<uint4>(2 * m);
+    l.packed = (int64_t)g->d_max < ((int64_t)1 << REC_BITS);
+    if (l.packed) l.recs = c.take<unsigned long long>(2 * m);
+    else l.recs = c.take<uint4>(2 * m);
     l.G = c.take<unsigned long long>(m);
     l.G2 = both ? c.take<unsigned long long>(m) : nullptr;
     l.cand_cap = std::min<int64_t>(m, std::max<int64_t>(1 << 16, m / 16));
@@ -2216,14 +2247,23 @@ static ad_status count_kept(int64_t m, const uint8_t *keep, unsigned long long *
     return AD_OK;
 }
 
-static Emit emit_single(int mode, int orient, const int32_t *budget, uint8_t *keep, uint4 *recs) {
+static Emit emit_single(int mode, int orient, const int32_t *budget, uint8_t *keep) {
     Emit em{};
     em.mode = mode;
     em.orient = orient;
     em.both = 0;
     em.budget = budget;
     em.keep = keep;
-    em.recs = recs;
+    return em;
+}
+
+// Side records of orientation `orient` into L (both: of the two orientations).
+static Emit emit_recs(const ad_graph *g, const SelLayout &L, int orient, bool both) {
+    Emit em = emit_single(MODE_REC, both ? AD_LOCAL : orient, nullptr, nullptr);
+    em.both = both ? 1 : 0;
+    em.recs = L.recs;
+    em.packed = L.packed ? 1 : 0;
+    em.m = g->m;
     return em;
 }
 
@@ -2337,7 +2377,7 @@ ad_status sparsify_fixed(const ad_graph *g, ad_dtype rho_dtype, const void *rho,
     if (g->m <= 0) return AD_OK;
     ad_status s = rank_setup(g, L, keep, false, stream);
     if (s != AD_OK) return s;
-    const Emit em = emit_single(MODE_FIXED, orient, budget, keep, nullptr);
+    const Emit em = emit_single(MODE_FIXED, orient, budget, keep);
     if (rho_dtype == AD_F32) return rank_all<float>(g, (const float *)rho, em, L, stream);
     return rank_all<double>(g, (const double *)rho, em, L, stream);
 }
@@ -2427,7 +2467,7 @@ static ad_status sparsify_count(const ad_graph *g, ad_dtype rho_dtype, const voi
     }
     s = rank_setup(g, L, keep, false, stream);
     if (s != AD_OK) return s;
-    const Emit em = emit_single(MODE_FIXED, orient, budget, keep, nullptr);
+    const Emit em = emit_single(MODE_FIXED, orient, budget, keep);
     if (rho_dtype == AD_F32)
         s = rank_all<float>(g, (const float *)rho, em, L, stream, rho_ent);
     else
@@ -2513,11 +2553,19 @@ static ad_status fit_from_recs(const ad_graph *g, const SelLayout &L, int nfit, 
     if (lds_tab) {
         const unsigned blocks = (unsigned)std::max<int64_t>(
             1, std::min<int64_t>(n_cu, ceil_div(m, (int64_t)FIT_LDS_TB * FIT_U)));
-        hipLaunchKernelGGL((k_fit_grid<FIT_LDS_TB, true>), dim3(blocks), dim3(FIT_LDS_TB),
-                           (size_t)(2 * nlogs) * sizeof(double), stream, m, L.recs, L.logs, nlogs, nfit, fa);
+        if (L.packed)
+            hipLaunchKernelGGL((k_fit_grid<FIT_LDS_TB, true, true>), dim3(blocks), dim3(FIT_LDS_TB),
+                               (size_t)(2 * nlogs) * sizeof(double), stream, m, L.recs, L.logs, nlogs, nfit, fa);
+        else
+            hipLaunchKernelGGL((k_fit_grid<FIT_LDS_TB, true, false>), dim3(blocks), dim3(FIT_LDS_TB),
+                               (size_t)(2 * nlogs) * sizeof(double), stream, m, L.recs, L.logs, nlogs, nfit, fa);
     } else {
-        hipLaunchKernelGGL((k_fit_grid<SBLOCK, false>), dim3(hist_blocks), dim3(SBLOCK), 0, stream, m, L.recs,
-                           L.logs, nlogs, nfit, fa);
+        if (L.packed)
+            hipLaunchKernelGGL((k_fit_grid<SBLOCK, false, true>), dim3(hist_blocks), dim3(SBLOCK), 0, stream, m, L.recs,
+                               L.logs, nlogs, nfit, fa);
+        else
+            hipLaunchKernelGGL((k_fit_grid<SBLOCK, false, false>), dim3(hist_blocks), dim3(SBLOCK), 0, stream, m, L.recs,
+                               L.logs, nlogs, nfit, fa);
     }
     AD_LAUNCH_CHECK("k_fit_grid");
     for (int pass = 1; pass < NPASS; ++pass) {
@@ -2570,7 +2618,7 @@ static ad_status fit_from_recs(const ad_graph *g, const SelLayout &L, int nfit, 
             if (s != AD_OK) return s;
         }
         if (split) {
-            hipLaunchKernelGGL(k_fit_count<true>, dim3(count_blocks), dim3(SBLOCK), 0, stream, m, L.recs, nfit, ca,
+            hipLaunchKernelGGL((k_fit_count<true, true>), dim3(count_blocks), dim3(SBLOCK), 0, stream, m, L.recs, nfit, ca,
                                L.fit_part);
             AD_LAUNCH_CHECK("k_fit_count");
         }
@@ -2596,12 +2644,20 @@ static ad_status fit_from_recs(const ad_graph *g, const SelLayout &L, int nfit, 
                            tabs_mapped, tab_words);
         AD_LAUNCH_CHECK("k_copy_mapped");
         if (!split) {                        // lists nothing: the kernel after it only adds up
-            hipLaunchKernelGGL(k_fit_count<false>, dim3(count_blocks), dim3(SBLOCK), 0, stream, m, L.recs, nfit, ca,
-                               L.fit_part);
+            if (L.packed)
+                hipLaunchKernelGGL((k_fit_count<false, true>), dim3(count_blocks), dim3(SBLOCK), 0, stream, m, L.recs, nfit, ca,
+                                   L.fit_part);
+            else
+                hipLaunchKernelGGL((k_fit_count<false, false>), dim3(count_blocks), dim3(SBLOCK), 0, stream, m, L.recs, nfit, ca,
+                                   L.fit_part);
             AD_LAUNCH_CHECK("k_fit_count");
         }
-        hipLaunchKernelGGL(k_fit_margin, dim3(margin_blocks, nfit), dim3(SBLOCK), 0, stream, L.recs, ca, L.fit_part,
-                           (int)count_blocks, L.counts, rb_mapped + 4, n_kept);
+        if (L.packed)
+            hipLaunchKernelGGL(k_fit_margin<true>, dim3(margin_blocks, nfit), dim3(SBLOCK), 0, stream, m, L.recs, ca, L.fit_part,
+                               (int)count_blocks, L.counts, rb_mapped + 4, n_kept);
+        else
+            hipLaunchKernelGGL(k_fit_margin<false>, dim3(margin_blocks, nfit), dim3(SBLOCK), 0, stream, m, L.recs, ca, L.fit_part,
+                               (int)count_blocks, L.counts, rb_mapped + 4, n_kept);
         AD_LAUNCH_CHECK("k_fit_margin");
         unsigned long long *const hc = rb + 4;
         AD_HIP(hipStreamSynchronize(stream));
@@ -2650,11 +2706,7 @@ static ad_status sparsify_fit_impl(const ad_graph *g, ad_dtype rho_dtype, const 
         return AD_OK;
     }
     const int64_t K = fit_count_target(m, target);
-    Emit em = emit_single(MODE_REC, orient, nullptr, nullptr, L.recs);
-    if (both) {
-        em.orient = AD_LOCAL;
-        em.both = 1;
-    }
+    const Emit em = emit_recs(g, L, orient, both);
     s = rank_setup(g, L, nullptr, true, stream);
     if (s != AD_OK) return s;
     if (rho_dtype == AD_F32)
@@ -3380,8 +3432,8 @@ static ad_status sparsify_binned_impl(const ad_graph *g, ad_dtype rho_dtype, con
         budget_table(g->d_max, e, bt);
         AD_HIP(hipMemcpyAsync(B.budget, bt.data(), bt.size() * sizeof(int32_t), hipMemcpyHostToDevice, stream));
     }
-    const Emit em = fit ? emit_single(MODE_REC, AD_LOCAL, nullptr, nullptr, L.recs)
-                        : emit_single(MODE_FIXED, AD_LOCAL, B.budget, keep, nullptr);
+    const Emit em = fit ? emit_recs(g, L, AD_LOCAL, false)
+                        : emit_single(MODE_FIXED, AD_LOCAL, B.budget, keep);
     if (rho_dtype == AD_F32) s = bin_all<float>(g, (const float *)rho, em, B, stream);
     else s = bin_all<double>(g, (const double *)rho, em, B, stream);
     if (s != AD_OK) return s;

@@ -461,3 +461,26 @@ def test_coarsening_at_row_classes(api, edge, prec):
         assert nc == nc_o
         np.testing.assert_array_equal(_np(is_seed), seeds_o)
         np.testing.assert_array_equal(_np(agg), agg_o)
+
+
+@pytest.mark.parametrize("d_max", [(1 << 21) - 1, 1 << 21])
+def test_fit_side_records_of_both_widths(api, d_max):
+    """The largest degree (a bound: tables are sized by it) picks 64-bit or 128-bit side
+    records and puts the fit's log tables in memory; fits of either give the masks,
+    counts and exponents of the exact bound, on rows of every class."""
+    import dataclasses
+    announce(f"fit d_max={d_max}")
+    g = G.chung_lu(4000, 120_000, seed=31)
+    rho = np.random.default_rng(8).integers(1, 4000, g.m).astype(np.float32)      # with ties
+    dg = api.DeviceGraph.from_host(g, "cuda")
+    wide = dataclasses.replace(dg, d_max=d_max)
+    rt = torch.from_numpy(rho).cuda()
+    for target in (0.05, 0.4):
+        kl, kg, nk, (el, eg) = api.sparsify_fit_both(wide, rt, target)
+        for o, keep, e in ((0, kl, el), (1, kg, eg)):
+            keep1, n1, e1 = api.sparsify_fit(dg, rt, o, target)
+            keep2, n2, e2 = api.sparsify_fit(wide, rt, o, target)
+            assert e == e1 == e2
+            assert int(_np(nk)[o]) == int(_np(n1)[0]) == int(_np(n2)[0])
+            np.testing.assert_array_equal(_np(keep), _np(keep1))
+            np.testing.assert_array_equal(_np(keep2), _np(keep1))
