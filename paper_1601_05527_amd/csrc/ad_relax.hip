@@ -88,45 +88,57 @@ __global__ __launch_bounds__(BLOCK) void k_weighted_degree(int64_t n, const int6
     }
 }
 
-// s_i for the listed long rows: a workgroup per row, strided FP64 partial
-// sums combined by a fixed tree in LDS.
+// s_i for the listed long rows: BLOCK strided FP64 partial sums combined by a
+// fixed tree, by one wave per row (lane l holds the partial sums l, l + 64, l + 128 and
+// l + 192, so the tree's first two levels stay in the lane and no barrier is
+// needed).  The rows are mostly a few hundred entries: a workgroup each, with the
+// tree in LDS, took 38 us at n = 2^20, m = 16M and 115 on an R-MAT graph of n = 2^21; 22 and 66 here.
 template <typename A>
 __global__ __launch_bounds__(BLOCK) void k_weighted_degree_hub(const int32_t *__restrict__ list,
                                                               const unsigned int *__restrict__ count,
                                                               const int64_t *__restrict__ row_ptr,
                                                               const float *__restrict__ w, A *__restrict__ inv_s,
                                                               float *__restrict__ sdeg, double *__restrict__ s64) {
-    __shared__ double part[BLOCK];
+    constexpr int PER = BLOCK / WAVE;
+    static_assert(PER == 4, "two levels of the tree in the lane");
+    const int lane = threadIdx.x & (WAVE - 1);
     const unsigned int nh = *count;
-    for (unsigned int h = blockIdx.x; h < nh; h += gridDim.x) {
+    const unsigned int nw = gridDim.x * PER;
+    for (unsigned int h = blockIdx.x * PER + (threadIdx.x >> 6); h < nh; h += nw) {
         const int64_t i = list[h];
         const int64_t b = row_ptr[i], e = row_ptr[i + 1];
-        double s = 0.0;
+        double s[PER] = {0.0, 0.0, 0.0, 0.0};
         if (w) {
-            int64_t p = b + threadIdx.x;
-            for (; p + 3 * BLOCK < e; p += 4 * BLOCK) {
-                const float w0 = w[p], w1 = w[p + BLOCK], w2 = w[p + 2 * BLOCK], w3 = w[p + 3 * BLOCK];
-                s += (double)w0;
-                s += (double)w1;
-                s += (double)w2;
-                s += (double)w3;
+            int64_t p = b + lane;
+            for (; p + (8 * PER - 1) * WAVE < e; p += 8 * BLOCK) {           // the longest rows
+                float v[8 * PER];
+#pragma unroll
+                for (int u = 0; u < 8 * PER; ++u) v[u] = w[p + u * WAVE];
+#pragma unroll
+                for (int u = 0; u < 8 * PER; ++u) s[u % PER] += (double)v[u];
             }
-            for (; p < e; p += BLOCK) s += (double)w[p];
-        } else if (threadIdx.x == 0) {
-            s = (double)(e - b);
+            for (; p + (2 * PER - 1) * WAVE < e; p += 2 * BLOCK) {
+                float v[2 * PER];
+#pragma unroll
+                for (int u = 0; u < 2 * PER; ++u) v[u] = w[p + u * WAVE];
+#pragma unroll
+                for (int u = 0; u < 2 * PER; ++u) s[u % PER] += (double)v[u];
+            }
+            float v[2 * PER];
+#pragma unroll
+            for (int u = 0; u < 2 * PER; ++u) v[u] = p + u * WAVE < e ? w[p + u * WAVE] : 0.0f;
+#pragma unroll
+            for (int u = 0; u < 2 * PER; ++u) s[u % PER] += (double)v[u];
+        } else if (lane == 0) {
+            s[0] = (double)(e - b);
         }
-        part[threadIdx.x] = s;
-        __syncthreads();
-        for (int d = BLOCK / 2; d >= 1; d >>= 1) {
-            if ((int)threadIdx.x < d) part[threadIdx.x] += part[threadIdx.x + d];
-            __syncthreads();
+        double t = (s[0] + s[2]) + (s[1] + s[3]);
+        for (int d = WAVE / 2; d >= 1; d >>= 1) t += shfl_down(t, d);
+        if (lane == 0) {
+            inv_s[i] = sweep_scale<A>(t);
+            sdeg[i] = (float)t;
+            if (s64) s64[i] = t;
         }
-        if (threadIdx.x == 0) {
-            inv_s[i] = sweep_scale<A>(part[0]);
-            sdeg[i] = (float)part[0];
-            if (s64) s64[i] = part[0];
-        }
-        __syncthreads();
     }
 }
 
@@ -301,16 +313,17 @@ __global__ __launch_bounds__(BLOCK) void k_comp_partials(int R, int64_t n_comp, 
 #pragma unroll
     for (int c = 0; c < 4; ++c) {
         const double v = wave_sum(acc[c]);
-        if (lane == 0 && 4 * q + c < R) part[ch * R + 4 * q + c] = v;
+        if (lane == 0 && 4 * q + c < R) part[(4 * q + c) * n_chunks + ch] = v;
     }
 }
 
-// Sums over the chunks of component c (chunk partials part[ch][r] and
-// part_s[ch]) for one wave: lane l adds chunks c0 + l, c0 + l + 64, ... in
+// Sums over the chunks of component c (chunk partials part_r[ch], one vector's, and
+// part_s[ch]; a vector's partials lie together, so that the lanes' loads share
+// lines: with a chunk's together the 8,192 chunks of an n = 2^21 component took
+// 21 us, 12 here) for one wave: lane l adds chunks c0 + l, c0 + l + 64, ... in
 // that order (eight loads in flight per lane), then a fixed shuffle tree
 // adds the lanes.  The order depends only on the component's chunk range.
-__device__ __forceinline__ void comp_chunk_sums(int64_t c0, int64_t c1, int R, int r,
-                                                const double *__restrict__ part,
+__device__ __forceinline__ void comp_chunk_sums(int64_t c0, int64_t c1, const double *__restrict__ part_r,
                                                 const double *__restrict__ part_s, double &S, double &X) {
     const int lane = threadIdx.x & (WAVE - 1);
     constexpr int B = 8;
@@ -321,7 +334,7 @@ __device__ __forceinline__ void comp_chunk_sums(int64_t c0, int64_t c1, int R, i
 #pragma unroll
         for (int u = 0; u < B; ++u) {
             b[u] = part_s[ch + (int64_t)u * WAVE];
-            a[u] = part[(ch + (int64_t)u * WAVE) * R + r];
+            a[u] = part_r[ch + (int64_t)u * WAVE];
         }
 #pragma unroll
         for (int u = 0; u < B; ++u) {
@@ -331,7 +344,7 @@ __device__ __forceinline__ void comp_chunk_sums(int64_t c0, int64_t c1, int R, i
     }
     for (; ch < c1; ch += WAVE) {
         s += part_s[ch];
-        x += part[ch * R + r];
+        x += part_r[ch];
     }
     S = wave_sum(s);
     X = wave_sum(x);
@@ -340,7 +353,8 @@ __device__ __forceinline__ void comp_chunk_sums(int64_t c0, int64_t c1, int R, i
 // shift[c][r] = the weighted mean of component c rounded to the 2^-24 grid:
 // one wave per (component, vector).  Also empties the running min / max codes
 // of every graph (MM_SLOTS copies, mm_count words).
-__global__ __launch_bounds__(BLOCK) void k_comp_finalize(int R, int64_t n_comp, const int64_t *__restrict__ chunk_start,
+__global__ __launch_bounds__(BLOCK) void k_comp_finalize(int R, int64_t n_comp, int64_t n_chunks,
+                                                        const int64_t *__restrict__ chunk_start,
                                                         const double *__restrict__ part,
                                                         const double *__restrict__ part_s, int centre,
                                                         double *__restrict__ shift, int64_t mm_count,
@@ -353,7 +367,7 @@ __global__ __launch_bounds__(BLOCK) void k_comp_finalize(int R, int64_t n_comp, 
         const int64_t c = idx / R;
         const int r = (int)(idx - c * R);
         double S, X;
-        comp_chunk_sums(chunk_start[c], chunk_start[c + 1], R, r, part, part_s, S, X);
+        comp_chunk_sums(chunk_start[c], chunk_start[c + 1], part + r * n_chunks, part_s, S, X);
         if ((threadIdx.x & (WAVE - 1)) == 0)
             shift[idx] = (centre && S > 0.0) ? rint((X / S) * 16777216.0) * (1.0 / 16777216.0) : 0.0;
     }
@@ -398,12 +412,13 @@ __global__ __launch_bounds__(BLOCK) void k_comp_drift_partials(int R, int64_t n_
 #pragma unroll
         for (int c = 0; c < G; ++c) {
             const double v = wave_sum(acc[c]);
-            if (lane == 0) part[ch * R + q0 + c] = v;
+            if (lane == 0) part[(q0 + c) * n_chunks + ch] = v;
         }
     }
 }
 
-__global__ __launch_bounds__(BLOCK) void k_comp_drift(int R, int64_t n_comp, const int64_t *__restrict__ chunk_start,
+__global__ __launch_bounds__(BLOCK) void k_comp_drift(int R, int64_t n_comp, int64_t n_chunks,
+                                                     const int64_t *__restrict__ chunk_start,
                                                      const double *__restrict__ part,
                                                      const double *__restrict__ part_s, float *__restrict__ drift,
                                                      double *__restrict__ shift) {
@@ -413,7 +428,7 @@ __global__ __launch_bounds__(BLOCK) void k_comp_drift(int R, int64_t n_comp, con
         const int64_t c = idx / R;
         const int r = (int)(idx - c * R);
         double S, X;
-        comp_chunk_sums(chunk_start[c], chunk_start[c + 1], R, r, part, part_s, S, X);
+        comp_chunk_sums(chunk_start[c], chunk_start[c + 1], part + r * n_chunks, part_s, S, X);
         if ((threadIdx.x & (WAVE - 1)) == 0) {
             const float d = S > 0.0 ? (float)(X / S) : 0.0f;
             drift[idx] = d;
@@ -1537,7 +1552,7 @@ static ad_status relax_impl(const ad_graph *g, const ad_relax_opts *o, const voi
         const int64_t cr = std::max<int64_t>(1, comp->n_comp * R);
         const int64_t mmc = (int64_t)MM_SLOTS * sg.G * 2 * R;
         hipLaunchKernelGGL(k_comp_finalize, dim3((unsigned)std::min<int64_t>(ceil_div(cr, BLOCK / WAVE), 1 << 16)), dim3(BLOCK), 0, st, R,
-                           comp->n_comp, comp->chunk_start, L.part, L.part_s, 1, shift, mmc, L.mm);
+                           comp->n_comp, comp->n_chunks, comp->chunk_start, L.part, L.part_s, 1, shift, mmc, L.mm);
         AD_LAUNCH_CHECK("k_comp_finalize");
     } else {
         if (n > 0 && nb > 0) {
@@ -1609,7 +1624,7 @@ static ad_status relax_impl(const ad_graph *g, const ad_relax_opts *o, const voi
                 AD_LAUNCH_CHECK("k_comp_drift_partials");
                 const int64_t cr = comp->n_comp * R;
                 hipLaunchKernelGGL(k_comp_drift, dim3((unsigned)std::min<int64_t>(ceil_div(cr, BLOCK / WAVE), 1 << 16)), dim3(BLOCK), 0, st, R,
-                                   comp->n_comp, comp->chunk_start, L.part, L.part_s, L.drift, shift);
+                                   comp->n_comp, comp->n_chunks, comp->chunk_start, L.part, L.part_s, L.drift, shift);
                 AD_LAUNCH_CHECK("k_comp_drift");
                 dr.c = L.drift;
                 dr.comp_of = comp->comp_of;
