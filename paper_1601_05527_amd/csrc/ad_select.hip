@@ -2147,14 +2147,15 @@ static ad_status rank_all(const ad_graph *g, const Tr *rho, const Emit &em, cons
             // graph (a power-law graph holds most long-row entries in its few
             // hundred longest rows, R-MAT spreads them over every class).  The
             // longest sorted class is split in two slices on two streams (its
-            // 512-thread workgroups need most of a compute unit and wait for
-            // room beside the other classes' work), and the rest spread so that
+            // workgroups need most of a compute unit and wait for room beside the
+            // other classes' work; 1,024 threads of 8 entries keep twice the waves
+            // of 512 of 16 there: the whole ranking of n = 2^20, m = 16M 1.5% shorter), and the rest spread so that
             // neither kind of graph piles its work on one stream; the bucket
             // partition follows the packed short rows on the caller's stream.
             if (g->d_max > 4096) {
                 const int halves = fk ? 2 : 1;
                 for (int h = 0; h < halves; ++h)
-                    hipLaunchKernelGGL((k_rank_radix<512, 16>), dim3(grid), dim3(512), 0, cls[h], lst[6], &L.cnt[6],
+                    hipLaunchKernelGGL((k_rank_radix<1024, 8>), dim3(grid), dim3(1024), 0, cls[h], lst[6], &L.cnt[6],
                                        AD_RANK_ARGS_R, h, halves);
             }
             if (g->d_max > 2048)
@@ -3368,8 +3369,11 @@ static ad_status bin_all(const ad_graph *g, const Tr *rho, const Emit &em, const
 #define AD_BIN_ROWS(TB, IPT, GRID, K, STREAM)                                                                  \
     if (g->d_max > CLASS_LO[K])                                                                                \
     hipLaunchKernelGGL((k_bin_rows<TB, IPT, Tr>), dim3(GRID), dim3(TB), 0, STREAM, L.lists + L.cb.off[K], &L.cnt[K], in, em)
-    AD_BIN_ROWS(512, 16, grid, 6, cf.cls[0]);
-    AD_BIN_ROWS(512, 8, grid, 5, cf.cls[1]);
+    // the two longest classes at most 128 registers a thread: with half the threads and
+    // twice the entries each one workgroup of 8 waves filled a compute unit (n = 2^20,
+    // m = 16M: 1,564 us for the selection's kernels, 1,478 so)
+    AD_BIN_ROWS(1024, 8, grid, 6, cf.cls[0]);
+    AD_BIN_ROWS(1024, 4, grid, 5, cf.cls[1]);
     AD_BIN_ROWS(256, 8, grid, 4, cf.cls[2]);
     const unsigned blocks = (unsigned)std::min<int64_t>(4096, ceil_div(n, SBLOCK / WAVE));
     hipLaunchKernelGGL((k_bin_packed<Tr>), dim3(blocks), dim3(SBLOCK), 0, st, L.plan, L.cnt + NCLASS, in, em);
