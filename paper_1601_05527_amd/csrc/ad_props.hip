@@ -83,7 +83,7 @@ __global__ void k_compact_entries(int64_t nnz, const int32_t *__restrict__ col, 
 // the row's place and the share's atomic.  A search of one end's whole row
 // per edge (3.6e9 lookups at n = 2^20, m = 16M, against 0.92e9 here, in a bitmap
 // that left one workgroup per compute unit): 17.2 ms for that graph and
-// its 30% selection together; 4.3 ms here.
+// its 30% selection together; 4.0 ms here.
 constexpr int TRI_SMALL = 64;            // rows up to here: 16 lanes each; longer: a workgroup
 constexpr int TRI_HUB = 4096;            // rows from here: TRI_SLICES workgroups
 constexpr int TRI_SLICES = 16;
@@ -111,17 +111,9 @@ __device__ __forceinline__ int tri_put(int32_t *key, int32_t x) {
         if (atomicCAS(&key[s], TRI_EMPTY, x) == TRI_EMPTY) return s;
 }
 
-// The slot of x, or -1.  Some bucket always has room, so the search ends.
-template <int SLOTS>
-__device__ __forceinline__ int tri_find(const int32_t *key, int32_t x) {
-    int b = tri_bucket<SLOTS>(x);
-    for (;;) {
-        const int4 k = *(const int4 *)(key + 4 * b);
-        const int at = k.x == x ? 0 : (k.y == x ? 1 : (k.z == x ? 2 : (k.w == x ? 3 : -1)));
-        if (at >= 0) return 4 * b + at;
-        if (k.w == TRI_EMPTY) return -1;
-        b = (b + 1) & (SLOTS / 4 - 1);
-    }
+// x's slot if it lies in bucket b (whose keys are k), else -1.
+__device__ __forceinline__ int tri_match(const int4 &k, int b, int32_t x) {
+    return k.x == x ? 4 * b : (k.y == x ? 4 * b + 1 : (k.z == x ? 4 * b + 2 : (k.w == x ? 4 * b + 3 : -1)));
 }
 
 // Walks dir[q0], dir[q0 + step], ... < q1, counting each entry found; returns the hits.
@@ -133,10 +125,24 @@ __device__ __forceinline__ unsigned int tri_walk(const int32_t *__restrict__ dir
         int32_t x[TRI_U];
 #pragma unroll
         for (int u = 0; u < TRI_U; ++u) x[u] = q0 + u * step < q1 ? dir[q0 + u * step] : TRI_EMPTY;
+        // every entry's bucket is read before the first is looked at
+        int4 k[TRI_U];
+        int b[TRI_U];
+#pragma unroll
+        for (int u = 0; u < TRI_U; ++u) {
+            b[u] = tri_bucket<SLOTS>(x[u]);
+            k[u] = ((const int4 *)key)[b[u]];
+        }
 #pragma unroll
         for (int u = 0; u < TRI_U; ++u) {
             if (x[u] == TRI_EMPTY) continue;
-            const int at = tri_find<SLOTS>(key, x[u]);
+            int at = tri_match(k[u], b[u], x[u]);
+            // a full bucket: the next ones (some bucket always has room, so the search ends)
+            while (at < 0 && k[u].w != TRI_EMPTY) {
+                b[u] = (b[u] + 1) & (SLOTS / 4 - 1);
+                k[u] = ((const int4 *)key)[b[u]];
+                at = tri_match(k[u], b[u], x[u]);
+            }
             if (at >= 0) {
                 atomicAdd(&cnt[at], 1u);
                 ++t;
@@ -320,6 +326,8 @@ __global__ __launch_bounds__(PBLOCK) void k_triangles_rows(const int32_t *__rest
     __shared__ int4 keys[SLOTS / 4];
     __shared__ unsigned int cnt[SLOTS];
     __shared__ unsigned long long wsum[PBLOCK / WAVE];
+    __shared__ uint8_t sel[PBLOCK / WAVE][WAVE];
+    __shared__ unsigned int hits[PBLOCK / WAVE][WAVE];
     int32_t *key = (int32_t *)keys;
     const int lane = threadIdx.x & (WAVE - 1), wv = threadIdx.x >> 6;
     for (int s = threadIdx.x; s < SLOTS; s += PBLOCK) {
@@ -354,31 +362,34 @@ __global__ __launch_bounds__(PBLOCK) void k_triangles_rows(const int32_t *__rest
                 const unsigned long long m4 = __ballot(len >= 2 && len <= 4 * TRI_U);
                 const unsigned long long m16 = __ballot(len > 4 * TRI_U && len <= 16 * TRI_U);
                 unsigned long long m64 = __ballot(len > 16 * TRI_U);
-                unsigned int mine = 0;                               // hits of this lane's a
-#pragma unroll
-                for (int r = 0; r < 4; ++r) {
-                    if (!((m4 >> (16 * r)) & 0xffffull)) continue;
-                    const int s = 16 * r + (lane >> 2);
+                // the lanes of either length in order, so that every round is full
+                const int n4 = __popcll(m4), n16 = __popcll(m16);
+                const unsigned long long below = (1ull << lane) - 1ull;
+                if ((m4 >> lane) & 1) sel[wv][__popcll(m4 & below)] = (uint8_t)lane;
+                if ((m16 >> lane) & 1) sel[wv][n4 + __popcll(m16 & below)] = (uint8_t)lane;
+                hits[wv][lane] = 0u;                                 // of this lane's a
+                __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+                __builtin_amdgcn_wave_barrier();
+                for (int r = 0; r < n4; r += 16) {
+                    const int k = r + (lane >> 2), s = k < n4 ? sel[wv][k] : 0;
                     const int64_t e0 = tri_start(__shfl(p, s, WAVE));
                     const int l = __shfl(len, s, WAVE);
-                    const int n_e = (m4 >> s) & 1 ? l : 0;
-                    unsigned int t = tri_walk<SLOTS>(dir, e0 + (lane & 3), e0 + n_e, 4, key, cnt);
+                    unsigned int t = tri_walk<SLOTS>(dir, e0 + (lane & 3), e0 + (k < n4 ? l : 0), 4, key, cnt);
                     t += __shfl_xor(t, 1, WAVE);
                     t += __shfl_xor(t, 2, WAVE);
-                    const unsigned int got = __shfl(t, (lane & 15) * 4, WAVE);
-                    if ((lane >> 4) == r && ((m4 >> lane) & 1)) mine = got;
+                    if ((lane & 3) == 0 && k < n4) hits[wv][s] = t;
                 }
-                for (int r = 0; r < 16; ++r) {
-                    if (!((m16 >> (4 * r)) & 0xfull)) continue;
-                    const int s = 4 * r + (lane >> 4);
+                for (int r = 0; r < n16; r += 4) {
+                    const int k = r + (lane >> 4), s = k < n16 ? sel[wv][n4 + k] : 0;
                     const int64_t e0 = tri_start(__shfl(p, s, WAVE));
                     const int l = __shfl(len, s, WAVE);
-                    const int n_e = (m16 >> s) & 1 ? l : 0;
-                    unsigned int t = tri_walk<SLOTS>(dir, e0 + (lane & 15), e0 + n_e, 16, key, cnt);
+                    unsigned int t = tri_walk<SLOTS>(dir, e0 + (lane & 15), e0 + (k < n16 ? l : 0), 16, key, cnt);
                     for (int o = 8; o >= 1; o >>= 1) t += __shfl_xor(t, o, WAVE);
-                    const unsigned int got = __shfl(t, (lane & 3) * 16, WAVE);
-                    if ((lane >> 2) == r && ((m16 >> lane) & 1)) mine = got;
+                    if ((lane & 15) == 0 && k < n16) hits[wv][s] = t;
                 }
+                __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+                __builtin_amdgcn_wave_barrier();
+                unsigned int mine = hits[wv][lane];
                 while (m64) {
                     const int s = __ffsll((long long)m64) - 1;
                     m64 &= m64 - 1;
