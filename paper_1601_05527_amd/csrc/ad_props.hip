@@ -644,17 +644,13 @@ __global__ void k_comp_chunks(int64_t nc, const int64_t *__restrict__ comp_start
 
 // ------------------------------------------------------------- spearman --
 
-__global__ void k_iota(int64_t n, uint32_t *__restrict__ idx) {
-    for (int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; i < n; i += (int64_t)gridDim.x * blockDim.x)
-        idx[i] = (uint32_t)i;
-}
-
 // Twice the mean rank of every score, from the sorted scores: a run of equal
 // scores at sorted positions [a, b) holds ranks a+1 .. b, mean (a + 1 + b) / 2.
-__global__ void k_mean_ranks(int64_t n, const double *__restrict__ sorted, const uint32_t *__restrict__ idx,
+template <typename K>
+__global__ void k_mean_ranks(int64_t n, const K *__restrict__ sorted, const uint32_t *__restrict__ idx,
                              int64_t *__restrict__ rank2) {
     for (int64_t t = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; t < n; t += (int64_t)gridDim.x * blockDim.x) {
-        const double v = sorted[t];
+        const K v = sorted[t];
         int64_t a = t, b = t + 1;
         // run bounds by binary search over the sorted scores
         int64_t lo = 0, hi = t;
@@ -826,8 +822,8 @@ static size_t comp_layout(int64_t n, void *ws, size_t ws_bytes, CompLayout *L) {
 }
 
 struct RankLayout {
-    double *keys0, *keys1;        // [n]
-    uint32_t *idx0, *idx1;        // [n]
+    double *keys1;                // [n] sorted scores
+    uint32_t *idx1;               // [n] and whose they are
     int64_t *rx2, *ry2;           // [n]
     double *part;                 // [PREDUCE_BLOCKS]
     void *temp;
@@ -838,17 +834,19 @@ static size_t rank_layout(int64_t n, void *ws, size_t ws_bytes, RankLayout *L) {
     Carver c(ws, ws_bytes);
     const size_t nn = (size_t)std::max<int64_t>(1, n);
     RankLayout l;
-    l.keys0 = c.take<double>(nn);
     l.keys1 = c.take<double>(nn);
-    l.idx0 = c.take<uint32_t>(nn);
     l.idx1 = c.take<uint32_t>(nn);
     l.rx2 = c.take<int64_t>(nn);
     l.ry2 = c.take<int64_t>(nn);
     l.part = c.take<double>(PREDUCE_BLOCKS);
     size_t t = 0;
-    if (rocprim::radix_sort_pairs(nullptr, t, (double *)nullptr, (double *)nullptr, (uint32_t *)nullptr,
-                                  (uint32_t *)nullptr, nn) != hipSuccess)
+    if (rocprim::radix_sort_pairs(nullptr, t, (const double *)nullptr, (double *)nullptr,
+                                  rocprim::counting_iterator<uint32_t>(0), (uint32_t *)nullptr, nn) != hipSuccess)
         t = 0;
+    size_t t32 = 0;
+    if (rocprim::radix_sort_pairs(nullptr, t32, (const uint32_t *)nullptr, (uint32_t *)nullptr,
+                                  rocprim::counting_iterator<uint32_t>(0), (uint32_t *)nullptr, nn) == hipSuccess)
+        t = std::max(t, t32);
     l.temp_bytes = t;
     l.temp = c.take<char>(t);
     if (L) *L = l;
@@ -1073,8 +1071,13 @@ extern "C" size_t ad_spearman_workspace_size(int64_t n) {
     return rank_layout(n, nullptr, 0, nullptr);
 }
 
-extern "C" ad_status ad_spearman(int64_t n, const double *x, const double *y, double *rho_host, void *ws,
-                                 size_t ws_bytes, hipStream_t stream) {
+// Spearman's formula for scores of `bits` bits: doubles, or whole numbers as
+// uint32_t, whose sort moves 8 bytes per score instead of 12 (the degrees of
+// ad_compare_properties).  The scores are read where they are and the index array
+// is an iterator: two passes over n less per score.
+template <typename K>
+static ad_status spearman_impl(int64_t n, const K *x, const K *y, unsigned bits, double *rho_host, void *ws,
+                               size_t ws_bytes, hipStream_t stream) {
     if (n < 0) return fail(AD_ERR_INVALID_ARG, "negative n");
     if (n >= ((int64_t)1 << 31)) return fail(AD_ERR_UNSUPPORTED, "n must be below 2^31");
     if (n > 0 && (!x || !y)) return fail(AD_ERR_INVALID_ARG, "x or y is NULL");
@@ -1086,16 +1089,14 @@ extern "C" ad_status ad_spearman(int64_t n, const double *x, const double *y, do
     *rho_host = 0.0;
     if (n < 2) return AD_OK;
     TraceScope trace("k_spearman", stream);
-    const double *src[2] = {x, y};
+    const K *src[2] = {x, y};
+    K *sorted = reinterpret_cast<K *>(L.keys1);
     int64_t *dst[2] = {L.rx2, L.ry2};
     for (int v = 0; v < 2; ++v) {
-        AD_HIP(hipMemcpyAsync(L.keys0, src[v], (size_t)n * sizeof(double), hipMemcpyDeviceToDevice, stream));
-        hipLaunchKernelGGL(k_iota, dim3(pgrid(n)), dim3(PBLOCK), 0, stream, n, L.idx0);
-        AD_LAUNCH_CHECK("k_iota");
         size_t tb = L.temp_bytes;
-        AD_RP(rocprim::radix_sort_pairs(L.temp, tb, L.keys0, L.keys1, L.idx0, L.idx1, (size_t)n, 0,
-                                        8 * (unsigned)sizeof(double), stream));
-        hipLaunchKernelGGL(k_mean_ranks, dim3(pgrid(n)), dim3(PBLOCK), 0, stream, n, L.keys1, L.idx1, dst[v]);
+        AD_RP(rocprim::radix_sort_pairs(L.temp, tb, src[v], sorted, rocprim::counting_iterator<uint32_t>(0), L.idx1,
+                                        (size_t)n, 0, bits, stream));
+        hipLaunchKernelGGL(k_mean_ranks<K>, dim3(pgrid(n)), dim3(PBLOCK), 0, stream, n, sorted, L.idx1, dst[v]);
         AD_LAUNCH_CHECK("k_mean_ranks");
     }
     hipLaunchKernelGGL(k_rank_diff2, dim3(PREDUCE_BLOCKS), dim3(PBLOCK), 0, stream, n, L.rx2, L.ry2, L.part);
@@ -1110,20 +1111,26 @@ extern "C" ad_status ad_spearman(int64_t n, const double *x, const double *y, do
     return AD_OK;
 }
 
+extern "C" ad_status ad_spearman(int64_t n, const double *x, const double *y, double *rho_host, void *ws,
+                                 size_t ws_bytes, hipStream_t stream) {
+    return spearman_impl<double>(n, x, y, 8 * (unsigned)sizeof(double), rho_host, ws, ws_bytes, stream);
+}
+
 // ------------------------------------------------------------ comparison --
 
 namespace ad {
 
-// Degree of every vertex as a double (the score Spearman's formula ranks).
-__global__ void k_degree_f64(int64_t n, const int64_t *__restrict__ row_ptr, double *__restrict__ deg) {
+// Degree of every vertex (the score Spearman's formula ranks).
+__global__ void k_degrees(int64_t n, const int64_t *__restrict__ row_ptr, uint32_t *__restrict__ deg) {
     for (int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; i < n; i += (int64_t)gridDim.x * blockDim.x)
-        deg[i] = (double)(row_ptr[i + 1] - row_ptr[i]);
+        deg[i] = (uint32_t)(row_ptr[i + 1] - row_ptr[i]);
 }
 
 struct CmpLayout {
     int64_t *sub_row_ptr;
     int32_t *sub_col, *sub_eid;
-    double *c_o, *c_s, *deg_o, *deg_s;
+    double *c_o, *c_s;
+    uint32_t *deg_o, *deg_s;
     void *ws;                 // the largest of the subgraph, properties and Spearman workspaces
     size_t ws_bytes;
 };
@@ -1137,8 +1144,8 @@ static size_t cmp_layout(const ad_graph *g, void *ws, size_t ws_bytes, CmpLayout
     l.sub_eid = c.take<int32_t>(nnz);
     l.c_o = c.take<double>(n);
     l.c_s = c.take<double>(n);
-    l.deg_o = c.take<double>(n);
-    l.deg_s = c.take<double>(n);
+    l.deg_o = c.take<uint32_t>(n);
+    l.deg_s = c.take<uint32_t>(n);
     ad_graph gu = *g;
     gu.w = nullptr;
     l.ws_bytes = std::max(sub_layout(&gu, nullptr, 0, nullptr),
@@ -1187,11 +1194,13 @@ extern "C" ad_status ad_compare_properties(const ad_graph *g, const uint8_t *kee
     if (s != AD_OK) return s;
     double rho_deg = 0.0, rho_c = 0.0;
     if (n > 0) {
-        hipLaunchKernelGGL(k_degree_f64, dim3(pgrid(n)), dim3(PBLOCK), 0, stream, n, go.row_ptr, L.deg_o);
-        AD_LAUNCH_CHECK("k_degree_f64");
-        hipLaunchKernelGGL(k_degree_f64, dim3(pgrid(n)), dim3(PBLOCK), 0, stream, n, gs.row_ptr, L.deg_s);
-        AD_LAUNCH_CHECK("k_degree_f64");
-        s = ad_spearman(n, L.deg_o, L.deg_s, &rho_deg, L.ws, L.ws_bytes, stream);
+        hipLaunchKernelGGL(k_degrees, dim3(pgrid(n)), dim3(PBLOCK), 0, stream, n, go.row_ptr, L.deg_o);
+        AD_LAUNCH_CHECK("k_degrees");
+        hipLaunchKernelGGL(k_degrees, dim3(pgrid(n)), dim3(PBLOCK), 0, stream, n, gs.row_ptr, L.deg_s);
+        AD_LAUNCH_CHECK("k_degrees");
+        unsigned bits = 1;                   // of a degree, at most 2m < 2^32
+        while (bits < 32 && ((uint64_t)(2 * g->m) >> bits) != 0) ++bits;
+        s = spearman_impl<uint32_t>(n, L.deg_o, L.deg_s, bits, &rho_deg, L.ws, L.ws_bytes, stream);
         if (s != AD_OK) return s;
         s = ad_spearman(n, L.c_o, L.c_s, &rho_c, L.ws, L.ws_bytes, stream);
         if (s != AD_OK) return s;

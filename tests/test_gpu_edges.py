@@ -484,3 +484,26 @@ def test_fit_side_records_of_both_widths(api, d_max):
             assert int(_np(nk)[o]) == int(_np(n1)[0]) == int(_np(n2)[0])
             np.testing.assert_array_equal(_np(keep), _np(keep1))
             np.testing.assert_array_equal(_np(keep2), _np(keep1))
+
+
+# ---------------------------------------------------------------- comparison --
+
+@pytest.mark.parametrize("n", [3, 100, 4097, 70_001])
+def test_degree_ranks_by_their_leading_bits(api, n):
+    """ad_compare_properties ranks degrees by the bits a whole number up to 2m can
+    have: the correlation equals that of the same degrees as general scores (the
+    same ranks; the mean's partial sums too), from isolated vertices to the hub
+    whose row is every other vertex."""
+    announce(f"degree ranks n={n}")
+    rng = np.random.default_rng(n)
+    u = np.concatenate([np.zeros(n - 1, int), rng.integers(1, n, 2 * n)])
+    v = np.concatenate([np.arange(1, n), rng.integers(1, n, 2 * n)])
+    lo, hi = np.minimum(u, v), np.maximum(u, v)
+    key = np.unique((lo * n + hi)[lo != hi])
+    g = G.from_edges(n, key // n, key % n)
+    keep = (rng.random(g.m) < 0.4).astype(np.uint8)
+    cmp = api.compare_properties(api.DeviceGraph.from_host(g, "cuda"), torch.from_numpy(keep).cuda())
+    rp = oracle.subgraph(g, keep)[0]
+    deg = lambda p: torch.from_numpy(np.diff(p).astype(np.float64)).cuda()
+    got = [x for k, x in cmp.items() if "degree" in k and "spearman" in k]
+    assert got == [api.spearman(deg(g.row_ptr), deg(rp))]
