@@ -3338,14 +3338,13 @@ static size_t bin_layout(const ad_graph *g, void *ws, size_t ws_bytes, BinLayout
     l.vkey = c.take<uint32_t>((size_t)std::max<int64_t>(1, g->n));
     l.cbrt_tab = c.take<double>((size_t)g->d_max + 1);
     l.budget = c.take<int32_t>((size_t)g->d_max + 1);
-    if (g->d_max > SORT_CAP) {
-        const int64_t nnz = std::max<int64_t>(1, 2 * g->m);
-        l.keys = c.take<unsigned long long>(nnz);
-        l.first_u = c.take<uint32_t>(nnz);
-        l.first_pos = c.take<uint32_t>(nnz);
-        l.order = c.take<uint32_t>(nnz);
-        l.rank = c.take<uint32_t>(nnz);
-    }
+    // of the rows longer than SORT_CAP
+    const int64_t nnz = g->d_max > SORT_CAP ? std::max<int64_t>(1, 2 * g->m) : 1;
+    l.keys = c.take<unsigned long long>(nnz);
+    l.first_u = c.take<uint32_t>(nnz);
+    l.first_pos = c.take<uint32_t>(nnz);
+    l.order = c.take<uint32_t>(nnz);
+    l.rank = c.take<uint32_t>(nnz);
     if (B) {
         l.sel = B->sel;
         *B = l;
