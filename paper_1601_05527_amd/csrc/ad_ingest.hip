@@ -558,16 +558,54 @@ __global__ void k_zero_counts(int64_t n, uint32_t *__restrict__ a, uint32_t *__r
 // starting at its vertex of least (degree, id)).
 constexpr uint32_t RC_UNSET = 0xffffffffu;
 
-__global__ void k_rc_init(int64_t n, const int64_t *__restrict__ row_ptr, const int32_t *__restrict__ root,
-                          uint32_t *__restrict__ size, unsigned long long *__restrict__ start,
-                          uint32_t *__restrict__ pos, uint32_t *__restrict__ par) {
-    for (int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; i < n; i += (int64_t)gridDim.x * blockDim.x) {
+// Sizes and starts of the components.  A workgroup takes a contiguous range of vertices
+// and gathers the share of its first vertex's component, mostly the giant one, in
+// LDS: two atomics on one address for every vertex took 11.9 ms at n = 2^20 (16M pairs
+// into this order 25.9 ms; 10.4 so).
+constexpr unsigned RC_BLOCKS = 512;
+
+__global__ __launch_bounds__(IBLOCK) void k_rc_init(int64_t n, const int64_t *__restrict__ row_ptr,
+                                                    const int32_t *__restrict__ root, uint32_t *__restrict__ size,
+                                                    unsigned long long *__restrict__ start,
+                                                    uint32_t *__restrict__ pos, uint32_t *__restrict__ par) {
+    __shared__ uint32_t cnt[IBLOCK / WAVE];
+    __shared__ unsigned long long low[IBLOCK / WAVE];
+    const int64_t per = ceil_div_dev(n, (int64_t)gridDim.x);
+    const int64_t i0 = (int64_t)blockIdx.x * per, i1 = min(n, i0 + per);
+    if (i0 >= i1) return;                                            // uniform over the workgroup
+    const int32_t own = root[i0];
+    uint32_t c = 0;
+    unsigned long long mn = ~0ull;
+    for (int64_t i = i0 + threadIdx.x; i < i1; i += IBLOCK) {
         const int32_t r = root[i];
         const unsigned long long d = (unsigned long long)(row_ptr[i + 1] - row_ptr[i]);
-        atomicAdd(&size[r], 1u);
-        atomicMin(&start[r], (d << 32) | (unsigned long long)i);
+        const unsigned long long code = (d << 32) | (unsigned long long)i;
+        if (r == own) {
+            ++c;
+            mn = min(mn, code);
+        } else {
+            atomicAdd(&size[r], 1u);
+            atomicMin(&start[r], code);
+        }
         pos[i] = RC_UNSET;
         par[i] = RC_UNSET;
+    }
+    for (int o = WAVE / 2; o >= 1; o >>= 1) {
+        c += __shfl_xor(c, o, WAVE);
+        mn = min(mn, (unsigned long long)__shfl_xor(mn, o, WAVE));
+    }
+    if ((threadIdx.x & (WAVE - 1)) == 0) {
+        cnt[threadIdx.x / WAVE] = c;
+        low[threadIdx.x / WAVE] = mn;
+    }
+    __syncthreads();
+    if (threadIdx.x == 0) {
+        for (int w = 1; w < IBLOCK / WAVE; ++w) {
+            c += cnt[w];
+            mn = min(mn, low[w]);
+        }
+        atomicAdd(&size[own], c);
+        atomicMin(&start[own], mn);
     }
 }
 
@@ -879,7 +917,7 @@ static ad_status rcm_order(int64_t n, int64_t m, const int64_t *row_ptr, const i
     if (s != AD_OK) return s;
     s = fill_i32((int32_t *)L.rc_cnt, 0, 2, st);
     if (s != AD_OK) return s;
-    hipLaunchKernelGGL(k_rc_init, dim3(igrid(n)), dim3(IBLOCK), 0, st, n, row_ptr, L.rc_root, L.rc_size, L.rc_start,
+    hipLaunchKernelGGL(k_rc_init, dim3(std::min<unsigned>(RC_BLOCKS, igrid(n))), dim3(IBLOCK), 0, st, n, row_ptr, L.rc_root, L.rc_size, L.rc_start,
                        L.rc_pos, L.rc_par);
     AD_LAUNCH_CHECK("k_rc_init");
     size_t tb = L.temp_bytes;
