@@ -477,7 +477,7 @@ struct MlAggregate {
         for (int u = 0; u < ML_U; ++u) {
             if (sj[u] != 1) continue;
             const double d = ml_strength(r[u], eps);
-            if (d < bd) continue;
+            if (!(d >= bd)) continue;                                // a NaN is never taken
             const int32_t k = orig_id ? orig_id[j[u]] : j[u];
             if (d > bd || k < bk) {
                 bd = d;

@@ -463,6 +463,43 @@ def test_coarsening_at_row_classes(api, edge, prec):
         np.testing.assert_array_equal(_np(agg), agg_o)
 
 
+@pytest.mark.parametrize("prec", ["f32", "f64"])
+@pytest.mark.parametrize("d", [5, 40, 200, 700, 3000])
+def test_coarsening_passes_over_nan_distances(api, d, prec):
+    """Rows of one step, of several, of a wave and of a workgroup with distances that
+    are NaN, infinite and tied: a vertex joins the seed neighbour of largest strength
+    among those that compare (NaN compares with nothing), ties by the smaller name.  Seeds equal the oracle's,
+    aggregates the rule's."""
+    announce(f"coarsening nan rows of {d} {prec}")
+    rng = np.random.default_rng(d)
+    n = 4 * d + 200
+    us, vs = [np.arange(8, n - 1)], [np.arange(9, n)]
+    for h in range(8):
+        us.append(np.full(d, h))
+        vs.append(rng.choice(np.arange(8, n), size=d, replace=False))
+    g = G.from_edges(n, np.concatenate(us), np.concatenate(vs))
+    g = G.relabel(g, rng.permutation(n))
+    rho = rng.integers(1, 6, g.m) / 8.0
+    pick = rng.integers(0, 4, g.m)
+    rho[pick == 0] = np.nan
+    rho[pick == 1] = np.inf
+    rho = rho.astype(np.float32 if prec == "f32" else np.float64)
+    agg, is_seed, nc = api.ml_aggregate(api.DeviceGraph.from_host(g, "cuda"), torch.from_numpy(rho).cuda(), 1e-12, 0.5)
+    seeds = oracle.ml_seeds(g, rho.astype(np.float64), 1e-12, 0.5)
+    np.testing.assert_array_equal(_np(is_seed), seeds)
+    rank = np.cumsum(seeds) - 1
+    want = np.where(seeds == 1, rank, -1)
+    r = rho.astype(np.float64)
+    delta = 1.0 / np.sqrt(r * r + 1e-12)
+    for i in np.nonzero(seeds == 0)[0]:
+        p = np.arange(g.row_ptr[i], g.row_ptr[i + 1])
+        p = p[(seeds[g.col[p]] == 1) & ~np.isnan(delta[g.eid[p]])]
+        if p.size:
+            want[i] = rank[g.col[p][np.lexsort((g.orig_id[g.col[p]], -delta[g.eid[p]]))[0]]]
+    assert nc == seeds.sum()
+    np.testing.assert_array_equal(_np(agg), want)
+
+
 @pytest.mark.parametrize("d_max", [(1 << 21) - 1, 1 << 21])
 def test_fit_side_records_of_both_widths(api, d_max):
     """The largest degree (a bound: tables are sized by it) picks 64-bit or 128-bit side
