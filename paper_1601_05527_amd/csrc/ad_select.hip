@@ -1564,7 +1564,8 @@ constexpr int STAGE = 2048;   // LDS staging of a block's candidates (entries)
 
 // Append the block's staged candidates to the global list (one reservation
 // per block and flush).  Every thread calls it, after a barrier that follows
-// the last staging write.
+// the last staging write; whether to call it is decided on a value of *n_stage that
+// no thread can have raised in between (it holds barriers).
 template <typename T>
 __device__ __forceinline__ void stage_flush(const T *stage, unsigned int *n_stage, unsigned long long *base_sh,
                                             T *dst, unsigned long long *dst_n, int64_t cap) {
@@ -1639,8 +1640,11 @@ __global__ __launch_bounds__(SBLOCK) void k_radix_hist(int64_t m, FitArrays fa, 
             }
         }
         if (COMPACT) {
+            // decided on one value by every wave: the next step's appends come after the second barrier
             __syncthreads();
-            if (n_stage > STAGE - STEP) stage_flush(stage, &n_stage, &base_sh, cs.v[o], &cs.n[o], cs.cap);
+            const unsigned int ns = n_stage;
+            __syncthreads();
+            if (ns > STAGE - STEP) stage_flush(stage, &n_stage, &base_sh, cs.v[o], &cs.n[o], cs.cap);
         }
     }
     run.flush(h);
@@ -1786,10 +1790,12 @@ __global__ __launch_bounds__(SBLOCK) void k_fit_count(int64_t m, const void *__r
             }
         }
         if (LIST) {
+            __syncthreads();                           // as in k_radix_hist
+            const unsigned int ns[2] = {n_stage[0], n_stage[1]};
             __syncthreads();
 #pragma unroll
             for (int o = 0; o < 2; ++o)
-                if (o < nfit && ca.active[o] && n_stage[o] > STAGE_M - SBLOCK * QU * 4)
+                if (o < nfit && ca.active[o] && ns[o] > STAGE_M - SBLOCK * QU * 4)
                     stage_flush(stage[LIST ? o : 0], &n_stage[o], &base_sh, ca.list[o], &ca.list_n[o], ca.list_cap);
         }
     }

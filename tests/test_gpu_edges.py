@@ -411,6 +411,51 @@ def test_fit_at_extreme_ranks(api, kind, target):
         np.testing.assert_array_equal(_np(keep), keep_o)
 
 
+def test_fit_stages_flushed_between_steps(api):
+    """2^24 edges of which the select's first digit and the exact check list whole steps of the
+    same workgroups (isolated edges, kept at every e, in 64 of every 2,048 blocks of 1,024 edges;
+    K_{128,128} elsewhere), so that the staged appends are flushed inside the loops while
+    the lists stay complete.  The smallest exponent is 0 with one edge a vertex; others are
+    checked against the selection at the exponent and one grid step (2^-40) below it."""
+    announce("fit stages")
+    P, d = 8, 128
+    per_n = 2 * 65_536 + 124 * 2 * d
+    a = torch.arange(65_536, device="cuda")
+    left = torch.arange(d, device="cuda").repeat_interleave(d)
+    right = d + torch.arange(d, device="cuda").repeat(d)
+    base = 2 * 65_536 + 2 * d * torch.arange(124, device="cuda")
+    u1 = torch.cat([2 * a, (base[:, None] + left).reshape(-1)])
+    v1 = torch.cat([2 * a + 1, (base[:, None] + right).reshape(-1)])
+    off = per_n * torch.arange(P, device="cuda")[:, None]
+    u, v = (off + u1).reshape(-1), (off + v1).reshape(-1)              # ascending: the edge ids
+    n, m = P * per_n, u.numel()
+    assert m == 1 << 24
+    e = torch.arange(m, device="cuda", dtype=torch.int32)
+    src, dst = torch.cat([u, v]), torch.cat([v, u])
+    o = torch.argsort(src * n + dst)
+    row_ptr = torch.zeros(n + 1, dtype=torch.int64, device="cuda")
+    row_ptr[1:] = torch.cumsum(torch.bincount(src, minlength=n), 0)
+    dg = api.DeviceGraph.from_tensors(dict(n=n, m=m, d_max=d, row_ptr=row_ptr, col=dst[o].to(torch.int32), w=None,
+                                           eid=torch.cat([e, e])[o], orig_id=torch.arange(n, device="cuda", dtype=torch.int32)))
+    gen = torch.Generator(device="cuda").manual_seed(3)
+    rho = torch.randperm(m, generator=gen, device="cuda").float()       # distinct
+    for target in (0.01, 0.045, 0.3):
+        kl, kg, nk, es = api.sparsify_fit_both(dg, rho, target)
+        K = int(np.ceil(target * m))
+        for orient, keep, e_fit, kept in ((0, kl, es[0], int(nk[0])), (1, kg, es[1], int(nk[1]))):
+            want, n_want = api.sparsify(dg, rho, orient, e_fit)
+            assert torch.equal(keep, want) and kept == int(n_want) == int(keep.sum(dtype=torch.int64))
+            assert kept >= K
+            if target == 0.01:
+                assert e_fit == 0.0
+                best = torch.full((n,), np.inf, device="cuda").scatter_reduce(
+                    0, src, torch.cat([rho, rho]) * (1 if orient == 0 else -1), "amin")
+                r = rho * (1 if orient == 0 else -1)
+                assert torch.equal(keep.bool(), (r == best[u]) | (r == best[v]))
+            else:
+                assert int(api.sparsify(dg, rho, orient, e_fit - 2.0 ** -40)[1]) < K
+
+
 # --------------------------------------------------- merging and coarsening --
 
 @pytest.mark.parametrize("spread", [1.0, 1e30])
