@@ -2080,13 +2080,26 @@ static ad_status rank_setup(const ad_graph *g, const SelLayout &L, uint8_t *zero
 }
 
 // A selection's streams for the row classes: three helper streams forked from
-// the caller's (rule above), or the caller's own.
+// the caller's (rule above), or the caller's own.  A call that returns an error between
+// open() and join() joins them too, in the destructor: their kernels use the
+// caller's workspace and outputs.
 struct ClassFork {
     RankFork *fk = nullptr;
     std::unique_lock<std::mutex> hold;
-    hipStream_t cls[3];
+    hipStream_t cls[3], caller = nullptr;
+    bool joined = false;
+    ClassFork() = default;
+    ClassFork(const ClassFork &) = delete;
+    ClassFork &operator=(const ClassFork &) = delete;
+    ~ClassFork() {
+        if (!fk || joined) return;
+        for (int h = 0; h < 3; ++h)
+            if (hipEventRecord(fk->join[h], fk->side[h]) != hipSuccess ||
+                hipStreamWaitEvent(caller, fk->join[h], 0) != hipSuccess)
+                (void)hipGetLastError();
+    }
     ad_status open(const ad_graph *g, hipStream_t st) {
-        cls[0] = cls[1] = cls[2] = st;
+        cls[0] = cls[1] = cls[2] = caller = st;
         if (g->d_max <= 64 || 2 * g->m < FORK_ENTRIES) return AD_OK;
         hipStreamCaptureStatus cap = hipStreamCaptureStatusNone;
         if (hipStreamIsCapturing(st, &cap) == hipSuccess && cap == hipStreamCaptureStatusNone) fk = rank_fork();
@@ -2101,12 +2114,13 @@ struct ClassFork {
         return AD_OK;
     }
     // the caller's stream waits for the three class streams
-    ad_status join(hipStream_t st) {
+    ad_status join() {
         if (!fk) return AD_OK;
         for (int h = 0; h < 3; ++h) {
             AD_HIP(hipEventRecord(fk->join[h], fk->side[h]));
-            AD_HIP(hipStreamWaitEvent(st, fk->join[h], 0));
+            AD_HIP(hipStreamWaitEvent(caller, fk->join[h], 0));
         }
+        joined = true;
         return AD_OK;
     }
 };
@@ -2214,7 +2228,7 @@ static ad_status rank_all(const ad_graph *g, const Tr *rho, const Emit &em, cons
             hipLaunchKernelGGL(k_hub_emit, dim3(2048), dim3(SBLOCK), 0, st, g->row_ptr, g->col, g->eid, em, L.hub);
             AD_LAUNCH_CHECK("k_hub_emit");
         }
-        const ad_status s = cf.join(st);
+        const ad_status s = cf.join();
         if (s != AD_OK) return s;
     } else {
         // FP64 rows: the same sorts on 64-bit codes, every class on the caller's stream
@@ -3410,7 +3424,7 @@ static ad_status bin_all(const ad_graph *g, const Tr *rho, const Emit &em, const
             AD_LAUNCH_CHECK("k_hub_rank");
         }
     }
-    return cf.join(st);
+    return cf.join();
 }
 
 static ad_status sparsify_binned_impl(const ad_graph *g, ad_dtype rho_dtype, const void *rho, uint64_t seed,

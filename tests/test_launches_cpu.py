@@ -1,0 +1,60 @@
+"""What calls enqueue, looked at without a device (fake_hip.c): the helper streams of a
+selection whose launch fails."""
+import json
+import os
+import shutil
+import subprocess
+import sys
+
+import pytest
+
+HERE = os.path.dirname(os.path.abspath(__file__))
+LIB = os.path.join(os.path.dirname(HERE), "paper_1601_05527_amd", "libad.so")
+STREAM = "7"
+
+
+@pytest.fixture(scope="module")
+def run(tmp_path_factory):
+    cc = shutil.which("gcc") or shutil.which("cc")
+    if cc is None or not os.path.exists(LIB):
+        pytest.skip("needs a C compiler and the built library")
+    shim = str(tmp_path_factory.mktemp("hip") / "libfake_hip.so")
+    subprocess.run([cc, "-O1", "-shared", "-fPIC", os.path.join(HERE, "fake_hip.c"), "-o", shim], check=True)
+
+    def call(*calls):
+        r = subprocess.run([sys.executable, os.path.join(HERE, "fake_launches.py"), shim, LIB, json.dumps(calls)],
+                           capture_output=True, text=True, timeout=300)
+        assert r.returncode == 0, r.stderr[-2000:]
+        return [json.loads(line) for line in r.stdout.splitlines()]
+
+    return call
+
+
+def _unjoined(log):
+    """Streams with work of this call that the caller's stream does not wait for at its end."""
+    last, event_of, joined = {}, {}, {}
+    for at, (what, *a) in enumerate(log):
+        if what == "launch":
+            last[a[0]] = at
+        elif what == "wait" and a[0] != STREAM:
+            last[a[0]] = at
+        elif what == "record":
+            event_of[a[1]] = (a[0], at)
+        elif what == "wait" and a[1] in event_of:
+            joined[event_of[a[1]][0]] = event_of[a[1]][1]
+    return [s for s, at in last.items() if s != STREAM and joined.get(s, -1) < at]
+
+
+@pytest.mark.parametrize("call,dtype", [("sparsify", 1), ("binned", 1), ("binned", 0)])
+def test_helper_streams_joined_when_a_launch_fails(run, call, dtype):
+    """Whichever launch of a selection on helper streams fails, the caller's stream waits for what
+    the helper streams were given before the call returns its error."""
+    c = dict(call=call, dtype=dtype, n=1 << 20, m=1 << 24, d_max=20_000)
+    whole = run(c)[0]
+    assert whole["status"] == 0 and not _unjoined(whole["log"])
+    n = sum(x[0] == "launch" for x in whole["log"])
+    assert n > 10 and len({x[1] for x in whole["log"] if x[0] == "launch"}) == 4
+    for at, r in enumerate(run(*[dict(c, fail_at=k) for k in range(1, n + 1)]), 1):
+        assert r["status"] != 0, at
+        assert not _unjoined(r["log"]), (at, r["log"])
+        assert r["pending"] == 0, at
