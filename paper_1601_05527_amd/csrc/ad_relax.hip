@@ -260,10 +260,42 @@ __device__ __forceinline__ double wave_sum(double v) {
     return v;
 }
 
-// A wave takes four vectors (one Philox block's words) of a chunk; the first also
-// sums s_i.  All of a chunk's vectors on one wave left the chip idle on small
-// graphs: 20 us at n = 2,000, R = 12, 8.5 here.
-template <typename T>
+// The component of chunk ch: the last one that starts at or before it.  Every component
+// has a chunk, so component c starts at chunk c or up to n_chunks - n_comp later.
+__device__ __forceinline__ int64_t chunk_comp(const int64_t *__restrict__ chunk_start, int64_t n_comp, int64_t n_chunks,
+                                              int64_t ch) {
+    int64_t lo = max((int64_t)0, ch - (n_chunks - n_comp)), hi = min(n_comp - 1, ch);
+    while (lo < hi) {
+        const int64_t mid = (lo + hi + 1) >> 1;
+        if (chunk_start[mid] <= ch) lo = mid;
+        else hi = mid - 1;
+    }
+    return lo;
+}
+
+// Where vector r's sum of chunk ch lies: part[r * per_r + ch * per_ch].  A vector's
+// sums together, so that the lanes that add a component's chunks share lines (with a chunk's
+// together the 8,192 chunks of an n = 2^21 component took 32 us, 14 so); a chunk's
+// together where at most two chunks make a component on average, and a chunk's wave
+// writes what nobody adds (2^18 components of two vertices: k_comp_partials a tenth
+// longer with a vector's together).
+struct PartAt {
+    int64_t per_r, per_ch;
+};
+static PartAt comp_part_at(int R, int64_t n_comp, int64_t n_chunks) {
+    return n_chunks <= 2 * n_comp ? PartAt{1, R} : PartAt{n_chunks, 1};
+}
+
+// Waves per chunk: one for every four vectors (a Philox block's words) where the
+// chunks alone leave the chip idle, else one, which finds its component and its members once.
+// R = 16, one wave / a wave per four: 16 chunks 20 / 8 us, 256 21 / 8.5, 1,024 23 / 16
+// (of two vertices each 13 / 9); 4,096 47 / 47 (20 / 24), 16,384 154 / 172 (57 / 85), 2^18 of two
+// vertices 684 / 1,440.
+constexpr int64_t COMP_SPLIT = 2048;     // chunks
+
+// The chunks' sums, a wave to a chunk or (SPLIT) to four vectors of it; the first also
+// sums s_i.
+template <typename T, bool SPLIT>
 __global__ __launch_bounds__(BLOCK) void k_comp_partials(int R, int64_t n_comp, int64_t n_chunks,
                                                         const int32_t *__restrict__ members,
                                                         const int64_t *__restrict__ comp_start,
@@ -272,59 +304,59 @@ __global__ __launch_bounds__(BLOCK) void k_comp_partials(int R, int64_t n_comp, 
                                                         const int32_t *__restrict__ orig_id, uint64_t seed,
                                                         uint64_t gid, const T *__restrict__ x0,
                                                         const int32_t *__restrict__ row_graph,
-                                                        double *__restrict__ part, double *__restrict__ part_s) {
+                                                        double *__restrict__ part, double *__restrict__ part_s,
+                                                        PartAt pa) {
     const int lane = threadIdx.x & (WAVE - 1);
     const int nq = (R + 3) >> 2;
-    const int64_t wv = (int64_t)blockIdx.x * (BLOCK / WAVE) + (threadIdx.x >> 6);
-    const int64_t ch = wv / nq;
-    const int q = (int)(wv - ch * nq);
-    if (ch >= n_chunks) return;                      // uniform across the wave
-    int64_t lo = 0, hi = n_comp - 1;                 // last component starting at or before ch
-    while (lo < hi) {
-        const int64_t mid = (lo + hi + 1) >> 1;
-        if (chunk_start[mid] <= ch) lo = mid;
-        else hi = mid - 1;
-    }
-    const int64_t p0 = comp_start[lo] + (ch - chunk_start[lo]) * COMP_CHUNK;
-    const int64_t p1 = min(comp_start[lo + 1], p0 + COMP_CHUNK);
-    double sacc = 0.0;
-    double acc[4] = {0.0, 0.0, 0.0, 0.0};
-    for (int64_t p = p0 + lane; p < p1; p += WAVE) {
-        const int32_t i = members[p];
-        const double s = (double)sdeg[i];
-        sacc += s;
-        if (x0) {
+    const int64_t nw = (int64_t)gridDim.x * (BLOCK / WAVE), items = SPLIT ? n_chunks * nq : n_chunks;
+    for (int64_t it = (int64_t)blockIdx.x * (BLOCK / WAVE) + (threadIdx.x >> 6); it < items; it += nw) {   // uniform across the wave
+        const int64_t ch = SPLIT ? it / nq : it;
+        const int qa = SPLIT ? (int)(it - ch * nq) : 0, qb = SPLIT ? qa + 1 : nq;
+        const int64_t lo = chunk_comp(chunk_start, n_comp, n_chunks, ch);
+        const int64_t p0 = comp_start[lo] + (ch - chunk_start[lo]) * COMP_CHUNK;
+        const int64_t p1 = min(comp_start[lo + 1], p0 + COMP_CHUNK);
+        double *out = part + 4 * qa * pa.per_r + ch * pa.per_ch;
+        for (int q = qa; q < qb; ++q) {
+            double sacc = 0.0;
+            double acc[4] = {0.0, 0.0, 0.0, 0.0};
+            for (int64_t p = p0 + lane; p < p1; p += WAVE) {
+                const int32_t i = members[p];
+                const double s = (double)sdeg[i];
+                sacc += s;
+                if (x0) {
 #pragma unroll
-            for (int c = 0; c < 4; ++c)
-                if (4 * q + c < R) acc[c] += s * (double)x0[(int64_t)i * R + 4 * q + c];
-        } else {
-            uint64_t words[4];
-            const int32_t key = orig_id ? orig_id[i] : i;
-            const uint64_t g = row_graph ? (uint64_t)row_graph[i] : 0ull;
-            philox4x64_10((uint64_t)(uint32_t)key, (uint64_t)q, 0, 0, seed, gid + g, words);
+                    for (int c = 0; c < 4; ++c)
+                        if (4 * q + c < R) acc[c] += s * (double)x0[(int64_t)i * R + 4 * q + c];
+                } else {
+                    uint64_t words[4];
+                    const int32_t key = orig_id ? orig_id[i] : i;
+                    const uint64_t g = row_graph ? (uint64_t)row_graph[i] : 0ull;
+                    philox4x64_10((uint64_t)(uint32_t)key, (uint64_t)q, 0, 0, seed, gid + g, words);
 #pragma unroll
-            for (int c = 0; c < 4; ++c) acc[c] += s * start_from_word(words[c]);
+                    for (int c = 0; c < 4; ++c) acc[c] += s * start_from_word(words[c]);
+                }
+            }
+            if (q == 0) {
+                sacc = wave_sum(sacc);
+                if (lane == 0) part_s[ch] = sacc;
+            }
+#pragma unroll
+            for (int c = 0; c < 4; ++c) {
+                const double v = wave_sum(acc[c]);
+                if (lane == 0 && 4 * q + c < R) *out = v;
+                out += pa.per_r;
+            }
         }
-    }
-    if (q == 0) {
-        sacc = wave_sum(sacc);
-        if (lane == 0) part_s[ch] = sacc;
-    }
-#pragma unroll
-    for (int c = 0; c < 4; ++c) {
-        const double v = wave_sum(acc[c]);
-        if (lane == 0 && 4 * q + c < R) part[(4 * q + c) * n_chunks + ch] = v;
     }
 }
 
-// Sums over the chunks of component c (chunk partials part_r[ch], one vector's, and
-// part_s[ch]; a vector's partials lie together, so that the lanes' loads share
-// lines: with a chunk's together the 8,192 chunks of an n = 2^21 component took
-// 21 us, 12 here) for one wave: lane l adds chunks c0 + l, c0 + l + 64, ... in
+// Sums over the chunks of component c (chunk partials part_r[ch * per_ch], one vector's, and
+// part_s[ch]) for one wave: lane l adds chunks c0 + l, c0 + l + 64, ... in
 // that order (eight loads in flight per lane), then a fixed shuffle tree
 // adds the lanes.  The order depends only on the component's chunk range.
 __device__ __forceinline__ void comp_chunk_sums(int64_t c0, int64_t c1, const double *__restrict__ part_r,
-                                                const double *__restrict__ part_s, double &S, double &X) {
+                                                int64_t per_ch, const double *__restrict__ part_s, double &S,
+                                                double &X) {
     const int lane = threadIdx.x & (WAVE - 1);
     constexpr int B = 8;
     double s = 0.0, x = 0.0;
@@ -334,7 +366,7 @@ __device__ __forceinline__ void comp_chunk_sums(int64_t c0, int64_t c1, const do
 #pragma unroll
         for (int u = 0; u < B; ++u) {
             b[u] = part_s[ch + (int64_t)u * WAVE];
-            a[u] = part_r[ch + (int64_t)u * WAVE];
+            a[u] = part_r[(ch + (int64_t)u * WAVE) * per_ch];
         }
 #pragma unroll
         for (int u = 0; u < B; ++u) {
@@ -344,7 +376,7 @@ __device__ __forceinline__ void comp_chunk_sums(int64_t c0, int64_t c1, const do
     }
     for (; ch < c1; ch += WAVE) {
         s += part_s[ch];
-        x += part_r[ch];
+        x += part_r[ch * per_ch];
     }
     S = wave_sum(s);
     X = wave_sum(x);
@@ -353,7 +385,7 @@ __device__ __forceinline__ void comp_chunk_sums(int64_t c0, int64_t c1, const do
 // shift[c][r] = the weighted mean of component c rounded to the 2^-24 grid:
 // one wave per (component, vector).  Also empties the running min / max codes
 // of every graph (MM_SLOTS copies, mm_count words).
-__global__ __launch_bounds__(BLOCK) void k_comp_finalize(int R, int64_t n_comp, int64_t n_chunks,
+__global__ __launch_bounds__(BLOCK) void k_comp_finalize(int R, int64_t n_comp, PartAt pa,
                                                         const int64_t *__restrict__ chunk_start,
                                                         const double *__restrict__ part,
                                                         const double *__restrict__ part_s, int centre,
@@ -367,7 +399,7 @@ __global__ __launch_bounds__(BLOCK) void k_comp_finalize(int R, int64_t n_comp, 
         const int64_t c = idx / R;
         const int r = (int)(idx - c * R);
         double S, X;
-        comp_chunk_sums(chunk_start[c], chunk_start[c + 1], part + r * n_chunks, part_s, S, X);
+        comp_chunk_sums(chunk_start[c], chunk_start[c + 1], part + r * pa.per_r, pa.per_ch, part_s, S, X);
         if ((threadIdx.x & (WAVE - 1)) == 0)
             shift[idx] = (centre && S > 0.0) ? rint((X / S) * 16777216.0) * (1.0 / 16777216.0) : 0.0;
     }
@@ -384,16 +416,12 @@ __global__ __launch_bounds__(BLOCK) void k_comp_drift_partials(int R, int64_t n_
                                                               const int64_t *__restrict__ comp_start,
                                                               const int64_t *__restrict__ chunk_start,
                                                               const float *__restrict__ sdeg,
-                                                              const T *__restrict__ x, double *__restrict__ part) {
+                                                              const T *__restrict__ x, double *__restrict__ part,
+                                                              PartAt pa) {
     const int lane = threadIdx.x & (WAVE - 1);
     const int64_t ch = (int64_t)blockIdx.x * (BLOCK / WAVE) + (threadIdx.x >> 6);
     if (ch >= n_chunks) return;                      // uniform across the wave
-    int64_t lo = 0, hi = n_comp - 1;
-    while (lo < hi) {
-        const int64_t mid = (lo + hi + 1) >> 1;
-        if (chunk_start[mid] <= ch) lo = mid;
-        else hi = mid - 1;
-    }
+    const int64_t lo = chunk_comp(chunk_start, n_comp, n_chunks, ch);
     const int64_t p0 = comp_start[lo] + (ch - chunk_start[lo]) * COMP_CHUNK;
     const int64_t p1 = min(comp_start[lo + 1], p0 + COMP_CHUNK);
     // G vectors per pass (G divides R), read with one load per member
@@ -412,12 +440,12 @@ __global__ __launch_bounds__(BLOCK) void k_comp_drift_partials(int R, int64_t n_
 #pragma unroll
         for (int c = 0; c < G; ++c) {
             const double v = wave_sum(acc[c]);
-            if (lane == 0) part[(q0 + c) * n_chunks + ch] = v;
+            if (lane == 0) part[(q0 + c) * pa.per_r + ch * pa.per_ch] = v;
         }
     }
 }
 
-__global__ __launch_bounds__(BLOCK) void k_comp_drift(int R, int64_t n_comp, int64_t n_chunks,
+__global__ __launch_bounds__(BLOCK) void k_comp_drift(int R, int64_t n_comp, PartAt pa,
                                                      const int64_t *__restrict__ chunk_start,
                                                      const double *__restrict__ part,
                                                      const double *__restrict__ part_s, float *__restrict__ drift,
@@ -428,7 +456,7 @@ __global__ __launch_bounds__(BLOCK) void k_comp_drift(int R, int64_t n_comp, int
         const int64_t c = idx / R;
         const int r = (int)(idx - c * R);
         double S, X;
-        comp_chunk_sums(chunk_start[c], chunk_start[c + 1], part + r * n_chunks, part_s, S, X);
+        comp_chunk_sums(chunk_start[c], chunk_start[c + 1], part + r * pa.per_r, pa.per_ch, part_s, S, X);
         if ((threadIdx.x & (WAVE - 1)) == 0) {
             const float d = S > 0.0 ? (float)(X / S) : 0.0f;
             drift[idx] = d;
@@ -1537,22 +1565,29 @@ static ad_status relax_impl(const ad_graph *g, const ad_relax_opts *o, const voi
 
     // the shifts: written straight into shift_out when the caller wants them
     double *shift = shift_out ? shift_out : L.shift;
+    const PartAt pa = comp ? comp_part_at(R, comp->n_comp, comp->n_chunks) : PartAt{1, R};
     if (n > 0) {
         s = weighted_degree_impl<A>(g, (A *)L.inv_s, L.sdeg, L.s64, P.p32, st);
         if (s != AD_OK) return s;
     }
     if (comp) {
         if (n > 0 && comp->n_chunks > 0) {
-            hipLaunchKernelGGL((k_comp_partials<T>), dim3((unsigned)ceil_div(comp->n_chunks * ((R + 3) / 4), BLOCK / WAVE)),
-                               dim3(BLOCK), 0, st, R, comp->n_comp, comp->n_chunks, comp->members, comp->comp_start,
-                               comp->chunk_start, L.sdeg, g->orig_id, o->seed, o->graph_id, (const T *)x0,
-                               sg.row_graph, L.part, L.part_s);
+            const bool split = comp->n_chunks <= COMP_SPLIT;
+            const int64_t waves = comp->n_chunks * (split ? (R + 3) / 4 : 1);
+            const dim3 pgrid((unsigned)std::min<int64_t>((int64_t)1 << 20, ceil_div(waves, BLOCK / WAVE)));
+#define AD_PARTIALS(SPLIT)                                                                                      \
+    hipLaunchKernelGGL((k_comp_partials<T, SPLIT>), pgrid, dim3(BLOCK), 0, st, R, comp->n_comp, comp->n_chunks,  \
+                       comp->members, comp->comp_start, comp->chunk_start, L.sdeg, g->orig_id, o->seed,        \
+                       o->graph_id, (const T *)x0, sg.row_graph, L.part, L.part_s, pa)
+            if (split) AD_PARTIALS(true);
+            else AD_PARTIALS(false);
+#undef AD_PARTIALS
             AD_LAUNCH_CHECK("k_comp_partials");
         }
         const int64_t cr = std::max<int64_t>(1, comp->n_comp * R);
         const int64_t mmc = (int64_t)MM_SLOTS * sg.G * 2 * R;
         hipLaunchKernelGGL(k_comp_finalize, dim3((unsigned)std::min<int64_t>(ceil_div(cr, BLOCK / WAVE), 1 << 16)), dim3(BLOCK), 0, st, R,
-                           comp->n_comp, comp->n_chunks, comp->chunk_start, L.part, L.part_s, 1, shift, mmc, L.mm);
+                           comp->n_comp, pa, comp->chunk_start, L.part, L.part_s, 1, shift, mmc, L.mm);
         AD_LAUNCH_CHECK("k_comp_finalize");
     } else {
         if (n > 0 && nb > 0) {
@@ -1613,7 +1648,7 @@ static ad_status relax_impl(const ad_graph *g, const ad_relax_opts *o, const voi
             if (L.drift && dst.t == AD_BF16 && t >= 2 && comp->n_comp > 0) {
                 const dim3 dgrid((unsigned)ceil_div(comp->n_chunks, BLOCK / WAVE));
 #define AD_DRIFT_ARGS R, comp->n_comp, comp->n_chunks, comp->members, comp->comp_start, comp->chunk_start, L.sdeg, \
-                      (const bf16 *)cur.p, L.part
+                      (const bf16 *)cur.p, L.part, pa
                 if (R % 8 == 0)
                     hipLaunchKernelGGL((k_comp_drift_partials<bf16, 8>), dgrid, dim3(BLOCK), 0, st, AD_DRIFT_ARGS);
                 else if (R % 4 == 0)
@@ -1624,7 +1659,7 @@ static ad_status relax_impl(const ad_graph *g, const ad_relax_opts *o, const voi
                 AD_LAUNCH_CHECK("k_comp_drift_partials");
                 const int64_t cr = comp->n_comp * R;
                 hipLaunchKernelGGL(k_comp_drift, dim3((unsigned)std::min<int64_t>(ceil_div(cr, BLOCK / WAVE), 1 << 16)), dim3(BLOCK), 0, st, R,
-                                   comp->n_comp, comp->n_chunks, comp->chunk_start, L.part, L.part_s, L.drift, shift);
+                                   comp->n_comp, pa, comp->chunk_start, L.part, L.part_s, L.drift, shift);
                 AD_LAUNCH_CHECK("k_comp_drift");
                 dr.c = L.drift;
                 dr.comp_of = comp->comp_of;

@@ -382,6 +382,51 @@ def test_plans_at_their_sizes(api, n, R):
         np.testing.assert_allclose(rho, want, rtol=1e-11, atol=1e-12)
 
 
+# ------------------------------------------------------ centring of components --
+
+@pytest.mark.parametrize("chunks", [1, 2047, 2048, 2049])
+@pytest.mark.parametrize("R", [3, 16])
+def test_centring_at_chunk_counts(api, chunks, R):
+    """One component of so many chunks (256 members each) and as many components of one, around
+    the count where a chunk goes from several waves to one.  FP64 storage: the
+    oracle's values up to the summation order of a mean, as for the plans."""
+    announce(f"centring chunks={chunks} R={R}")
+    for kind in ("one", "each"):
+        n = 256 * chunks - 3 if kind == "one" else 3 * chunks
+        u, v = np.arange(n - 1), np.arange(1, n)
+        if kind == "each":
+            u, v = u[v % 3 != 0], v[v % 3 != 0]
+        g = G.from_edges(n, u, v)
+        dg = api.DeviceGraph.from_host(g, "cuda")
+        c = dg.components()
+        assert (c.n_comp, c.n_chunks) == ((1, chunks) if kind == "one" else (chunks, chunks))
+        res = api.relax(dg, R, 3, omega=0.5, seed=4, store="f64")
+        rho = _np(api.edge_dist(dg, res.x, res.minmax))
+        np.testing.assert_allclose(rho, oracle.algebraic_distance(g, R, 3, 0.5, seed=4), rtol=1e-11, atol=1e-12)
+
+
+@pytest.mark.parametrize("store", ["f32", "f64", "bf16"])
+@pytest.mark.parametrize("R", [6, 16])
+def test_centring_sums_of_either_layout(api, store, R):
+    """Small components relax to the same bits beside a component of a thousand chunks
+    (whose sums lie by vector) and without it (by chunk)."""
+    announce(f"centring layouts {store} R={R}")
+    small = np.arange(0, 900)
+    u, v = small[:-1][small[1:] % 3 != 0], small[1:][small[1:] % 3 != 0]
+    long_ = np.arange(900, 900 + 256 * 1000)
+    both = G.from_edges(long_[-1] + 1, np.concatenate([u, long_[:-1]]), np.concatenate([v, long_[1:]]))
+    out = []
+    for g in (G.from_edges(900, u, v), both):
+        dg = api.DeviceGraph.from_host(g, "cuda")
+        c = dg.components()
+        assert c.n_comp == (300 if g.n == 900 else 301) and c.n_chunks == (300 if g.n == 900 else 1300)
+        kw = dict(fp32_tail=3, fp64_tail=1) if store == "bf16" else {}
+        res = api.relax(dg, R, 12, omega=0.5, seed=9, store=store, **kw)
+        out.append((_np(res.x)[:900], _np(res.shift)[_np(c.comp_of)[:900]]))
+    np.testing.assert_array_equal(out[0][0], out[1][0])
+    np.testing.assert_array_equal(out[0][1], out[1][1])
+
+
 # ------------------------------------------------------------ retention fit --
 
 @pytest.mark.parametrize("target", [1e-9, 0.34, 0.999999, 1.0])

@@ -1,5 +1,5 @@
 """What calls enqueue, looked at without a device (fake_hip.c): the helper streams of a
-selection whose launch fails."""
+selection whose launch fails, and launch shapes at sizes beyond any test's memory."""
 import json
 import os
 import shutil
@@ -58,3 +58,20 @@ def test_helper_streams_joined_when_a_launch_fails(run, call, dtype):
         assert r["status"] != 0, at
         assert not _unjoined(r["log"]), (at, r["log"])
         assert r["pending"] == 0, at
+
+
+def _check_shapes(r):
+    """The runtime takes fewer than 2^32 threads per grid dimension, and none empty."""
+    assert r["status"] == 0
+    for x in r["log"]:
+        if x[0] == "launch":
+            g = [int(v) for v in x[3:9]]
+            assert all(0 < g[i] * g[i + 3] < 1 << 32 for i in range(3)), x
+
+
+@pytest.mark.parametrize("store", [0, 1, 2])
+@pytest.mark.parametrize("R", [16, 20, 64])
+def test_relaxation_of_many_components_launches(run, store, R):
+    n_comp = 1 << 24                      # of two vertices each
+    _check_shapes(run(dict(call="relax", n=2 * n_comp, m=1 << 28, d_max=5000, R=R, k=3, store=store, n_comp=n_comp,
+                           n_chunks=n_comp))[0])
