@@ -299,7 +299,8 @@ __global__ __launch_bounds__(BB) void k_adj_step(int64_t n, const int64_t *__res
                                                  const float *__restrict__ mu, float *__restrict__ g,
                                                  float *__restrict__ lam_out, float *__restrict__ mu_out, int R,
                                                  int CP, int S, int64_t hub_d, const int32_t *__restrict__ hubs,
-                                                 const unsigned int *__restrict__ hub_count, unsigned int hub_blocks) {
+                                                 const unsigned int *__restrict__ hub_count, unsigned int hub_blocks,
+                                                 int64_t row_blocks) {
     constexpr int NW = BB / WAVE;
     __shared__ float part[NW][WAVE][2 * VEC];
     const int c = threadIdx.x % CP;
@@ -307,8 +308,10 @@ __global__ __launch_bounds__(BB) void k_adj_step(int64_t n, const int64_t *__res
     a.off = c * VEC;
     a.on = a.off < R;
     const bool hub = blockIdx.x < hub_blocks;
-    const unsigned int nh = hub ? *hub_count : 1u;
-    for (unsigned int h = hub ? blockIdx.x : 0u; h < nh; h += hub ? hub_blocks : 1u) {
+    // the workgroup's listed rows, or its blocks of BB / (CP * S) rows
+    const int64_t items = hub ? (int64_t)*hub_count : row_blocks;
+    const unsigned int stride = hub ? hub_blocks : gridDim.x - hub_blocks;
+    for (int64_t h = hub ? blockIdx.x : blockIdx.x - hub_blocks; h < items; h += stride) {
         int64_t row;
         if (hub) {
             row = hubs[h];
@@ -316,14 +319,14 @@ __global__ __launch_bounds__(BB) void k_adj_step(int64_t n, const int64_t *__res
             a.step = BB / CP;
         } else {
             const int group = CP * S;
-            row = (int64_t)(blockIdx.x - hub_blocks) * (BB / group) + threadIdx.x / group;
+            row = h * (BB / group) + threadIdx.x / group;
             a.slot = (threadIdx.x % group) / CP;
             a.step = S;
-            if (row >= n) return;                                    // uniform over the group
+            if (row >= n) continue;                                  // uniform over the group
         }
         a.beg = row_ptr[row];
         a.end = row_ptr[row + 1];
-        if (!hub && a.end - a.beg > hub_d) return;                   // uniform over the group
+        if (!hub && a.end - a.beg > hub_d) continue;                 // uniform over the group
         a.is = inv_s[row];
         float li[VEC], ay[VEC], am[VEC], xv[ADJ_U][VEC];
 #pragma unroll
@@ -451,6 +454,10 @@ static ad_status launch_rb(const ad_graph *g, const ad_relax_opts *o, const floa
     return AD_OK;
 }
 
+// Workgroups for rows, each with several blocks of them on larger graphs: 64 lanes to
+// every row of a graph of 2^26 would be 2^32 threads, more than a launch takes.
+constexpr int64_t STEP_BLOCKS = (int64_t)1 << 16;
+
 template <int VEC>
 static ad_status launch_step(const ad_graph *g, const BwdLayout &L, const SweepPlan &plan, float omega,
                              const float *xprev, const float *lam, const float *mu, float *lam_out, float *mu_out,
@@ -459,16 +466,19 @@ static ad_status launch_step(const ad_graph *g, const BwdLayout &L, const SweepP
     while (cp * VEC < R) cp *= 2;
     // slots: a chunk holds 1.5 times the average row, so that most rows need one.  Average
     // 4, R = 8, entries per slot x slots: 4 x 2 19.4 us a step, 4 x 1 21.4, 2 x 2 22.1,
-    // 2 x 4 25.1, 8 x 1 22.7, 8 x 2 32.1
+    // 2 x 4 25.1, 8 x 1 22.7, 8 x 2 32.1.  One count for all rows also serves skewed
+    // degrees (a gradient with the former sweeps, lanes planned per 64 rows / here: power law of
+    // average 32, n = 2^16, R = 8 3.75 / 1.50 ms, n = 2^20 25.4 / 15.2, 10 sweeps; R-MAT 2^17 17.4 / 4.4)
     const double avg = 2.0 * (double)g->m / (double)g->n;
     int slots = 1;
     while (2 * cp * slots <= WAVE && 2 * slots * ADJ_U < 3 * avg) slots *= 2;
     // a listed row has more than hub_d of the 2m entries
     const unsigned hub_blocks = (unsigned)std::min<int64_t>(512, 2 * g->m / (plan.sh.hub_d + 1));
     const int64_t blocks = ceil_div(g->n, BB / (cp * slots));
-    hipLaunchKernelGGL((k_adj_step<VEC>), dim3((unsigned)(hub_blocks + blocks)), dim3(BB), 0, st, g->n, g->row_ptr,
+    const unsigned grid = hub_blocks + (unsigned)std::min<int64_t>(STEP_BLOCKS, blocks);
+    hipLaunchKernelGGL((k_adj_step<VEC>), dim3(grid), dim3(BB), 0, st, g->n, g->row_ptr,
                        g->col, g->w, L.inv_s, omega, xprev, lam, mu, L.g, lam_out, mu_out, R, cp, slots,
-                       plan.sh.hub_d, plan.hub_list, plan.hub_count, hub_blocks);
+                       plan.sh.hub_d, plan.hub_list, plan.hub_count, hub_blocks, blocks);
     AD_LAUNCH_CHECK("k_adj_step");
     return AD_OK;
 }

@@ -353,6 +353,30 @@ def test_adjoint_rows_of_every_kind(api, R, kind):
     assert per.max() <= 1e-3
 
 
+@pytest.mark.parametrize("n", [262_144, 262_145, 600_001])
+def test_adjoint_of_more_rows_than_lanes_in_flight(api, n):
+    """R = 33 takes 64 lanes a row: from 262,145 rows on, a workgroup of the reverse step handles
+    several blocks of rows.  Bounds as above."""
+    announce(f"adjoint n={n}")
+    rng = np.random.default_rng(n)
+    R, k = 33, 3
+    hub = rng.choice(np.arange(3, n), size=700, replace=False)
+    u, v = np.concatenate([np.arange(n - 1), np.full(700, 1)]), np.concatenate([np.arange(1, n), hub])
+    g = G.from_edges(n, u, v)
+    g = G.with_weights(g, rng.uniform(0.5, 2.0, g.m).astype(np.float32))
+    c = rng.normal(size=g.m)
+    dg = api.DeviceGraph.from_host(g, "cuda")
+    w = torch.from_numpy(g.edge_w.astype(np.float32)).cuda().requires_grad_(True)
+    rho = api.AlgDist.apply(w, dg, R, k, 0.5, 3, 2)
+    (torch.from_numpy(c.astype(np.float32)).cuda() * rho).sum().backward()
+    got = _np(w.grad).astype(np.float64)
+    want = oracle.grad_weights(g, c, R, k, 0.5, x0=oracle.start_vectors(g.n, R, 3, 0, g.orig_id))
+    per = np.abs(got - want) / (np.abs(want) + 1e-3 * np.abs(want).max())
+    print(f"rel L2 {np.linalg.norm(got - want) / np.linalg.norm(want):.3e}  max per-edge {per.max():.3e}")
+    assert np.linalg.norm(got - want) <= 1e-4 * np.linalg.norm(want)
+    assert per.max() <= 1e-3
+
+
 # ------------------------------------------- launch plans and set-up passes --
 
 @pytest.mark.parametrize("n", [3, 64, 65, 1024, 1025, 2048, 2049, 32_768, 32_769, 262_144, 262_145])

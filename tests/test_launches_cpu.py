@@ -75,3 +75,10 @@ def test_relaxation_of_many_components_launches(run, store, R):
     n_comp = 1 << 24                      # of two vertices each
     _check_shapes(run(dict(call="relax", n=2 * n_comp, m=1 << 28, d_max=5000, R=R, k=3, store=store, n_comp=n_comp,
                            n_chunks=n_comp))[0])
+
+
+@pytest.mark.parametrize("n,m,R", [(1 << 27, 1 << 30, 16), ((1 << 26) + 5, 1 << 26, 33), ((1 << 26) + 5, 1 << 20, 63),
+                                   (1 << 30, 1 << 30, 8)])
+def test_gradient_of_many_rows_launches(run, n, m, R):
+    _check_shapes(run(dict(call="backward", n=n, m=m, d_max=5000, R=R, k=4, store=1, ckpt=2, n_comp=1,
+                           n_chunks=n // 256 + 1))[0])
