@@ -1035,73 +1035,151 @@ __global__ void k_plan_fill(int64_t n, const int *__restrict__ tile_lg, const un
     }
 }
 
-// The plan and the hub list (hub_list not NULL) of one graph in a single launch: a
-// wave per tile, one append per workgroup of PLAN_WG tiles to the plan and to
-// the list; with one workgroup the counts start in LDS, otherwise they are zeroed
-// before.  The plan's order is then that of the workgroups' appends, which a static
-// walk does not mind.  For up to PLAN_ONCE tiles: the appends of one address
-// are served one by one, 45 ns each, and beyond 256 of them cost what
-// the tiles, three scans and the fill take in launches (seven with the hub list, 27 us
-// at any size up to there; 6.8 us here at n = 2,000).
+// The plan and the hub list (hub_list not NULL) of one graph, both in row order, in one
+// launch of one workgroup (up to PLAN_SOLO tiles) or in two: every workgroup of
+// PLAN_WG tiles, a wave each, adds up its entries, then places them behind those of the
+// workgroups before it, whose sums it reads.  In the order of the workgroups' arrival
+// (an append by each) the walk loses the balance that rows stored by degree give it:
+// n = 2^16, m = 500,000, FP64, R = 16, 20 sweeps 742 us, 582 in row order.  Up to PLAN_ONCE
+// tiles, where a workgroup's sums to read are at most one per thread; the general form
+// takes six launches, or eight with the hub list: n = 2^20, m = 16M 46 us, 16 so (the
+// distances' plan, with a search per row, 69 / 40); n = 2^18 38 / 10.
 constexpr int PLAN_WG = 16;
-constexpr int64_t PLAN_ONCE = 4096, PLAN_SOLO = 32;     // tiles; one workgroup up to PLAN_SOLO
+constexpr int64_t PLAN_ONCE = (int64_t)PLAN_WG * PLAN_WG * WAVE, PLAN_SOLO = 32;     // tiles
 
-__global__ __launch_bounds__(PLAN_WG * WAVE) void k_plan_once(int64_t n, const int64_t *__restrict__ row_ptr,
+struct PlanRows {                          // one tile, of the wave that holds it
+    int64_t r0, r1;                        // r1 <= r0: no tile
+    int lg;
+    unsigned int nw;                       // plan entries
+    unsigned long long hubs;               // lanes whose row is long
+};
+__device__ __forceinline__ unsigned long long plan_hubs(const int64_t *__restrict__ row_ptr, int64_t r0, int64_t r1,
+                                                        int64_t hub_d) {
+    const int64_t i = r0 + (threadIdx.x & (WAVE - 1));
+    return __ballot(i < r1 && row_ptr[i + 1] - row_ptr[i] > hub_d);
+}
+__device__ __forceinline__ PlanRows plan_rows(int64_t n, const int64_t *__restrict__ row_ptr,
+                                              const int32_t *__restrict__ col, int upper_only, int64_t hub_d,
+                                              int spr_max, int rpw_fixed, int64_t t) {
+    PlanRows p;
+    p.r0 = t * PLAN_TILE;
+    p.r1 = min(n, p.r0 + PLAN_TILE);
+    const int64_t i = p.r0 + (threadIdx.x & (WAVE - 1));
+    int64_t d = 0;
+    bool hub = false;
+    if (i < p.r1) {
+        const int64_t beg = row_ptr[i], end = row_ptr[i + 1];
+        hub = end - beg > hub_d;
+        if (!hub) d = upper_only ? end - upper_start(col, beg, end, i) : end - beg;
+    }
+    for (int o = WAVE / 2; o >= 1; o >>= 1) d = max(d, (int64_t)__shfl_xor(d, o, WAVE));
+    p.lg = tile_lg_of(d, spr_max, rpw_fixed);
+    p.nw = p.r1 > p.r0 ? (unsigned int)ceil_div_dev(p.r1 - p.r0, (int64_t)1 << p.lg) : 0u;
+    p.hubs = __ballot(hub);
+    return p;
+}
+// The tile's entries from plan[po] on, its hub rows from hub_list[ho] on.
+__device__ __forceinline__ void plan_put(const PlanRows &p, unsigned int po, unsigned int ho,
+                                         long long *__restrict__ plan, int32_t *__restrict__ hub_list) {
+    const int lane = threadIdx.x & (WAVE - 1);
+    if ((unsigned int)lane < p.nw) {
+        const int64_t r = p.r0 + ((int64_t)lane << p.lg);
+        plan[po + lane] = ((long long)r << 16) | ((long long)min((int64_t)1 << p.lg, p.r1 - r) << 8) | p.lg;
+    }
+    if (hub_list && ((p.hubs >> lane) & 1))
+        hub_list[ho + __popcll(p.hubs & (((unsigned long long)1 << lane) - 1))] = (int32_t)(p.r0 + lane);
+}
+
+__global__ __launch_bounds__(PLAN_WG * WAVE) void k_plan_solo(int64_t n, const int64_t *__restrict__ row_ptr,
                                                               const int32_t *__restrict__ col, int upper_only,
                                                               int64_t hub_d, int spr_max, int rpw_fixed,
                                                               long long *__restrict__ plan,
                                                               unsigned int *__restrict__ plan_count,
                                                               int32_t *__restrict__ hub_list,
                                                               unsigned int *__restrict__ hub_count, int64_t ntiles) {
-    __shared__ unsigned int waves[PLAN_WG], hubs[PLAN_WG], base[2], count[2];
-    const int lane = threadIdx.x & (WAVE - 1), wv = threadIdx.x >> 6;
-    const bool solo = gridDim.x == 1;
-    if (threadIdx.x < 2) count[threadIdx.x] = 0u;
-    for (int64_t t0 = (int64_t)blockIdx.x * PLAN_WG; t0 < ntiles; t0 += (int64_t)gridDim.x * PLAN_WG) {
-        const int64_t r0 = (t0 + wv) * PLAN_TILE, r1 = min(n, r0 + PLAN_TILE);   // r1 <= r0: no tile
-        const int64_t i = r0 + lane;
-        int64_t d = 0;
-        bool hub = false;
-        if (i < r1) {
-            const int64_t beg = row_ptr[i], end = row_ptr[i + 1];
-            hub = end - beg > hub_d;
-            if (!hub) d = upper_only ? end - upper_start(col, beg, end, i) : end - beg;
-        }
-        int64_t dm = d;
-        for (int o = WAVE / 2; o >= 1; o >>= 1) dm = max(dm, (int64_t)__shfl_xor(dm, o, WAVE));
-        const int lg = tile_lg_of(dm, spr_max, rpw_fixed);
-        const unsigned int nw = r1 > r0 ? (unsigned int)ceil_div_dev(r1 - r0, (int64_t)1 << lg) : 0u;
-        const unsigned long long hm = hub_list ? __ballot(hub) : 0ull;
-        if (lane == 0) {
-            waves[wv] = nw;
-            hubs[wv] = (unsigned int)__popcll(hm);
+    __shared__ unsigned int waves[PLAN_WG], hubs[PLAN_WG];
+    const int wv = threadIdx.x >> 6;
+    unsigned int po = 0, ho = 0;                                     // before this turn's tiles
+    for (int64_t t0 = 0; t0 < ntiles; t0 += PLAN_WG) {
+        const PlanRows p = plan_rows(n, row_ptr, col, upper_only, hub_d, spr_max, rpw_fixed, t0 + wv);
+        if ((threadIdx.x & (WAVE - 1)) == 0) {
+            waves[wv] = p.nw;
+            hubs[wv] = (unsigned int)__popcll(p.hubs);
         }
         __syncthreads();
-        if (threadIdx.x < 2) {
-            const unsigned int *of = threadIdx.x == 0 ? waves : hubs;
-            unsigned int tot = 0;
-            for (int w = 0; w < PLAN_WG; ++w) tot += of[w];
-            unsigned int b = count[threadIdx.x];
-            if (solo) count[threadIdx.x] = b + tot;
-            else if (tot) b = atomicAdd(threadIdx.x == 0 ? plan_count : hub_count, tot);
-            base[threadIdx.x] = b;
-        }
-        __syncthreads();
-        unsigned int po = base[0], ho = base[1];
-        for (int w = 0; w < wv; ++w) {
+        unsigned int pb = po, hb = ho;
+        for (int w = 0; w < PLAN_WG; ++w) {
+            if (w == wv) {
+                pb = po;
+                hb = ho;
+            }
             po += waves[w];
             ho += hubs[w];
         }
-        if ((unsigned int)lane < nw) {
-            const int64_t r = r0 + ((int64_t)lane << lg);
-            plan[po + lane] = ((long long)r << 16) | ((long long)min((int64_t)1 << lg, r1 - r) << 8) | lg;
-        }
-        if ((hm >> lane) & 1) hub_list[ho + __popcll(hm & (((unsigned long long)1 << lane) - 1))] = (int32_t)i;
-        __syncthreads();                                             // waves, hubs and base are written again
+        plan_put(p, pb, hb, plan, hub_list);
+        __syncthreads();                                             // waves and hubs are written again
     }
-    if (solo && threadIdx.x == 0) {
-        *plan_count = count[0];
-        if (hub_list) *hub_count = count[1];
+    if (threadIdx.x == 0) {
+        *plan_count = po;
+        if (hub_list) *hub_count = ho;
+    }
+}
+
+// Hub rows (upper half) and plan entries of every workgroup's tiles.
+__global__ __launch_bounds__(PLAN_WG * WAVE) void k_plan_sums(int64_t n, const int64_t *__restrict__ row_ptr,
+                                                              const int32_t *__restrict__ col, int upper_only,
+                                                              int64_t hub_d, int spr_max, int rpw_fixed,
+                                                              int *__restrict__ tile_lg,
+                                                              unsigned long long *__restrict__ sums, int64_t ntiles) {
+    __shared__ unsigned long long part[PLAN_WG];
+    const int wv = threadIdx.x >> 6;
+    const int64_t t = (int64_t)blockIdx.x * PLAN_WG + wv;
+    const PlanRows p = plan_rows(n, row_ptr, col, upper_only, hub_d, spr_max, rpw_fixed, t);
+    if ((threadIdx.x & (WAVE - 1)) == 0) {
+        if (t < ntiles) tile_lg[t] = p.lg;
+        part[wv] = ((unsigned long long)__popcll(p.hubs) << 32) | p.nw;
+    }
+    __syncthreads();
+    if (threadIdx.x == 0) {
+        unsigned long long s = 0;
+        for (int w = 0; w < PLAN_WG; ++w) s += part[w];
+        sums[blockIdx.x] = s;
+    }
+}
+
+__global__ __launch_bounds__(PLAN_WG * WAVE) void k_plan_place(int64_t n, const int64_t *__restrict__ row_ptr,
+                                                               int64_t hub_d, const int *__restrict__ tile_lg,
+                                                               const unsigned long long *__restrict__ sums,
+                                                               long long *__restrict__ plan,
+                                                               unsigned int *__restrict__ plan_count,
+                                                               int32_t *__restrict__ hub_list,
+                                                               unsigned int *__restrict__ hub_count, int64_t ntiles) {
+    __shared__ unsigned long long part[PLAN_WG], own[PLAN_WG];
+    const int lane = threadIdx.x & (WAVE - 1), wv = threadIdx.x >> 6;
+    const int64_t t = (int64_t)blockIdx.x * PLAN_WG + wv;
+    unsigned long long s = threadIdx.x < blockIdx.x ? sums[threadIdx.x] : 0ull;
+    PlanRows p;
+    p.r0 = t * PLAN_TILE;
+    p.r1 = min(n, p.r0 + PLAN_TILE);
+    p.lg = t < ntiles ? tile_lg[t] : 0;
+    p.nw = p.r1 > p.r0 ? (unsigned int)ceil_div_dev(p.r1 - p.r0, (int64_t)1 << p.lg) : 0u;
+    p.hubs = hub_list ? plan_hubs(row_ptr, p.r0, p.r1, hub_d) : 0ull;
+    for (int o = WAVE / 2; o >= 1; o >>= 1) s += __shfl_xor(s, o, WAVE);
+    if (lane == 0) {
+        part[wv] = s;
+        own[wv] = ((unsigned long long)__popcll(p.hubs) << 32) | p.nw;
+    }
+    __syncthreads();
+    unsigned long long at = 0, mine = 0;
+    for (int w = 0; w < PLAN_WG; ++w) at += part[w];
+    for (int w = 0; w < PLAN_WG; ++w) {
+        if (w == wv) mine = at;
+        at += own[w];
+    }
+    plan_put(p, (unsigned int)mine, (unsigned int)(mine >> 32), plan, hub_list);
+    if (blockIdx.x == gridDim.x - 1 && threadIdx.x == 0) {
+        *plan_count = (unsigned int)at;
+        if (hub_list) *hub_count = (unsigned int)(at >> 32);
     }
 }
 
@@ -1230,9 +1308,9 @@ void sweep_plan_carve(Carver &c, int64_t n, int64_t ntiles_cap, SweepPlan &p) {
     const int64_t nn = std::max<int64_t>(1, n);
     const int64_t ntiles = std::max<int64_t>(1, ntiles_cap);
     p.hub_list = c.take<int32_t>(nn);
-    p.hub_count = c.take<unsigned int>(2);
-    p.plan_count = p.hub_count ? p.hub_count + 1 : nullptr;      // zeroed together
+    p.hub_count = c.take<unsigned int>(1);
     p.plan = c.take<long long>(nn + ntiles);
+    p.plan_count = c.take<unsigned int>(1);
     p.tile_lg = c.take<int>(ntiles);
     p.tile_waves = c.take<unsigned int>(ntiles);
     p.tile_nnz = c.take<unsigned long long>(ntiles);
@@ -1250,16 +1328,19 @@ ad_status sweep_plan_build(const ad_graph *g, SweepPlan &p, bool build_hubs, con
     const int64_t ntiles = sg.tile_off ? sg.ntiles : ceil_div(g->n, PLAN_TILE);
     if (p.xcd_groups <= 1 && !sg.tile_off && ntiles > 0 && ntiles <= PLAN_ONCE) {
         p.turn = 0;
-        if (ntiles > PLAN_SOLO) {
-            // hub_count is another plan's when the hubs are not built here
-            s = fill_i32((int32_t *)(build_hubs ? p.hub_count : p.plan_count), 0, build_hubs ? 2 : 1, st);
-            if (s != AD_OK) return s;
+        int32_t *const hubs = build_hubs ? p.hub_list : nullptr;
+        const unsigned wgs = (unsigned)ceil_div(ntiles, PLAN_WG);
+        if (ntiles <= PLAN_SOLO) {
+            hipLaunchKernelGGL(k_plan_solo, dim3(1), dim3(PLAN_WG * WAVE), 0, st, g->n, g->row_ptr, g->col,
+                               p.sh.upper_only, p.sh.hub_d, p.sh.SPRW, p.sh.rpw_fixed, p.plan, p.plan_count, hubs,
+                               p.hub_count, ntiles);
+        } else {
+            hipLaunchKernelGGL(k_plan_sums, dim3(wgs), dim3(PLAN_WG * WAVE), 0, st, g->n, g->row_ptr, g->col,
+                               p.sh.upper_only, p.sh.hub_d, p.sh.SPRW, p.sh.rpw_fixed, p.tile_lg, p.tile_nnz, ntiles);
+            hipLaunchKernelGGL(k_plan_place, dim3(wgs), dim3(PLAN_WG * WAVE), 0, st, g->n, g->row_ptr, p.sh.hub_d,
+                               p.tile_lg, p.tile_nnz, p.plan, p.plan_count, hubs, p.hub_count, ntiles);
         }
-        hipLaunchKernelGGL(k_plan_once, dim3(ntiles <= PLAN_SOLO ? 1u : (unsigned)ceil_div(ntiles, PLAN_WG)),
-                           dim3(PLAN_WG * WAVE), 0, st, g->n, g->row_ptr, g->col, p.sh.upper_only, p.sh.hub_d,
-                           p.sh.SPRW, p.sh.rpw_fixed, p.plan, p.plan_count, build_hubs ? p.hub_list : nullptr,
-                           p.hub_count, ntiles);
-        AD_LAUNCH_CHECK("k_plan_once");
+        AD_LAUNCH_CHECK("k_plan_place");
         return AD_OK;
     }
     // every queue set starts at zero; each launch then clears the set the launch after next uses

@@ -406,6 +406,28 @@ def test_plans_at_their_sizes(api, n, R):
         np.testing.assert_allclose(rho, want, rtol=1e-11, atol=1e-12)
 
 
+@pytest.mark.parametrize("n", [(1 << 20) - 63, 1 << 20, (1 << 20) + 1])
+def test_plans_of_a_thousand_workgroups(api, n):
+    """The plan's two-launch form up to the last workgroup whose predecessors' sums are one per
+    thread, and the general form after it; long rows at both ends.  Tolerance as above."""
+    announce(f"plans n={n}")
+    rng = np.random.default_rng(n)
+    us, vs = [np.arange(n - 1)], [np.arange(1, n)]
+    for h, d in ((n - 1, 600), (7, 300), (n // 2, 5000)):
+        us.append(np.full(d, h))
+        vs.append(rng.choice(n, size=d, replace=False))
+    u, v = np.concatenate(us), np.concatenate(vs)
+    lo, hi = np.minimum(u, v), np.maximum(u, v)
+    key = np.unique((lo * n + hi)[lo != hi])
+    g = G.from_edges(n, key // n, key % n)
+    dg = api.DeviceGraph.from_host(g, "cuda")
+    want = oracle.algebraic_distance(g, 2, 3, 0.5, seed=4)
+    for hub in (0, 1):
+        res = api.relax(dg, 2, 3, omega=0.5, seed=4, store="f64", hub_degree=hub)
+        rho = _np(api.edge_dist(dg, res.x, res.minmax))
+        np.testing.assert_allclose(rho, want, rtol=1e-11, atol=1e-12)
+
+
 # ------------------------------------------------------ centring of components --
 
 @pytest.mark.parametrize("chunks", [1, 2047, 2048, 2049])
