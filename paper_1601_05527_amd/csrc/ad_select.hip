@@ -772,6 +772,7 @@ __device__ __forceinline__ void rank_radix_row(RadixShared<TB, IPT, Tr> &sh, int
             const int64_t p = beg + v[s];
             const int32_t id = nbr_id(p, col[p], col_orig, orig_id);
             int before = 0;
+#pragma unroll 4
             for (int r = a; r < b; ++r) {
                 const int64_t pr = beg + sh.row.place[r];
                 before += nbr_id(pr, col[pr], col_orig, orig_id) < id ? 1 : 0;
@@ -1152,80 +1153,112 @@ __global__ __launch_bounds__(SBLOCK) void k_hub_rank32(
 
 // The same for a partition on the 64-bit codes of FP64 distances: keys in
 // hs.key, places in hs.pos, every entry emitted here (a NaN with the ranks
-// k_rank_radix gives it).
+// k_rank_radix gives it).  A wave ranks a piece of HUB_PIECE keys against the whole
+// bucket: the first HUB_WGS workgroups take the buckets' first pieces; equal distances
+// share a bucket of any size, whose further pieces go round HUB_REST workgroups, each with a
+// lane per bucket to find those that have any.  (One wave for a whole bucket: 100,000 equal
+// distances in a row 8.3 s, counting the row's entries against one another 4.7 s.)
+constexpr int HUB_PIECE = HUB_KPL / 2 * WAVE;
+constexpr unsigned HUB_WGS = 2048, HUB_REST = 2048, HUB_TURN = 32;     // HUB_TURN: waves per 64 buckets
+static_assert((HUB_TURN & (HUB_TURN - 1)) == 0, "turns count modulo 2^32");
+
+__device__ __forceinline__ void hub_rank64_piece(const int64_t *__restrict__ row_ptr, const int32_t *__restrict__ col,
+                                                 const int32_t *__restrict__ eid, const int32_t *__restrict__ orig_id,
+                                                 const int32_t *__restrict__ col_orig, const Emit &em,
+                                                 const HubScratch &hs, unsigned int w, uint32_t c, uint32_t c0) {
+    constexpr int KPL = HUB_PIECE / WAVE;
+    const int lane = threadIdx.x & (WAVE - 1);
+    const int64_t row = hs.bk_row[w];
+    const int64_t beg = row_ptr[row];
+    const int64_t d = row_ptr[row + 1] - beg;
+    const uint32_t off = hs.bk_off[w];
+    const unsigned long long *bk = hs.key + beg + off;
+    const uint32_t *bp = hs.pos + beg + off;
+    unsigned long long key[KPL];
+    int64_t pos[KPL];
+    int32_t id[KPL];
+    int lt[KPL], eq[KPL], eqlt[KPL];
+    bool tie = false;
+#pragma unroll
+    for (int t = 0; t < KPL; ++t) {
+        const uint32_t q = c0 + t * WAVE + lane;
+        key[t] = q < c ? bk[q] : 0ull;
+        pos[t] = q < c ? beg + bp[q] : beg;
+        lt[t] = eq[t] = eqlt[t] = id[t] = 0;
+    }
+    for (uint32_t s0 = 0; s0 < c; s0 += WAVE) {
+        const unsigned long long mine = (s0 + lane < c) ? bk[s0 + lane] : 0ull;
+        const int lim = (int)min((uint32_t)WAVE, c - s0);
+        for (int src = 0; src < lim; ++src) {
+            const unsigned long long kb = shfl(mine, src);
+#pragma unroll
+            for (int t = 0; t < KPL; ++t) {
+                lt[t] += (kb < key[t]) ? 1 : 0;
+                eq[t] += (kb == key[t]) ? 1 : 0;
+            }
+        }
+    }
+#pragma unroll
+    for (int t = 0; t < KPL; ++t) tie = tie || (c0 + t * WAVE + lane < c && eq[t] > 1);
+    if (__any(tie)) {                          // uniform across the wave
+#pragma unroll
+        for (int t = 0; t < KPL; ++t)
+            if (c0 + t * WAVE + lane < c) id[t] = nbr_id(pos[t], col[pos[t]], col_orig, orig_id);
+        for (uint32_t s0 = 0; s0 < c; s0 += WAVE) {
+            unsigned long long mine = 0ull;
+            int32_t mid = 0;
+            if (s0 + lane < c) {
+                mine = bk[s0 + lane];
+                const int64_t p = beg + bp[s0 + lane];
+                mid = nbr_id(p, col[p], col_orig, orig_id);
+            }
+            const int lim = (int)min((uint32_t)WAVE, c - s0);
+            for (int src = 0; src < lim; ++src) {
+                const unsigned long long kb = shfl(mine, src);
+                const int32_t ib = shfl(mid, src);
+#pragma unroll
+                for (int t = 0; t < KPL; ++t) eqlt[t] += (kb == key[t] && ib < id[t]) ? 1 : 0;
+            }
+        }
+    }
+#pragma unroll
+    for (int t = 0; t < KPL; ++t) {
+        if (c0 + t * WAVE + lane >= c) continue;
+        int64_t rl = (int64_t)off + lt[t] + eqlt[t], rg = d - (int64_t)off - lt[t] - eq[t] + eqlt[t];
+        if (rank_code_nan(key[t])) {
+            rl = 0;
+            rg = d;
+        }
+        emit_ranks(em, row, col[pos[t]], eid[pos[t]], d, rl, rg);
+    }
+}
+
 __global__ __launch_bounds__(SBLOCK) void k_hub_rank64(
     const int64_t *__restrict__ row_ptr, const int32_t *__restrict__ col, const int32_t *__restrict__ eid,
     const int32_t *__restrict__ orig_id, const int32_t *__restrict__ col_orig, Emit em, HubScratch hs) {
-    constexpr int KPL = HUB_KPL / 2;
-    const int lane = threadIdx.x & (WAVE - 1);
+    const int lane = threadIdx.x & (WAVE - 1), wave = threadIdx.x >> 6;
     const unsigned int nb = (unsigned int)min((int64_t)(*hs.nbk), hs.cap);
-    const unsigned int waves = gridDim.x * (SBLOCK / WAVE);
-    for (unsigned int w = blockIdx.x * (SBLOCK / WAVE) + (threadIdx.x >> 6); w < nb; w += waves) {
-        const uint32_t c = hs.bk_cnt[w];
-        const int64_t row = hs.bk_row[w];
-        const int64_t beg = row_ptr[row];
-        const int64_t d = row_ptr[row + 1] - beg;
-        const uint32_t off = hs.bk_off[w];
-        const unsigned long long *bk = hs.key + beg + off;
-        const uint32_t *bp = hs.pos + beg + off;
-        for (uint32_t c0 = 0; c0 < c; c0 += KPL * WAVE) {
-            unsigned long long key[KPL];
-            int64_t pos[KPL];
-            int32_t id[KPL];
-            int lt[KPL], eq[KPL], eqlt[KPL];
-            bool tie = false;
-#pragma unroll
-            for (int t = 0; t < KPL; ++t) {
-                const uint32_t q = c0 + t * WAVE + lane;
-                key[t] = q < c ? bk[q] : 0ull;
-                pos[t] = q < c ? beg + bp[q] : beg;
-                lt[t] = eq[t] = eqlt[t] = id[t] = 0;
-            }
-            for (uint32_t s0 = 0; s0 < c; s0 += WAVE) {
-                const unsigned long long mine = (s0 + lane < c) ? bk[s0 + lane] : 0ull;
-                const int lim = (int)min((uint32_t)WAVE, c - s0);
-                for (int src = 0; src < lim; ++src) {
-                    const unsigned long long kb = shfl(mine, src);
-#pragma unroll
-                    for (int t = 0; t < KPL; ++t) {
-                        lt[t] += (kb < key[t]) ? 1 : 0;
-                        eq[t] += (kb == key[t]) ? 1 : 0;
-                    }
-                }
-            }
-#pragma unroll
-            for (int t = 0; t < KPL; ++t) tie = tie || (c0 + t * WAVE + lane < c && eq[t] > 1);
-            if (__any(tie)) {                          // uniform across the wave
-#pragma unroll
-                for (int t = 0; t < KPL; ++t)
-                    if (c0 + t * WAVE + lane < c) id[t] = nbr_id(pos[t], col[pos[t]], col_orig, orig_id);
-                for (uint32_t s0 = 0; s0 < c; s0 += WAVE) {
-                    unsigned long long mine = 0ull;
-                    int32_t mid = 0;
-                    if (s0 + lane < c) {
-                        mine = bk[s0 + lane];
-                        const int64_t p = beg + bp[s0 + lane];
-                        mid = nbr_id(p, col[p], col_orig, orig_id);
-                    }
-                    const int lim = (int)min((uint32_t)WAVE, c - s0);
-                    for (int src = 0; src < lim; ++src) {
-                        const unsigned long long kb = shfl(mine, src);
-                        const int32_t ib = shfl(mid, src);
-#pragma unroll
-                        for (int t = 0; t < KPL; ++t) eqlt[t] += (kb == key[t] && ib < id[t]) ? 1 : 0;
-                    }
-                }
-            }
-#pragma unroll
-            for (int t = 0; t < KPL; ++t) {
-                if (c0 + t * WAVE + lane >= c) continue;
-                int64_t rl = (int64_t)off + lt[t] + eqlt[t], rg = d - (int64_t)off - lt[t] - eq[t] + eqlt[t];
-                if (rank_code_nan(key[t])) {
-                    rl = 0;
-                    rg = d;
-                }
-                emit_ranks(em, row, col[pos[t]], eid[pos[t]], d, rl, rg);
-            }
+    if (blockIdx.x < HUB_WGS) {
+        for (unsigned int w = blockIdx.x * (SBLOCK / WAVE) + wave; w < nb; w += HUB_WGS * (SBLOCK / WAVE)) {
+            const uint32_t c = hs.bk_cnt[w];
+            if (c) hub_rank64_piece(row_ptr, col, eid, orig_id, col_orig, em, hs, w, c, 0u);
+        }
+        return;
+    }
+    constexpr unsigned GROUPS = HUB_REST / HUB_TURN * (SBLOCK / WAVE);     // 64 buckets each, HUB_TURN waves to a group
+    const unsigned int turn = (blockIdx.x - HUB_WGS) % HUB_TURN;
+    for (unsigned int g = (blockIdx.x - HUB_WGS) / HUB_TURN * (SBLOCK / WAVE) + wave; (uint64_t)g * WAVE < nb; g += GROUPS) {
+        const unsigned int b0 = g * WAVE;
+        const uint32_t mine = b0 + lane < nb ? hs.bk_cnt[b0 + lane] : 0u;
+        unsigned long long todo = __ballot(mine > HUB_PIECE);
+        unsigned int k = 0;                                          // further pieces so far, dealt to the turns
+        while (todo) {
+            const int s = __ffsll((long long)todo) - 1;
+            todo &= todo - 1;
+            const uint32_t c = __shfl(mine, s, WAVE), np = (c - 1) / HUB_PIECE;
+            for (unsigned int q = (turn - k) % HUB_TURN; q < np; q += HUB_TURN)
+                hub_rank64_piece(row_ptr, col, eid, orig_id, col_orig, em, hs, b0 + s, c, (q + 1) * HUB_PIECE);
+            k += np;
         }
     }
 }
@@ -2251,7 +2284,7 @@ static ad_status rank_all(const ad_graph *g, const Tr *rho, const Emit &em, cons
                                lst[HUB_CLASS], &L.cnt[HUB_CLASS], g->row_ptr, g->eid, rd, (const double *)nullptr,
                                (const unsigned long long *)nullptr, L.hub);
             AD_LAUNCH_CHECK("k_hub_partition");
-            hipLaunchKernelGGL(k_hub_rank64, dim3(2048), dim3(SBLOCK), 0, st, g->row_ptr, g->col, g->eid, g->orig_id,
+            hipLaunchKernelGGL(k_hub_rank64, dim3(HUB_WGS + HUB_REST), dim3(SBLOCK), 0, st, g->row_ptr, g->col, g->eid, g->orig_id,
                                g->col_orig, em, L.hub);
             AD_LAUNCH_CHECK("k_hub_rank64");
         }

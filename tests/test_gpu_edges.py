@@ -209,6 +209,38 @@ def test_fp64_rows_of_every_length(api, values):
         assert int(nk.item()) == ref.sum()
 
 
+@pytest.mark.parametrize("d", [8196, 8448, 20_000])
+@pytest.mark.parametrize("values", [1, 2, 40])
+def test_fp64_long_rows_of_equal_distances(api, d, values):
+    """A hub whose distances take a few values, so that a bucket holds thousands of ties, which
+    names decide; its neighbours, joined in fours, never choose the hub's edge.  Kept edges
+    equal those of ranks counted on the host."""
+    announce(f"fp64 ties d={d} values={values}")
+    rng = np.random.default_rng(d + values)
+    leaf = np.arange(1, d + 1)
+    a, b = np.triu_indices(4, 1)
+    quad = 1 + 4 * np.arange(d // 4)[:, None]
+    g = G.from_edges(d + 1, np.concatenate([np.zeros(d, int), (quad + a).ravel()]),
+                     np.concatenate([leaf, (quad + b).ravel()]))
+    g = G.relabel(g, rng.permutation(g.n))
+    hub = int(np.argmax(np.diff(g.row_ptr)))
+    of_hub = (g.edge_u == hub) | (g.edge_v == hub)
+    dg = api.DeviceGraph.from_host(g, "cuda")
+    for orient in (0, 1):
+        rho = np.where(of_hub, 2.0 + rng.integers(0, values, g.m), rng.random(g.m) + (0.0 if orient == 0 else 1000.0))
+        if values == 40:
+            rho[of_hub & (rng.random(g.m) < 0.3)] = np.nan
+        keep, nk = api.sparsify(dg, torch.from_numpy(rho).cuda(), orient, 0.4)
+        bud = api.budget_table(g.d_max, 0.4)
+        ref = np.zeros(g.m, np.uint8)
+        for i in range(g.n):
+            p = slice(g.row_ptr[i], g.row_ptr[i + 1])
+            ref[g.eid[p][_counted_ranks(g, rho, i)[orient] < bud[p.stop - p.start]]] = 1
+        assert ref[of_hub].sum() < d and (orient == 1 or ref[of_hub].sum() > 0)    # the GLOBAL order ranks NaNs first
+        np.testing.assert_array_equal(_np(keep), ref)
+        assert int(nk.item()) == ref.sum()
+
+
 # ------------------------------------------------- plan of the short rows --
 
 @pytest.mark.parametrize("n", [1, 63, 64, 65, 1023, 1025, 70_000])
