@@ -466,12 +466,51 @@ __global__ void k_clustering(int64_t n, const int64_t *__restrict__ row_ptr, con
 // Every vertex starts under the smaller of itself and its first neighbour (the
 // smallest one: rows are ascending), a plain store per vertex.  In a
 // connected power-law graph stored by degree that already hangs most
-// vertices under vertex 0, two or three steps up.
-__global__ void k_hook_first(int64_t n, const int64_t *__restrict__ row_ptr, const int32_t *__restrict__ col,
-                             int32_t *__restrict__ parent) {
-    for (int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; i < n; i += (int64_t)gridDim.x * blockDim.x) {
-        const int64_t b = row_ptr[i];
-        parent[i] = row_ptr[i + 1] > b ? min((int32_t)i, col[b]) : (int32_t)i;
+// vertices under vertex 0, two or three steps up.  Where neighbours are stored near one another
+// (meshes row by row, banded orders) it makes chains as long as the band is narrow, so
+// a workgroup first follows the parents inside its HOOK_ROWS vertices in LDS, by
+// doubling, until they lie outside or are roots.
+constexpr int HOOK_TB = 1024, HOOK_ROWS = 4096;
+
+__global__ __launch_bounds__(HOOK_TB) void k_hook_first(int64_t n, const int64_t *__restrict__ row_ptr,
+                                                        const int32_t *__restrict__ col,
+                                                        int32_t *__restrict__ parent) {
+    constexpr int K = HOOK_ROWS / HOOK_TB;
+    __shared__ int32_t par[HOOK_ROWS];
+    const int64_t base = (int64_t)blockIdx.x * HOOK_ROWS;
+#pragma unroll
+    for (int u = 0; u < K; ++u) {
+        const int k = u * HOOK_TB + (int)threadIdx.x;
+        const int64_t i = base + k;
+        int32_t p = (int32_t)i;
+        if (i < n) {
+            const int64_t b = row_ptr[i];
+            if (row_ptr[i + 1] > b) p = min(p, col[b]);
+        }
+        par[k] = p;
+    }
+    // any value read is an ancestor, whichever thread wrote it last
+    auto at = [&](int k) { return __hip_atomic_load(&par[k], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP); };
+    int moved;
+    do {
+        __syncthreads();
+        moved = 0;
+#pragma unroll
+        for (int u = 0; u < K; ++u) {
+            const int k = u * HOOK_TB + (int)threadIdx.x;
+            const int32_t p = at(k);
+            if (p < base || p == base + k) continue;
+            const int32_t q = at((int)(p - base));
+            if (q != p) {
+                __hip_atomic_store(&par[k], q, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+                moved = 1;
+            }
+        }
+    } while (__syncthreads_or(moved));
+#pragma unroll
+    for (int u = 0; u < K; ++u) {
+        const int k = u * HOOK_TB + (int)threadIdx.x;
+        if (base + k < n) parent[base + k] = at(k);
     }
 }
 
@@ -535,12 +574,22 @@ __device__ __forceinline__ void uf_union(int32_t *parent, int32_t a, int32_t b) 
 // ancestor, so a late halving by another thread cannot replace it).  Between
 // the joins the root may be out of date, which is harmless; after the last
 // join's kernel it is the tree's.
-__global__ void k_flatten(int64_t n, int32_t *__restrict__ parent) {
-    for (int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; i < n; i += (int64_t)gridDim.x * blockDim.x) {
-        const int32_t p = uf_seen(parent, (int32_t)i);
-        if (p == (int32_t)i || p == 0) continue;
-        const int32_t r = uf_root(parent, p);
-        if (r != p) atomicMin(&parent[i], r);
+// A wave whose parents are all one vertex looks its root up once.
+__global__ __launch_bounds__(PBLOCK) void k_flatten(int64_t n, int32_t *__restrict__ parent) {
+    const int lane = threadIdx.x & (WAVE - 1);
+    const int64_t step = (int64_t)gridDim.x * blockDim.x;
+    for (int64_t base = (int64_t)blockIdx.x * blockDim.x + (threadIdx.x - lane); base < n; base += step) {
+        const int64_t i = base + lane;
+        const int32_t p = i < n ? uf_seen(parent, (int32_t)i) : 0;
+        const bool go = p != 0 && p != (int32_t)i;
+        const unsigned long long want = __ballot(go);
+        if (!want) continue;
+        const int lead = __ffsll((long long)want) - 1;
+        const bool one = __all(!go || p == __shfl(p, lead, WAVE));
+        int32_t r = p;
+        if (one ? lane == lead : go) r = uf_root(parent, p);
+        if (one) r = __shfl(r, lead, WAVE);
+        if (go && r != p) atomicMin(&parent[i], r);
     }
 }
 
@@ -565,8 +614,10 @@ __global__ void k_union_roots(int64_t n, const int64_t *__restrict__ row_ptr, co
 }
 
 // All entries of the remaining rows (an entry joined before finds its two
-// roots equal): a wave finds the rows of its 64 that do not hang under 0 and
-// walks each of them with all its lanes.
+// roots equal): a wave finds the rows of its 64 that do not hang under 0; rows of up to
+// UF_LANE entries are walked by their own lanes, longer ones by all of the wave's.
+constexpr int64_t UF_LANE = 4;
+
 __global__ __launch_bounds__(PBLOCK) void k_union_rest(int64_t n, const int64_t *__restrict__ row_ptr,
                                                        const int32_t *__restrict__ col, int32_t *__restrict__ parent) {
     const int lane = threadIdx.x & (WAVE - 1);
@@ -579,7 +630,10 @@ __global__ __launch_bounds__(PBLOCK) void k_union_rest(int64_t n, const int64_t 
             b = row_ptr[mine];
             e = row_ptr[mine + 1];
         }
-        unsigned long long todo = __ballot(b < e);
+        const bool small = e - b <= UF_LANE;
+        if (small)
+            for (int64_t p = b; p < e; ++p) uf_union(parent, (int32_t)mine, col[p]);
+        unsigned long long todo = __ballot(!small);
         while (todo) {
             const int t = __ffsll((long long)todo) - 1;
             todo &= todo - 1;
@@ -761,11 +815,14 @@ static size_t prop_layout(const ad_graph *g, void *ws, size_t ws_bytes, PropLayo
 // Bound by the dependent parent lookups.  n = 2^20, m = 16M stored by degree:
 // 2.3 ms with the first two entries of every row joined by compare-and-swap
 // and every lookup at device scope (2.1 ms of it one address, the hub's),
-// 0.035 ms here (six launches).
+// 0.035 ms here (six launches).  A component build, so / here, and with the chains left to
+// k_flatten: 2,048 x 2,048 mesh row by row 3.63 / 0.49 (0.65) ms, path of 2^22 vertices in order
+// 8 to 11 / 0.53 (16.3), 2^19 pairs 0.34 / 0.29 (their rows walked by whole waves: 0.37).
 ad_status label_components(const ad_graph *g, int32_t *parent, unsigned int *flags, hipStream_t stream) {
     (void)flags;
     const int64_t n = g->n;
-    hipLaunchKernelGGL(k_hook_first, dim3(pgrid(n)), dim3(PBLOCK), 0, stream, n, g->row_ptr, g->col, parent);
+    hipLaunchKernelGGL(k_hook_first, dim3((unsigned)std::max<int64_t>(1, ceil_div(n, HOOK_ROWS))), dim3(HOOK_TB), 0, stream, n,
+                       g->row_ptr, g->col, parent);
     AD_LAUNCH_CHECK("k_hook_first");
     if (g->m > 0) {
         hipLaunchKernelGGL(k_flatten, dim3(pgrid(n)), dim3(PBLOCK), 0, stream, n, parent);

@@ -132,6 +132,30 @@ def test_component_labels(api, kind):
     assert got["n_components"] == ref["n_components"]
 
 
+@pytest.mark.parametrize("n", [2, 4095, 4096, 4097, 8193, 70_001])
+@pytest.mark.parametrize("stride", [1, 3, 64, 5000])
+def test_component_labels_of_banded_orders(api, n, stride):
+    """Paths through every stride-th vertex, with cuts, stored in order: chains of parents inside
+    and across the workgroups' ranges of 4,096 vertices.  A vertex's label is the smallest of its path."""
+    announce(f"component labels of bands n={n} stride={stride}")
+    u = np.arange(max(0, n - stride))
+    u = u[(u // stride) % 1777 != 1776]
+    if u.size == 0:
+        u = np.array([0])
+    g = G.from_edges(n, u, np.minimum(u + stride, n - 1))
+    want = np.arange(n)
+    for a, b in zip(g.edge_u, g.edge_v):               # ascending
+        want[b] = want[a]
+    dg = api.DeviceGraph.from_host(g, "cuda")
+    got = api.graph_properties(dg)
+    np.testing.assert_array_equal(_np(got["comp"]), want)
+    assert got["n_components"] == np.unique(want).size
+    c = dg.components()
+    live = np.diff(g.row_ptr) > 0
+    assert c.n_comp == np.unique(want[live]).size
+    np.testing.assert_array_equal(_np(c.comp_of)[:n] >= 0, live)
+
+
 # ------------------------------------------------------------------ batch --
 
 @pytest.mark.parametrize("sizes", [(16384, 1, 16383, 15, 17, 16385), (3, 5, 7, 40_000, 2), (32768,)])
