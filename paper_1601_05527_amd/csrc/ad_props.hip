@@ -88,7 +88,14 @@ constexpr int TRI_SMALL = 64;            // rows up to here: 16 lanes each; long
 constexpr int TRI_HUB = 4096;            // rows from here: TRI_SLICES workgroups
 constexpr int TRI_SLICES = 16;
 constexpr int TRI_CAP = 512;             // N+ entries in a workgroup's table (1,024: 10% slower, fewer
-                                         // workgroups fit); more take further passes
+                                         // workgroups fit)
+// More take further passes, each of which walks all rows of N-: where that would be three or
+// more (dense graphs), a table of TRI_WIDE_CAP entries at half load, by TRI_WIDE_SLICES
+// workgroups of TRI_WIDE_B.  Cliques of 2,000 and 4,000: 7.6 and 84 ms in passes of 512 (searching
+// whole rows 7.0 and 51), 6.0 and 44 so; n = 4,000, m = 4.2M 20.0 and 16.2.  From one entry past
+// TRI_CAP on, a clique of 1,000 would take 1.20 ms for 0.95.
+constexpr int TRI_WIDE = 2 * TRI_CAP;    // N+ entries from which on a row is wide
+constexpr int TRI_WIDE_CAP = 2048, TRI_WIDE_B = 512, TRI_WIDE_SLICES = 4;
 constexpr int TRI_U = 8;                 // loads in flight per lane (4: 25% slower)
 constexpr int TRI_TEAM = 16;
 constexpr int32_t TRI_EMPTY = -1;
@@ -175,13 +182,15 @@ __global__ __launch_bounds__(TRI_LIST_B) void k_triangles_lists(int64_t n, const
 }
 
 // dir: every row with N+ first and N- after it, either in any order; place[i]:
-// where N+(i) lies.  Bound by the gathers of the neighbours' degrees.
+// where N+(i) lies; wide: the rows with more than TRI_WIDE upper neighbours (count[2]).
+// Bound by the gathers of the neighbours' degrees.
 __global__ __launch_bounds__(PBLOCK) void k_triangles_orient(int64_t n, const int64_t *__restrict__ row_ptr,
                                                              const int32_t *__restrict__ col,
                                                              const int32_t *__restrict__ deg,
                                                              const int32_t *__restrict__ rows,
-                                                             const unsigned int *__restrict__ count,
-                                                             int32_t *__restrict__ dir, uint64_t *__restrict__ place) {
+                                                             unsigned int *__restrict__ count,
+                                                             int32_t *__restrict__ dir, uint64_t *__restrict__ place,
+                                                             int32_t *__restrict__ wide) {
     __shared__ unsigned int n_up, n_down;
     const int lane = threadIdx.x & (WAVE - 1);
     for (int c = 0; c < 2; ++c) {
@@ -219,7 +228,10 @@ __global__ __launch_bounds__(PBLOCK) void k_triangles_orient(int64_t n, const in
                 }
             }
             __syncthreads();
-            if (threadIdx.x == 0) place[i] = tri_place(b0, (int)n_up);
+            if (threadIdx.x == 0) {
+                place[i] = tri_place(b0, (int)n_up);
+                if (n_up > (unsigned)TRI_WIDE) wide[atomicAdd(&count[2], 1u)] = (int32_t)i;
+            }
             __syncthreads();
         }
     }
@@ -313,24 +325,27 @@ __global__ __launch_bounds__(PBLOCK) void k_triangles_small(int64_t n, const int
 }
 
 // Listed rows, a workgroup each, or TRI_SLICES (grid y) for the rows from TRI_HUB
-// entries, each with every TRI_SLICES-th block of PBLOCK lower neighbours.
+// entries and TRI_WIDE_SLICES for the wide ones, each with every so many-th block of TB lower
+// neighbours.
 // Lower neighbours a are read 64 to a wave, then their rows walked
-// with 4, 16 or 64 lanes each by length, TRI_U loads in flight per lane.
-__global__ __launch_bounds__(PBLOCK) void k_triangles_rows(const int32_t *__restrict__ rows,
+// with 4, 16 or 64 lanes each by length, TRI_U loads in flight per lane.  The table
+// takes CAP entries of N+ at a time; unless WIDE, rows of more than TRI_WIDE are left out.
+template <int TB, int CAP, int SLOTS, bool WIDE>
+__global__ __launch_bounds__(TB) void k_triangles_rows(const int32_t *__restrict__ rows,
                                                            const unsigned int *__restrict__ count,
                                                            const int64_t *__restrict__ row_ptr,
                                                            const int32_t *__restrict__ dir,
                                                            const uint64_t *__restrict__ place,
                                                            unsigned long long *__restrict__ lam) {
-    constexpr int SLOTS = 4 * TRI_CAP, K = TRI_CAP / PBLOCK;
+    constexpr int K = CAP / TB;
     __shared__ int4 keys[SLOTS / 4];
     __shared__ unsigned int cnt[SLOTS];
-    __shared__ unsigned long long wsum[PBLOCK / WAVE];
-    __shared__ uint8_t sel[PBLOCK / WAVE][WAVE];
-    __shared__ unsigned int hits[PBLOCK / WAVE][WAVE];
+    __shared__ unsigned long long wsum[TB / WAVE];
+    __shared__ uint8_t sel[TB / WAVE][WAVE];
+    __shared__ unsigned int hits[TB / WAVE][WAVE];
     int32_t *key = (int32_t *)keys;
     const int lane = threadIdx.x & (WAVE - 1), wv = threadIdx.x >> 6;
-    for (int s = threadIdx.x; s < SLOTS; s += PBLOCK) {
+    for (int s = threadIdx.x; s < SLOTS; s += TB) {
         key[s] = TRI_EMPTY;
         cnt[s] = 0u;
     }
@@ -340,21 +355,21 @@ __global__ __launch_bounds__(PBLOCK) void k_triangles_rows(const int32_t *__rest
         const int64_t b = rows[h];
         const int64_t b0 = row_ptr[b], b1 = row_ptr[b + 1];
         const int up = tri_len(place[b]);
-        const int64_t first = b0 + up + (int64_t)blockIdx.y * PBLOCK;
-        if (up == 0 || first >= b1) continue;                        // uniform over the workgroup
+        const int64_t first = b0 + up + (int64_t)blockIdx.y * TB;
+        if (up == 0 || first >= b1 || (!WIDE && up > TRI_WIDE)) continue; // uniform over the workgroup
         unsigned long long own = 0;
-        for (int c0 = 0; c0 < up; c0 += TRI_CAP) {
+        for (int c0 = 0; c0 < up; c0 += CAP) {
             int32_t x[K];
             int slot[K];
 #pragma unroll
             for (int u = 0; u < K; ++u) {
-                const int q = c0 + u * PBLOCK + (int)threadIdx.x;
+                const int q = c0 + u * TB + (int)threadIdx.x;
                 x[u] = q < up ? dir[b0 + q] : TRI_EMPTY;
             }
 #pragma unroll
             for (int u = 0; u < K; ++u) slot[u] = x[u] != TRI_EMPTY ? tri_put<SLOTS>(key, x[u]) : -1;
             __syncthreads();
-            for (int64_t q0 = first + wv * WAVE; q0 < b1; q0 += (int64_t)gridDim.y * PBLOCK) {
+            for (int64_t q0 = first + wv * WAVE; q0 < b1; q0 += (int64_t)gridDim.y * TB) {
                 const bool have = q0 + lane < b1;
                 const int32_t a = have ? dir[q0 + lane] : 0;
                 const uint64_t p = have ? place[a] : 0;
@@ -417,7 +432,7 @@ __global__ __launch_bounds__(PBLOCK) void k_triangles_rows(const int32_t *__rest
         __syncthreads();
         if (threadIdx.x == 0) {
             unsigned long long tot = 0;
-            for (int w = 0; w < PBLOCK / WAVE; ++w) tot += wsum[w];
+            for (int w = 0; w < TB / WAVE; ++w) tot += wsum[w];
             if (tot) atomicAdd(&lam[b], tot);
         }
         // wsum is written again only after the next row's barriers
@@ -777,6 +792,7 @@ struct PropLayout {
     unsigned long long *lam;      // [n]
     unsigned int *flags;          // [4]: rows per list of long rows
     int32_t *tri_rows;            // [2][n]: the long rows
+    int32_t *tri_wide;            // [m / (TRI_WIDE + 1) + 1]: rows with more than TRI_WIDE upper neighbours
     int32_t *deg;                 // [n]
     int32_t *dir;                 // [2m]: rows, upper neighbours first
     uint64_t *place;              // [n]: upper neighbours' places in dir
@@ -793,6 +809,7 @@ static size_t prop_layout(const ad_graph *g, void *ws, size_t ws_bytes, PropLayo
     l.lam = c.take<unsigned long long>(n);
     l.flags = c.take<unsigned int>(4);
     l.tri_rows = c.take<int32_t>(2 * n);
+    l.tri_wide = c.take<int32_t>(m / (TRI_WIDE + 1) + 1);
     l.deg = c.take<int32_t>(n);
     l.dir = c.take<int32_t>(2 * m);
     l.place = c.take<uint64_t>(n);
@@ -1005,16 +1022,22 @@ extern "C" ad_status ad_graph_properties(const ad_graph *g, int64_t *lambda, dou
         AD_LAUNCH_CHECK("k_triangles_lists");
         const unsigned teams = (unsigned)std::min<int64_t>(4096, ceil_div(n, PBLOCK / TRI_TEAM));
         hipLaunchKernelGGL(k_triangles_orient, dim3(teams), dim3(PBLOCK), 0, stream, n, g->row_ptr, g->col, L.deg,
-                           L.tri_rows, L.flags, L.dir, L.place);
+                           L.tri_rows, L.flags, L.dir, L.place, L.tri_wide);
         AD_LAUNCH_CHECK("k_triangles_orient");
         // a listed row has more than TRI_HUB (TRI_SMALL) of the 2m entries
         const int64_t hubs = 2 * g->m / (TRI_HUB + 1), longs = 2 * g->m / (TRI_SMALL + 1);
+        // a wide row has TRI_WIDE + 1 upper neighbours, each of at least as long a row
+        if (g->m >= (int64_t)(TRI_WIDE + 1) * (TRI_WIDE + 2) / 2)
+            hipLaunchKernelGGL((k_triangles_rows<TRI_WIDE_B, TRI_WIDE_CAP, 2 * TRI_WIDE_CAP, true>), dim3(256, TRI_WIDE_SLICES),
+                               dim3(TRI_WIDE_B), 0, stream, L.tri_wide, L.flags + 2, g->row_ptr, L.dir, L.place, L.lam);
         if (hubs > 0)
-            hipLaunchKernelGGL(k_triangles_rows, dim3((unsigned)std::min<int64_t>(512, hubs), TRI_SLICES),
-                               dim3(PBLOCK), 0, stream, L.tri_rows + n, L.flags + 1, g->row_ptr, L.dir, L.place, L.lam);
+            hipLaunchKernelGGL((k_triangles_rows<PBLOCK, TRI_CAP, 4 * TRI_CAP, false>),
+                               dim3((unsigned)std::min<int64_t>(512, hubs), TRI_SLICES), dim3(PBLOCK), 0, stream,
+                               L.tri_rows + n, L.flags + 1, g->row_ptr, L.dir, L.place, L.lam);
         if (longs > 0)
-            hipLaunchKernelGGL(k_triangles_rows, dim3((unsigned)std::min<int64_t>(4096, longs), 1), dim3(PBLOCK), 0,
-                               stream, L.tri_rows, L.flags, g->row_ptr, L.dir, L.place, L.lam);
+            hipLaunchKernelGGL((k_triangles_rows<PBLOCK, TRI_CAP, 4 * TRI_CAP, false>),
+                               dim3((unsigned)std::min<int64_t>(4096, longs), 1), dim3(PBLOCK), 0, stream, L.tri_rows,
+                               L.flags, g->row_ptr, L.dir, L.place, L.lam);
         AD_LAUNCH_CHECK("k_triangles_rows");
         hipLaunchKernelGGL(k_triangles_small, dim3(teams), dim3(PBLOCK), 0, stream, n, g->row_ptr, L.dir, L.place,
                            L.lam);

@@ -74,6 +74,19 @@ def test_triangles_of_cliques(api, k):
     assert lam[k] == 0
 
 
+@pytest.mark.parametrize("k,leaves", [(2049, 0), (2050, 0), (2200, 0), (1200, 3000)])
+def test_triangles_of_wide_cliques(api, k, leaves):
+    """Lists of upper neighbours up to, at and past the wide table, the last on rows of
+    several workgroups (every vertex of the clique with leaves of its own)."""
+    announce(f"triangles of a clique of {k} with {leaves} leaves each")
+    a, b = np.triu_indices(k, 1)
+    hub = np.repeat(np.arange(k), leaves)
+    g = G.from_edges(k + hub.size, np.concatenate([a, hub]), np.concatenate([b, k + np.arange(hub.size)]))
+    lam = _np(api.graph_properties(api.DeviceGraph.from_host(g, "cuda"))["lambda"])
+    np.testing.assert_array_equal(lam[:k], np.full(k, (k - 1) * (k - 2) // 2))
+    assert not lam[k:].any()
+
+
 def test_triangles_of_hubs(api):
     """Rows beyond one workgroup: two joined hubs that share 9,000 neighbours,
     consecutive ones of which are joined."""
