@@ -341,6 +341,8 @@ struct SweepPlan {
     SweepShape sh;
     int32_t *hub_list;
     unsigned int *hub_count;
+    unsigned int *hub_first = nullptr;  // optional, set before the build: first work item (of hub_d entries) of
+                                        // every hub row, and their number behind the last
     long long *plan;            // (first row << 16) | (rows << 8) | log2(rows per wave), per wave
     unsigned int *plan_count;
     unsigned int *splits;       // [XCDS + 1] plan offsets of the XCD groups' ranges

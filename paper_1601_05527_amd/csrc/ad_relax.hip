@@ -1052,11 +1052,10 @@ struct PlanRows {                          // one tile, of the wave that holds i
     int lg;
     unsigned int nw;                       // plan entries
     unsigned long long hubs;               // lanes whose row is long
+    unsigned int items;                    // work items of hub_d entries of this lane's row, if long
 };
-__device__ __forceinline__ unsigned long long plan_hubs(const int64_t *__restrict__ row_ptr, int64_t r0, int64_t r1,
-                                                        int64_t hub_d) {
-    const int64_t i = r0 + (threadIdx.x & (WAVE - 1));
-    return __ballot(i < r1 && row_ptr[i + 1] - row_ptr[i] > hub_d);
+__device__ __forceinline__ unsigned int hub_items(int64_t len, int64_t hub_d) {
+    return (unsigned int)(((uint32_t)len - 1u) / (uint32_t)min(hub_d, (int64_t)0x7fffffff)) + 1u;
 }
 __device__ __forceinline__ PlanRows plan_rows(int64_t n, const int64_t *__restrict__ row_ptr,
                                               const int32_t *__restrict__ col, int upper_only, int64_t hub_d,
@@ -1067,10 +1066,12 @@ __device__ __forceinline__ PlanRows plan_rows(int64_t n, const int64_t *__restri
     const int64_t i = p.r0 + (threadIdx.x & (WAVE - 1));
     int64_t d = 0;
     bool hub = false;
+    p.items = 0u;
     if (i < p.r1) {
         const int64_t beg = row_ptr[i], end = row_ptr[i + 1];
         hub = end - beg > hub_d;
-        if (!hub) d = upper_only ? end - upper_start(col, beg, end, i) : end - beg;
+        if (hub) p.items = hub_items(end - beg, hub_d);
+        else d = upper_only ? end - upper_start(col, beg, end, i) : end - beg;
     }
     for (int o = WAVE / 2; o >= 1; o >>= 1) d = max(d, (int64_t)__shfl_xor(d, o, WAVE));
     p.lg = tile_lg_of(d, spr_max, rpw_fixed);
@@ -1078,109 +1079,171 @@ __device__ __forceinline__ PlanRows plan_rows(int64_t n, const int64_t *__restri
     p.hubs = __ballot(hub);
     return p;
 }
-// The tile's entries from plan[po] on, its hub rows from hub_list[ho] on.
-__device__ __forceinline__ void plan_put(const PlanRows &p, unsigned int po, unsigned int ho,
-                                         long long *__restrict__ plan, int32_t *__restrict__ hub_list) {
-    const int lane = threadIdx.x & (WAVE - 1);
-    if ((unsigned int)lane < p.nw) {
-        const int64_t r = p.r0 + ((int64_t)lane << p.lg);
-        plan[po + lane] = ((long long)r << 16) | ((long long)min((int64_t)1 << p.lg, p.r1 - r) << 8) | p.lg;
+// Plan entries, hub rows and their items, of a wave's or several workgroups' tiles.
+struct PlanAt {
+    unsigned int plan, hubs, items;
+    __device__ __forceinline__ void add(const PlanAt &o) {
+        plan += o.plan;
+        hubs += o.hubs;
+        items += o.items;
     }
-    if (hub_list && ((p.hubs >> lane) & 1))
-        hub_list[ho + __popcll(p.hubs & (((unsigned long long)1 << lane) - 1))] = (int32_t)(p.r0 + lane);
+};
+__device__ __forceinline__ PlanAt plan_sum(const PlanRows &p) {
+    unsigned int it = p.items;
+    for (int o = WAVE / 2; o >= 1; o >>= 1) it += __shfl_xor(it, o, WAVE);
+    return PlanAt{p.nw, (unsigned int)__popcll(p.hubs), it};
 }
+// What a plan is written to: hub_list and hub_first (first item of every hub row, and their
+// number behind the last) may be NULL.
+struct PlanOut {
+    long long *plan;
+    unsigned int *plan_count;
+    int32_t *hub_list;
+    unsigned int *hub_count, *hub_first;
+    __device__ __forceinline__ void put(const PlanRows &p, const PlanAt &at) const {
+        const int lane = threadIdx.x & (WAVE - 1);
+        if ((unsigned int)lane < p.nw) {
+            const int64_t r = p.r0 + ((int64_t)lane << p.lg);
+            plan[at.plan + lane] = ((long long)r << 16) | ((long long)min((int64_t)1 << p.lg, p.r1 - r) << 8) | p.lg;
+        }
+        if (!hub_list || p.hubs == 0) return;                        // uniform across the wave
+        const unsigned int h = at.hubs + (unsigned int)__popcll(p.hubs & (((unsigned long long)1 << lane) - 1));
+        const bool hub = (p.hubs >> lane) & 1;
+        if (hub) hub_list[h] = (int32_t)(p.r0 + lane);
+        if (!hub_first) return;
+        unsigned int inc = p.items;
+        for (int o = 1; o < WAVE; o <<= 1) {
+            const unsigned int y = __shfl_up(inc, o, WAVE);
+            if (lane >= o) inc += y;
+        }
+        if (hub) hub_first[h] = at.items + inc - p.items;
+    }
+    __device__ __forceinline__ void counts(const PlanAt &all) const {
+        *plan_count = all.plan;
+        if (hub_list) *hub_count = all.hubs;
+        if (hub_first) hub_first[all.hubs] = all.items;
+    }
+};
 
 __global__ __launch_bounds__(PLAN_WG * WAVE) void k_plan_solo(int64_t n, const int64_t *__restrict__ row_ptr,
                                                               const int32_t *__restrict__ col, int upper_only,
-                                                              int64_t hub_d, int spr_max, int rpw_fixed,
-                                                              long long *__restrict__ plan,
-                                                              unsigned int *__restrict__ plan_count,
-                                                              int32_t *__restrict__ hub_list,
-                                                              unsigned int *__restrict__ hub_count, int64_t ntiles) {
-    __shared__ unsigned int waves[PLAN_WG], hubs[PLAN_WG];
+                                                              int64_t hub_d, int spr_max, int rpw_fixed, PlanOut out,
+                                                              int64_t ntiles) {
+    __shared__ PlanAt part[PLAN_WG];
     const int wv = threadIdx.x >> 6;
-    unsigned int po = 0, ho = 0;                                     // before this turn's tiles
+    PlanAt at{0, 0, 0};                                              // before this turn's tiles
     for (int64_t t0 = 0; t0 < ntiles; t0 += PLAN_WG) {
         const PlanRows p = plan_rows(n, row_ptr, col, upper_only, hub_d, spr_max, rpw_fixed, t0 + wv);
-        if ((threadIdx.x & (WAVE - 1)) == 0) {
-            waves[wv] = p.nw;
-            hubs[wv] = (unsigned int)__popcll(p.hubs);
-        }
+        const PlanAt own = plan_sum(p);
+        if ((threadIdx.x & (WAVE - 1)) == 0) part[wv] = own;
         __syncthreads();
-        unsigned int pb = po, hb = ho;
+        PlanAt mine = at;
         for (int w = 0; w < PLAN_WG; ++w) {
-            if (w == wv) {
-                pb = po;
-                hb = ho;
-            }
-            po += waves[w];
-            ho += hubs[w];
+            if (w == wv) mine = at;
+            at.add(part[w]);
         }
-        plan_put(p, pb, hb, plan, hub_list);
-        __syncthreads();                                             // waves and hubs are written again
+        out.put(p, mine);
+        __syncthreads();                                             // part is written again
     }
-    if (threadIdx.x == 0) {
-        *plan_count = po;
-        if (hub_list) *hub_count = ho;
-    }
+    if (threadIdx.x == 0) out.counts(at);
 }
 
-// Hub rows (upper half) and plan entries of every workgroup's tiles.
+// Every workgroup's sums: sums[2 b] (hub rows in the upper half, plan entries in the lower),
+// sums[2 b + 1] (items).
 __global__ __launch_bounds__(PLAN_WG * WAVE) void k_plan_sums(int64_t n, const int64_t *__restrict__ row_ptr,
                                                               const int32_t *__restrict__ col, int upper_only,
                                                               int64_t hub_d, int spr_max, int rpw_fixed,
                                                               int *__restrict__ tile_lg,
                                                               unsigned long long *__restrict__ sums, int64_t ntiles) {
-    __shared__ unsigned long long part[PLAN_WG];
+    __shared__ PlanAt part[PLAN_WG];
     const int wv = threadIdx.x >> 6;
     const int64_t t = (int64_t)blockIdx.x * PLAN_WG + wv;
     const PlanRows p = plan_rows(n, row_ptr, col, upper_only, hub_d, spr_max, rpw_fixed, t);
+    const PlanAt own = plan_sum(p);
     if ((threadIdx.x & (WAVE - 1)) == 0) {
         if (t < ntiles) tile_lg[t] = p.lg;
-        part[wv] = ((unsigned long long)__popcll(p.hubs) << 32) | p.nw;
+        part[wv] = own;
     }
     __syncthreads();
     if (threadIdx.x == 0) {
-        unsigned long long s = 0;
-        for (int w = 0; w < PLAN_WG; ++w) s += part[w];
-        sums[blockIdx.x] = s;
+        PlanAt s{0, 0, 0};
+        for (int w = 0; w < PLAN_WG; ++w) s.add(part[w]);
+        sums[2 * blockIdx.x] = ((unsigned long long)s.hubs << 32) | s.plan;
+        sums[2 * blockIdx.x + 1] = s.items;
     }
 }
 
 __global__ __launch_bounds__(PLAN_WG * WAVE) void k_plan_place(int64_t n, const int64_t *__restrict__ row_ptr,
                                                                int64_t hub_d, const int *__restrict__ tile_lg,
                                                                const unsigned long long *__restrict__ sums,
-                                                               long long *__restrict__ plan,
-                                                               unsigned int *__restrict__ plan_count,
-                                                               int32_t *__restrict__ hub_list,
-                                                               unsigned int *__restrict__ hub_count, int64_t ntiles) {
-    __shared__ unsigned long long part[PLAN_WG], own[PLAN_WG];
+                                                               PlanOut out, int64_t ntiles) {
+    __shared__ PlanAt before[PLAN_WG], part[PLAN_WG];
     const int lane = threadIdx.x & (WAVE - 1), wv = threadIdx.x >> 6;
     const int64_t t = (int64_t)blockIdx.x * PLAN_WG + wv;
-    unsigned long long s = threadIdx.x < blockIdx.x ? sums[threadIdx.x] : 0ull;
+    const bool have = threadIdx.x < blockIdx.x;
+    const unsigned long long s = have ? sums[2 * threadIdx.x] : 0ull;
+    PlanAt b{(unsigned int)s, (unsigned int)(s >> 32), have ? (unsigned int)sums[2 * threadIdx.x + 1] : 0u};
     PlanRows p;
     p.r0 = t * PLAN_TILE;
     p.r1 = min(n, p.r0 + PLAN_TILE);
     p.lg = t < ntiles ? tile_lg[t] : 0;
     p.nw = p.r1 > p.r0 ? (unsigned int)ceil_div_dev(p.r1 - p.r0, (int64_t)1 << p.lg) : 0u;
-    p.hubs = hub_list ? plan_hubs(row_ptr, p.r0, p.r1, hub_d) : 0ull;
-    for (int o = WAVE / 2; o >= 1; o >>= 1) s += __shfl_xor(s, o, WAVE);
+    p.items = 0u;
+    if (out.hub_list) {
+        const int64_t i = p.r0 + lane, len = i < p.r1 ? row_ptr[i + 1] - row_ptr[i] : 0;
+        if (len > hub_d) p.items = hub_items(len, hub_d);
+    }
+    p.hubs = __ballot(p.items != 0u);
+    const PlanAt own = plan_sum(p);
+    for (int o = WAVE / 2; o >= 1; o >>= 1)
+        b.add(PlanAt{__shfl_xor(b.plan, o, WAVE), __shfl_xor(b.hubs, o, WAVE), __shfl_xor(b.items, o, WAVE)});
     if (lane == 0) {
-        part[wv] = s;
-        own[wv] = ((unsigned long long)__popcll(p.hubs) << 32) | p.nw;
+        before[wv] = b;
+        part[wv] = own;
     }
     __syncthreads();
-    unsigned long long at = 0, mine = 0;
-    for (int w = 0; w < PLAN_WG; ++w) at += part[w];
+    PlanAt at{0, 0, 0}, mine{0, 0, 0};
+    for (int w = 0; w < PLAN_WG; ++w) at.add(before[w]);
     for (int w = 0; w < PLAN_WG; ++w) {
         if (w == wv) mine = at;
-        at += own[w];
+        at.add(part[w]);
     }
-    plan_put(p, (unsigned int)mine, (unsigned int)(mine >> 32), plan, hub_list);
-    if (blockIdx.x == gridDim.x - 1 && threadIdx.x == 0) {
-        *plan_count = (unsigned int)at;
-        if (hub_list) *hub_count = (unsigned int)(at >> 32);
+    out.put(p, mine);
+    if (blockIdx.x == gridDim.x - 1 && threadIdx.x == 0) out.counts(at);
+}
+
+// hub_first of a hub list built otherwise, by one workgroup.
+__global__ __launch_bounds__(1024) void k_hub_first(const int32_t *__restrict__ hub_list,
+                                                    const unsigned int *__restrict__ hub_count,
+                                                    const int64_t *__restrict__ row_ptr, int64_t hub_d,
+                                                    unsigned int *__restrict__ hub_first) {
+    __shared__ unsigned int part[1024 / WAVE];
+    const int lane = threadIdx.x & (WAVE - 1), wv = threadIdx.x >> 6;
+    const unsigned int nh = *hub_count;
+    unsigned int at = 0;
+    for (unsigned int h0 = 0; h0 < nh; h0 += 1024) {
+        const unsigned int h = h0 + threadIdx.x;
+        unsigned int items = 0;
+        if (h < nh) {
+            const int64_t i = hub_list[h];
+            items = hub_items(row_ptr[i + 1] - row_ptr[i], hub_d);
+        }
+        unsigned int inc = items;
+        for (int o = 1; o < WAVE; o <<= 1) {
+            const unsigned int y = __shfl_up(inc, o, WAVE);
+            if (lane >= o) inc += y;
+        }
+        if (lane == WAVE - 1) part[wv] = inc;
+        __syncthreads();
+        unsigned int mine = at;
+        for (int w = 0; w < 1024 / WAVE; ++w) {
+            if (w < wv) mine += part[w];
+            at += part[w];
+        }
+        if (h < nh) hub_first[h] = mine + inc - items;
+        __syncthreads();                                             // part is written again
     }
+    if (threadIdx.x == 0) hub_first[nh] = at;
 }
 
 // Per-vector min and max of x^(k) = x + shift over non-isolated rows
@@ -1328,17 +1391,18 @@ ad_status sweep_plan_build(const ad_graph *g, SweepPlan &p, bool build_hubs, con
     const int64_t ntiles = sg.tile_off ? sg.ntiles : ceil_div(g->n, PLAN_TILE);
     if (p.xcd_groups <= 1 && !sg.tile_off && ntiles > 0 && ntiles <= PLAN_ONCE) {
         p.turn = 0;
-        int32_t *const hubs = build_hubs ? p.hub_list : nullptr;
+        const PlanOut out{p.plan, p.plan_count, build_hubs ? p.hub_list : nullptr, p.hub_count,
+                          build_hubs ? p.hub_first : nullptr};
         const unsigned wgs = (unsigned)ceil_div(ntiles, PLAN_WG);
         if (ntiles <= PLAN_SOLO) {
             hipLaunchKernelGGL(k_plan_solo, dim3(1), dim3(PLAN_WG * WAVE), 0, st, g->n, g->row_ptr, g->col,
-                               p.sh.upper_only, p.sh.hub_d, p.sh.SPRW, p.sh.rpw_fixed, p.plan, p.plan_count, hubs,
-                               p.hub_count, ntiles);
+                               p.sh.upper_only, p.sh.hub_d, p.sh.SPRW, p.sh.rpw_fixed, out, ntiles);
         } else {
+            static_assert(PLAN_WG >= 2, "tile_nnz holds two sums per workgroup");
             hipLaunchKernelGGL(k_plan_sums, dim3(wgs), dim3(PLAN_WG * WAVE), 0, st, g->n, g->row_ptr, g->col,
                                p.sh.upper_only, p.sh.hub_d, p.sh.SPRW, p.sh.rpw_fixed, p.tile_lg, p.tile_nnz, ntiles);
             hipLaunchKernelGGL(k_plan_place, dim3(wgs), dim3(PLAN_WG * WAVE), 0, st, g->n, g->row_ptr, p.sh.hub_d,
-                               p.tile_lg, p.tile_nnz, p.plan, p.plan_count, hubs, p.hub_count, ntiles);
+                               p.tile_lg, p.tile_nnz, out, ntiles);
         }
         AD_LAUNCH_CHECK("k_plan_place");
         return AD_OK;
@@ -1352,6 +1416,11 @@ ad_status sweep_plan_build(const ad_graph *g, SweepPlan &p, bool build_hubs, con
         if (s != AD_OK) return s;
         s = collect_rows(g, p.sh.hub_d, (int64_t)1 << 62, p.hub_list, p.hub_count, st);
         if (s != AD_OK) return s;
+        if (p.hub_first) {
+            hipLaunchKernelGGL(k_hub_first, dim3(1), dim3(1024), 0, st, p.hub_list, p.hub_count, g->row_ptr,
+                               p.sh.hub_d, p.hub_first);
+            AD_LAUNCH_CHECK("k_hub_first");
+        }
     }
     if (ntiles <= 0) {
         ad_status s0 = fill_i32((int32_t *)p.splits, 0, XCDS + 1, st);

@@ -170,12 +170,29 @@ __device__ __forceinline__ void dist_span(const int32_t *__restrict__ col, const
     }
 }
 
+// The hub row of item `it` (the last one whose first item is not past it), 64 probes at
+// a time; it is the wave's.
+__device__ __forceinline__ unsigned int hub_of(const unsigned int *__restrict__ first, unsigned int nh,
+                                               unsigned int it) {
+    const unsigned int lane = threadIdx.x & (WAVE - 1);
+    unsigned int lo = 0, n = nh;                          // in [lo, lo + n)
+    while (n > 1) {
+        const unsigned int step = (n + WAVE - 1) / WAVE;
+        const unsigned int at = lane * step;
+        const unsigned long long le = __ballot(at < n && first[lo + min(at, n - 1)] <= it);
+        const unsigned int k = (unsigned int)__popcll(le) - 1u;       // lane 0 is always in
+        lo += k * step;
+        n = min(step, n - k * step);
+    }
+    return lo;
+}
+
 // rho for every edge, visited from its upper entry (j > i; the suffix of the
 // row after upper_start); with ALL, from both of its entries (whole rows),
 // every entry's value also in rho_ent in CSR order.  The first hub_blocks workgroups take the rows
 // longer than hub_d, their upper suffix cut into work items of hub_d
-// entries (row h of the hub list, segment s < hub_segs; items past the row's
-// end are skipped), one wave per item.  The other waves walk the launch plan (first row, rows in the tile,
+// entries (row h of the hub list has items hub_first[h] on, or without that list every row
+// hub_segs; items past the row's end are skipped), one wave per item.  The other waves walk the launch plan (first row, rows in the tile,
 // log2 rows per wave) as the sweep does, with SPRW / rpw slots per row.
 // Every edge's value is computed by the same lane arithmetic on either path.
 template <typename Tx, typename Tr, int VEC, int U, bool ALL>
@@ -184,6 +201,7 @@ __global__ __launch_bounds__(SBLOCK) void k_edge_dist(
     const int32_t *__restrict__ eid, const Tx *__restrict__ x, const double *__restrict__ minmax,
     Tr *__restrict__ rho, Tr *__restrict__ rho_ent, int R, int C, int SPRW, int64_t hub_d, int hub_blocks, int64_t hub_segs,
     const int32_t *__restrict__ hub_list, const unsigned int *__restrict__ hub_count,
+    const unsigned int *__restrict__ hub_first,
     const long long *__restrict__ plan, const unsigned int *__restrict__ plan_count,
     const unsigned int *__restrict__ splits, int xcd_groups, const int32_t *__restrict__ row_graph) {
     const int lane = threadIdx.x & (WAVE - 1);
@@ -193,13 +211,22 @@ __global__ __launch_bounds__(SBLOCK) void k_edge_dist(
         const int slot = lane / C;
         const int chunk = lane - slot * C;
         const bool active = lane < group;
-        const unsigned long long items = (unsigned long long)(*hub_count) * (unsigned long long)hub_segs;
+        const unsigned int nh = *hub_count;
+        const unsigned long long items =
+            hub_first ? (unsigned long long)hub_first[nh] : (unsigned long long)nh * (unsigned long long)hub_segs;
         const unsigned long long stride = (unsigned long long)hub_blocks * (SBLOCK / WAVE);
         for (unsigned long long it = (unsigned long long)blockIdx.x * (SBLOCK / WAVE) + wave; it < items;
              it += stride) {
-            const int64_t row = hub_list[it / hub_segs];
+            int64_t row, skip;
+            if (hub_first) {
+                const unsigned int h = hub_of(hub_first, nh, (unsigned int)it);
+                row = hub_list[h];
+                skip = (int64_t)((unsigned int)it - hub_first[h]) * hub_d;
+            } else {
+                row = hub_list[it / hub_segs];
+                skip = (int64_t)(it % hub_segs) * hub_d;
+            }
             const int64_t re = row_ptr[row + 1], r0 = row_ptr[row];
-            const int64_t skip = (int64_t)(it % hub_segs) * hub_d;
             if (skip >= re - r0) continue;                // uniform across the wave, as below
             const int64_t b0 = (ALL ? r0 : upper_start(col, r0, re, row)) + skip;
             if (b0 >= re) continue;
@@ -2364,23 +2391,41 @@ static SweepShape dist_shape(int R, ad_dtype x_dtype, int64_t m, int64_t d_max, 
     return sh;
 }
 
-size_t edge_dist_segs_workspace(const ad_graph *g, const Segs &sg) {
-    return sweep_plan_bytes(g->n, sg.tile_off ? sg.ntiles : ceil_div(g->n, PLAN_TILE));
+// The rows' first items are listed (in the plan's own launches, or by one of one
+// workgroup) for up to so many hub rows, always where items are short.  Without the list every row counts as
+// many items as the longest one has: a row of 300,000 entries beside 2,500 of 270 made
+// 2.9M items of 256 entries of 6,200: 303 us a pass (127 with items of 4,096), @NEW@ with the list.
+constexpr int64_t DIST_LISTED = 16384;
+
+struct DistLayout {
+    SweepPlan plan;
+    int64_t hub;
+};
+static size_t dist_layout(const ad_graph *g, const Segs &sg, void *ws, size_t ws_bytes, DistLayout *D) {
+    Carver c(ws, ws_bytes);
+    DistLayout l;
+    l.hub = dist_hub(g->m);
+    sweep_plan_carve(c, g->n, sg.tile_off ? sg.ntiles : ceil_div(g->n, PLAN_TILE), l.plan);
+    const int64_t rows = std::min<int64_t>(g->n, 2 * g->m / (l.hub + 1));
+    if (rows <= DIST_LISTED) l.plan.hub_first = c.take<unsigned int>((size_t)rows + 1);
+    if (D) *D = l;
+    return c.ok() ? c.used : 0;
 }
+
+size_t edge_dist_segs_workspace(const ad_graph *g, const Segs &sg) { return dist_layout(g, sg, nullptr, 0, nullptr); }
 
 ad_status edge_dist_segs(const ad_graph *g, int32_t R, ad_dtype x_dtype, const void *x, const double *minmax,
                          ad_dtype rho_dtype, void *rho, void *ws, size_t ws_bytes, const Segs &sg,
                          hipStream_t stream, float *rho_ent) {
-    Carver c(ws, ws_bytes);
-    SweepPlan pl;
-    sweep_plan_carve(c, g->n, sg.tile_off ? sg.ntiles : ceil_div(g->n, PLAN_TILE), pl);
-    if (!c.ok()) return fail(AD_ERR_WORKSPACE, "workspace too small");
+    DistLayout L;
+    if (dist_layout(g, sg, ws, ws_bytes, &L) == 0) return fail(AD_ERR_WORKSPACE, "workspace too small");
+    SweepPlan &pl = L.plan;
     if (g->n <= 0 || g->m <= 0) return AD_OK;
     // FP64 vectors with FP32 distances (the FP64 tail of FP32 storage) take
     // the FP32 lane layout: four values, 32 bytes, per lane
     if (rho_ent && rho_dtype != AD_F32) return fail(AD_ERR_INTERNAL, "entry-ordered distances are FP32");
     pl.sh = dist_shape(R, (x_dtype == AD_F64 && rho_dtype == AD_F32) ? AD_F32 : x_dtype, g->m, g->d_max, rho_ent != nullptr);
-    const int64_t hub = dist_hub(g->m);
+    const int64_t hub = L.hub;
     const bool hubs = g->d_max > hub;
     ad_status s = sweep_plan_build(g, pl, hubs, sg, stream);
     if (s != AD_OK) return s;
@@ -2396,7 +2441,7 @@ ad_status edge_dist_segs(const ad_graph *g, int32_t R, ad_dtype x_dtype, const v
 #define AD_DIST_ALL(TX, TR, V, ALL)                                                                         \
     hipLaunchKernelGGL((k_edge_dist<TX, TR, V, dist_unroll<TX>(), ALL>), dim3(nb), dim3(SBLOCK), 0, stream,  \
                        g->n, g->row_ptr, g->col, g->eid, (const TX *)x, minmax, (TR *)rho, (TR *)rho_ent, R,  \
-                       pl.sh.C, pl.sh.SPRW, pl.sh.hub_d, (int)hub_blocks, hub_segs, pl.hub_list, pl.hub_count, \
+                       pl.sh.C, pl.sh.SPRW, pl.sh.hub_d, (int)hub_blocks, hub_segs, pl.hub_list, pl.hub_count, pl.hub_first, \
                        pl.plan, pl.plan_count, pl.splits, pl.xcd_groups, sg.row_graph)
 #define AD_DIST(TX, TR, V)                   \
     do {                                     \
