@@ -356,6 +356,59 @@ def test_binned_rows_of_every_length(api, values):
     np.testing.assert_array_equal(_np(keep), keep_o)
 
 
+# ------------------------------------------ selections on the helper streams --
+
+_FORK_DEGS = [64, 65, 128, 129, 256, 257, 512, 513, 1024, 1025, 2048, 2049, 4096, 4097, 8192, 8193, 20_000]
+
+
+def _fork_graph():
+    """Just above 2^21 stored entries: rows at the bounds of every class, 20 of each, their
+    neighbours drawn from one pool (rows of about 18), under random names."""
+    rng = np.random.default_rng(21)
+    degs = np.repeat(_FORK_DEGS, 20)
+    pool = degs.size + np.arange(60_000)
+    u = np.repeat(np.arange(degs.size), degs)
+    v = np.concatenate([rng.choice(pool, size=d, replace=False) for d in degs])
+    g = G.from_edges(degs.size + pool.size, u, v)
+    assert 1 << 21 <= 2 * g.m < 1.1 * (1 << 21)
+    g.orig_id = rng.permutation(g.n).astype(np.int32)
+    return g
+
+
+@pytest.fixture(scope="module")
+def fork_graph():
+    return _fork_graph()
+
+
+@pytest.mark.parametrize("prec", ["f32", "f64"])
+@pytest.mark.parametrize("ties", [False, True])
+def test_selection_on_helper_streams(api, fork_graph, prec, ties):
+    """Every class's launch of the forked dispatch (FP64 rankings stay on one stream), with distinct
+    and with tied distances: masks, counts and exponents of the oracle."""
+    announce(f"forked selection {prec} ties={ties}")
+    g = fork_graph
+    rng = np.random.default_rng(5)
+    rho = rng.integers(1, 200, g.m) / 64.0 if ties else (1.0 + rng.permutation(g.m)) / (1 << 21)
+    rho = rho.astype(np.float32 if prec == "f32" else np.float64)
+    ref = rho.astype(np.float64)
+    dg = api.DeviceGraph.from_host(g, "cuda")
+    t = torch.from_numpy(rho).cuda()
+    for orient, e in ((0, 0.45), (1, 0.8)):
+        keep, nk = api.sparsify(dg, t, orient, e)
+        keep_o, kept_o = oracle.sparsify(g, ref, orient, e)
+        np.testing.assert_array_equal(_np(keep), keep_o)
+        assert int(nk.item()) == kept_o
+    kl, kg, nk, es = api.sparsify_fit_both(dg, t, 0.35)
+    for orient, keep in ((0, kl), (1, kg)):
+        e_o, keep_o, kept_o = oracle.fit_exponent(g, ref, orient, 0.35)
+        assert es[orient] == e_o and int(_np(nk)[orient]) == kept_o
+        np.testing.assert_array_equal(_np(keep), keep_o)
+    keep, nk, _ = api.sparsify_binned(dg, t, seed=5, e=0.6)
+    keep_o, kept_o = oracle.sparsify_binned(g, ref, 0.6, 5)
+    np.testing.assert_array_equal(_np(keep), keep_o)
+    assert int(nk.item()) == kept_o
+
+
 # ----------------------------------------------------------------- ingest --
 
 @pytest.mark.parametrize("n", [2, 3, 4, 255, 256, 257, 4096, 4097, 65536, 65537, 1 << 22, (1 << 22) + 1])
