@@ -909,7 +909,7 @@ static ad_status rcm_order(int64_t n, int64_t m, const int64_t *row_ptr, const i
     g.row_ptr = row_ptr;
     g.col = m > 0 ? col : nullptr;
     g.eid = m > 0 ? eid : nullptr;
-    ad_status s = label_components(&g, L.rc_root, nullptr, st);
+    ad_status s = label_components(&g, L.rc_root, st);
     if (s != AD_OK) return s;
     s = fill_i32((int32_t *)L.rc_size, 0, n, st);
     if (s != AD_OK) return s;

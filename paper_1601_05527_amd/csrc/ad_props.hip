@@ -827,16 +827,14 @@ static size_t prop_layout(const ad_graph *g, void *ws, size_t ws_bytes, PropLayo
 // larger root under the smaller with a compare-and-swap, then every vertex
 // is pointed at its root.  A parent is always smaller than its child, so the
 // trees have no cycles, every root search ends, and each component's root is
-// its smallest vertex whatever the order of the joins.  flags is unused.  No
-// host round trips.
+// its smallest vertex whatever the order of the joins.  No host round trips.
 // Bound by the dependent parent lookups.  n = 2^20, m = 16M stored by degree:
 // 2.3 ms with the first two entries of every row joined by compare-and-swap
 // and every lookup at device scope (2.1 ms of it one address, the hub's),
 // 0.035 ms here (six launches).  A component build, so / here, and with the chains left to
 // k_flatten: 2,048 x 2,048 mesh row by row 3.63 / 0.49 (0.65) ms, path of 2^22 vertices in order
 // 8 to 11 / 0.53 (16.3), 2^19 pairs 0.34 / 0.29 (their rows walked by whole waves: 0.37).
-ad_status label_components(const ad_graph *g, int32_t *parent, unsigned int *flags, hipStream_t stream) {
-    (void)flags;
+ad_status label_components(const ad_graph *g, int32_t *parent, hipStream_t stream) {
     const int64_t n = g->n;
     hipLaunchKernelGGL(k_hook_first, dim3((unsigned)std::max<int64_t>(1, ceil_div(n, HOOK_ROWS))), dim3(HOOK_TB), 0, stream, n,
                        g->row_ptr, g->col, parent);
@@ -859,7 +857,6 @@ ad_status label_components(const ad_graph *g, int32_t *parent, unsigned int *fla
 
 struct CompLayout {
     int32_t *parent;              // [n]
-    unsigned int *flags;          // [4]
     uint32_t *key0, *key1, *val0, *val1, *head, *before;   // [n]
     int64_t *cnt;                 // [n + 1]
     void *temp;
@@ -871,7 +868,6 @@ static size_t comp_layout(int64_t n, void *ws, size_t ws_bytes, CompLayout *L) {
     const size_t nn = (size_t)std::max<int64_t>(1, n);
     CompLayout l;
     l.parent = c.take<int32_t>(nn);
-    l.flags = c.take<unsigned int>(4);
     l.key0 = c.take<uint32_t>(nn);
     l.key1 = c.take<uint32_t>(nn);
     l.val0 = c.take<uint32_t>(nn);
@@ -1046,9 +1042,9 @@ extern "C" ad_status ad_graph_properties(const ad_graph *g, int64_t *lambda, dou
     hipLaunchKernelGGL(k_clustering, dim3(PREDUCE_BLOCKS), dim3(PBLOCK), 0, stream, n, g->row_ptr, L.lam, lambda, c,
                        L.part_sum, L.part_cnt);
     AD_LAUNCH_CHECK("k_clustering");
-    // components: hook and jump until no hook changes a parent
+    // components by union-find, in a fixed number of launches
     int32_t *parent = comp ? comp : L.parent;
-    s = label_components(g, parent, L.flags, stream);
+    s = label_components(g, parent, stream);
     if (s != AD_OK) return s;
     s = fill_u64(L.roots, 0, 1, stream);
     if (s != AD_OK) return s;
@@ -1101,9 +1097,7 @@ extern "C" ad_status ad_components_build(const ad_graph *g, int32_t *comp_of, in
         AD_HIP(hipStreamSynchronize(stream));
         return AD_OK;
     }
-    s = fill_i32((int32_t *)L.flags, 0, 4, stream);
-    if (s != AD_OK) return s;
-    s = label_components(g, L.parent, L.flags, stream);
+    s = label_components(g, L.parent, stream);
     if (s != AD_OK) return s;
     hipLaunchKernelGGL(k_comp_keys, dim3(pgrid(n)), dim3(PBLOCK), 0, stream, n, g->row_ptr, L.parent, L.key0, L.val0);
     AD_LAUNCH_CHECK("k_comp_keys");

@@ -342,16 +342,15 @@ __device__ __forceinline__ int32_t nbr_id(int64_t p, int32_t j, const int32_t *_
     return col_orig ? col_orig[p] : (orig_id ? orig_id[j] : j);
 }
 
-// Where ranks go.  MODE_FIXED marks keep[e] when rank < budget[d] (with
-// `both`, the LOCAL rank against (budget, keep) and the GLOBAL rank against
-// (budget2, keep2); otherwise the rank of `orient`).  MODE_REC stores the
+// Where ranks go.  MODE_FIXED marks keep[e] when the rank of `orient` is below
+// budget[d].  MODE_REC stores the
 // side record {d, first rank, second rank} at recs[e + (row > j ? m : 0)]: with
 // `both` the LOCAL and the GLOBAL rank, otherwise the rank of `orient` in
 // both places; one store per entry.
 struct Emit {
     int mode, orient, both;
-    const int32_t *budget, *budget2;
-    uint8_t *keep, *keep2;
+    const int32_t *budget;
+    uint8_t *keep;
     void *recs;
     int packed;
     int64_t m;
@@ -387,12 +386,7 @@ __device__ __forceinline__ void emit_ranks(const Emit &em, int64_t row, int32_t 
                                            int64_t rank_local, int64_t rank_global) {
     const int64_t rank_o = em.orient == AD_LOCAL ? rank_local : rank_global;
     if (em.mode == MODE_FIXED) {
-        if (em.both) {
-            if (rank_local < em.budget[d]) em.keep[e] = 1;
-            if (rank_global < em.budget2[d]) em.keep2[e] = 1;
-        } else if (rank_o < em.budget[d]) {
-            em.keep[e] = 1;
-        }
+        if (rank_o < em.budget[d]) em.keep[e] = 1;
         return;
     }
     const int64_t at = (int64_t)e + (row > j ? em.m : 0);
