@@ -605,7 +605,7 @@ struct AggLayout {
     uint32_t *resume;             // [n] where a waiting vertex's next seed round reads its row from
     uint32_t *acnt;               // [n] strongly coupled neighbours ahead
     int32_t *alist;               // [nnz] their lists, from row_ptr[i] on
-    double *rho_ent;              // [nnz] distances in entry order (FP32 ones fill half of it)
+    void *rho_ent;                // [nnz] distances in entry order, in their type
     int32_t *hubs;                // [n] rows longer than ML_HUB
     unsigned int *hub_count;      // [1]
     unsigned int *rank;           // [n] seed flags, scanned in place into aggregate ids
@@ -614,7 +614,8 @@ struct AggLayout {
     ScanScratch scan;
 };
 
-static size_t agg_layout(int64_t n, int64_t nnz, void *ws, size_t ws_bytes, AggLayout *L) {
+// rho_bytes: of one distance.
+static size_t agg_layout(int64_t n, int64_t nnz, size_t rho_bytes, void *ws, size_t ws_bytes, AggLayout *L) {
     Carver c(ws, ws_bytes);
     const size_t nn = (size_t)std::max<int64_t>(1, n);
     AggLayout l;
@@ -623,7 +624,7 @@ static size_t agg_layout(int64_t n, int64_t nnz, void *ws, size_t ws_bytes, AggL
     l.resume = c.take<uint32_t>(nn);
     l.acnt = c.take<uint32_t>(nn);
     l.alist = c.take<int32_t>((size_t)std::max<int64_t>(1, nnz));
-    l.rho_ent = c.take<double>((size_t)std::max<int64_t>(1, nnz));
+    l.rho_ent = c.take<char>((size_t)std::max<int64_t>(1, nnz) * rho_bytes);
     l.hubs = c.take<int32_t>(nn);
     l.hub_count = c.take<unsigned int>(1);
     l.rank = c.take<unsigned int>(nn);
@@ -663,7 +664,7 @@ static ad_status aggregate_impl(const ad_graph *g, const Tr *rho, double eps, do
     const int64_t n = g->n;
     *nc_host = 0;
     if (n == 0) return AD_OK;
-    Tr *rho_ent = reinterpret_cast<Tr *>(L.rho_ent);
+    Tr *rho_ent = static_cast<Tr *>(L.rho_ent);
     const MlHubs hubs = ml_hubs(g, L);
     ad_status s;
     if (hubs.blocks) {
@@ -950,10 +951,10 @@ static ad_status ml_level(const ad_graph *g, const ad_ml_opts *o, int l, uint8_t
     int64_t nc = 0;
     if (!coarsest) {
         ML_TRY(dev_alloc(agg, (size_t)n * sizeof(int32_t)));
-        const size_t ab = agg_layout(n, 2 * m, nullptr, 0, nullptr);
+        const size_t ab = agg_layout(n, 2 * m, sizeof(Tr), nullptr, 0, nullptr);
         ML_TRY(dev_alloc(aws, ab));
         AggLayout L;
-        agg_layout(n, 2 * m, aws.p, aws.bytes, &L);
+        agg_layout(n, 2 * m, sizeof(Tr), aws.p, aws.bytes, &L);
         ML_TRY(aggregate_impl<Tr>(g, rho.get<const Tr>(), o->eps, o->theta, agg.get<int32_t>(), nullptr, &nc, L, st));
         if ((double)nc > 0.9 * (double)n) coarsest = true;
     }
@@ -965,7 +966,7 @@ static ad_status ml_level(const ad_graph *g, const ad_ml_opts *o, int l, uint8_t
     ML_TRY(dev_alloc(cw, (size_t)m * sizeof(float)));
     ML_TRY(dev_alloc(names, (size_t)nc * sizeof(int32_t)));
     AggLayout L;                          // still holds the hub rows and the states
-    agg_layout(n, 2 * m, aws.p, aws.bytes, &L);
+    agg_layout(n, 2 * m, sizeof(Tr), aws.p, aws.bytes, &L);
     MlPairs kp{};
     kp.col = g->col;
     kp.w = g->w;
@@ -1081,7 +1082,7 @@ extern "C" ad_status ad_ml_level_span(int32_t n_levels, int32_t span, int32_t se
 extern "C" size_t ad_ml_aggregate_workspace_size(const ad_graph *g) {
     if (!g || g->n < 0 || g->n >= ((int64_t)1 << 31)) return 0;
     if (g->m < 0 || g->m >= ((int64_t)1 << 31)) return 0;
-    return agg_layout(g->n, 2 * g->m, nullptr, 0, nullptr);
+    return agg_layout(g->n, 2 * g->m, sizeof(double), nullptr, 0, nullptr);
 }
 
 extern "C" ad_status ad_ml_aggregate(const ad_graph *g, ad_dtype rho_dtype, const void *rho, double eps, double theta,
@@ -1096,11 +1097,11 @@ extern "C" ad_status ad_ml_aggregate(const ad_graph *g, ad_dtype rho_dtype, cons
     if (!(eps >= 0.0) || !(theta >= 0.0 && theta <= 1.0))
         return fail(AD_ERR_INVALID_ARG, "eps must be >= 0 and theta in [0, 1]");
     if (g->n >= ((int64_t)1 << 31)) return fail(AD_ERR_UNSUPPORTED, "graph too large");
-    const size_t need = agg_layout(g->n, 2 * g->m, nullptr, 0, nullptr);
+    const size_t need = agg_layout(g->n, 2 * g->m, sizeof(double), nullptr, 0, nullptr);
     s = ml_check_ws(ws, need, ws_bytes);
     if (s != AD_OK) return s;
     AggLayout L;
-    agg_layout(g->n, 2 * g->m, ws, ws_bytes, &L);
+    agg_layout(g->n, 2 * g->m, sizeof(double), ws, ws_bytes, &L);
     TraceScope trace("k_ml_aggregate", stream);
     return rho_dtype == AD_F64
                ? aggregate_impl<double>(g, (const double *)rho, eps, theta, agg, is_seed, n_coarse_host, L, stream)
