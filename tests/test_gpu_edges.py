@@ -436,6 +436,35 @@ def test_ingest_at_id_widths(api, n, order):
             np.testing.assert_array_equal(_np(dg.w), we)
 
 
+@pytest.mark.parametrize("off", [1, 2, 3])
+@pytest.mark.parametrize("m", [500, 70_000])
+def test_inputs_off_their_vector_alignment(api, off, m):
+    """Edge lists, weights and scores that start `off` elements into an allocation: sorted where
+    they are, equal to the oracle's."""
+    announce(f"inputs off={off} m={m}")
+    rng = np.random.default_rng(off)
+    n = 700
+
+    def view(a):
+        buf = torch.zeros(a.size + 8, dtype=torch.from_numpy(a).dtype, device="cuda")
+        buf[off:off + a.size] = torch.from_numpy(a).cuda()
+        t = buf[off:off + a.size]
+        assert t.is_contiguous() and t.data_ptr() % 16 == off * a.itemsize % 16
+        return t
+
+    u, v = (rng.integers(0, n, m).astype(np.int32) for _ in range(2))
+    w = rng.lognormal(0.0, 1.0, m).astype(np.float32)
+    for order in (0, 1):
+        dg = api.ingest(n, view(u), view(v), view(w), by_degree=order == 1)
+        row_ptr, col, we, eid, orig, m_o, dropped = oracle.ingest(n, u, v, w, order=order)
+        assert dg.m == m_o
+        np.testing.assert_array_equal(_np(dg.row_ptr), row_ptr)
+        np.testing.assert_array_equal(_np(dg.col), col)
+        np.testing.assert_array_equal(_np(dg.w), we)
+    x, y = rng.integers(0, 50, m).astype(np.float64), rng.random(m)
+    assert api.spearman(view(x), view(y)) == api.spearman(torch.from_numpy(x).cuda(), torch.from_numpy(y).cuda())
+
+
 # ---------------------------------------------------------------- adjoint --
 
 @pytest.mark.parametrize("R", [1, 2, 4, 6, 8, 12, 24, 33, 64])
