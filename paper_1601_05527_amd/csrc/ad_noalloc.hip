@@ -57,7 +57,7 @@ extern "C" ad_status ad_edge_dist_noalloc(const ad_graph *g, int32_t R, ad_dtype
     if (rho_dtype != AD_F32 && rho_dtype != AD_F64) return fail(AD_ERR_INVALID_ARG, "rho must be F32 or F64");
     if (rho_dtype == AD_F64 && x_dtype != AD_F64) return fail(AD_ERR_UNSUPPORTED, "FP64 rho needs FP64 x");
     if (g->m > 0 && (!x || !minmax || !rho)) return fail(AD_ERR_INVALID_ARG, "x, minmax or rho is NULL");
-    const size_t need = edge_dist_segs_workspace(g, Segs());
+    const size_t need = sweep_plan_bytes(g->n, ceil_div(g->n, PLAN_TILE));    // the list behind the plan is optional
     if (need > NOALLOC_SCRATCH_BYTES)
         return fail(AD_ERR_UNSUPPORTED, "the graph's distance plan needs " + std::to_string(need) +
                                              " bytes; the fixed scratch array holds " +

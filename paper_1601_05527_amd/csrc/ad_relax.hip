@@ -1371,9 +1371,9 @@ void sweep_plan_carve(Carver &c, int64_t n, int64_t ntiles_cap, SweepPlan &p) {
     const int64_t nn = std::max<int64_t>(1, n);
     const int64_t ntiles = std::max<int64_t>(1, ntiles_cap);
     p.hub_list = c.take<int32_t>(nn);
-    p.hub_count = c.take<unsigned int>(1);
+    p.hub_count = c.take<unsigned int>(2);
+    p.plan_count = p.hub_count ? p.hub_count + 1 : nullptr;
     p.plan = c.take<long long>(nn + ntiles);
-    p.plan_count = c.take<unsigned int>(1);
     p.tile_lg = c.take<int>(ntiles);
     p.tile_waves = c.take<unsigned int>(ntiles);
     p.tile_nnz = c.take<unsigned long long>(ntiles);

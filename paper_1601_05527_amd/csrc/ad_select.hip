@@ -2386,23 +2386,24 @@ static SweepShape dist_shape(int R, ad_dtype x_dtype, int64_t m, int64_t d_max, 
 }
 
 // The rows' first items are listed (in the plan's own launches, or by one of one
-// workgroup) for up to so many hub rows, always where items are short.  Without the list every row counts as
+// workgroup) for up to DIST_LISTED hub rows, which items shorter than 4,096 entries never
+// exceed, where the workspace has room behind the plan.  Without the list every row counts as
 // many items as the longest one has: a row of 300,000 entries beside 2,500 of 270 made
-// 2.9M items of 256 entries of 6,200: 303 us a pass (127 with items of 4,096), @NEW@ with the list.
+// 2.9M items of 256 entries out of 6,200, 303 us a pass (127 with items of 4,096; 46 with the list).
 constexpr int64_t DIST_LISTED = 16384;
 
-struct DistLayout {
-    SweepPlan plan;
-    int64_t hub;
-};
-static size_t dist_layout(const ad_graph *g, const Segs &sg, void *ws, size_t ws_bytes, DistLayout *D) {
+static size_t dist_layout(const ad_graph *g, const Segs &sg, void *ws, size_t ws_bytes, SweepPlan *P) {
     Carver c(ws, ws_bytes);
-    DistLayout l;
-    l.hub = dist_hub(g->m);
-    sweep_plan_carve(c, g->n, sg.tile_off ? sg.ntiles : ceil_div(g->n, PLAN_TILE), l.plan);
-    const int64_t rows = std::min<int64_t>(g->n, 2 * g->m / (l.hub + 1));
-    if (rows <= DIST_LISTED) l.plan.hub_first = c.take<unsigned int>((size_t)rows + 1);
-    if (D) *D = l;
+    SweepPlan p;
+    sweep_plan_carve(c, g->n, sg.tile_off ? sg.ntiles : ceil_div(g->n, PLAN_TILE), p);
+    const int64_t rows = std::min<int64_t>(g->n, 2 * g->m / (dist_hub(g->m) + 1));
+    Carver with = c;
+    unsigned int *const first = with.take<unsigned int>((size_t)rows + 1);
+    if (rows <= DIST_LISTED && with.ok()) {
+        p.hub_first = first;
+        c = with;
+    }
+    if (P) *P = p;
     return c.ok() ? c.used : 0;
 }
 
@@ -2411,15 +2412,14 @@ size_t edge_dist_segs_workspace(const ad_graph *g, const Segs &sg) { return dist
 ad_status edge_dist_segs(const ad_graph *g, int32_t R, ad_dtype x_dtype, const void *x, const double *minmax,
                          ad_dtype rho_dtype, void *rho, void *ws, size_t ws_bytes, const Segs &sg,
                          hipStream_t stream, float *rho_ent) {
-    DistLayout L;
-    if (dist_layout(g, sg, ws, ws_bytes, &L) == 0) return fail(AD_ERR_WORKSPACE, "workspace too small");
-    SweepPlan &pl = L.plan;
+    SweepPlan pl;
+    if (dist_layout(g, sg, ws, ws_bytes, &pl) == 0) return fail(AD_ERR_WORKSPACE, "workspace too small");
     if (g->n <= 0 || g->m <= 0) return AD_OK;
     // FP64 vectors with FP32 distances (the FP64 tail of FP32 storage) take
     // the FP32 lane layout: four values, 32 bytes, per lane
     if (rho_ent && rho_dtype != AD_F32) return fail(AD_ERR_INTERNAL, "entry-ordered distances are FP32");
     pl.sh = dist_shape(R, (x_dtype == AD_F64 && rho_dtype == AD_F32) ? AD_F32 : x_dtype, g->m, g->d_max, rho_ent != nullptr);
-    const int64_t hub = L.hub;
+    const int64_t hub = dist_hub(g->m);
     const bool hubs = g->d_max > hub;
     ad_status s = sweep_plan_build(g, pl, hubs, sg, stream);
     if (s != AD_OK) return s;

@@ -88,6 +88,16 @@ def backward(c):
                                  P(dev()), P(dev()), SZ(ws), P(STREAM))
 
 
+def dist_noalloc(c):
+    return lib.ad_edge_dist_noalloc(ctypes.byref(graph(c)), 16, 1, P(dev()), P(dev()), 1, P(dev()), P(STREAM))
+
+
+def dist(c):
+    g = graph(c)
+    ws = size("ad_edge_dist_workspace_size", ctypes.byref(g)) - c.get("short", 0)
+    return lib.ad_edge_dist(ctypes.byref(g), 16, 1, P(dev()), P(dev()), 1, P(dev()), P(dev()), SZ(ws), P(STREAM))
+
+
 for c in json.loads(sys.argv[3]):
     shim.fake_reset(c.get("fail_at", -1))
     status = globals()[c["call"]](c)

@@ -82,3 +82,33 @@ def test_relaxation_of_many_components_launches(run, store, R):
 def test_gradient_of_many_rows_launches(run, n, m, R):
     _check_shapes(run(dict(call="backward", n=n, m=m, d_max=5000, R=R, k=4, store=1, ckpt=2, n_comp=1,
                            n_chunks=n // 256 + 1))[0])
+
+
+def test_long_rows_take_no_room_from_the_fixed_scratch(run):
+    """The largest graph that the allocation-free distances accept does not depend on its edges,
+    and a graph at that bound goes without the list of its long rows' items."""
+    def most(m, d_max):
+        lo, hi = 1 << 20, 1 << 23                     # accepted, refused
+        while lo + 1 < hi:
+            cut = sorted({lo + (hi - lo) * k // 65 for k in range(1, 65)} - {lo, hi})
+            got = [r["status"] == 0 for r in run(*[dict(call="dist_noalloc", n=n, m=m, d_max=d_max) for n in cut])]
+            assert got == sorted(got, reverse=True)
+            k = sum(got)
+            lo, hi = (cut[k - 1] if k else lo), (cut[k] if k < len(cut) else hi)
+        return lo
+
+    n = most(10, 3)
+    assert n > 2_400_000 and most(1 << 22, 5000) == n
+    few, many = run(*[dict(call="dist_noalloc", n=k, m=1 << 22, d_max=5000) for k in (n, n // 2)])
+    assert few["status"] == many["status"] == 0
+    assert [any("k_hub_first" in x[2] for x in r["log"]) for r in (few, many)] == [False, True]
+    _check_shapes(few)
+
+
+def test_distances_without_room_for_the_list(run):
+    """A workspace that holds the plan alone still serves; a shorter one is refused."""
+    c = dict(call="dist", n=300_000, m=1 << 21, d_max=9000)
+    rows = min(300_000, (1 << 22) // 513)
+    room = (4 * (rows + 1) + 255) // 256 * 256
+    whole, plan, short = run(c, dict(c, short=room), dict(c, short=room + 1))
+    assert whole["status"] == plan["status"] == 0 and short["status"] == 3
