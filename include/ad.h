@@ -38,12 +38,13 @@
  *     ordered by the caller).
  *   - Library-owned state: the selection calls on FP32 distances
  *     (ad_sparsify, ad_sparsify_fit, ad_sparsify_fit_both,
- *     ad_edge_dist_sparsify, ad_edge_dist_fit_both, ad_sparsify_binned)
+ *     ad_edge_dist_sparsify, ad_edge_dist_fit_both) and ad_sparsify_binned on
+ *     either type
  *     rank rows longer than 64 of graphs with at least 2^21 stored entries on
  *     three helper streams per device, of default priority, created on first
  *     use and kept until the process ends; they are forked from the caller's stream with an
  *     event after the call's first kernels and joined back into it with
- *     events before the call returns, so the caller's stream orders all of
+ *     events before the call returns, also with an error, so the caller's stream orders all of
  *     the call's work, and a per-device mutex serialises the forks of calls
  *     made from several host threads.  Under stream capture the call stays
  *     on the caller's stream.  The retention fits (ad_sparsify_fit,

@@ -17,8 +17,8 @@
 //
 // The pipeline: canonical pair keys of 2 log2(n) bits, a radix sort (rocPRIM) of
 // (key, weight), a scan of the run heads (edge ids), and
-// the exact weight sum of every run (one thread per short run, one wave per
-// long run); for
+// the exact weight sum of every run (a short run by its wave's lanes together, longer ones by
+// a wave or a workgroup each); for
 // the degree order a stable sort of the vertices by degree and a second pair sort
 // under the new labels (for reverse Cuthill-McKee, the graph placed under
 // the listed ids, its components, and a level-by-level search with two
@@ -113,8 +113,8 @@ static CountIt counts_of(const uint32_t *cnt, int64_t n) {
 // double and the double sum, rounded to float, is the answer; otherwise the
 // run is summed as an integer count of 2^-149 in XDIG base-2^32 digits with
 // deferred carries.
-constexpr uint32_t MERGE_SHORT = 16;     // runs up to this length are summed by one thread,
-constexpr uint32_t MERGE_WAVE = 4096;    // up to this one by one wave, longer ones by a workgroup
+constexpr uint32_t MERGE_SHORT = 16;     // runs up to this length are summed by the wave's lanes together,
+constexpr uint32_t MERGE_WAVE = 4096;    // up to this one by a wave each, longer ones by a workgroup each
 constexpr int MERGE_TB = 1024;           // threads of a long run's workgroup
 constexpr int XDIG = 11;                 // 352 bits: 2^31 floats below 2^277 units each
 
