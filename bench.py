@@ -200,8 +200,8 @@ def traced(api, timer, fn, reps):
 
 LIMITER = ("memory-side line-request rate: random 64-128 B row gathers, each a 128 B line request "
            "when it misses the XCD's 4 MB L2; random line requests are served at about 55 G/s whether "
-           "the lines sit in the Infinity Cache or in HBM, and the FP32 sweep issues about 20.7M per launch "
-           "(about 56 G/s) -- see profiles/k_sweep_chung_lu_n2e20_memory_counters.md")
+           "the lines sit in the Infinity Cache or in HBM, and the FP32 sweep issues about 20.1M per launch "
+           "(about 55 G/s) -- see profiles/k_sweep_chung_lu_n2e20_memory_counters.md")
 
 
 def roofline(kern: dict, bytes_per_launch: float, traffic=None) -> dict:
